@@ -120,6 +120,7 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
   a.partial = (float*)((char*)workspace_d + COUNTER_BYTES + plan_area_bytes(plan_words));
   a.plan = plan;
   a.row_base = nullptr;
+  a.row_lo = nullptr;
   a.NQ = step->NQ;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)kv->head_dim) : sm_scale) * LOG2E;
   a.B = state->B;
@@ -139,11 +140,11 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
   } while (0)
   if (v.kernel == KERNEL_BF16_ROWS) {
     if (D == 128)
-      ASPD_LAUNCH((attn_bf16_rows_kernel<128, ROWS_NT, ROWS_NW>), ROWS_NW * 64,
-                  (rows_smem_bytes<128, ROWS_NT, ROWS_NW>()));
+      ASPD_LAUNCH((attn_bf16_rows_kernel<128, ROWS_NW>), ROWS_NW * 64,
+                  (rows_smem_bytes<128>()));
     else
-      ASPD_LAUNCH((attn_bf16_rows_kernel<64, ROWS_NT, ROWS_NW>), ROWS_NW * 64,
-                  (rows_smem_bytes<64, ROWS_NT, ROWS_NW>()));
+      ASPD_LAUNCH((attn_bf16_rows_kernel<64, ROWS_NW>), ROWS_NW * 64,
+                  (rows_smem_bytes<64>()));
   } else if (v.kernel == KERNEL_BF16_STREAM) {
     // pages that no second row group reads are fetched with non-temporal loads
 #define ASPD_BF16_CASE(DD, NN)                                                                            \
@@ -315,12 +316,13 @@ extern "C" int aspd_attn_full_sequence(const aspd_kv* kv, const aspd_state* stat
   a.partial = nullptr;
   a.plan = step->plan_d;
   a.row_base = step->plan_d + SEQ_PLAN_HDR;
+  a.row_lo = step->plan_d + aspd_sequence_plan_lo(G, state->B, step->NQ);
   a.NQ = step->NQ;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)kv->head_dim) : sm_scale) * LOG2E;
   a.B = state->B;
   a.G = G;
   a.qpg = qpg;
-  a.rows_cap = ROWS_NW * 16 * ROWS_NT;
+  a.rows_cap = ROWS_NW * 32;
   // one workgroup per compute unit, never more than there are row groups to take
   long nwg = aspd_device_cu_count();
   nwg = std::min(nwg, ((long)state->B + step->NQ / qpg) * kv->num_kv_heads);
@@ -328,15 +330,15 @@ extern "C" int aspd_attn_full_sequence(const aspd_kv* kv, const aspd_state* stat
   a.nwg = (int)std::max(1L, nwg);
   hipStream_t hs = (hipStream_t)stream;
   if (kv->head_dim == 128) {
-    rc = allow_big_lds((const void*)attn_bf16_seq_kernel<128, ROWS_NT, ROWS_NW>);
+    rc = allow_big_lds((const void*)attn_bf16_seq_kernel<128, ROWS_NW>);
     if (rc != ASPD_OK) return rc;
-    hipLaunchKernelGGL((attn_bf16_seq_kernel<128, ROWS_NT, ROWS_NW>), dim3(a.nwg), dim3(ROWS_NW * 64),
-                       (rows_smem_bytes<128, ROWS_NT, ROWS_NW>()), hs, a);
+    hipLaunchKernelGGL((attn_bf16_seq_kernel<128, ROWS_NW>), dim3(a.nwg), dim3(ROWS_NW * 64),
+                       (rows_smem_bytes<128>()), hs, a);
   } else {
-    rc = allow_big_lds((const void*)attn_bf16_seq_kernel<64, ROWS_NT, ROWS_NW>);
+    rc = allow_big_lds((const void*)attn_bf16_seq_kernel<64, ROWS_NW>);
     if (rc != ASPD_OK) return rc;
-    hipLaunchKernelGGL((attn_bf16_seq_kernel<64, ROWS_NT, ROWS_NW>), dim3(a.nwg), dim3(ROWS_NW * 64),
-                       (rows_smem_bytes<64, ROWS_NT, ROWS_NW>()), hs, a);
+    hipLaunchKernelGGL((attn_bf16_seq_kernel<64, ROWS_NW>), dim3(a.nwg), dim3(ROWS_NW * 64),
+                       (rows_smem_bytes<64>()), hs, a);
   }
   ASPD_HIP_CHECK(hipGetLastError());
   return ASPD_OK;

@@ -35,8 +35,7 @@ constexpr int PLAN_IDS = 16;
 constexpr int MAX_WG = 1024;         // upper bound of any attention grid
 constexpr int NT_MAX = 3;            // 16-row MFMA tiles per row group of the streaming bf16 kernel
 constexpr int F32_ROWS = 4;          // rows per row group of the fp32 kernel
-constexpr int ROWS_NW = 8;           // waves per workgroup of the row-splitting (chunk) kernel
-constexpr int ROWS_NT = 2;           // 16-row tiles per wave there
+constexpr int ROWS_NW = 8;           // waves per workgroup of the row-splitting (chunk) kernel, 32 rows each
 constexpr int MAX_WG_ROWS = 256;     // its largest grid
 constexpr int MIN_PAGES_PER_WG = 16; // key ranges are not split finer than this
 constexpr int PAD_STREAM = 32;       // fixed cost of a segment in pages, bandwidth-bound kernel at head_dim 128
@@ -84,14 +83,21 @@ int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, const i
 //                           main-branch row); NQ4 = NQ rounded up to a multiple of 4
 //   then 4 words per row group, in the order workgroups take them: sequence, first packed row,
 //                           tokens, pages of its key range
+//   then NQ4 words          per packed row, the first slot of the row's own branch in its stage (its own slot
+//                           for a main-branch row): a row sees [0, stage start) and [this, its own slot]
 constexpr int SEQ_PLAN_HDR = 16;
 // Tokens per row group: what the row-splitting kernel holds per workgroup.
-static inline int aspd_sequence_qpg(int G) { return ROWS_NW * 16 * ROWS_NT / G; }
+static inline int aspd_sequence_qpg(int G) { return ROWS_NW * 32 / G; }
 // Identifies such a plan; no value aspd_plan_key returns has bit 62 set.
 static inline uint64_t aspd_sequence_plan_key(int qpg, int32_t B) {
   return ((uint64_t)1 << 62) | ((uint64_t)qpg << 16) | (uint64_t)B;
 }
 size_t aspd_sequence_plan_words(const aspd_kv* kv, int32_t B, int32_t NQ);
+// Index of the row groups and of the branch starts in it.
+static inline size_t aspd_sequence_plan_items(int32_t NQ) { return (size_t)SEQ_PLAN_HDR + (((size_t)NQ + 3) & ~(size_t)3); }
+static inline size_t aspd_sequence_plan_lo(int G, int32_t B, int32_t NQ) {
+  return aspd_sequence_plan_items(NQ) + 4 * ((size_t)B + (size_t)NQ / aspd_sequence_qpg(G));
+}
 
 // Compute units of the current device (256 when there is none to ask, as on a build host).
 int aspd_device_cu_count();

@@ -523,8 +523,8 @@ int aspd_choose_variant(const aspd_kv* kv, int32_t B, int32_t NQ, int32_t max_ne
     const bool many_rows = (long)max_new_per_seq * G > 16 * NT_MAX;
     const bool by_rows = (long)NQ * G > 16 * NT_MAX && (many_rows || (chunk_call && max_new_per_seq == 0));
     v->kernel = by_rows ? KERNEL_BF16_ROWS : KERNEL_BF16_STREAM;
-    v->nt = by_rows ? ROWS_NT : tiles;
-    v->rows_cap = by_rows ? ROWS_NW * 16 * ROWS_NT : 16 * tiles;
+    v->nt = by_rows ? 0 : tiles;
+    v->rows_cap = by_rows ? ROWS_NW * 32 : 16 * tiles;
   } else {
     if (G > F32_ROWS) return 0;
     v->kernel = KERNEL_F32;

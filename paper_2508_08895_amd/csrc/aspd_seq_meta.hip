@@ -26,7 +26,8 @@ struct LayoutView {
 };
 
 __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView kv, StateView st, StepView sp,
-                                                                         LayoutView lay, int32_t* __restrict__ plan,
+                                                                         LayoutView lay, int32_t* __restrict__ row_base,
+                                                                         int32_t* __restrict__ row_lo,
                                                                          bool same_seq, bool same_max, int fix_n) {
   __shared__ int run_slot0[ASPD_MAX_RUNS_PER_SEQ + 1];  // first slot of every run; [nr] = tokens of the sequence
   __shared__ int run_pos0[ASPD_MAX_RUNS_PER_SEQ];       // position id of the run's first token
@@ -127,7 +128,6 @@ __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView 
   __syncthreads();
   if (!sh_ok) return;
   const int T = run_slot0[nr];
-  int32_t* row_base = plan + SEQ_PLAN_HDR;
   for (int j = tid; j < T; j += SEQ_META_THREADS) {
     // the run that holds slot j: the last one whose first slot is <= j and that is not empty
     int lo = 0, hi = nr - 1;
@@ -149,6 +149,7 @@ __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView 
     // its stage and its own branch up to itself
     sp.kv_len[row] = b == 0 ? j + 1 : run_base[lo] + t + 1;
     row_base[row] = b == 0 ? j : run_base[lo];
+    row_lo[row] = b == 0 ? j : run_slot0[lo];
     if (st.slot_owner) st.slot_owner[(long)s * st.owner_stride + j] = (uint8_t)b;
   }
 }
@@ -213,9 +214,7 @@ __global__ __launch_bounds__(1024) void sequence_worklist_kernel(const int32_t* 
 
 size_t aspd_sequence_plan_words(const aspd_kv* kv, int32_t B, int32_t NQ) {
   const int G = kv->num_q_heads / kv->num_kv_heads;
-  const int qpg = aspd_sequence_qpg(G);
-  const size_t items = (size_t)B + (size_t)NQ / qpg;
-  return (size_t)SEQ_PLAN_HDR + (((size_t)NQ + 3) & ~(size_t)3) + 4 * items;
+  return aspd_sequence_plan_lo(G, B, NQ) + (((size_t)NQ + 3) & ~(size_t)3);
 }
 
 extern "C" size_t aspd_sequence_plan_bytes(const aspd_kv* kv, int32_t B, int32_t NQ) {
@@ -251,7 +250,8 @@ extern "C" int aspd_build_sequence_meta(const aspd_kv* kv, aspd_state* state, co
   const int qpg = aspd_sequence_qpg(G);
   LayoutView lay{layout->cu_runs_d, layout->run_branch_d, layout->run_len_d};
   hipLaunchKernelGGL(meta_sequence_kernel, dim3(state->B), dim3(SEQ_META_THREADS), 0, hs, make_view(kv), make_view(state),
-                     make_view(out), lay, out->plan_d, mode == ASPD_POS_SAME_SEQ, mode == ASPD_POS_SAME_MAX, fix_n);
+                     make_view(out), lay, out->plan_d + SEQ_PLAN_HDR,
+                     out->plan_d + aspd_sequence_plan_lo(G, state->B, out->NQ), mode == ASPD_POS_SAME_SEQ, mode == ASPD_POS_SAME_MAX, fix_n);
   ASPD_HIP_CHECK(hipGetLastError());
   const int max_items = state->B + out->NQ / qpg;
   hipLaunchKernelGGL(sequence_worklist_kernel, dim3(1), dim3(1024), 0, hs, out->cu_seq_new_d, state->seq_len_d, state->B,

@@ -49,14 +49,6 @@ typedef u32x4 __attribute__((aligned(4))) u32x4_a4;
 __device__ __forceinline__ u32x4 load_tags_uniform(const uint8_t* p /* same in all lanes, 4-byte aligned */) {
   return *(const __attribute__((address_space(4))) u32x4_a4*)(uintptr_t)p;
 }
-// The lane's four keys (4g .. 4g + 3) out of a page's sixteen tags.
-__device__ __forceinline__ uint32_t lane_tags(const u32x4& t, int g) {
-  uint32_t r = t[0];
-  r = (g == 1) ? t[1] : r;
-  r = (g == 2) ? t[2] : r;
-  r = (g == 3) ? t[3] : r;
-  return r;
-}
 // A pointer every lane holds, as a value the compiler knows to be the same in all of them.
 __device__ __forceinline__ const uint8_t* uniform_ptr(const uint8_t* p) {
   const uint64_t v = (uint64_t)p;
@@ -107,7 +99,6 @@ struct RowState {
   f32x4 acc[NT][D / 16];
   float m_run[NT], l_run[NT];
   int slot[NT], tag[NT];
-  int base[NT];  // first slot of the row's own stage (kernels whose rows may belong to different stages)
 };
 
 // Largest of eight scores in four instructions.  Written as assembly because fmaxf() makes the compiler
@@ -135,13 +126,11 @@ __device__ __forceinline__ float max8(const float (&x)[8]) {
 // `stage` holds K page 0, K page 1, V page 0, V page 1 (padded rows), `qtile` the rows' Q (padded rows).
 // kr_even / kr_odd / vu are the lane's LDS bases (see the caller).  KB k-steps of K and VB d-tiles of
 // V are fetched from LDS at a time: large batches hide the LDS latency, small ones save registers.
-// QREG: the rows' Q operands come from registers (qr[n * KSTEPS + t]) instead of `qtile`.
-// ROWBASE: every row brings the first slot of its own stage (ts.base) instead of the common `L`.
-template <int D, int NT, int KB, int VB, bool QREG = false, bool ROWBASE = false>
+template <int D, int NT, int KB, int VB>
 __device__ __forceinline__ void pair_compute(const u32x4* stage, const u32x4* qtile, RowState<D, NT>& ts,
                                              int kr_even, int kr_odd, const int (&vu)[4], int g, int L,
                                              int mask_from, int P0, bool second_valid, uint32_t own0,
-                                             uint32_t own1, float scale_log2, const bf16x8* qr = nullptr) {
+                                             uint32_t own1, float scale_log2) {
   using C = Bf16Cfg<D>;
     // ---- S^T = K Q^T for both pages.  LDS operands are fetched KB k-steps (VB d-tiles below) at a
     // time: large batches hide the LDS latency, small ones leave registers to wide row groups.
@@ -165,7 +154,7 @@ __device__ __forceinline__ void pair_compute(const u32x4* stage, const u32x4* qt
 #pragma unroll
         for (int tt = 0; tt < KB; ++tt) {
           const int kr = (((t0 + tt) & 1) ? kr_odd : kr_even) + 8 * ((t0 + tt) >> 1);
-          const bf16x8 qb = QREG ? qr[n * C::KSTEPS + t0 + tt] : *(const bf16x8*)&qtile[16 * n * C::LROW + kr];
+          const bf16x8 qb = *(const bf16x8*)&qtile[16 * n * C::LROW + kr];
           st[0][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[tt], qb, st[0][n], 0, 0, 0);
           st[1][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kb[tt], qb, st[1][n], 0, 0, 0);
         }
@@ -207,8 +196,7 @@ __device__ __forceinline__ void pair_compute(const u32x4* stage, const u32x4* qt
         for (int e = 0; e < 8; ++e) {
           const int jk = slot0 + (e & 3) + (e >> 2) * ASPD_BLOCK;
           const int own = (int)(((e < 4 ? own0 : own1) >> (8 * (e & 3))) & 0xff);
-          const int stage_first = ROWBASE ? ts.base[n] : L;
-          bool vis = (jk <= ts.slot[n]) && (jk < stage_first || ts.tag[n] == 0 || own == ts.tag[n]);
+          bool vis = (jk <= ts.slot[n]) && (jk < L || ts.tag[n] == 0 || own == ts.tag[n]);
           if (e >= 4 && !second_valid) vis = false;
           sc[e] = vis ? sc[e] : -INFINITY;
         }
@@ -263,123 +251,6 @@ __device__ __forceinline__ void pair_compute(const u32x4* stage, const u32x4* qt
       }
     }
 #undef ASPD_V_UNIT
-}
-
-// ---------------------------------------------------------------------------------------------
-// A staged group of PPS pairs of pages that every row of the wave sees in full (keys of the prefix and of
-// earlier stages: most of a long context).  No mask, no owner tags, and straight-line code but for one rarely
-// taken branch per group: all score products first, then one test whether any row's softmax reference must
-// be raised (the lazy reference of pair_compute, against the largest score of the whole group), then the
-// weights and second products of all pairs.  Counters on the general path show the row-splitting kernel
-// bound by the number of instructions a wave issues per pair (about 240, of which 32 MFMA), not by a
-// pipeline: this form issues about a third fewer.
-// ---------------------------------------------------------------------------------------------
-template <int D, int NT, int PPS>
-__device__ __forceinline__ void group_compute_open(const u32x4* stage, RowState<D, NT>& ts, int kr_even, int kr_odd,
-                                                   const int (&vu)[4], float scale_log2, const bf16x8* qr) {
-  using C = Bf16Cfg<D>;
-  // LDS operands are fetched a whole pair at a time and one step ahead of their use (the K pages of the next
-  // pair before the score products of this one, the V pages of a pair before its weights are computed), so
-  // that a wave waits for LDS once per phase and not once per MFMA.
-  auto fetch_k = [&](const u32x4* sp, bf16x8 (&k)[2][C::KSTEPS]) {
-#pragma unroll
-    for (int t = 0; t < C::KSTEPS; ++t) {
-      const int kr = ((t & 1) ? kr_odd : kr_even) + 8 * (t >> 1);
-      k[0][t] = *(const bf16x8*)&sp[0 * C::LPAGE_U4 + kr];
-      k[1][t] = *(const bf16x8*)&sp[1 * C::LPAGE_U4 + kr];
-    }
-  };
-  auto fetch_v = [&](const u32x4* sp, bf16x8 (&v)[C::MT]) {
-    const s16x4* vs0 = (const s16x4*)(sp + 2 * C::LPAGE_U4);
-    const s16x4* vs1 = (const s16x4*)(sp + 3 * C::LPAGE_U4);
-#pragma unroll
-    for (int mt = 0; mt < C::MT; ++mt) {
-      const int unit = vu[mt & 3] + 16 * (mt >> 2);
-      const s16x4 va = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vs0 + unit));
-      const s16x4 vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vs1 + unit));
-      s16x8 v8;
-      v8[0] = va[0]; v8[1] = va[1]; v8[2] = va[2]; v8[3] = va[3];
-      v8[4] = vb[0]; v8[5] = vb[1]; v8[6] = vb[2]; v8[7] = vb[3];
-      v[mt] = __builtin_bit_cast(bf16x8, v8);
-    }
-  };
-  f32x4 st[PPS][2][NT];
-  {
-    bf16x8 kop[2][2][C::KSTEPS];
-    fetch_k(stage, kop[0]);
-#pragma unroll
-    for (int h = 0; h < PPS; ++h) {
-      if (h + 1 < PPS) fetch_k(stage + (h + 1) * 4 * C::LPAGE_U4, kop[(h + 1) & 1]);
-#pragma unroll
-      for (int n = 0; n < NT; ++n) st[h][0][n] = st[h][1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < C::KSTEPS; ++t) {
-#pragma unroll
-        for (int n = 0; n < NT; ++n) {
-          st[h][0][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[h & 1][0][t], qr[n * C::KSTEPS + t], st[h][0][n], 0, 0, 0);
-          st[h][1][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[h & 1][1][t], qr[n * C::KSTEPS + t], st[h][1][n], 0, 0, 0);
-        }
-      }
-    }
-  }
-  bf16x8 vop[C::MT];
-  fetch_v(stage, vop);
-  // ---- the rows' references against the largest score of the group
-  float mx[NT];
-  bool up = false;
-#pragma unroll
-  for (int n = 0; n < NT; ++n) {
-#pragma unroll
-    for (int h = 0; h < PPS; ++h) {
-      float sc[8];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        sc[e] = st[h][0][n][e];
-        sc[4 + e] = st[h][1][n][e];
-      }
-      const float m8 = max8(sc);
-      mx[n] = (h == 0) ? m8 : fmaxf(mx[n], m8);
-    }
-    mx[n] *= scale_log2;  // scale > 0: the maximum commutes with it
-    up |= mx[n] > ts.m_run[n] + LAZY;
-  }
-  if (__any(up)) {
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-      float m = mx[n];
-      m = fmaxf(m, __shfl_xor(m, 16));
-      m = fmaxf(m, __shfl_xor(m, 32));
-      const float m_new = fmaxf(ts.m_run[n], m);
-      const float alpha = __builtin_amdgcn_exp2f(ts.m_run[n] - exp2_safe_ref(m_new));
-      ts.m_run[n] = m_new;
-      ts.l_run[n] *= alpha;
-#pragma unroll
-      for (int mt = 0; mt < C::MT; ++mt) ts.acc[n][mt] *= alpha;
-    }
-  }
-  // ---- weights and second products
-#pragma unroll
-  for (int h = 0; h < PPS; ++h) {
-    bf16x8 p[NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) {
-      const float neg_ref = -exp2_safe_ref(ts.m_run[n]);
-      float psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float w = __builtin_amdgcn_exp2f(fmaf(st[h][e >> 2][n][e & 3], scale_log2, neg_ref));
-        psum += w;
-        p[n][e] = (__bf16)w;
-      }
-      ts.l_run[n] += psum;
-    }
-#pragma unroll
-    for (int mt = 0; mt < C::MT; ++mt) {
-#pragma unroll
-      for (int n = 0; n < NT; ++n) ts.acc[n][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop[mt], p[n], ts.acc[n][mt], 0, 0, 0);
-    }
-    if (h + 1 < PPS) fetch_v(stage + (h + 1) * 4 * C::LPAGE_U4, vop);
-  }
 }
 
 }  // namespace

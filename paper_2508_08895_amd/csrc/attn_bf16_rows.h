@@ -6,105 +6,200 @@
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// bf16, many rows per KV head (branch chunks): the waves of a workgroup split the ROWS instead of
-// the keys.  Every group of ROWS_PPS pairs of pages is loaded once per workgroup, cooperatively, into a
-// double-buffered LDS stage that all waves read; each wave keeps its own 16*NT rows (Q operands,
-// accumulators, softmax state, all in registers) for the whole segment, so there is no reduction
-// across waves.  One barrier per group.  With NW waves a row group holds NW * 16 * NT rows, and the pages of a KV head
-// are fetched once per that many rows.  The product per pair is compute-bound here (rows x 32 keys x
-// D on the MFMA units, the softmax on the vector ALU, the operands out of LDS), which is why the
-// waves share the loads rather than the keys.  Measured: 8 waves of 32 rows beat 8 of 48 (whose Q
-// operands no longer fit in registers) and 4 of 64 (one wave per SIMD overlaps nothing).
-// A wave skips the arithmetic for pairs that none of its rows can see (the chunks and earlier
-// tokens of other branches).  The groups of a window that lie wholly below everything a wave's rows must
-// mask (the prefix, earlier stages) are taken first, in a loop of their own without tags, masks or
-// per-pair tests: the kernel's time follows the number of instructions a wave issues per pair.
+// bf16, many rows per KV head (branch chunks, prefills, whole sequences): the waves of a workgroup split
+// the ROWS instead of the keys.  Every group of ROWS_PPS pairs of pages is loaded once per workgroup,
+// cooperatively and straight into LDS, three groups ahead, for all waves to read; each wave keeps its own 32 rows
+// (Q operands, accumulators, softmax state, all in registers) for the whole segment, so there is no
+// reduction across waves.  One barrier per group.  With NW waves a row group holds NW * 32 rows, and the
+// pages of a KV head are fetched once per that many rows.
+//
+// What bounds it is the issue slots of a SIMD (two waves): MFMA and vector instructions of both waves go
+// through them.  So the products run on 32x32x16 MFMA tiles (half the MFMA instructions of 16x16x32 at the
+// same rate, and one softmax row per lane instead of two), the running reference is tested on the sum of the
+// weights (which is needed anyway) instead of on a maximum of the scores, and the pair loop is pipelined: a
+// step issues the score products of pair p + 1 and the value products of pair p - 1, which depend on nothing
+// in it, beside the softmax of pair p, so that a wave by itself keeps the matrix unit and the vector unit
+// busy together.  Measured against 16x16x32 tiles without the pipeline: 64 whole sequences (18.8 TFLOP) 22.1 -> 20.8 ms,
+// where the matrix unit's share of the cycles went from 41 % to 53 % and the shader clock from 1.91 to 1.58 GHz (the
+// launch runs into the power limit); prompts of 90 to 2000 tokens 403 -> 225 us a layer.
+//
+// 32x32x16 layout: S^T[key][row] = K * Q^T, lane (c, h) = (lane % 32, lane / 32) holds, of row c, the keys
+// 8 b + 4 h + j (b, j = 0 .. 3) of the pair, which is the B-operand layout of O^T[d][row] = V^T * P^T when the
+// eight keys of a lane's k-slice are taken in that order; V^T comes from the LDS transpose read.
 // ---------------------------------------------------------------------------------------------
-template <int D, int NT, int NW>
-size_t rows_smem_bytes() {
-  return 2 * ROWS_PPS * Bf16Cfg<D>::STAGE_BYTES + (BLK_WIN + 4) * 4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+template <int D>
+struct RowsCfg {
+  static constexpr int CH = D / 8;          // 16-byte chunks per row
+  static constexpr int PAGE_U4 = 16 * CH;
+  static constexpr int KSTEPS = D / 16;     // k-steps of the score product
+  static constexpr int MT = D / 32;         // 32-wide d-tiles of the value product
+  static constexpr int PAGE_B = PAGE_U4 * 16;
+  static constexpr int PAIR_B = 2 * PAGE_B;               // both pages of a pair: 32 consecutive rows
+  static constexpr int STAGE_B = 2 * ROWS_PPS * PAIR_B;   // K pairs, then V pairs
+  // Pages lie in LDS as they do in the cache (they are loaded straight into it, 64 x 16 bytes in a row per
+  // instruction), but for the order of the 16-byte chunks inside a row, which is chosen so that no read has a bank
+  // conflict: a K operand read takes one chunk of sixteen rows at a time, a transposing V read 64 bytes of four.
+  static __device__ __forceinline__ int kswz(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+  static __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+};
+constexpr int ROWS_BUFS = 4;  // groups in LDS: the one being computed, three on their way
+
+template <int D>
+constexpr size_t rows_smem_bytes() { return (size_t)ROWS_BUFS * RowsCfg<D>::STAGE_B; }
+
+// Sixteen bytes per lane from global memory straight into LDS: lane l's go to byte lds + 16 l.  (Assembly because
+// the compiler makes every later LDS read wait for all such loads in flight; rows_wait() says which have to be
+// there.  It reads no vector register but the offset, and writes none.)
+__device__ __forceinline__ void load_to_lds(const void* base /* uniform */, uint32_t offset, uint32_t lds /* uniform */) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+}
+
+// One wave's 32 rows: lane (c, h) keeps the statistics of row c (its share of the sum) and O^T[32 mt + 8 b + 4 h +
+// j][c] in acc[mt][4 b + j].
+template <int D>
+struct Rows32 {
+  f32x16 acc[D / 32];
+  float m_run, l_run;
+  float neg_ref;  // minus the running reference, 0 while there is none
+  float limit;    // weight sum above which the references are raised: below any sum while a row of the wave has none
+};
+
+// Largest weight sum of a lane's sixteen keys before the row's reference is raised (see rows_raise).
+constexpr float ROWS_SUM_MAX = 1024.f;
+
+// LDS operands by byte address.
+__device__ __forceinline__ bf16x8 rows_k_operand(uint32_t at) {
+  return *(const __attribute__((address_space(3))) bf16x8*)at;
+}
+template <int D>
+__device__ __forceinline__ bf16x8 rows_v_operand(uint32_t at) {
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at + 8 * D * 2));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Weights of one pair against the rows' lazily raised references (log2 domain, scaled scores; a reference is
+// not necessarily the row maximum).  The weights are computed first and their sum, which the row needs anyway,
+// tells whether a reference has to go up: while no lane's sixteen weights sum to more than ROWS_SUM_MAX none of
+// them exceeds it, which is harmless in fp32 and in the bf16 operand, whose precision is relative.  Otherwise, and
+// while a row of the wave has no reference, the references are raised to the largest score so far, the accumulators
+// rescaled and the weights formed again.  (Testing the sum costs one comparison per pair; the maximum it replaces
+// cost eight instructions and the wait states in front of them.)
+template <int D>
+__device__ __forceinline__ float rows_weights(const f32x16& s, const Rows32<D>& rs, bf16x8 (&p)[2], float scale_log2) {
+  float sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float w = __builtin_amdgcn_exp2f(fmaf(s[i], scale_log2, rs.neg_ref));
+    sum += w;
+    p[i >> 3][i & 7] = (__bf16)w;
+  }
+  return sum;
+}
+// The references go up to the largest score so far; returns the sum of the weights formed again.
+template <int D>
+__device__ __forceinline__ float rows_raise(const f32x16& s, Rows32<D>& rs, bf16x8 (&p)[2], float scale_log2) {
+  float lo[8], hi[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    lo[i] = s[i];
+    hi[i] = s[8 + i];
+  }
+  float mx = fmaxf(max8(lo), max8(hi));
+  mx = fmaxf(mx, __shfl_xor(mx, 32)) * scale_log2;  // scale > 0: the maximum commutes with it
+  const float m_new = fmaxf(rs.m_run, mx);
+  const float ref = exp2_safe_ref(m_new);
+  const float alpha = __builtin_amdgcn_exp2f(rs.m_run - ref);
+  rs.m_run = m_new;
+  rs.neg_ref = -ref;
+  rs.l_run *= alpha;
+#pragma unroll
+  for (int mt = 0; mt < D / 32; ++mt) rs.acc[mt] *= alpha;
+  rs.limit = __any(m_new == -INFINITY) ? -1.f : ROWS_SUM_MAX;
+  return rows_weights<D>(s, rs, p, scale_log2);
 }
 
 // SEQ: the rows are tokens of a whole multi-stage sequence (aspd_attn_full_sequence): each brings the first
-// slot of its own stage (a.row_base) and its branch number within that stage; otherwise all rows belong to
-// the sequence's running stage, which starts at it.L.
-template <int D, int NT, int NW, bool SEQ = false>
+// slot of its own stage (a.row_base) and the first slot of its own branch there (a.row_lo), which are all of
+// what it sees: [0, base) and [lo, slot].  Otherwise all rows belong to the sequence's running stage, which
+// starts at it.L, and owner tags tell whose a slot of that stage is.
+template <int D, int NW, bool SEQ = false>
 __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool complete, float* pslot) {
-  using C = Bf16Cfg<D>;
-  constexpr int ROWS = 16 * NT;        // rows per wave
+  using C = RowsCfg<D>;
   constexpr int THREADS = NW * 64;
-  constexpr int PPS = ROWS_PPS;          // pairs per stage: all of them are staged, then computed, between two barriers
-  constexpr int ARR = 4 * PPS;           // page arrays of a stage: K0 K1 V0 V1 of every pair
-  constexpr int PER_PAGE = THREADS / ARR;  // threads that share the load of one page
-  static_assert(THREADS % ARR == 0 && C::PAGE_U4 % PER_PAGE == 0, "page not divisible among its loaders");
-  constexpr int LPT = C::PAGE_U4 / PER_PAGE;  // 16-byte loads per thread and page
+  constexpr int PPS = ROWS_PPS;
+  static_assert(PPS == 2 && NW == 4 * PPS, "one wave per page of a group");
+  constexpr int LPT = C::PAGE_U4 / 64;      // 16-byte loads per lane and page
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = lane & 15;
-  const int g = lane >> 4;
+  const int c = lane & 31;
+  const int h = lane >> 5;
   const int R = it.nq * a.G;                       // rows of the whole row group
   const int page0 = it.page0, page1 = it.page1;
-  const int Rw = min(ROWS, R - wave * ROWS);       // rows this wave owns (<= 0: none)
+  const int Rw = min(32, R - wave * 32);           // rows this wave owns (<= 0: none)
   const bool wave_active = Rw > 0;
 
-  u32x4* stage0 = (u32x4*)smem;                 // [2][PPS][K0 K1 V0 V1]
-  int* blk_lds = (int*)(smem + 2 * PPS * C::STAGE_BYTES);
-
-  const int* bt = a.kv.block_tables + (long)it.s * a.kv.max_blocks_per_seq;
-  const uint8_t* owner_row = a.slot_owner ? uniform_ptr(a.slot_owner + (long)it.s * a.owner_stride) : nullptr;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;  // [ROWS_BUFS] stages
+  typedef const __attribute__((address_space(4))) int32_t* const_i32;  // (block tables: no kernel writes them)
+  const const_i32 bt = (const_i32)(uintptr_t)(a.kv.block_tables + (long)it.s * a.kv.max_blocks_per_seq);
+  const uint8_t* owner_row = (!SEQ && a.slot_owner) ? uniform_ptr(a.slot_owner + (long)it.s * a.owner_stride) : nullptr;
   // The rows of a group are packed in the order of their slots: the last row's slot bounds what any row
   // of the group may see.  Slots past it have never been written (the tail of the last page) and may hold
   // anything; their V rows are cleared on the way into LDS (zero weight times a NaN would be a NaN).
   const int last_slot = __builtin_amdgcn_readfirstlane(a.logical_slot[it.q0 + it.nq - 1]);
 
-  // ---- start-up: block ids of the first window; this wave's Q operands and row descriptors go
-  // straight to registers (lane (c, g) holds, of row c of every tile, the 16-byte pieces 4t + g)
-  constexpr int BPT = BLK_WIN / THREADS;
-  int blkreg[BPT];
+  // Pairs of pages of the segment, numbered without the ones no row of the group sees: whole sequences lay a
+  // stage's branches one after the other, so between the start of a stage and the first branch that the group
+  // has rows in lies a run of sibling tokens.
+  int npairs = (page1 - page0 + 1) >> 1;
+  int hole_at = npairs, hole = 0;
+  if (SEQ) {
+    const int b0 = a.row_base[it.q0], b1 = a.row_base[it.q0 + it.nq - 1], lo0 = a.row_lo[it.q0];
+    if (b0 == b1) {
+      const int from = (b0 + 31) >> 5, to = min(lo0 >> 5, npairs);
+      if (to > from) {
+        hole_at = __builtin_amdgcn_readfirstlane(from);
+        hole = __builtin_amdgcn_readfirstlane(to - from);
+      }
+    }
+    npairs -= hole;
+  }
+  auto page_of_pair = [&](int p) -> int { return page0 + 2 * (p < hole_at ? p : p + hole); };
+
+  // ---- this wave's Q operands and row descriptors go straight to registers
+  bf16x8 qr[C::KSTEPS];
+  int slot, tag = 0, base, lo = 0;
+  {
+    const int rr = min(wave * 32 + c, R - 1);  // padding rows (and idle waves) repeat the last row
+    const int q = it.q0 + rr / a.G;
+    const int head = it.h * a.G + rr % a.G;
+    const u32x4* qsrc = (const u32x4*)a.q + ((long)q * a.kv.num_q_heads + head) * C::CH + h;
 #pragma unroll
-  for (int k = 0; k < BPT; ++k) blkreg[k] = bt[min(page0 + tid + k * THREADS, page1 - 1)];
-  RowState<D, NT> ts;
-  bf16x8 qr[NT * C::KSTEPS];
+    for (int t = 0; t < C::KSTEPS; ++t) qr[t] = __builtin_bit_cast(bf16x8, qsrc[2 * t]);
+    slot = a.logical_slot[q];
+    if (SEQ) {
+      // (no owner tags: the shared mask, every row is treated like a main-branch row)
+      base = a.slot_owner ? a.row_base[q] : slot;
+      lo = a.slot_owner ? a.row_lo[q] : slot;
+    } else {
+      const int qb = a.q_branch[q];
+      tag = (qb < 0 || !a.cu_branches) ? 0 : qb - a.cu_branches[it.s] + 1;
+      base = it.L;
+    }
+  }
   // What the wave's rows have in common decides which pairs need a mask and which can be left out:
   //   mask_from  every key below this slot is visible to every row (below every row's stage and slot);
   //   slot_hi    no key above this slot is visible to any row;
   //   base_hi    the latest stage start among the rows.  A row of an earlier stage lies below it, so keys
   //              from base_hi on are visible, if at all, only to the rows of that latest stage, and only
-  //              where their branch tags match: [tag_lo, tag_hi] is the range of those rows' tags.
-  int mask_from = 0x7fffffff, slot_hi = 0, base_hi = 0;
+  //              from their branches: [own_lo, own_hi] is the range of those rows' tags, or own_lo the first
+  //              slot any of their branches starts at.
+  int mask_from = min(slot, base), slot_hi = slot, base_hi = base;
 #pragma unroll
-  for (int n = 0; n < NT; ++n) {
-    const int rr = min(wave * ROWS + 16 * n + c, R - 1);  // padding rows (and idle waves) repeat the last row
-    const int q = it.q0 + rr / a.G;
-    const int head = it.h * a.G + rr % a.G;
-    const u32x4* qsrc = (const u32x4*)a.q + ((long)q * a.kv.num_q_heads + head) * C::CH + g;
-#pragma unroll
-    for (int t = 0; t < C::KSTEPS; ++t) qr[n * C::KSTEPS + t] = __builtin_bit_cast(bf16x8, qsrc[4 * t]);
-    ts.slot[n] = a.logical_slot[q];
-    const int qb = a.q_branch[q];
-    if (SEQ) {
-      // (no owner tags: the shared mask, every row is treated like a main-branch row)
-      ts.tag[n] = a.slot_owner ? max(qb, -1) + 1 : 0;
-      ts.base[n] = a.slot_owner ? a.row_base[q] : ts.slot[n];
-    } else {
-      ts.tag[n] = (qb < 0 || !a.cu_branches) ? 0 : qb - a.cu_branches[it.s] + 1;
-      ts.base[n] = it.L;
-    }
-    mask_from = min(mask_from, min(ts.slot[n], ts.base[n]));
-    slot_hi = max(slot_hi, ts.slot[n]);
-    base_hi = max(base_hi, ts.base[n]);
-    ts.m_run[n] = -INFINITY;
-    ts.l_run[n] = 0.f;
-#pragma unroll
-    for (int mt = 0; mt < C::MT; ++mt) ts.acc[n][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  __syncthreads();  // LDS of the previous segment is free
-#pragma unroll
-  for (int k = 0; k < BPT; ++k) blk_lds[tid + k * THREADS] = min(max(blkreg[k], 0), a.kv.num_blocks - 1);
-  __syncthreads();
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
+  for (int off = 1; off < 32; off <<= 1) {
     mask_from = min(mask_from, __shfl_xor(mask_from, off));
     slot_hi = max(slot_hi, __shfl_xor(slot_hi, off));
     base_hi = max(base_hi, __shfl_xor(base_hi, off));
@@ -112,183 +207,330 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   mask_from = __builtin_amdgcn_readfirstlane(mask_from);
   slot_hi = __builtin_amdgcn_readfirstlane(slot_hi);
   base_hi = __builtin_amdgcn_readfirstlane(base_hi);
-  int tag_lo = 0x7fffffff, tag_hi = 0;
+  int own_lo = base == base_hi ? (SEQ ? lo : tag) : 0x7fffffff;
+  int own_hi = base == base_hi ? tag : 0;
 #pragma unroll
-  for (int n = 0; n < NT; ++n) {
-    if (ts.base[n] == base_hi) {
-      tag_lo = min(tag_lo, ts.tag[n]);
-      tag_hi = max(tag_hi, ts.tag[n]);
-    }
+  for (int off = 1; off < 32; off <<= 1) {
+    own_lo = min(own_lo, __shfl_xor(own_lo, off));
+    own_hi = max(own_hi, __shfl_xor(own_hi, off));
   }
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    tag_lo = min(tag_lo, __shfl_xor(tag_lo, off));
-    tag_hi = max(tag_hi, __shfl_xor(tag_hi, off));
-  }
-  tag_lo = __builtin_amdgcn_readfirstlane(tag_lo);
-  tag_hi = __builtin_amdgcn_readfirstlane(tag_hi);
+  own_lo = __builtin_amdgcn_readfirstlane(own_lo);
+  own_hi = __builtin_amdgcn_readfirstlane(own_hi);
 
-  // LDS bases of this lane (same layout as the streaming kernel)
-  const int kr_even = lds_pos<D>(c, g);
-  const int kr_odd = lds_pos<D>(c, 4 + g);
-  const int vkey = 4 * g + (c >> 2);
-  int vu[4];
+  Rows32<D> rs;
+  rs.m_run = -INFINITY;
+  rs.l_run = 0.f;
+  rs.neg_ref = 0.f;
+  rs.limit = -1.f;
 #pragma unroll
-  for (int b = 0; b < 4; ++b) vu[b] = vkey * (2 * C::LROW) + 4 * b + (c & 3);
-  // cooperative load: PER_PAGE threads share one page array, consecutive threads consecutive 16 bytes
-  const int lpage = tid / PER_PAGE;          // pair lpage / 4 of the group, array lpage % 4: K0, K1, V0, V1
-  const int lt = tid - lpage * PER_PAGE;
-  const bool l_is_k = (lpage & 3) < 2;
-  int lpos[LPT];                             // positions inside the page in LDS
+  for (int mt = 0; mt < C::MT; ++mt)
 #pragma unroll
-  for (int k = 0; k < LPT; ++k) {
-    const int i = lt + k * PER_PAGE;         // chunk index inside the page
-    const int row = i / C::CH, ch = i - row * C::CH;
-    lpos[k] = lds_pos<D>(row, ch);
-  }
+    for (int i = 0; i < 16; ++i) rs.acc[mt][i] = 0.f;
 
-  u32x4 nxt[LPT];  // this thread's slice of the group on its way
-  for (int wbase = page0; wbase < page1; wbase += BLK_WIN) {  // windows of block ids; normally one
-    const int wend = min(page1, wbase + BLK_WIN);
-    const int wpages = wend - wbase;
-    const int npairs = (wpages + 1) >> 1;
-    const int ngroups = (npairs + PPS - 1) / PPS;
-    if (wbase != page0) {
-      __syncthreads();
+  // LDS addresses of this lane in the stage of the current group (next_group moves them on): K operand of k-step t (row
+  // c, chunk 2 t + h), V operand of d-tile mt (key 4 h + (lane % 16) / 4, then the same plus 8; d 32 mt + 16 (lane / 16
+  // % 2) + 4 (lane % 4))
+  uint32_t ka[C::KSTEPS], va[C::MT];
+  {
+    const uint32_t first = lds0 + (ROWS_BUFS - 1) * C::STAGE_B;  // group -1
 #pragma unroll
-      for (int k = 0; k < BPT; ++k)
-        blk_lds[tid + k * THREADS] = min(max(bt[min(wbase + tid + k * THREADS, page1 - 1)], 0), a.kv.num_blocks - 1);
-      __syncthreads();
+    for (int t = 0; t < C::KSTEPS; ++t) ka[t] = first + c * (D * 2) + (((2 * t + h) ^ C::kswz(c)) << 4);
+    const int key = 4 * h + ((lane & 15) >> 2);
+#pragma unroll
+    for (int mt = 0; mt < C::MT; ++mt)
+      va[mt] = first + PPS * C::PAIR_B + key * (D * 2) +
+               (((4 * mt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ C::vswz(key)) << 4) + 8 * (lane & 1);
+  }
+  auto buffer_of = [&](int i) -> int { return i & (ROWS_BUFS - 1); };
+  auto next_group = [&](int i) {  // from group i's stage to the next
+    const int d = buffer_of(i) == ROWS_BUFS - 1 ? -(ROWS_BUFS - 1) * C::STAGE_B : C::STAGE_B;
+#pragma unroll
+    for (int t = 0; t < C::KSTEPS; ++t) ka[t] += d;
+#pragma unroll
+    for (int mt = 0; mt < C::MT; ++mt) va[mt] += d;
+  };
+  auto k_operand = [&](int u, int t) { return rows_k_operand(ka[t] + u * C::PAIR_B); };
+  auto v_operand = [&](int u, int j) { return rows_v_operand<D>(va[j % C::MT] + u * C::PAIR_B + (j / C::MT) * C::PAGE_B); };
+
+  // ---- staging.  Group i holds the K pages of pairs 2 i + 1 and 2 i + 2 and the V pages of pairs 2 i - 1 and
+  // 2 i (what the two steps of the group multiply); wave w fetches one page of it.  Pairs outside the segment
+  // are fetched as the nearest one inside and not used.
+  const bool l_is_k = wave < 4;
+  const int l_pair = (wave >> 1) & 1;
+  const int n_last = npairs - 1;
+  auto page_of_group = [&](int i) -> int {
+    const int p = min(max(2 * i + l_pair + (l_is_k ? 1 : -1), 0), n_last);
+    return min(page_of_pair(p) + (wave & 1), page1 - 1);
+  };
+  const char* const pool = (const char*)(l_is_k ? a.kv.k : a.kv.v) + (long)it.h * C::PAGE_B;
+  const uint32_t l_at = lds0 + (l_is_k ? 0 : PPS * C::PAIR_B) + l_pair * C::PAIR_B + (wave & 1) * C::PAGE_B;
+  // Which 16 bytes of its page the lane fetches with the first load; with the k-th, 1024 k bytes on, and with the
+  // chunk order of the rows there (bit 2 of a K row's order changes with every load).
+  uint32_t goff;
+  {
+    const int row = lane / C::CH;
+    goff = row * (D * 2) + ((lane % C::CH ^ (l_is_k ? C::kswz(row) : C::vswz(row))) << 4);
+  }
+  const uint32_t goff_flip = l_is_k ? 64 : 0;
+
+  // owner tags of a group's K pairs that reach into the branch region
+  auto tags_of = [&](int i, u32x4 (&t)[PPS][2]) {
+    if (SEQ || !owner_row) return;
+#pragma unroll
+    for (int u = 0; u < PPS; ++u) {
+      const int p = 2 * i + 1 + u;
+      const int P = page0 + 2 * p;
+      if (p >= 0 && p < npairs && (P + 2) * ASPD_BLOCK > mask_from) {
+        t[u][0] = load_tags_uniform(owner_row + P * ASPD_BLOCK);
+        t[u][1] = load_tags_uniform(owner_row + min(P + 1, page1 - 1) * ASPD_BLOCK);  // stays inside the owner row
+      }
     }
-    // the page (of the window) this thread loads for group gi; past the end of the window the last pages
-    // again, which the caches hold
-    auto page_of = [&](int gi) -> int {
-      const int p = min(gi * PPS + (lpage >> 2), npairs - 1);
-      return min(2 * p + (lpage & 1), wpages - 1);
-    };
-    auto issue = [&](int gi) {
-      const int pg = page_of(gi);
-      const int b = blk_lds[pg];
-      const u32x4* src = (const u32x4*)(l_is_k ? a.kv.k : a.kv.v) + ((long)b * a.kv.num_kv_heads + it.h) * C::PAGE_U4;
+  };
+  auto lane_own = [&](const u32x4 (&t)[2], uint32_t (&own)[4]) {  // the tags of the lane's sixteen keys
 #pragma unroll
-      for (int k = 0; k < LPT; ++k) nxt[k] = src[lt + k * PER_PAGE];
-    };
-    // owner tags of the pairs that reach into the branch region, fetched one group ahead like the pages
-    auto tags_of = [&](int gi, u32x4 (&t)[PPS][2]) {
+    for (int b = 0; b < 4; ++b) own[b] = h ? t[b >> 1][2 * (b & 1) + 1] : t[b >> 1][2 * (b & 1)];
+  };
+  // Whether the wave's rows see pair p at all (bit 0) and whether some of them only in part (bit 1).
+  auto look = [&](int p, const u32x4 (&t)[2]) -> int {
+    if (p < 0 || p >= npairs) return 0;
+    const int P = page_of_pair(p);
+    const int k0 = P * ASPD_BLOCK;
+    if (k0 > slot_hi) return 0;
+    if (k0 + 2 * ASPD_BLOCK <= mask_from && P + 1 < page1) return 1;
+    if (k0 >= base_hi) {  // wholly inside the latest stage: is any key of a branch that the wave has rows in?
+      if (SEQ) {
+        if (k0 + 2 * ASPD_BLOCK <= own_lo) return 0;
+      } else if (owner_row && own_lo > 0) {
+        uint32_t own[4];
+        lane_own(t, own);
+        bool mine = own_lo != own_hi;  // (rows of several branches: taken to see something)
 #pragma unroll
-      for (int h = 0; h < PPS; ++h) {
-        const int P = wbase + 2 * (gi * PPS + h);
-        if (owner_row && P < wend && (P + 2) * ASPD_BLOCK > mask_from) {
-          t[h][0] = load_tags_uniform(owner_row + P * ASPD_BLOCK);
-          t[h][1] = load_tags_uniform(owner_row + min(P + 1, page1 - 1) * ASPD_BLOCK);  // stays inside the owner row
+        for (int b = 0; b < 4; ++b) {  // a zero byte in own ^ tags
+          const uint32_t x = own[b] ^ (0x01010101u * (uint32_t)own_lo);
+          mine |= ((x - 0x01010101u) & ~x & 0x80808080u) != 0;
         }
+        if (!__any(mine)) return 0;
+      }
+    }
+    return 3;
+  };
+
+  f32x16 s0, s1;         // scores of the pair whose weights are next (even, odd)
+  bf16x8 p0[2], p1[2];   // weights of the pair whose value products are next (even, odd)
+  u32x4 tg[PPS][2];      // owner tags of the group's K pairs
+  u32x4 tc[2];           // owner tags of the pair whose weights are next
+  int see_prev = 0, see = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s0[i] = s1[i] = 0.f;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p0[u][i] = p1[u][i] = (__bf16)0.f;
+  tc[0] = tc[1] = u32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int u = 0; u < PPS; ++u) tg[u][0] = tg[u][1] = u32x4{0, 0, 0, 0};
+
+  // Step p (slot u of its group): scores of pair p + 1 (into `s_next`), value products of pair p - 1 (weights `p_prev`),
+  // softmax of pair p.  In a full step all three take part.  Its order is written out, one slot per matrix
+  // instruction, and held by the scheduling barriers: score and value products in turn (neighbours never wait for each
+  // other), LDS operands some products ahead of their use, and in every slot its share of the softmax.  Left to
+  // itself the compiler fetches each operand right before its product, and the wave waits for LDS sixteen times a step.
+  constexpr int NP = C::KSTEPS;  // score products of a pair, and as many value products
+  constexpr int RK = 4, RV = 2;  // score and value products their operands are fetched ahead
+  static_assert(NP == 2 * C::MT && NP % RK == 0 && NP % RV == 0 && 16 % (2 * NP) == 0, "slots of a full step");
+  bf16x8 kf[RK], vf[RV];
+  f32x16 z;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = 0.f;
+  auto fetch_first = [&](int u) {
+#pragma unroll
+    for (int t = 0; t < RK; ++t) kf[t] = k_operand(u, t);
+#pragma unroll
+    for (int t = 0; t < RV; ++t) vf[t] = v_operand(u, t);
+  };
+  // `ahead`: the operands are there, and the first ones of slot 1 are fetched on the way
+  auto step_full = [&](int u, bool ahead, const f32x16& s_cur, f32x16& s_next, const bf16x8 (&p_prev)[2], bf16x8 (&p_cur)[2]) {
+    constexpr int PER = 16 / (2 * NP);  // weights per slot
+    float sum = 0.f;
+    auto weights = [&](int slot_index) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) {
+        const int i = slot_index * PER + e;
+        const float w = __builtin_amdgcn_exp2f(fmaf(s_cur[i], a.scale_log2, rs.neg_ref));
+        sum += w;
+        p_cur[i >> 3][i & 7] = (__bf16)w;
+        // (converted here and not after the test of the sum, where sixteen registers would hold them until then)
+        if ((i & 7) == 7) asm volatile("" : "+v"(p_cur[i >> 3]));
       }
     };
-    issue(0);
-
-    // ---- the leading groups of the window that every row of this wave sees in full (whole pairs below
-    // mask_from): nothing to mask, no tags, nothing to clear (they end below the last row's slot).  The
-    // count differs between the waves of a workgroup; every group costs one barrier in either loop, and
-    // what a wave stages for a group does not depend on the loop it is in.
-    const int g_open = max(0, min(ngroups, (min(wend, mask_from / ASPD_BLOCK) - wbase) / (2 * PPS)));
-    for (int gi = 0; gi < g_open; ++gi) {
-      u32x4* stage = stage0 + (gi & 1) * (PPS * C::STAGE_BYTES / 16);
 #pragma unroll
-      for (int k = 0; k < LPT; ++k) stage[lpage * C::LPAGE_U4 + lpos[k]] = nxt[k];
-      issue(gi + 1);
-      __syncthreads();  // the group is staged; everyone is done with the other buffer's previous group
-      if (wave_active) group_compute_open<D, NT, PPS>(stage, ts, kr_even, kr_odd, vu, a.scale_log2, qr);
+    for (int j = 0; j < NP; ++j) {
+      s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j % RK], qr[j], j == 0 ? z : s_next, 0, 0, 0);
+      if (j + RK < NP) kf[j % RK] = k_operand(u, j + RK);
+      else if (ahead) kf[j % RK] = k_operand(1, j + RK - NP);
+      weights(2 * j);
+      __builtin_amdgcn_sched_barrier(0);
+      rs.acc[j % C::MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[j % RV], p_prev[j / C::MT], rs.acc[j % C::MT], 0, 0, 0);
+      if (j + RV < NP) vf[j % RV] = v_operand(u, j + RV);
+      else if (ahead) vf[j % RV] = v_operand(1, j + RV - NP);
+      weights(2 * j + 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
-
-    // ---- the rest of the window: pairs that may need the mask, the tags, the tail
-    u32x4 tn[PPS][2];
+    return sum;
+  };
+  // The same for pairs that need a mask or are not seen at all, one part after the other.
+  auto step = [&](int p, int u, const u32x4 (&tn)[2], f32x16& s_cur, f32x16& s_next, const bf16x8 (&p_prev)[2],
+                  bf16x8 (&p_cur)[2]) {
+    const int see_next = look(p + 1, tn);
+    if (see_prev) {
 #pragma unroll
-    for (int h = 0; h < PPS; ++h) tn[h][0] = tn[h][1] = u32x4{0, 0, 0, 0};
-    if (g_open < ngroups) tags_of(g_open, tn);
-    for (int gi = g_open; gi < ngroups; ++gi) {
-      u32x4* stage = stage0 + (gi & 1) * (PPS * C::STAGE_BYTES / 16);
-      const int key0 = (wbase + page_of(gi)) * ASPD_BLOCK;  // first slot of the page this thread staged
-      if (!l_is_k && key0 + ASPD_BLOCK > last_slot + 1) {
+      for (int t = 0; t < RV; ++t) vf[t] = v_operand(u, t);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        rs.acc[j % C::MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[j % RV], p_prev[j / C::MT], rs.acc[j % C::MT], 0, 0, 0);
+        if (j + RV < NP) vf[j % RV] = v_operand(u, j + RV);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (see) {
+      if (see & 2) {
+        const int k0 = page_of_pair(p) * ASPD_BLOCK + 4 * h;
+        const int end = min(slot, page1 * ASPD_BLOCK - 1);
+        uint32_t own[4];
+        lane_own(tc, own);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int jk = k0 + 8 * (i >> 2) + (i & 3);
+          const int o = (int)((own[i >> 2] >> (8 * (i & 3))) & 0xff);
+          const bool vis = jk <= end && (jk < base || (SEQ ? jk >= lo : (tag == 0 || o == tag)));
+          s_cur[i] = vis ? s_cur[i] : -INFINITY;
+        }
+      }
+      float sum = rows_weights<D>(s_cur, rs, p_cur, a.scale_log2);
+      if (__any(sum > rs.limit)) sum = rows_raise<D>(s_cur, rs, p_cur, a.scale_log2);
+      rs.l_run += sum;
+    }
+    if (see_next) {
+#pragma unroll
+      for (int t = 0; t < RK; ++t) kf[t] = k_operand(u, t);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j % RK], qr[j], j == 0 ? z : s_next, 0, 0, 0);
+        if (j + RK < NP) kf[j % RK] = k_operand(u, j + RK);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    see_prev = see;
+    see = see_next;
+    tc[0] = tn[0];
+    tc[1] = tn[1];
+  };
+
+  // One barrier per group: every wave has its page of the group in LDS, and is done with the stage that the group three
+  // further on goes to.  The V rows of slots past the last row's are cleared before it.
+  const int i_last = npairs >> 1;
+  int block = 0;  // block id of the group that is sent for next
+  auto send = [&](int i) {
+    if (i > i_last) return;
+    const char* src = pool + (long)min(max(block, 0), a.kv.num_blocks - 1) * a.kv.num_kv_heads * C::PAGE_B;
+#pragma unroll
+    for (int k = 0; k < LPT; ++k) load_to_lds(src + k * 1024, goff ^ (k * goff_flip), l_at + buffer_of(i) * C::STAGE_B + k * 1024);
+    block = bt[page_of_group(i + 1)];
+  };
+  auto arrive = [&](int i, bool tail) {
+    if (i + 2 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPT) : "memory");
+    else if (i + 1 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (tail && !l_is_k) {
+      const int key0 = page_of_group(i) * ASPD_BLOCK;
+      if (key0 + ASPD_BLOCK > last_slot + 1) {
 #pragma unroll
         for (int k = 0; k < LPT; ++k)
-          if (key0 + (lt + k * PER_PAGE) / C::CH > last_slot) nxt[k] = u32x4{0u, 0u, 0u, 0u};
-      }
-#pragma unroll
-      for (int k = 0; k < LPT; ++k) stage[lpage * C::LPAGE_U4 + lpos[k]] = nxt[k];
-      u32x4 tc[PPS][2];
-#pragma unroll
-      for (int h = 0; h < PPS; ++h) {
-        tc[h][0] = tn[h][0];
-        tc[h][1] = tn[h][1];
-      }
-      issue(gi + 1);
-      if (gi + 1 < ngroups) tags_of(gi + 1, tn);
-      __syncthreads();  // the group is staged; everyone is done with the other buffer's previous group
-
-      if (!wave_active) continue;
-#pragma unroll
-      for (int h = 0; h < PPS; ++h) {
-        const int P0 = wbase + 2 * (gi * PPS + h);
-        if (P0 >= wend) break;
-        // keys past the last of this wave's rows (whole sequences only: the rows of a decode or chunk step
-        // sit at the tail of their sequence, and the test costs the chunk launch 3 %)
-        if (SEQ && P0 * ASPD_BLOCK > slot_hi) continue;
-        const bool second_valid = (P0 + 1) < wend;
-        uint32_t own0 = 0, own1 = 0;
-        if (owner_row && (P0 + 2) * ASPD_BLOCK > mask_from) {
-          own0 = lane_tags(tc[h][0], g);
-          own1 = lane_tags(tc[h][1], g);
-          // pairs wholly inside the latest stage: skip if no key belongs to a branch of this wave's rows there
-          if (P0 * ASPD_BLOCK >= base_hi && tag_lo > 0) {
-            bool mine = false;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const int own = (int)(((e < 4 ? own0 : own1) >> (8 * (e & 3))) & 0xff);
-              mine |= (own >= tag_lo && own <= tag_hi);
-            }
-            if (!__any(mine)) continue;
-          }
-        }
-        constexpr int KB = 2;
-        constexpr int VB = 4;
-        pair_compute<D, NT, KB, VB, true, true>(stage + h * 4 * C::LPAGE_U4, nullptr, ts, kr_even, kr_odd, vu, g, 0,
-                                                mask_from, P0, second_valid, own0, own1, a.scale_log2, qr);
+          if (key0 + (64 * k + lane) / C::CH > last_slot)
+            *(__attribute__((address_space(3))) u32x4*)(l_at + buffer_of(i) * C::STAGE_B + k * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
       }
     }
+    __syncthreads();
+    send(i + 3);
+  };
+  auto general_groups = [&](int from, int to) {
+    for (int i = from; i < to; ++i) {
+      tags_of(i, tg);
+      arrive(i, true);
+      if (wave_active) {
+        if (i >= 0) step(2 * i, 0, tg[0], s0, s1, p1, p0);
+        step(2 * i + 1, 1, tg[1], s1, s0, p0, p1);
+      }
+      next_group(i);
+    }
+  };
+  // Groups whose two steps touch only pairs that every row of this wave sees in full (the leading pairs that lie
+  // below mask_from): pairs 2 i - 1 .. 2 i + 2.  The range differs between the waves of a workgroup; every group
+  // costs one barrier and is staged the same way in either kind of step.
+  const int open_pairs = min(hole_at, (min(page1, mask_from / ASPD_BLOCK) - page0) >> 1);
+  const int i_open = wave_active ? (open_pairs - 1) >> 1 : 0;  // 2 i + 2 <= open_pairs - 1
+  __syncthreads();  // LDS of the previous segment is free
+  block = bt[page_of_group(-1)];
+#pragma unroll 1
+  for (int i = -1; i < 2; ++i) send(i);
+  general_groups(-1, 0);  // (the scores of pair 0)
+  int i = 0;
+  if (i_open > 0) {
+    for (; i < i_open; ++i) {
+      arrive(i, false);
+      fetch_first(0);
+      float sum = step_full(0, true, s0, s1, p1, p0);
+      if (__any(sum > rs.limit)) sum = rows_raise<D>(s0, rs, p0, a.scale_log2);
+      rs.l_run += sum;
+      sum = step_full(1, false, s1, s0, p0, p1);
+      if (__any(sum > rs.limit)) sum = rows_raise<D>(s1, rs, p1, a.scale_log2);
+      rs.l_run += sum;
+      next_group(i);
+    }
+    see_prev = 1;
+    tags_of(i - 1, tg);
+    see = look(2 * i, tg[1]);
+    tc[0] = tg[1][0];
+    tc[1] = tg[1][1];
   }
+  general_groups(i, i_last + 1);
 
   // ---- every wave writes its own rows
   if (!wave_active) return;
+  rs.l_run += __shfl_xor(rs.l_run, 32);
+  const int r = wave * 32 + c;  // row inside the row group
+  if (c >= Rw) return;
+  if (complete) {
+    const int q = it.q0 + r / a.G;
+    const int head = it.h * a.G + r % a.G;
+    const float inv = 1.f / rs.l_run;
+    __bf16* dst = (__bf16*)a.out + ((long)q * a.kv.num_q_heads + head) * D + 4 * h;
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 #pragma unroll
-  for (int n = 0; n < NT; ++n) {
-    ts.l_run[n] += __shfl_xor(ts.l_run[n], 16);
-    ts.l_run[n] += __shfl_xor(ts.l_run[n], 32);
-    const int r = wave * ROWS + 16 * n + c;  // row inside the row group
-    if (16 * n + c >= Rw) continue;
-    if (complete) {
-      const int q = it.q0 + r / a.G;
-      const int head = it.h * a.G + r % a.G;
-      const float inv = 1.f / ts.l_run[n];
-      __bf16* dst = (__bf16*)a.out + ((long)q * a.kv.num_q_heads + head) * D;
-      typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+    for (int mt = 0; mt < C::MT; ++mt) {
 #pragma unroll
-      for (int mt = 0; mt < C::MT; ++mt) {
+      for (int b = 0; b < 4; ++b) {
         bf16x4 ov;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(ts.acc[n][mt][e] * inv);
-        *(bf16x4*)(dst + 16 * mt + 4 * g) = ov;
+        for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(rs.acc[mt][4 * b + e] * inv);
+        *(bf16x4*)(dst + 32 * mt + 8 * b) = ov;
       }
-      if (a.lse && g == 0) a.lse[(long)q * a.kv.num_q_heads + head] = (ts.m_run[n] + log2f(ts.l_run[n])) * LN2;
-    } else {
-      float* dst = partial_acc(pslot, r, D);
-#pragma unroll
-      for (int mt = 0; mt < C::MT; ++mt) store_device_scope_x4(dst + 16 * mt + 4 * g, ts.acc[n][mt]);
-      if (g == 0) store_device_scope_x4(partial_stat(a, pslot, r, D), f32x4{ts.m_run[n], ts.l_run[n], 0.f, 0.f});
     }
+    if (a.lse && h == 0) a.lse[(long)q * a.kv.num_q_heads + head] = (rs.m_run + log2f(rs.l_run)) * LN2;
+  } else {
+    float* dst = partial_acc(pslot, r, D) + 4 * h;
+#pragma unroll
+    for (int mt = 0; mt < C::MT; ++mt) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        store_device_scope_x4(dst + 32 * mt + 8 * b, f32x4{rs.acc[mt][4 * b], rs.acc[mt][4 * b + 1], rs.acc[mt][4 * b + 2],
+                                                            rs.acc[mt][4 * b + 3]});
+    }
+    if (h == 0) store_device_scope_x4(partial_stat(a, pslot, r, D), f32x4{rs.m_run, rs.l_run, 0.f, 0.f});
   }
 }
 
-template <int D, int NT, int NW>
+template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void attn_bf16_rows_kernel(
     AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -304,7 +546,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
     }
     const bool complete = seg_complete(seg);
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
-    segment_rows<D, NT, NW>(a, smem, seg, complete, pslot);
+    segment_rows<D, NW>(a, smem, seg, complete, pslot);
     if (!complete) announce_partial<D, true, THREADS, 2>(a, seg, &merge_flag);
   }
 }
@@ -317,7 +559,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
 // workgroup to finish puts back to zero.  Every group is computed whole by one workgroup with the
 // row-splitting arithmetic above: nothing is split, nothing merged.
 // ---------------------------------------------------------------------------------------------
-template <int D, int NT, int NW>
+template <int D, int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void attn_bf16_seq_kernel(
     AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -348,7 +590,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
                     (int)(seg.nq <= a.qpg) & (int)(seg.q0 <= a.NQ - seg.nq) & (int)(seg.np >= 1) &
                     (int)(seg.np <= a.kv.max_blocks_per_seq);
     if (!ok) continue;
-    segment_rows<D, NT, NW, true>(a, smem, seg, true, nullptr);
+    segment_rows<D, NW, true>(a, smem, seg, true, nullptr);
   }
   // the last workgroup to leave puts the two counters back to zero for the next launch
   if (threadIdx.x == 0) {

@@ -51,6 +51,7 @@ struct AttnArgs {
   int            G;             // query heads per KV head
   int            rows_cap;      // rows per row group the partial slots are sized for
   const int32_t* row_base;      // whole-sequence launches: per packed row, the first slot of the row's stage
+  const int32_t* row_lo;        // ... and the first slot of its own branch there
 };
 
 // ---------------------------------------------------------------------------------------------
