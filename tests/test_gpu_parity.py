@@ -462,6 +462,43 @@ def test_rope_append_then_attention(A, seed, dtype, theta):
         assert err <= tol
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,hd", [("bf16", 64, 8, 128), ("bf16", 2, 1, 64), ("f32", 40, 5, 128), ("f32", 4, 2, 64)])
+@pytest.mark.parametrize("NQ,shift", [(1, 0), (7, 1), (300, 0)])
+def test_rope_append_rows_and_alignment(A, dtype, hq, hkv, hd, NQ, shift):
+    """Rows of fewer and of more units than a workgroup's threads take at once, tokens without a place in the pools (Q
+    is turned, nothing is written), and rows that start `shift` elements off a 16-byte boundary, against float64."""
+    from oracle import rope_append
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(NQ + hd)
+    rng = np.random.default_rng(NQ + hd)
+
+    def rows(h):  # a contiguous [NQ][h][hd] block, `shift` elements into its storage
+        return torch.randn(NQ * h * hd + shift, generator=g).to(tdt).cuda()[shift:].view(NQ, h, hd)
+
+    q, k_new, v_new = rows(hq), rows(hkv), rows(hkv)
+    blocks = NQ // 16 + 2
+    pools = [torch.randn(blocks, hkv, 16, hd, generator=g).to(tdt).cuda() for _ in range(2)]
+    kv = A.KVCache(*pools, torch.zeros(1, 1, dtype=torch.int32, device="cuda"), hq)
+    step = A.Step(NQ, 1, 1, torch.device("cuda"))
+    pos = rng.integers(0, 40000, size=NQ).astype(np.int32)
+    slots = rng.permutation(blocks * 16)[:NQ].astype(np.int64)
+    lost = rng.random(NQ) < 0.1
+    step.position_ids.copy_(torch.from_numpy(pos))
+    step.slot_mapping.copy_(torch.from_numpy(np.where(lost, np.where(pos % 2 == 0, -1, blocks * 16), slots)))
+    ins = [t.double().cpu().numpy() for t in (q, k_new, v_new)]
+    k64, v64 = (t.double().cpu().numpy() for t in pools)
+    keep = ~lost
+    rope_append(ins[0][keep], ins[1][keep], ins[2][keep], pos[keep], slots[keep], k64, v64, 1e6)
+    q_ref = rope_append(ins[0], ins[1], ins[2], pos, np.zeros(NQ, dtype=np.int64), np.zeros((1, hkv, 16, hd)),
+                        np.zeros((1, hkv, 16, hd)), 1e6)
+    A.aspd_rope_append(kv, step, q, k_new, v_new, 1e6)
+    # |a c - b s| <= |(a, b)| <= 8 for these draws: one rounding of the result, four fp32 roundings before it
+    tol = 8 * (2.0 ** -8 if dtype == "bf16" else 4 * 2.0 ** -24)
+    for got, ref in ((q, q_ref), (pools[0], k64)):
+        assert np.abs(got.double().cpu().numpy() - ref).max() <= tol
+    assert np.array_equal(pools[1].double().cpu().numpy(), v64)
+
+
 # --------------------------------------------------------------------------------------------- position paradigms
 @pytest.mark.parametrize("mode", ["same_max", ("fix", 48)])
 def test_position_paradigms_of_the_ablation(A, mode):
