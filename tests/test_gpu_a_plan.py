@@ -151,3 +151,46 @@ def test_plan_covers_every_item_once(A, case):
         torch.cuda.synchronize()
         assert gb.fault() == 0
         _check_plan(gb, step, f"{case} serial")
+
+
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (8, 8), (12, 4)])
+@pytest.mark.parametrize("cap", [0, 7])
+def test_items_of_a_long_append_end_at_their_own_rows(A, hq, hkv, cap):
+    """Prompts of several row groups, on empty sequences and behind tokens: where a group holds whole pages' worth
+    of queries (32/8 and 8/8 heads: 64 and 256 of them; 12/4: 85, where it does not) its item ends at the page of its
+    last row.  Every such item is covered once, by consecutive runs of consecutive workgroups."""
+    new = np.array([1, 64, 65, 1000, 257, 0, 2030], dtype=np.int32)
+    held = np.array([0, 0, 31, 17, 0, 5, 160], dtype=np.int32)
+    B, pages = len(new), -(-(new + held) // 16)
+    tables = np.full((B, int(pages.max())), -1, dtype=np.int32)
+    for s in range(B):
+        tables[s, :pages[s]] = pages[:s].sum() + np.arange(pages[s])
+    dev = torch.device("cuda")
+    pool = torch.zeros(int(pages.sum()), hkv, 16, 64, dtype=torch.bfloat16, device=dev)
+    kv = A.KVCache(pool, pool.clone(), torch.from_numpy(tables).to(dev), hq)
+    state = A.BatchState(B, tables.shape[1] * 16, dev)
+    A.aspd_build_branch_meta(kv, state, A.STAGE_SERIAL, torch.from_numpy(held).to(dev), NQ=int(held.sum()), plan=False)
+    step = A.aspd_build_branch_meta(kv, state, A.STAGE_SERIAL, torch.from_numpy(new).to(dev), NQ=int(new.sum()),
+                                    max_new_per_seq=int(new.max()), max_workgroups=cap)
+    assert int(state.fault.item()) == 0
+    _, _, qpg, nwg = _decode_key(step.plan_key)
+    assert qpg == 256 // (hq // hkv)
+    plan, cu = step.plan.cpu().numpy().view(np.int32), step.cu_seq_new.cpu().numpy()
+    runs = {}
+    for w in range(nwg):
+        hdr = plan[HDR * w: HDR * (w + 1)]
+        for i in range(int(hdr[NSEG])):
+            at = HDR * w if i == 0 else HDR * nwg + SEG * (int(hdr[NEXT]) + i - 1)
+            d = plan[at: at + SEG]
+            runs.setdefault((int(d[0]) & 0xffff, int(np.uint32(d[0]) >> 16), int(d[1])), []).append(
+                (w, *(int(x) for x in d[2:6]), int(d[6]) & 0xffff, int(np.uint32(d[6]) >> 16)))
+    for s in range(B):
+        for h in range(hkv):
+            for g in range(-(-int(new[s]) // qpg)):
+                rows = min(qpg, int(new[s]) - g * qpg)
+                end = held[s] + (g * qpg + rows if qpg % 16 == 0 else new[s])
+                r = sorted(runs.pop((s, h, int(cu[s]) + g * qpg)))
+                assert r[0][2] == 0 and r[-1][3] == -(-int(end) // 16), (s, h, g, r)
+                assert all(a[3] == b[2] and b[0] == a[0] + 1 for a, b in zip(r, r[1:])), (s, h, g, r)
+                assert all(x[1] == rows and x[2] < x[3] <= x[4] == r[-1][3] and x[5:] == (r[0][0], r[-1][0]) for x in r), (s, h, g, r)
+    assert not runs

@@ -499,6 +499,25 @@ def test_rope_append_rows_and_alignment(A, dtype, hq, hkv, hd, NQ, shift):
     assert np.array_equal(pools[1].double().cpu().numpy(), v64)
 
 
+@pytest.mark.parametrize("hq,hkv,hd", [(32, 8, 128), (8, 8, 128), (16, 4, 64), (12, 4, 64)])
+def test_prompts_of_many_row_groups(A, hq, hkv, hd):
+    """Prompts of several row groups behind ragged tokens, whose items end at different pages: group sizes that are whole
+    pages and one (12/4 heads) that is not, against the oracle."""
+    from gpu_drive import GpuBatch, assert_step_equal
+    wl = W.random_small(seed=77 + hq, num_q_heads=hq, num_kv_heads=hkv, head_dim=hd, batch=3, prefix_range=(500, 900),
+                        branches_range=(1, 2), branch_len_range=(1, 4))
+    gb = GpuBatch(wl)
+    tt = TokenTable(wl.block_tables, wl.block_size)
+    first = np.array([0, 33, 160], dtype=np.int32)
+    for new_len in (first, wl.prefix_len - first):
+        new_len = new_len.astype(np.int32)
+        meta = tt.append_serial(new_len)
+        step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_SERIAL, gb._dev_i32(new_len), NQ=int(new_len.sum()),
+                                        max_new_per_seq=int(new_len.max()))
+        assert_step_equal(step, meta)
+        _compare_attention(A, gb, tt, wl, step, meta, A.aspd_attn_serial_decode, label=f"prompts {hq}/{hkv}")
+
+
 # --------------------------------------------------------------------------------------------- position paradigms
 @pytest.mark.parametrize("mode", ["same_max", ("fix", 48)])
 def test_position_paradigms_of_the_ablation(A, mode):
