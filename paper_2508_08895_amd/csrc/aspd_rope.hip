@@ -13,8 +13,8 @@
 // thousand) and their sines and cosines are computed once per row and pair and shared through LDS.
 // One workgroup per row: four or eight rows per workgroup (an angle for every thread) measured 3 to 8 % slower from
 // 4096 rows on (32768 rows, 32/8 heads of 128: 159 against 151 us) and the same below.
-// Before, a thread took 2-byte elements and each of its wave's heads had its own sines: 6000 rows 39.6 -> 30.6 us,
-// 550 rows 8.7 -> 5.9 us, 4 rows 4.7 -> 3.5 us; 330000 rows 1.81 -> 1.75 ms, the rate of a plain copy (4.6 TB/s).
+// Before, a thread took 2-byte elements and each of its wave's heads had its own sines: 6000 rows 39.7 -> 28.5 us,
+// 550 rows 8.7 -> 6.1 us, 4 rows 4.5 -> 2.9 us; 330000 rows 1.68 -> 1.45 ms, 5.6 TB/s (a plain copy: 4.7).
 #include "aspd_common.h"
 
 namespace {
