@@ -153,10 +153,10 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
 
   // Pairs of pages of the segment, numbered without the ones no row of the group sees: whole sequences lay a
   // stage's branches one after the other, so between the start of a stage and the first branch that the group
-  // has rows in lies a run of sibling tokens.
+  // has rows in lies a run of sibling tokens.  (Under the shared mask, without owner tags, rows see their siblings.)
   int npairs = (page1 - page0 + 1) >> 1;
   int hole_at = npairs, hole = 0;
-  if (SEQ) {
+  if (SEQ && a.slot_owner) {
     const int b0 = a.row_base[it.q0], b1 = a.row_base[it.q0 + it.nq - 1], lo0 = a.row_lo[it.q0];
     if (b0 == b1) {
       const int from = (b0 + 31) >> 5, to = min(lo0 >> 5, npairs);

@@ -424,6 +424,52 @@ def test_shared_mask_is_plain_causal_attention(A):
     assert np.abs(iso - got).max() > 0.05
 
 
+LATE_BRANCHES = [[(0, 100), (1, 100), (2, 100), (3, 100), (0, 50)],
+                 [(0, 40), (1, 100), (2, 400)],
+                 [(0, 33), (1, 70), (2, 300), (0, 7), (1, 80), (2, 130), (3, 260), (0, 3)]]
+
+
+def _groups_behind_siblings(layouts, qpg):
+    """Row groups of `qpg` tokens that lie in one stage and have a whole pair of pages (32 slots) between the stage's
+    start and the first slot of their first row's branch."""
+    count = 0
+    for runs in layouts:
+        base, lo, at, start = [], [], 0, 0
+        for b, n in runs:
+            start = at if b <= 1 else start
+            base += [start] * n if b else list(range(at, at + n))
+            lo += [at] * n if b else list(range(at, at + n))
+            at += n
+        for r0 in range(0, at, qpg):
+            last = min(r0 + qpg, at) - 1
+            count += base[r0] == base[last] and lo[r0] // 32 > -(-base[r0] // 32)
+    return count
+
+
+@pytest.mark.parametrize("hq,hkv,hd", [(32, 8, 128), (8, 2, 64), (8, 8, 128), (4, 4, 64)])
+def test_groups_behind_whole_pairs_of_siblings_under_both_masks(A, hq, hkv, hd):
+    """Row groups that start in a later branch of a long stage: under the branch mask the siblings between the stage's
+    start and that branch are left out, under the shared mask every one of them counts.  Output and log-sum-exp."""
+    from gpu_drive import GpuBatch
+    assert _groups_behind_siblings(LATE_BRANCHES, 256 // (hq // hkv)) >= (1 if hq == hkv else 5)
+    wl = W.random_small(seed=6150 + hd + hq, num_q_heads=hq, num_kv_heads=hkv, head_dim=hd, batch=3, prefix_range=(880, 880),
+                        branches_range=(1, 1), branch_len_range=(1, 1))
+    tt, meta = replay_layout(wl.block_tables, wl.block_size, LATE_BRANCHES)
+    gb = GpuBatch(wl)
+    step = _build(A, gb, LATE_BRANCHES)
+    q = wl.draw_q(meta.NQ)
+    for shared in (1, 0):
+        step.shared_mask = shared
+        lse = torch.full((meta.NQ, hq), float("nan"), dtype=torch.float32, device=gb.dev)
+        out = A.aspd_attn_full_sequence(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace, lse=lse)
+        torch.cuda.synchronize()
+        ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache, shared_mask=bool(shared))
+        err = np.abs(out.double().cpu().numpy() - ref).max()
+        lerr = np.abs(lse.double().cpu().numpy() - ref_lse).max()
+        print(f"[late branches {hq}/{hkv}/{hd} shared={shared}] max|out-ref|={err:.3e} max|lse-ref|={lerr:.3e}", flush=True)
+        assert err <= TOL and lerr <= LSE_TOL, (shared, err, lerr)
+
+
 def test_re_prefill_with_rotary_append_end_to_end(A):
     """The three calls of a re-prefill in a row (Same-Re, Sec. 4.5.3): metadata of whole sequences, rotary encoding of
     all their tokens by the position ids of Eq. 4 with the K and V rows written into the cache, attention over the
