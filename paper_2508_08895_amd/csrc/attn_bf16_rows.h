@@ -253,8 +253,9 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   auto v_operand = [&](int u, int j) { return rows_v_operand<D>(va[j % C::MT] + u * C::PAIR_B + (j / C::MT) * C::PAGE_B); };
 
   // ---- staging.  Group i holds the K pages of pairs 2 i + 1 and 2 i + 2 and the V pages of pairs 2 i - 1 and
-  // 2 i (what the two steps of the group multiply); wave w fetches one page of it.  Pairs outside the segment
-  // are fetched as the nearest one inside and not used.
+  // 2 i (what the two steps of the group multiply); wave w fetches one page of it.  Pages outside the segment
+  // are fetched as the nearest one inside.  Their scores are not used; V pages that a step multiplies all the same, with
+  // weight zero (pair -1 by the first full step, the second page of an odd last pair), are zeros in LDS.
   const bool l_is_k = wave < 4;
   const int l_pair = (wave >> 1) & 1;
   const int n_last = npairs - 1;
@@ -427,7 +428,8 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   };
 
   // One barrier per group: every wave has its page of the group in LDS, and is done with the stage that the group three
-  // further on goes to.  The V rows of slots past the last row's are cleared before it.
+  // further on goes to.  The V rows of slots past the last row's or past the segment are cleared before it: they may
+  // hold anything, or an infinity that belongs to another slot, and zero times either would be a NaN.
   const int i_last = npairs >> 1;
   int block = 0;  // block id of the group that is sent for next
   auto send = [&](int i) {
@@ -437,17 +439,20 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
     for (int k = 0; k < LPT; ++k) load_to_lds(src + k * 1024, goff ^ (k * goff_flip), l_at + buffer_of(i) * C::STAGE_B + k * 1024);
     block = bt[page_of_group(i + 1)];
   };
+  const int v_last = min(last_slot, page1 * ASPD_BLOCK - 1);
+  auto clear_v = [&](int i, int k) {
+    *(__attribute__((address_space(3))) u32x4*)(l_at + buffer_of(i) * C::STAGE_B + k * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+  };
   auto arrive = [&](int i, bool tail) {
     if (i + 2 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPT) : "memory");
     else if (i + 1 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (tail && !l_is_k) {
-      const int key0 = page_of_group(i) * ASPD_BLOCK;
-      if (key0 + ASPD_BLOCK > last_slot + 1) {
+      const int key0 = (page_of_pair(2 * i - 1 + l_pair) + (wave & 1)) * ASPD_BLOCK;
+      if (key0 + ASPD_BLOCK > v_last + 1) {
 #pragma unroll
         for (int k = 0; k < LPT; ++k)
-          if (key0 + (64 * k + lane) / C::CH > last_slot)
-            *(__attribute__((address_space(3))) u32x4*)(l_at + buffer_of(i) * C::STAGE_B + k * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+          if (key0 + (64 * k + lane) / C::CH > v_last) clear_v(i, k);
       }
     }
     __syncthreads();
@@ -471,8 +476,16 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   const int i_open = wave_active ? (open_pairs - 1) >> 1 : 0;  // 2 i + 2 <= open_pairs - 1
   __syncthreads();  // LDS of the previous segment is free
   block = bt[page_of_group(-1)];
-#pragma unroll 1
-  for (int i = -1; i < 2; ++i) send(i);
+  send(-1);
+  if (!l_is_k && l_pair == 0) {  // V of pair -1, which the first full step multiplies with weights zero
+#pragma unroll
+    for (int k = 0; k < LPT; ++k) clear_v(0, k);
+    // (no load in flight for group 0 here: this wave's wait for group -1, whose V pages nobody reads, may come up early)
+    block = bt[page_of_group(1)];
+  } else {
+    send(0);
+  }
+  send(1);
   general_groups(-1, 0);  // (the scores of pair 0)
   int i = 0;
   if (i_open > 0) {

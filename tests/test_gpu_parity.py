@@ -866,6 +866,37 @@ def test_unwritten_slots_may_hold_anything(A):
         assert_state_equal(gb, tt)
 
 
+@pytest.mark.parametrize("hq,hkv,hd,prefix", [(32, 8, 128, 700), (8, 8, 64, 300), (32, 8, 64, 6000)])
+def test_an_infinity_in_v_stays_one(A, hq, hkv, hd, prefix):
+    """Infinite V elements in every pair of pages before the stage, in chunks and in a long serial append (key ranges
+    whole and split): every row sees them and gets an infinity there (not a NaN, which is what a zero weight would
+    make of one), and its other elements are what they would be."""
+    wl = W.random_small(140 + hd, num_q_heads=hq, num_kv_heads=hkv, head_dim=hd, batch=2, prefix_range=(prefix, prefix),
+                        branches_range=(4, 4), branch_len_range=(1, 3), extra_tokens_per_seq=80)
+    for s in range(wl.B):
+        for page in range(0, prefix // 16, 2):
+            wl.v_cache[int(wl.block_tables[s, page]), :, 5, 3] = float("inf")
+    gb, tt = _grow_both(A, wl, wl.branch_len, False)
+    rest = np.arange(hd) != 3
+
+    def check(meta, step, fn):
+        q = wl.draw_q(meta.NQ)
+        out = fn(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace)
+        torch.cuda.synchronize()
+        ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache)
+        got = out.double().cpu().numpy()
+        assert bool(np.isposinf(got[:, :, 3]).all()), fn.__name__
+        assert np.abs(got[:, :, rest] - ref[:, :, rest]).max() <= TOL["bf16"], fn.__name__
+
+    chunk = np.full(wl.NB, 17, dtype=np.int32)
+    check(tt.append_parallel(chunk), gb.parallel(chunk), A.aspd_attn_branch_chunk)
+    tt.merge()
+    gb.merge()
+    new = np.full(wl.B, 80, dtype=np.int32)
+    step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_SERIAL, gb._dev_i32(new), NQ=80 * wl.B, max_new_per_seq=80)
+    check(tt.append_serial(new), step, A.aspd_attn_serial_decode)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_shared_mask_of_the_ablation(A, dtype):
     """aspd_step.shared_mask: branch rows attend like main-branch rows (every slot up to their own, siblings

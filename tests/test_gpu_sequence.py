@@ -470,6 +470,30 @@ def test_groups_behind_whole_pairs_of_siblings_under_both_masks(A, hq, hkv, hd):
         assert err <= TOL and lerr <= LSE_TOL, (shared, err, lerr)
 
 
+@pytest.mark.parametrize("hq,hkv,hd", [(32, 8, 128), (8, 8, 64)])
+def test_an_infinity_in_v_stays_one(A, hq, hkv, hd):
+    """An infinite V element of an early slot: every row that sees the slot gets an infinity there (not a NaN, which is
+    what a zero weight would make of it), and its other elements are what they would be."""
+    from gpu_drive import GpuBatch
+    wl = W.random_small(seed=6250 + hd, num_q_heads=hq, num_kv_heads=hkv, head_dim=hd, batch=2, prefix_range=(700, 700),
+                        branches_range=(1, 1), branch_len_range=(1, 1))
+    layouts = [[(0, 700)], [(0, 210), (1, 130), (2, 190), (0, 90)]]
+    tt, meta = replay_layout(wl.block_tables, wl.block_size, layouts)
+    for s in range(2):
+        wl.v_cache[int(wl.block_tables[s, 0]), :, 5, 3] = float("inf")
+    gb = GpuBatch(wl)
+    step = _build(A, gb, layouts)
+    q = wl.draw_q(meta.NQ)
+    out = A.aspd_attn_full_sequence(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace)
+    torch.cuda.synchronize()
+    sees = np.nonzero(meta.logical_slot >= 5)[0]
+    ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache, rows=sees)
+    got = out.double().cpu().numpy()[sees]
+    assert bool(np.isposinf(got[:, :, 3]).all())
+    rest = np.arange(hd) != 3
+    assert np.abs(got[:, :, rest] - ref[sees][:, :, rest]).max() <= TOL
+
+
 def test_re_prefill_with_rotary_append_end_to_end(A):
     """The three calls of a re-prefill in a row (Same-Re, Sec. 4.5.3): metadata of whole sequences, rotary encoding of
     all their tokens by the position ids of Eq. 4 with the K and V rows written into the cache, attention over the
