@@ -304,12 +304,10 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
       } else if (owner_row && own_lo > 0) {
         uint32_t own[4];
         lane_own(t, own);
-        bool mine = own_lo != own_hi;  // (rows of several branches: taken to see something)
+        uint32_t over = 0xffffffffu;  // how far the lane's tags lie above own_lo at least (below it: very far)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {  // a zero byte in own ^ tags
-          const uint32_t x = own[b] ^ (0x01010101u * (uint32_t)own_lo);
-          mine |= ((x - 0x01010101u) & ~x & 0x80808080u) != 0;
-        }
+        for (int i = 0; i < 16; ++i) over = min(over, ((own[i >> 2] >> (8 * (i & 3))) & 0xff) - (uint32_t)own_lo);
+        const bool mine = over <= (uint32_t)(own_hi - own_lo);
         if (!__any(mine)) return 0;
       }
     }

@@ -897,6 +897,35 @@ def test_an_infinity_in_v_stays_one(A, hq, hkv, hd, prefix):
     check(tt.append_serial(new), step, A.aspd_attn_serial_decode)
 
 
+@pytest.mark.parametrize("hq,hkv,hd,chunk", [(8, 8, 128, 13), (8, 8, 64, 16), (4, 4, 64, 5), (32, 8, 128, 3), (32, 8, 64, 7)])
+def test_pages_of_siblings_stay_out_of_waves_with_several_branches(A, hq, hkv, hd, chunk):
+    """Chunks of many short branches, so that the 32 rows of a wave belong to several.  Pairs of pages whose keys all
+    belong to branches before the wave's first are left out, not weighed with zero: infinite V elements in a page of
+    the stage's beginning do not reach the rows of later waves."""
+    K, prefix = 24, 48
+    wl = W.random_small(150 + hd + hq, num_q_heads=hq, num_kv_heads=hkv, head_dim=hd, batch=2, prefix_range=(prefix, prefix),
+                        branches_range=(K, K), branch_len_range=(1, 1))
+    gb, tt = _grow_both(A, wl, np.zeros(wl.NB, dtype=np.int32), False)
+    for s in range(wl.B):  # slots 16 .. 31 of the stage
+        gb.kv.v[int(wl.block_tables[s, prefix // 16 + 1])] = float("inf")
+    new_len = np.full(wl.NB, chunk, dtype=np.int32)
+    meta, step = tt.append_parallel(new_len), gb.parallel(new_len)
+    q = wl.draw_q(meta.NQ)
+    out = A.aspd_attn_branch_chunk(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace)
+    torch.cuda.synchronize()
+    # waves that start in a branch behind slots 0 .. 47 (whichever two pages make the pair), by row of a sequence
+    branch = np.arange(K * chunk) // chunk
+    per_wave = 32 // (hq // hkv)
+    start = branch[np.arange(K * chunk) // per_wave * per_wave]
+    behind = start > branch[47]
+    assert (branch[behind] > start[behind]).any()  # ... rows of several branches among them
+    rows = np.nonzero(np.tile(behind, wl.B))[0]
+    ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache, rows=rows)
+    got = out.double().cpu().numpy()
+    assert np.isfinite(got[rows]).all()
+    assert np.abs(got[rows] - ref[rows]).max() <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_shared_mask_of_the_ablation(A, dtype):
     """aspd_step.shared_mask: branch rows attend like main-branch rows (every slot up to their own, siblings
