@@ -63,11 +63,18 @@ struct Rows32 {
   f32x16 acc[D / 32];
   float m_run, l_run;
   float neg_ref;  // minus the running reference, 0 while there is none
-  float limit;    // weight sum above which the references are raised: below any sum while a row of the wave has none
+  float limit;    // weight sum above which the references are raised; below any sum before and at the second raise
 };
 
-// Largest weight sum of a lane's sixteen keys before the row's reference is raised (see rows_raise).
-constexpr float ROWS_SUM_MAX = 1024.f;
+// Largest weight sum of a lane's sixteen keys before the row's reference is raised (see rows_raise).  A thousand would be
+// as safe in fp32 and in the bf16 operand.  What the value decides is the rounding of the weights: the weight of the
+// key that gave the reference is 1 and has no error, and where few keys carry a row the error of the largest weights
+// is that of the output.  With 20, and with the references raised at the second pair in any case (so that they are
+// the largest of 64 scores at least), the error against float64 is 0.1 to 4 % below that of references taken from a
+// group of 64 keys and raised at a score 2^6 above (as before the 32x32x16 tiles) for queries ~ N(0, 1) and N(0, 36),
+// 3 to 8 % for N(0, 4).  With 1024 and the first pair's maximum it was 0.8, 4 to 8 and 10 % above.  The raise at the
+// second pair costs up to 1 us a launch (short whole sequences 143.6 -> 145.5 us, prompts 439.5 -> 444).
+constexpr float ROWS_SUM_MAX = 20.f;
 
 // LDS operands by byte address.
 __device__ __forceinline__ bf16x8 rows_k_operand(uint32_t at) {
@@ -83,10 +90,9 @@ __device__ __forceinline__ bf16x8 rows_v_operand(uint32_t at) {
 // Weights of one pair against the rows' lazily raised references (log2 domain, scaled scores; a reference is
 // not necessarily the row maximum).  The weights are computed first and their sum, which the row needs anyway,
 // tells whether a reference has to go up: while no lane's sixteen weights sum to more than ROWS_SUM_MAX none of
-// them exceeds it, which is harmless in fp32 and in the bf16 operand, whose precision is relative.  Otherwise, and
-// while a row of the wave has no reference, the references are raised to the largest score so far, the accumulators
-// rescaled and the weights formed again.  (Testing the sum costs one comparison per pair; the maximum it replaces
-// cost eight instructions and the wait states in front of them.)
+// them exceeds it.  Otherwise, while a row of the wave has no reference, and once more after that, the references are
+// raised to the largest score so far, the accumulators rescaled and the weights formed again.  (Testing the sum costs
+// one comparison per pair; the maximum it replaces cost eight instructions and the wait states in front of them.)
 template <int D>
 __device__ __forceinline__ float rows_weights(const f32x16& s, const Rows32<D>& rs, bf16x8 (&p)[2], float scale_log2) {
   float sum = 0.f;
@@ -117,7 +123,7 @@ __device__ __forceinline__ float rows_raise(const f32x16& s, Rows32<D>& rs, bf16
   rs.l_run *= alpha;
 #pragma unroll
   for (int mt = 0; mt < D / 32; ++mt) rs.acc[mt] *= alpha;
-  rs.limit = __any(m_new == -INFINITY) ? -1.f : ROWS_SUM_MAX;
+  rs.limit = __any(m_new == -INFINITY) ? -2.f : (rs.limit < -1.f ? -1.f : ROWS_SUM_MAX);
   return rows_weights<D>(s, rs, p, scale_log2);
 }
 
@@ -221,7 +227,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   rs.m_run = -INFINITY;
   rs.l_run = 0.f;
   rs.neg_ref = 0.f;
-  rs.limit = -1.f;
+  rs.limit = -2.f;
 #pragma unroll
   for (int mt = 0; mt < C::MT; ++mt)
 #pragma unroll

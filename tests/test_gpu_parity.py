@@ -897,6 +897,59 @@ def test_an_infinity_in_v_stays_one(A, hq, hkv, hd, prefix):
     check(tt.append_serial(new), step, A.aspd_attn_serial_decode)
 
 
+@pytest.mark.parametrize("hq,hkv,hd", [(32, 8, 128), (8, 8, 64)])
+@pytest.mark.parametrize("at,log2_ratio", [(45, 2.0), (150, 6.4)])
+@pytest.mark.parametrize("call", ["chunk", "append", "sequence"])
+def test_the_largest_weight_carries_no_rounding(A, hq, hkv, hd, at, log2_ratio, call):
+    """A row's weights are rounded to bf16 relative to its running reference, so the weight of the key that the
+    reference was taken from is exact.  Slot 3 gives the first pair of pages its maximum, slot `at` a score 2 to 3.9
+    (2^2 .. 2^3.9 times the weight) or 6.4 to 9.8 above it in the log2 domain, all others weigh nothing, and only slot
+    `at` has a value: the output is that value times w / (1 + w), rounded once.  (A rounded weight adds up to 2^-8, in
+    a fourth of the elements more than the one rounding allows.)"""
+    from gpu_drive import GpuBatch
+    wl = W.random_small(160 + hd, num_q_heads=hq, num_kv_heads=hkv, head_dim=hd, batch=2, prefix_range=(300, 300),
+                        branches_range=(5, 5), branch_len_range=(1, 1), extra_tokens_per_seq=140)
+    step_up = log2_ratio * math.log(2) * math.sqrt(hd)
+    wl.k_cache.zero_()
+    wl.v_cache.zero_()
+    wl.k_cache[..., 0] = -2048.0
+    for s in range(wl.B):
+        wl.k_cache[int(wl.block_tables[s, 0]), :, 3, 0] = 0.0
+        wl.k_cache[int(wl.block_tables[s, at // 16]), :, at % 16, 0] = step_up
+        wl.v_cache[int(wl.block_tables[s, at // 16]), :, at % 16] = torch.randn(
+            hkv, hd, generator=torch.Generator().manual_seed(s)).to(torch.bfloat16)
+    gb = GpuBatch(wl)
+    if call == "sequence":
+        step = A.aspd_build_sequence_meta(gb.kv, gb.state, gb._dev_i32([0, 1, 2]), gb._dev_i32([0, 0]), gb._dev_i32([410, 333]),
+                                          NQ=743)
+        fn = A.aspd_attn_full_sequence
+    else:
+        gb.serial(wl.prefix_len)
+        if call == "chunk":
+            gb.open_parallel()
+            step, fn = gb.parallel(np.full(wl.NB, 17, dtype=np.int32)), A.aspd_attn_branch_chunk
+        else:
+            new, fn = np.array([110, 95], dtype=np.int32), A.aspd_attn_serial_decode
+            step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_SERIAL, gb._dev_i32(new), NQ=205, max_new_per_seq=110)
+    assert gb.fault() == 0
+    q = torch.zeros(step.NQ, hq, hd, dtype=torch.bfloat16)
+    q[..., 0] = 1 + torch.arange(step.NQ * hq).reshape(step.NQ, hq) % 17 * (1 / 32 if log2_ratio > 4 else 15 / 256)
+    out = fn(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace).double().cpu().numpy()
+    torch.cuda.synchronize()
+    seq, slot = step.q_seq.cpu().numpy()[:step.NQ], step.logical_slot.cpu().numpy()[:step.NQ]
+    key = float(wl.k_cache[int(wl.block_tables[0, at // 16]), 0, at % 16, 0])
+    w = np.exp(q[..., 0].double().numpy() * key / math.sqrt(hd))
+    v = np.stack([wl.v_cache[int(wl.block_tables[s, at // 16]), :, at % 16].double().numpy() for s in range(wl.B)])
+    want = (w / (1 + w))[..., None] * np.repeat(v, hq // hkv, axis=1)[seq]
+    sees = slot >= at
+    half_ulp = 2.0 ** (np.floor(np.log2(np.abs(want[sees]) + 1e-30)) - 8)
+    err = np.abs(out[sees] - want[sees])
+    # (fp32 sums and exponentials: 2e-6 of the value)
+    over = err > half_ulp * (1 + 1e-9) + 2e-6 * np.abs(want[sees])
+    print(f"[{call} {hd} {at}] rows {int(sees.sum())}, {int(over.sum())} of {over.size} elements rounded more than once", flush=True)
+    assert not over.any()
+
+
 @pytest.mark.parametrize("hq,hkv,hd,chunk", [(8, 8, 128, 13), (8, 8, 64, 16), (4, 4, 64, 5), (32, 8, 128, 3), (32, 8, 64, 7)])
 def test_pages_of_siblings_stay_out_of_waves_with_several_branches(A, hq, hkv, hd, chunk):
     """Chunks of many short branches, so that the 32 rows of a wave belong to several.  Pairs of pages whose keys all
