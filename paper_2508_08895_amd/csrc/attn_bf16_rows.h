@@ -73,7 +73,8 @@ struct Rows32 {
 // the largest of 64 scores at least), the error against float64 is 0.1 to 4 % below that of references taken from a
 // group of 64 keys and raised at a score 2^6 above (as before the 32x32x16 tiles) for queries ~ N(0, 1) and N(0, 36),
 // 3 to 8 % for N(0, 4).  With 1024 and the first pair's maximum it was 0.8, 4 to 8 and 10 % above.  The raise at the
-// second pair costs up to 1 us a launch (short whole sequences 143.6 -> 145.5 us, prompts 439.5 -> 444).
+// second pair costs about 1 us a launch (three short whole sequences, two layers 143.0 -> 144.5 us, eight prompts
+// 438 -> 444) and 0.6 % of the 64-sequence ones (chunk 1790 -> 1801 us, whole sequences 23.81 -> 23.94 ms).
 constexpr float ROWS_SUM_MAX = 20.f;
 
 // LDS operands by byte address.
@@ -399,15 +400,20 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
     }
     if (see) {
       if (see & 2) {
+        // No short-circuits: they become branches on the execution mask, one behind the other for sixteen keys, which took
+        // more than the rest of a masked pair (1 000 to 1 600 cycles of it by the clock in the kernel).  Four layers,
+        // before -> after: 8/8 heads, 27 sequences of 200 to 430 tokens, chunks of 4 to 16 in 2 to 8 branches
+        // 213.6 -> 200.3 us; 16/4 heads of 64, 20 sequences of 100 to 2500: 226.1 -> 205.6.
         const int k0 = page_of_pair(p) * ASPD_BLOCK + 4 * h;
-        const int end = min(slot, page1 * ASPD_BLOCK - 1);
+        const int n_end = min(slot, page1 * ASPD_BLOCK - 1) - k0;
+        const int n_base = (SEQ || tag != 0 ? base : 0x7fffffff) - k0, n_lo = lo - k0;
         uint32_t own[4];
         lane_own(tc, own);
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-          const int jk = k0 + 8 * (i >> 2) + (i & 3);
+          const int e = 8 * (i >> 2) + (i & 3);
           const int o = (int)((own[i >> 2] >> (8 * (i & 3))) & 0xff);
-          const bool vis = jk <= end && (jk < base || (SEQ ? jk >= lo : (tag == 0 || o == tag)));
+          const int vis = (int)(e <= n_end) & ((int)(e < n_base) | (SEQ ? (int)(e >= n_lo) : (int)(o == tag)));
           s_cur[i] = vis ? s_cur[i] : -INFINITY;
         }
       }
