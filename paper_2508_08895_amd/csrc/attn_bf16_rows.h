@@ -51,9 +51,12 @@ constexpr size_t rows_smem_bytes() { return (size_t)ROWS_BUFS * RowsCfg<D>::STAG
 
 // Sixteen bytes per lane from global memory straight into LDS: lane l's go to byte lds + 16 l.  (Assembly because
 // the compiler makes every later LDS read wait for all such loads in flight; rows_wait() says which have to be
-// there.  It reads no vector register but the offset, and writes none.)
+// there.  It reads no vector register but the offset, and writes none.  It brings its own wait states: one behind the
+// write of m0, and five in front of the load for a base that a vector instruction has written, as the reload of a spilled
+// scalar register is; the compiler does not see that a memory instruction in here reads it.)
 __device__ __forceinline__ void load_to_lds(const void* base /* uniform */, uint32_t offset, uint32_t lds /* uniform */) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base)
+               : "memory", "m0");
 }
 
 // One wave's 32 rows: lane (c, h) keeps the statistics of row c (its share of the sum) and O^T[32 mt + 8 b + 4 h +

@@ -166,17 +166,13 @@ def test_rope_append_and_renumber_reject_bad_arguments_before_launch():
     assert renumber(st_over=dict(cu_branches_d=None)) == A.ERR_INVALID_ARG
 
 
-def test_assembly_that_may_read_mfma_results_brings_its_wait_states():
-    """The matrix unit does not interlock with a vector or memory instruction that reads an MFMA result too
-    soon, and the compiler pads only the instructions it emits itself.  Every inline-assembly statement of the
-    kernels that contains a vector or memory instruction with register inputs must therefore start with its own
-    wait states (`s_nop 15`), so that it is safe wherever the scheduler puts it."""
+def _assembly_statements():
+    """(file, text) of every inline-assembly statement of the kernels' sources."""
     import glob, os, re
     here = os.path.dirname(os.path.abspath(__file__))
     files = sorted(glob.glob(os.path.join(here, "..", "paper_2508_08895_amd", "csrc", "*.h")) +
                    glob.glob(os.path.join(here, "..", "paper_2508_08895_amd", "csrc", "*.hip")))
     assert files
-    seen = 0
     for f in files:
         src = open(f).read()
         for m in re.finditer(r"\basm\s*(?:volatile)?\s*\(", src):
@@ -188,11 +184,37 @@ def test_assembly_that_may_read_mfma_results_brings_its_wait_states():
                 i += 1
                 if depth == 0:
                     break
-            stmt = src[m.start():i]
-            text = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', stmt.split(":")[0]))
-            text = text.replace("\\n", " ").replace("\\t", " ")
-            if not re.search(r"\b(v_[a-z0-9_]+|global_store_[a-z0-9]+|ds_write_[a-z0-9]+)\b", text):
-                continue
-            seen += 1
-            assert text.lstrip().startswith("s_nop 15"), (os.path.basename(f), text[:60])
+            text = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', src[m.start():i].split(":")[0]))
+            yield os.path.basename(f), text.replace("\\t", " ").replace("\\n", "\n")
+
+
+def test_assembly_that_may_read_mfma_results_brings_its_wait_states():
+    """The matrix unit does not interlock with a vector or memory instruction that reads an MFMA result too
+    soon, and the compiler pads only the instructions it emits itself.  Every inline-assembly statement of the
+    kernels that contains a vector or memory instruction with register inputs must therefore start with its own
+    wait states (`s_nop 15`), so that it is safe wherever the scheduler puts it."""
+    import re
+    seen = 0
+    for f, text in _assembly_statements():
+        if not re.search(r"\b(v_[a-z0-9_]+|global_store_[a-z0-9]+|ds_write_[a-z0-9]+)\b", text):
+            continue
+        seen += 1
+        assert text.lstrip().startswith("s_nop 15"), (f, text[:60])
     assert seen >= 2   # the three-operand maximum and the write-through store
+
+
+def test_assembly_loads_with_a_scalar_address_bring_their_wait_states():
+    """A memory instruction may read a scalar register five wait states after a vector instruction wrote it (a lane
+    read, as in the reload of a spilled scalar register) at the earliest.  Nothing interlocks and the compiler does
+    not look into assembly, so the wait states stand in the statement, in front of the load."""
+    import re
+    seen = 0
+    for f, text in _assembly_statements():
+        waits = 0
+        for line in filter(None, (x.strip() for x in text.split("\n"))):
+            if re.match(r"(global|buffer)_load", line):
+                seen += 1
+                assert waits >= 5, (f, text[:80])
+            nop = re.match(r"s_nop (\d+)", line)
+            waits += int(nop[1]) + 1 if nop else 1
+    assert seen >= 1   # the load that goes straight into LDS
