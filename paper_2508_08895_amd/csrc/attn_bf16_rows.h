@@ -54,10 +54,13 @@ constexpr size_t rows_smem_bytes() { return (size_t)ROWS_BUFS * RowsCfg<D>::STAG
 // there.  It reads no vector register but the offset, and writes none.  It brings its own wait states: one behind the
 // write of m0, and five in front of the load for a base that a vector instruction has written, as the reload of a spilled
 // scalar register is; the compiler does not see that a memory instruction in here reads it.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // (m0 is reserved; in the code as built nothing else uses it)
 __device__ __forceinline__ void load_to_lds(const void* base /* uniform */, uint32_t offset, uint32_t lds /* uniform */) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base)
                : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // One wave's 32 rows: lane (c, h) keeps the statistics of row c (its share of the sum) and O^T[32 mt + 8 b + 4 h +
 // j][c] in acc[mt][4 b + j].
@@ -82,12 +85,12 @@ constexpr float ROWS_SUM_MAX = 20.f;
 
 // LDS operands by byte address.
 __device__ __forceinline__ bf16x8 rows_k_operand(uint32_t at) {
-  return *(const __attribute__((address_space(3))) bf16x8*)at;
+  return *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)at;
 }
 template <int D>
 __device__ __forceinline__ bf16x8 rows_v_operand(uint32_t at) {
-  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)at);
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(at + 8 * D * 2));
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)at);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(at + 8 * D * 2));
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
@@ -454,7 +457,8 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   };
   const int v_last = min(last_slot, page1 * ASPD_BLOCK - 1);
   auto clear_v = [&](int i, int k) {
-    *(__attribute__((address_space(3))) u32x4*)(l_at + buffer_of(i) * C::STAGE_B + k * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+    *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(l_at + buffer_of(i) * C::STAGE_B + k * 1024 + lane * 16) =
+        u32x4{0u, 0u, 0u, 0u};
   };
   auto arrive = [&](int i, bool tail) {
     if (i + 2 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPT) : "memory");
