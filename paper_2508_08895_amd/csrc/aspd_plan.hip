@@ -59,9 +59,10 @@ __device__ __forceinline__ int groups_of(const PlanArgs& a, const Sched& sc, int
   return (sc.q0[s + 1] - sc.q0[s] + a.qpg - 1) / a.qpg;
 }
 
-// Pages of a sequence's row groups.  A step's rows are the last slots of the sequence, in order, so no row of group j
-// sees past the group's last slot: with `held` slots before the step that is slot held + (j + 1) qpg - 1, and the
-// item ends there instead of at the sequence's end.  For an append that is long against what it follows (a
+// Pages of a sequence's row groups in the ragged regime.  A step's rows are the last slots of the sequence, in order, so
+// no row of group j sees past the group's last slot: with `held` slots before the step that is slot held + (j + 1) qpg - 1,
+// and the item ends there instead of at the sequence's end (in the even regime every item has all pages of its
+// sequence; pieces that no row of the group sees are written and merged as empty partials).  For an append that is long against what it follows (a
 // prompt) this halves the pages: 8 prompts of 90 to 2000 tokens 225 -> 163 us a layer.
 // Groups of whole pages only (qpg a multiple of 16: the lengths are then an arithmetic series, which the
 // flattened index is solved for); otherwise, and where the lengths do not add up (a refused sequence), every item has

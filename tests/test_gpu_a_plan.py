@@ -154,13 +154,15 @@ def test_plan_covers_every_item_once(A, case):
 
 
 @pytest.mark.parametrize("hq,hkv", [(32, 8), (8, 8), (12, 4)])
-@pytest.mark.parametrize("cap", [0, 7])
-def test_items_of_a_long_append_end_at_their_own_rows(A, hq, hkv, cap):
+@pytest.mark.parametrize("cap,alone", [(0, False), (7, False), (0, True), (7, True)])
+def test_items_of_a_long_append_end_at_their_own_rows(A, hq, hkv, cap, alone):
     """Prompts of several row groups, on empty sequences and behind tokens: where a group holds whole pages' worth
-    of queries (32/8 and 8/8 heads: 64 and 256 of them; 12/4: 85, where it does not) its item ends at the page of its
-    last row.  Every such item is covered once, by consecutive runs of consecutive workgroups."""
-    new = np.array([1, 64, 65, 1000, 257, 0, 2030], dtype=np.int32)
-    held = np.array([0, 0, 31, 17, 0, 5, 160], dtype=np.int32)
+    of queries (32/8 and 8/8 heads: 64 and 256 of them; 12/4: 85, where it does not) and items share workgroups (more
+    items than workgroups, or a batch too uneven for pieces of one length), its item ends at the page of its last row.
+    One prompt alone on the whole chip is cut into pieces of one length instead, and its items have all pages.  Every
+    item is covered once, by consecutive runs of consecutive workgroups."""
+    new = np.array([1000] if alone else [1, 64, 65, 1000, 257, 0, 2030], dtype=np.int32)
+    held = np.array([40] if alone else [0, 0, 31, 17, 0, 5, 160], dtype=np.int32)
     B, pages = len(new), -(-(new + held) // 16)
     tables = np.full((B, int(pages.max())), -1, dtype=np.int32)
     for s in range(B):
@@ -176,6 +178,8 @@ def test_items_of_a_long_append_end_at_their_own_rows(A, hq, hkv, cap):
     _, _, qpg, nwg = _decode_key(step.plan_key)
     assert qpg == 256 // (hq // hkv)
     plan, cu = step.plan.cpu().numpy().view(np.int32), step.cu_seq_new.cpu().numpy()
+    even = alone and cap == 0
+    assert not even or all(int(plan[HDR * w + NSEG]) <= 1 for w in range(nwg))
     runs = {}
     for w in range(nwg):
         hdr = plan[HDR * w: HDR * (w + 1)]
@@ -188,7 +192,7 @@ def test_items_of_a_long_append_end_at_their_own_rows(A, hq, hkv, cap):
         for h in range(hkv):
             for g in range(-(-int(new[s]) // qpg)):
                 rows = min(qpg, int(new[s]) - g * qpg)
-                end = held[s] + (g * qpg + rows if qpg % 16 == 0 else new[s])
+                end = held[s] + (g * qpg + rows if qpg % 16 == 0 and not even else new[s])
                 r = sorted(runs.pop((s, h, int(cu[s]) + g * qpg)))
                 assert r[0][2] == 0 and r[-1][3] == -(-int(end) // 16), (s, h, g, r)
                 assert all(a[3] == b[2] and b[0] == a[0] + 1 for a, b in zip(r, r[1:])), (s, h, g, r)

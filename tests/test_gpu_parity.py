@@ -518,6 +518,22 @@ def test_prompts_of_many_row_groups(A, hq, hkv, hd):
         _compare_attention(A, gb, tt, wl, step, meta, A.aspd_attn_serial_decode, label=f"prompts {hq}/{hkv}")
 
 
+@pytest.mark.parametrize("hq,hkv,hd,held,new", [(32, 8, 128, 0, 1000), (32, 8, 64, 40, 150), (8, 8, 128, 7, 900), (12, 4, 64, 0, 333)])
+def test_one_prompt_alone(A, hq, hkv, hd, held, new):
+    """A single prompt with fewer row groups than the chip has workgroups: its items are cut into pieces of one length, and
+    those at the end of an early row group's pages hold no key that any of its rows sees."""
+    from gpu_drive import GpuBatch
+    wl = W.random_small(seed=91 + hq + hd, num_q_heads=hq, num_kv_heads=hkv, head_dim=hd, batch=1,
+                        prefix_range=(held + new, held + new), branches_range=(1, 1), branch_len_range=(1, 1))
+    gb = GpuBatch(wl)
+    tt = TokenTable(wl.block_tables, wl.block_size)
+    for n in filter(None, (held, new)):
+        one = np.array([n], dtype=np.int32)
+        meta = tt.append_serial(one)
+        step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_SERIAL, gb._dev_i32(one), NQ=n, max_new_per_seq=n)
+    _compare_attention(A, gb, tt, wl, step, meta, A.aspd_attn_serial_decode, label=f"one prompt {held}+{new} {hq}/{hkv}")
+
+
 # --------------------------------------------------------------------------------------------- position paradigms
 @pytest.mark.parametrize("mode", ["same_max", ("fix", 48)])
 def test_position_paradigms_of_the_ablation(A, mode):
