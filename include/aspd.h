@@ -283,9 +283,9 @@ ASPD_API size_t aspd_sequence_plan_bytes(const aspd_kv* kv, int32_t B, int32_t N
  * physical slots, kv_len (the keys Eq. 2-3 let the token see, itself included), q_seq, and in q_branch the
  * token's branch number within its own stage minus one (-1 for main-branch tokens).  cu_new_d is not
  * written.  out->NQ must equal the sum of run_len (else ASPD_FAULT_ROW_COUNT); out->plan_d is required
- * (aspd_sequence_plan_bytes): it receives, per row, the first slot of the row's own stage, and the list of
- * row groups the attention call works through.  The state is left as after a merge of the last stage:
- * seq_len = stage_base = tokens of the sequence, stage_open = 0, main_pos = the next main-branch position,
+ * (aspd_sequence_plan_bytes): it receives, per row, the first slot of the row's own stage and that of its own
+ * branch there, and the list of row groups the attention call works through.  The state is left as after a
+ * merge of the last stage: seq_len = stage_base = tokens of the sequence, stage_open = 0, main_pos = the next main-branch position,
  * branch_len of the sequence's entries untouched; slot_owner[s][j] = branch number of slot j within its
  * stage (0 for main-branch slots).  Decoding continues from there with aspd_build_branch_meta.
  * Faults as in aspd_build_branch_meta (a sequence that does not fit its block table or owner row, or breaks
@@ -298,8 +298,9 @@ ASPD_API int aspd_build_sequence_meta(const aspd_kv* kv, aspd_state* state, cons
  * own that are main-branch slots, slots of other stages, or slots of its own branch.  `step` is one built by
  * aspd_build_sequence_meta (anything else: ASPD_ERR_INVALID_ARG); the K and V rows of all its tokens are in
  * the cache (aspd_rope_append with the same step writes them).  bf16 only (ASPD_ERR_UNSUPPORTED for fp32).
- * Key pages beyond a row group's last slot are never read, and a wave skips the pages of a stage that hold
- * only sibling branches of its rows.  With step->shared_mask = 1 every row attends every slot up to and including its
+ * Key pages beyond a row group's last slot are never read, nor, for a group whose rows all lie in one stage,
+ * those between the stage's start and the group's first branch; a wave skips the pages between the start of its
+ * rows' latest stage and their first branch there.  With step->shared_mask = 1 every row attends every slot up to and including its
  * own (plain causal attention over the sequence: the "Shared" mask of Sec. 4.5.2, and what a re-prefill of a
  * sequence without parallel stages computes).  Other arguments as aspd_attn_parallel_decode; the workspace needs
  * aspd_workspace_bytes(kv, B, NQ) like any other call (only its counters are used). */

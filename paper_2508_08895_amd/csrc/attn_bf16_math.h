@@ -42,9 +42,10 @@ struct PairRegs {
   uint32_t own[2];  // owner tags of this lane's four keys in either page (pairs that need masking only)
 };
 
-// Owner tags through the scalar (constant) path, for the kernel whose waves fetch pages cooperatively:
-// the address is the same for the whole wave, and scalar loads are counted apart from the vector
-// loads, so waiting for the tags of a pair never means waiting for the pages of the next pair.
+// Owner tags through the scalar (constant) path, for the kernels whose waves fetch pages cooperatively and
+// straight into LDS: the address is the same for the whole wave, and scalar loads are counted apart from the
+// vector loads, whose count those kernels wait on for pages (a vector load of tags among them would have to
+// be waited for together with every group of pages sent before it).
 typedef u32x4 __attribute__((aligned(4))) u32x4_a4;
 __device__ __forceinline__ u32x4 load_tags_uniform(const uint8_t* p /* same in all lanes, 4-byte aligned */) {
   return *(const __attribute__((address_space(4))) u32x4_a4*)(uintptr_t)p;

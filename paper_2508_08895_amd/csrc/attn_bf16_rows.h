@@ -141,7 +141,6 @@ __device__ __forceinline__ float rows_raise(const f32x16& s, Rows32<D>& rs, bf16
 template <int D, int NW, bool SEQ = false>
 __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool complete, float* pslot) {
   using C = RowsCfg<D>;
-  constexpr int THREADS = NW * 64;
   constexpr int PPS = ROWS_PPS;
   static_assert(PPS == 2 && NW == 4 * PPS, "one wave per page of a group");
   constexpr int LPT = C::PAGE_U4 / 64;      // 16-byte loads per lane and page
@@ -225,7 +224,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
 #pragma unroll
   for (int off = 1; off < 32; off <<= 1) {
     own_lo = min(own_lo, __shfl_xor(own_lo, off));
-    own_hi = max(own_hi, __shfl_xor(own_hi, off));
+    if (!SEQ) own_hi = max(own_hi, __shfl_xor(own_hi, off));
   }
   own_lo = __builtin_amdgcn_readfirstlane(own_lo);
   own_hi = __builtin_amdgcn_readfirstlane(own_hi);
