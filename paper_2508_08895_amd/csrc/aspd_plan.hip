@@ -28,9 +28,9 @@ struct PlanArgs {
 struct Item {
   int s, rg, h;     // sequence, row group, KV head
   int np;           // pages of the item
-  int lp;           // pages of it that lie wholly before stage_base (no owner tags, no masking)
+  int lp;           // even regime: pages of it that lie wholly before stage_base (no owner tags, no masking)
   int q0, nq;       // first packed query row and number of queries of the row group
-  int first_unit;   // flattened index of the item's page 0
+  int first_unit;   // ragged regime: flattened index of the item's first unit
 };
 
 // Per-sequence scalars in LDS and the table of share boundaries.
@@ -39,6 +39,7 @@ struct Sched {
   int* T;         // [B]   seq_len
   int* L;         // [B]   stage_base
   int* q0;        // [B+1] cu_seq_new
+  int* ng;        // [B]   row groups
   int* wgb;       // [MAX_WG+1] first unit of every workgroup's share (ragged regime only)
 };
 __device__ __forceinline__ Sched sched_at(int* base, int B) {
@@ -47,23 +48,21 @@ __device__ __forceinline__ Sched sched_at(int* base, int B) {
   sc.T = base + (B + 1);
   sc.L = sc.T + B;
   sc.q0 = sc.L + B;
-  sc.wgb = sc.q0 + (B + 1);
+  sc.ng = sc.q0 + (B + 1);
+  sc.wgb = sc.ng + B;
   return sc;
 }
-constexpr int sched_ints(int B) { return (4 * B + 2 + MAX_WG + 1 + 3) & ~3; }  // (what follows stays 16-byte aligned)
+constexpr int sched_ints(int B) { return (5 * B + 2 + MAX_WG + 1 + 3) & ~3; }  // (what follows stays 16-byte aligned)
 
 __device__ __forceinline__ int pages_of(const PlanArgs& a, const Sched& sc, int s) {
   return min((sc.T[s] + ASPD_BLOCK - 1) / ASPD_BLOCK, a.max_blocks_per_seq);
-}
-__device__ __forceinline__ int groups_of(const PlanArgs& a, const Sched& sc, int s) {
-  return (sc.q0[s + 1] - sc.q0[s] + a.qpg - 1) / a.qpg;
 }
 
 // Pages of a sequence's row groups in the ragged regime.  A step's rows are the last slots of the sequence, in order, so
 // no row of group j sees past the group's last slot: with `held` slots before the step that is slot held + (j + 1) qpg - 1,
 // and the item ends there instead of at the sequence's end (in the even regime every item has all pages of its
-// sequence; pieces that no row of the group sees are written and merged as empty partials).  For an append that is long against what it follows (a
-// prompt) this halves the pages: 8 prompts of 90 to 2000 tokens 225 -> 163 us a layer.
+// sequence; pieces that no row of the group sees are written and merged as empty partials).  For an append that is long
+// against what it follows (a prompt) this halves the pages: 8 prompts of 90 to 2000 tokens 225 -> 163 us a layer.
 // Groups of whole pages only (qpg a multiple of 16: the lengths are then an arithmetic series, which the
 // flattened index is solved for); otherwise, and where the lengths do not add up (a refused sequence), every item has
 // all pages.
@@ -79,15 +78,19 @@ struct Groups {
   }
   __device__ __forceinline__ int pages(int j) const { return j < n - 1 ? first + (j + 1) * step : np; }
 };
-__device__ __forceinline__ Groups groups_at(const PlanArgs& a, int T, int rows) {
+__device__ __forceinline__ Groups groups_at(const PlanArgs& a, int T, int rows, int n) {
   Groups g;
-  g.n = (rows + a.qpg - 1) / a.qpg;
+  g.n = n;
   const int all = (T + ASPD_BLOCK - 1) / ASPD_BLOCK;
   g.np = min(all, a.max_blocks_per_seq);
   const bool ends = (int)(g.n > 1) & (int)(a.qpg % ASPD_BLOCK == 0) & (int)(T >= rows) & (int)(all == g.np);
   g.first = ends ? (T - rows + ASPD_BLOCK - 1) / ASPD_BLOCK : g.np;
   g.step = ends ? a.qpg / ASPD_BLOCK : 0;
   return g;
+}
+
+__device__ __forceinline__ Groups groups_of(const PlanArgs& a, const Sched& sc, int s) {
+  return groups_at(a, sc.T[s], sc.q0[s + 1] - sc.q0[s], sc.ng[s]);
 }
 
 // Shares of the unit space, one per workgroup used.  A unit is a page of an item or, in the ragged
@@ -113,50 +116,64 @@ struct Shares {
   __device__ __forceinline__ int nominal_begin(int w) const { return min(total, (int)((double)w * share)); }
 };
 
-// The item that holds unit `u`, and the unit's index within it (padding first, then the pages).
-// `hint`: a sequence at or before the one that holds u, or -1 (a walk moves forward: the item it was at).
-__device__ Item locate(const PlanArgs& a, const Sched& sc, int pad, int u, int* vpage, int hint = -1) {
+// Row group `rg` of sequence it->s.
+__device__ __forceinline__ void set_group(const PlanArgs& a, const Sched& sc, const Groups& g, int rg, Item* it) {
+  const int qs = sc.q0[it->s];
+  it->rg = rg;
+  it->np = g.pages(rg);
+  it->q0 = qs + rg * a.qpg;
+  it->nq = min(a.qpg, sc.q0[it->s + 1] - it->q0);
+}
+
+// The item that holds unit `u` (ragged regime), its sequence's groups, and the unit's index within it (padding first, then
+// the pages).
+__device__ Item locate(const PlanArgs& a, const Sched& sc, int pad, int u, Groups* groups, int* vpage) {
   int lo = 0, hi = a.B - 1;  // the last sequence that starts at or before u
-  if (hint >= 0) {
-    // the same sequence or one of the next two, else search from there on
-    lo = hint;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      if (lo < hi && sc.cu_units[lo + 1] <= u) ++lo; else hi = lo;
-    }
-    if (lo < a.B - 1 && sc.cu_units[lo + 1] <= u) hi = a.B - 1;  // further on: bisect the rest
-  }
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (sc.cu_units[mid] <= u) lo = mid; else hi = mid - 1;
   }
   Item it;
   it.s = lo;
-  const int qs = sc.q0[lo];
-  const int nq = sc.q0[lo + 1] - qs;
-  const Groups g = groups_at(a, sc.T[lo], nq);
+  const Groups g = groups_of(a, sc, lo);
   const int per_head = g.before(g.n, pad);
   int rel = u - sc.cu_units[lo];
   it.h = rel / per_head;      // row groups of one KV head are neighbours: they read the same pages
   rel -= it.h * per_head;
+  int rg = 0;
   if (g.step == 0) {
-    it.rg = rel / (g.np + pad);
+    if (g.n > 1) rg = rel / (g.np + pad);
   } else {
-    int r0 = 0, r1 = g.n - 1;  // the last group that starts at or before rel
-    while (r0 < r1) {
-      const int mid = (r0 + r1 + 1) >> 1;
-      if (g.before(mid, pad) <= rel) r0 = mid; else r1 = mid - 1;
+    int hi_rg = g.n - 1;  // the last group that starts at or before rel
+    while (rg < hi_rg) {
+      const int mid = (rg + hi_rg + 1) >> 1;
+      if (g.before(mid, pad) <= rel) rg = mid; else hi_rg = mid - 1;
     }
-    it.rg = r0;
   }
-  it.np = g.pages(it.rg);
-  const int start = g.before(it.rg, pad);
+  set_group(a, sc, g, rg, &it);
+  const int start = g.before(rg, pad);
   *vpage = rel - start;
   it.first_unit = sc.cu_units[lo] + it.h * per_head + start;
-  it.lp = a.has_owner ? min(it.np, sc.L[lo] / ASPD_BLOCK) : it.np;
-  it.q0 = qs + it.rg * a.qpg;
-  it.nq = min(a.qpg, nq - it.rg * a.qpg);
+  *groups = g;
   return it;
+}
+
+// The item after `it`; there has to be one.  (The kernel is one workgroup whose threads each walk a workgroup's share, so
+// what a step of the walk takes adds up: with a look-up of every item, three divisions and two searches, the plan of a
+// 64-sequence chunk took 38.0 us, 28.0 now; of eight prompts 21.7 -> 15.4, of 64 decoding sequences 22.0 -> 18.9.)
+__device__ __forceinline__ void advance(const PlanArgs& a, const Sched& sc, int pad, Item* it, Groups* g) {
+  it->first_unit += it->np + pad;
+  int rg = it->rg + 1;
+  if (rg >= g->n) {
+    rg = 0;
+    if (++it->h >= a.num_kv_heads) {
+      it->h = 0;
+      do ++it->s;  // sequences without units start where the next one does
+      while (it->s < a.B - 1 && sc.cu_units[it->s + 1] <= it->first_unit);
+      *g = groups_of(a, sc, it->s);
+    }
+  }
+  set_group(a, sc, *g, rg, it);
 }
 
 // Cutting one item among its k workgroups (even regime).  A page of the branch region costs a wave
@@ -180,7 +197,8 @@ __device__ int share_begin(const PlanArgs& a, const Sched& sc, const Shares& sh,
   if (w >= sh.n) return sh.total;
   const int nominal = sh.nominal_begin(w);
   int vpage;
-  const Item it = locate(a, sc, sh.pad, nominal, &vpage);
+  Groups g;
+  const Item it = locate(a, sc, sh.pad, nominal, &g, &vpage);
   const int vl = it.np + sh.pad;
   if (vpage <= sh.pad + sh.tol) return it.first_unit;
   if (vl - vpage <= sh.tol) return it.first_unit + vl;
@@ -208,7 +226,8 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
       sc.L[s] = a.stage_base[s];
       sc.q0[s] = q0;
       if (s == a.B - 1) sc.q0[a.B] = q1;
-      const Groups g = groups_at(a, T, q1 - q0);
+      const Groups g = groups_at(a, T, q1 - q0, (q1 - q0 + a.qpg - 1) / a.qpg);
+      sc.ng[s] = g.n;
       const int np = g.np;
       if (np > 0 && g.n > 0) {
         mine_i[j] = g.n * a.num_kv_heads;
@@ -381,7 +400,7 @@ __device__ bool even_share(const PlanArgs& a, const Sched& sc, const Shares& sh,
   const int k = (it.np + sh.piece - 1) / sh.piece;  // workgroups per item of this sequence
   const int local = w - sc.cu_units[lo];
   const int idx = local / k, j = local - idx * k;
-  const int ngroups = groups_of(a, sc, lo);
+  const int ngroups = sc.ng[lo];
   it.h = idx / ngroups;       // row groups of one KV head are neighbours: they read the same pages
   it.rg = idx - it.h * ngroups;
   it.first_unit = 0;
@@ -397,37 +416,22 @@ __device__ bool even_share(const PlanArgs& a, const Sched& sc, const Shares& sh,
   return *page1 > *page0;
 }
 
-// Ragged regime: the next run of real pages in [*u, end), or false at the end.
-__device__ bool next_segment(const PlanArgs& a, const Sched& sc, const Shares& sh, int* u, int end, int* s_hint,
-                             Item* it, int* page0, int* page1) {
-  while (*u < end) {
-    int v0;
-    *it = locate(a, sc, sh.pad, *u, &v0, *s_hint);
-    *s_hint = it->s;
-    const int v1 = min(it->np + sh.pad, v0 + (end - *u));
-    *u += v1 - v0;
-    *page0 = max(0, v0 - sh.pad);
-    *page1 = max(0, v1 - sh.pad);
-    if (*page1 > *page0) return true;
-  }
-  return false;
-}
-
 // A workgroup's walk over its share, as an iterator: each step gives a segment and the first and last
 // workgroup that hold a part of its item.
 struct Walk {
   int u, end;
-  int s_hint;  // sequence of the item the walk was at last (-1: none yet)
+  Item it;      // ragged regime: the item that holds u, while u < end
+  Groups g;     // its sequence's groups
+  int vpage;    // index of u within it
   bool even_pending;
 };
-__device__ __forceinline__ Walk walk_begin(const Sched& sc, const Shares& sh, int w) {
-  Walk wk;
-  wk.u = wk.end = 0;
-  wk.s_hint = -1;
+__device__ __forceinline__ Walk walk_begin(const PlanArgs& a, const Sched& sc, const Shares& sh, int w) {
+  Walk wk = {};
   wk.even_pending = sh.even && w < sh.n;
   if (!sh.even && w < sh.n) {
     wk.u = sc.wgb[w];
     wk.end = sc.wgb[w + 1];
+    if (wk.u < wk.end) wk.it = locate(a, sc, sh.pad, wk.u, &wk.g, &wk.vpage);
   }
   return wk;
 }
@@ -438,10 +442,25 @@ __device__ __forceinline__ bool walk_next(const PlanArgs& a, const Sched& sc, co
     wk->even_pending = false;
     return even_share(a, sc, sh, w, it, page0, page1, owner, w_last);
   }
-  if (!next_segment(a, sc, sh, &wk->u, wk->end, &wk->s_hint, it, page0, page1)) return false;
-  *owner = *page0 == 0 ? w : share_owner(sc, sh, it->first_unit + sh.pad);
-  *w_last = *page1 == it->np ? w : share_owner(sc, sh, it->first_unit + sh.pad + it->np - 1);
-  return true;
+  // the next run of real pages in [u, end)
+  while (wk->u < wk->end) {
+    const int v0 = wk->vpage;
+    const int v1 = min(wk->it.np + sh.pad, v0 + (wk->end - wk->u));
+    *it = wk->it;
+    *page0 = max(0, v0 - sh.pad);
+    *page1 = max(0, v1 - sh.pad);
+    wk->u += v1 - v0;
+    if (wk->u < wk->end) {  // the item ends here
+      advance(a, sc, sh.pad, &wk->it, &wk->g);
+      wk->vpage = 0;
+    }
+    if (*page1 > *page0) {
+      *owner = *page0 == 0 ? w : share_owner(sc, sh, it->first_unit + sh.pad);
+      *w_last = *page1 == it->np ? w : share_owner(sc, sh, it->first_unit + sh.pad + it->np - 1);
+      return true;
+    }
+  }
+  return false;
 }
 
 // Segments of a workgroup that pass 1 keeps in LDS for pass 2 (8 words each); a workgroup with more is walked
@@ -465,7 +484,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(PlanArgs a) {
   int cnt = 0;
   Walk resume;  // where the walk stood after the cached segments
   if (w < a.nwg) {
-    Walk wk = walk_begin(sc, sh, w);
+    Walk wk = walk_begin(a, sc, sh, w);
     resume = wk;
     Item it;
     int p0, p1, owner, w_last;
