@@ -8,7 +8,7 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // bf16, many rows per KV head (branch chunks, prefills, whole sequences): the waves of a workgroup split
 // the ROWS instead of the keys.  Every group of ROWS_PPS pairs of pages is loaded once per workgroup,
-// cooperatively and straight into LDS, three groups ahead, for all waves to read; each wave keeps its own 32 rows
+// cooperatively and straight into LDS, two groups ahead, for all waves to read; each wave keeps its own 32 rows
 // (Q operands, accumulators, softmax state, all in registers) for the whole segment, so there is no
 // reduction across waves.  One barrier per group.  With NW waves a row group holds NW * 32 rows, and the
 // pages of a KV head are fetched once per that many rows.
@@ -44,14 +44,19 @@ struct RowsCfg {
   static __device__ __forceinline__ int kswz(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
   static __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 };
-constexpr int ROWS_BUFS = 4;  // groups in LDS: the one being computed, three on their way
+// Groups in LDS: the one being computed, two on their way (three stages would do; four make the ring a mask).  One group
+// ahead is too few where row groups are light and the read rate of the chip counts, a third one only costs scalar registers.
+// Groups ahead 1 / 2 / 3, whole steps, us: 64 sequences x 8000 tokens, two layers, 52 rows per KV head 806 / 776 / 778, 256
+// rows 1203 / 1207 / 1210, 64 rows of head size 64 292 / 242 / 243; 39 sequences of up to 500 tokens at 8/8 heads 343 / 352 /
+// 357, 12 of up to 1000 at 32/8 149 / 149 / 153; the 64-sequence chunk 1727 / 1739 / 1754; prompts 433 / 434 / 436.
+constexpr int ROWS_BUFS = 4;
 
 template <int D>
 constexpr size_t rows_smem_bytes() { return (size_t)ROWS_BUFS * RowsCfg<D>::STAGE_B; }
 
 // Sixteen bytes per lane from global memory straight into LDS: lane l's go to byte lds + 16 l.  (Assembly because
-// the compiler makes every later LDS read wait for all such loads in flight; rows_wait() says which have to be
-// there.  It reads no vector register but the offset, and writes none.  It brings its own wait states: one behind the
+// the compiler makes every later LDS read wait for all such loads in flight; segment_rows() counts which have to
+// be there.  It reads no vector register but the offset, and writes none.  It brings its own wait states: one behind the
 // write of m0, and five in front of the load for a base that a vector instruction has written, as the reload of a spilled
 // scalar register is; the compiler does not see that a memory instruction in here reads it.)
 #pragma clang diagnostic push
@@ -442,7 +447,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
     tc[1] = tn[1];
   };
 
-  // One barrier per group: every wave has its page of the group in LDS, and is done with the stage that the group three
+  // One barrier per group: every wave has its page of the group in LDS, and is done with the stage that the group two
   // further on goes to.  The V rows of slots past the last row's or past the segment are cleared before it: they may
   // hold anything, or an infinity that belongs to another slot, and zero times either would be a NaN.
   const int i_last = npairs >> 1;
@@ -460,8 +465,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
         u32x4{0u, 0u, 0u, 0u};
   };
   auto arrive = [&](int i, bool tail) {
-    if (i + 2 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LPT) : "memory");
-    else if (i + 1 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
+    if (i + 1 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (tail && !l_is_k) {
       const int key0 = (page_of_pair(2 * i - 1 + l_pair) + (wave & 1)) * ASPD_BLOCK;
@@ -472,7 +476,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
       }
     }
     __syncthreads();
-    send(i + 3);
+    send(i + 2);
   };
   auto general_groups = [&](int from, int to) {
     for (int i = from; i < to; ++i) {
@@ -501,7 +505,6 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   } else {
     send(0);
   }
-  send(1);
   general_groups(-1, 0);  // (the scores of pair 0)
   int i = 0;
   if (i_open > 0) {
