@@ -42,8 +42,9 @@ constexpr int PAD_STREAM = 32;       // fixed cost of a segment in pages, bandwi
 constexpr int PAD_COMPUTE = 8;       // the same for the fp32 kernel
 constexpr int PAD_ROWS = 32;         // and for the row-splitting kernel: a segment there costs about 17 us (Q operands
                                      // of 256 rows into registers, 64-128 KB of output or partial, its share of a
-                                     // merge), 25-40 pages' worth; measured on a 64-sequence chunk step: 8 -> 828 us,
-                                     // 16 -> 818, 24 -> 809, 32 -> 804, 48 -> 822, 64 -> 827
+                                     // merge), 25-40 pages' worth; steps with 16 / 32 / 48, us: 64-sequence chunk
+                                     // 1830 / 1750 / 1690, eight prompts 437 / 435 / 442, stage opening over 12
+                                     // sequences 317 each time
 
 enum AttnKernel { KERNEL_F32 = 0, KERNEL_BF16_STREAM = 1, KERNEL_BF16_ROWS = 2 };
 
