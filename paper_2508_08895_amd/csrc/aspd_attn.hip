@@ -26,6 +26,7 @@
 #include <cmath>
 #include <mutex>
 #include <set>
+#include <type_traits>
 #include <utility>
 
 #include "aspd_plan.h"
@@ -126,6 +127,7 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
   a.B = state->B;
   a.nwg = v.nwg;
   a.G = kv->num_q_heads / kv->num_kv_heads;
+  a.inv_G = 1.f / (float)a.G;
   a.qpg = v.qpg;
   a.rows_cap = v.rows_cap;
 
@@ -150,11 +152,9 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
 #define ASPD_BF16_CASE(DD, NN)                                                                            \
   do {                                                                                                    \
     if (v.stream_once)                                                                                    \
-      ASPD_LAUNCH((attn_bf16_kernel<DD, NN, STREAM_NW, STREAM_PF, true>), STREAM_NW * 64,                 \
-                  (bf16_smem_bytes<DD, NN, STREAM_NW>()));                                                \
+      ASPD_LAUNCH((attn_bf16_kernel<DD, NN, true>), STREAM_NW * 64, (StreamLds<DD, NN>::BYTES));          \
     else                                                                                                  \
-      ASPD_LAUNCH((attn_bf16_kernel<DD, NN, STREAM_NW, STREAM_PF, false>), STREAM_NW * 64,                \
-                  (bf16_smem_bytes<DD, NN, STREAM_NW>()));                                                \
+      ASPD_LAUNCH((attn_bf16_kernel<DD, NN, false>), STREAM_NW * 64, (StreamLds<DD, NN>::BYTES));         \
   } while (0)
     if (D == 128) {
       if (v.nt == 1) ASPD_BF16_CASE(128, 1);
@@ -321,6 +321,7 @@ extern "C" int aspd_attn_full_sequence(const aspd_kv* kv, const aspd_state* stat
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)kv->head_dim) : sm_scale) * LOG2E;
   a.B = state->B;
   a.G = G;
+  a.inv_G = 1.f / (float)G;
   a.qpg = qpg;
   a.rows_cap = ROWS_NW * 32;
   // one workgroup per compute unit, never more than there are row groups to take

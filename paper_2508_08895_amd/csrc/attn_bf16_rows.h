@@ -54,19 +54,6 @@ constexpr int ROWS_BUFS = 4;
 template <int D>
 constexpr size_t rows_smem_bytes() { return (size_t)ROWS_BUFS * RowsCfg<D>::STAGE_B; }
 
-// Sixteen bytes per lane from global memory straight into LDS: lane l's go to byte lds + 16 l.  (Assembly because
-// the compiler makes every later LDS read wait for all such loads in flight; segment_rows() counts which have to
-// be there.  It reads no vector register but the offset, and writes none.  It brings its own wait states: one behind the
-// write of m0, and five in front of the load for a base that a vector instruction has written, as the reload of a spilled
-// scalar register is; the compiler does not see that a memory instruction in here reads it.)
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"  // (m0 is reserved; in the code as built nothing else uses it)
-__device__ __forceinline__ void load_to_lds(const void* base /* uniform */, uint32_t offset, uint32_t lds /* uniform */) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(offset), "s"(base)
-               : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
 // One wave's 32 rows: lane (c, h) keeps the statistics of row c (its share of the sum) and O^T[32 mt + 8 b + 4 h +
 // j][c] in acc[mt][4 b + j].
 template <int D>
@@ -88,14 +75,11 @@ struct Rows32 {
 // 438 -> 444) and 0.6 % of the 64-sequence ones (chunk 1790 -> 1801 us, whole sequences 23.81 -> 23.94 ms).
 constexpr float ROWS_SUM_MAX = 20.f;
 
-// LDS operands by byte address.
-__device__ __forceinline__ bf16x8 rows_k_operand(uint32_t at) {
-  return *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)at;
-}
+// V operand: two transposing reads, eight rows apart.
 template <int D>
 __device__ __forceinline__ bf16x8 rows_v_operand(uint32_t at) {
-  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)at);
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(uintptr_t)(at + 8 * D * 2));
+  const s16x4 a = lds_operand_transposed(at);
+  const s16x4 b = lds_operand_transposed(at + 8 * D * 2);
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
@@ -159,7 +143,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   const int Rw = min(32, R - wave * 32);           // rows this wave owns (<= 0: none)
   const bool wave_active = Rw > 0;
 
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;  // [ROWS_BUFS] stages
+  const uint32_t lds0 = lds_address(smem);  // [ROWS_BUFS] stages
   typedef const __attribute__((address_space(4))) int32_t* const_i32;  // (block tables: no kernel writes them)
   const const_i32 bt = (const_i32)(uintptr_t)(a.kv.block_tables + (long)it.s * a.kv.max_blocks_per_seq);
   const uint8_t* owner_row = (!SEQ && a.slot_owner) ? uniform_ptr(a.slot_owner + (long)it.s * a.owner_stride) : nullptr;
@@ -266,7 +250,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
 #pragma unroll
     for (int mt = 0; mt < C::MT; ++mt) va[mt] += d;
   };
-  auto k_operand = [&](int u, int t) { return rows_k_operand(ka[t] + u * C::PAIR_B); };
+  auto k_operand = [&](int u, int t) { return lds_operand(ka[t] + u * C::PAIR_B); };
   auto v_operand = [&](int u, int j) { return rows_v_operand<D>(va[j % C::MT] + u * C::PAIR_B + (j / C::MT) * C::PAGE_B); };
 
   // ---- staging.  Group i holds the K pages of pairs 2 i + 1 and 2 i + 2 and the V pages of pairs 2 i - 1 and
@@ -594,7 +578,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
     const bool complete = seg_complete(seg);
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
     segment_rows<D, NW>(a, smem, seg, complete, pslot);
-    if (!complete) announce_partial<D, true, THREADS, 2>(a, seg, &merge_flag);
+    if (!complete) announce_partial<D, true, THREADS, 4, 4>(a, seg, &merge_flag);
   }
 }
 

@@ -6,418 +6,423 @@
 
 namespace {
 
-constexpr int BLK_WIN = 512;   // pages of a segment whose block ids are staged in LDS at once
+// ---------------------------------------------------------------------------------------------
+// Every wave takes pages of its segment, 16 keys of K and V, computes them against all rows of the row group (NT tiles of
+// 16 rows) and keeps its own accumulators; the waves are combined once per segment.
+//
+// Large launches are bound by the page stream, small ones by the chain around it (header, first pages, combination of the
+// waves, partial, merge), and that chain by instruction issue: a wave alone on its SIMD issues one instruction in eight
+// to nine cycles.  Hence eight waves (two per SIMD) on single pages, where it was four on pairs of pages, with the same
+// 64 KB per compute unit on their way; pages, queries and descriptors loaded straight into LDS, which leaves the waves
+// 256 registers for everything else; and no cross-lane step, division or barrier that can be had otherwise.  Attention
+// alone in graph replay, four waves with pairs in registers -> this, us: one sequence of 2 300 tokens 14.8 -> 9.5; 27
+// mixed sequences of up to 3 000, head size 64 16.1 -> 11.7; 16 sequences of 512 to 4 096 45.2 -> 41.7; four of 16 k,
+// six branches 52.2 -> 49.6, after the merge 50.7 -> 45.2; 64 sequences of up to 8 192 231 -> 219 (6.2 TB/s).
+//
+// S^T[key][row] = K * Q^T on 16x16x32 MFMA: lane (c, g) = (lane % 16, lane / 16) holds, of row c, the keys 4 g .. 4 g + 3
+// of the page, which is the B-operand layout of O^T[d][row] = V^T * P^T on 16x16x16 MFMA, whose A operand (V^T) comes
+// from the LDS transpose read.  The statistics of a row live in the four lanes c, c + 16, c + 32, c + 48.
+// ---------------------------------------------------------------------------------------------
+constexpr int BLK_WIN = 512;   // pages of a segment whose block ids are in LDS at once
 
-// The start-up loads of a segment, in registers: block ids of the first window, the Q rows, the row
-// descriptors, and the first pair of pages of every wave (pair `wave` of the segment).
-template <int D, int NT, int NW>
-struct SegLoads {
-  static constexpr int THREADS = NW * 64;
-  static constexpr int BPT = BLK_WIN / THREADS;  // block ids per thread and window
-  static constexpr int QL = (16 * NT * Bf16Cfg<D>::CH + THREADS - 1) / THREADS;  // Q chunks per thread
-  int blkreg[BPT];
-  u32x4 qreg[QL];
-  int d_slot, d_branch, first_branch;  // of the thread's row: logical slot, global branch; the sequence's first branch
-  int b0, b1;                          // block ids of the wave's first pair, as loaded from the block table
-  int used0, used1;                    // the block ids `first` was fetched with
-  PairRegs<D> first;
+template <int D, int NT>
+struct StreamLds {
+  static constexpr int NW = STREAM_NW;
+  static constexpr int CH = D / 8;                        // 16-byte chunks per row
+  static constexpr int PAGE_B = ASPD_BLOCK * D * 2;
+  static constexpr int LPP = PAGE_B / 1024;               // loads per page
+  static constexpr int STAGE_B = 2 * PAGE_B + 256;        // K page, V page, owner tags (16 bytes, loaded 16 times over)
+  static constexpr int LOADS = 2 * LPP + 1;               // loads of a stage
+  static constexpr int WAVE_B = 2 * STAGE_B;              // two stages, or the accumulators of two tiles
+  static constexpr int RED_ROW = D + 4;                   // floats per row there (the 16 rows a wave writes at once fall
+                                                          // on different banks)
+  static_assert(WAVE_B >= 2 * 16 * RED_ROW * 4, "two tiles of accumulators");
+  static constexpr int Q = NW * WAVE_B;                   // [16 NT] query rows, in pages of sixteen
+  static constexpr int BLK = Q + NT * PAGE_B;             // [BLK_WIN] block ids of the window
+  static constexpr int SLOT = BLK + BLK_WIN * 4;          // [64] logical slots of the row group's queries
+  static constexpr int BRANCH = SLOT + 256;               // [64] their branches
+  static constexpr int M = BRANCH + 256;                  // [16 NT][NW] references of the waves
+  static constexpr int L = M + 16 * NT * NW * 4;          // [16 NT][NW] sums
+  static constexpr int TAKE = L + 16 * NT * NW * 4;       // [64] next page nobody has taken (word 0; see take())
+  // (more than half of a compute unit's LDS: one workgroup per compute unit, as the grid is sized for)
+  static constexpr int USED = TAKE + 256;
+  static constexpr int BYTES = USED > 81 * 1024 ? USED : 81 * 1024;
+  // Order of the 16-byte chunks inside a row, so that no operand read has a bank conflict: a K (or Q) read takes one
+  // chunk of sixteen rows at a time, a transposing V read two chunks of eight.
+  static __device__ __forceinline__ int kswz(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
+  static __device__ __forceinline__ int vswz(int row) { return D == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); }
 };
 
-// Segment start-up, part one: the loads that depend on nothing but the segment.  The Q rows and row
-// descriptors are fetched alongside the block ids, and each wave fetches the two block ids of its
-// first pair itself.  Touches no LDS; every address stays in bounds for any `d` that passed seg_ok.
-template <int D, int NT, int NW>
-__device__ __forceinline__ void segment_issue_ids(const AttnArgs& a, const Seg& d, SegLoads<D, NT, NW>& ld) {
-  using C = Bf16Cfg<D>;
-  using LD = SegLoads<D, NT, NW>;
-  constexpr int ROWS = 16 * NT;
-  constexpr int THREADS = NW * 64;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 4;
-  const int R = d.nq * a.G;
-  const int* bt = a.kv.block_tables + (long)d.s * a.kv.max_blocks_per_seq;
-  const uint8_t* owner_row = a.slot_owner ? a.slot_owner + (long)d.s * a.owner_stride : nullptr;
-  // The wave's own first pair: the same two addresses in every lane.  A wave past the end of a short
-  // segment fetches the last page again (and never uses it) rather than branch: with the same loads in
-  // flight on every path, the compiler's wait counts stay exact.
-  const int P0 = min(d.page0 + 2 * wave, d.page1 - 1);
-  ld.b0 = bt[P0];
-  ld.b1 = bt[min(P0 + 1, d.page1 - 1)];
-  // no load below depends on another, so that all of them are one round trip
-  ld.first_branch = a.cu_branches ? a.cu_branches[d.s] : 0;
-#pragma unroll
-  for (int k = 0; k < LD::BPT; ++k) {
-    const int P = min(d.page0 + tid + k * THREADS, d.page1 - 1);
-    ld.blkreg[k] = bt[P];
-  }
-#pragma unroll
-  for (int k = 0; k < LD::QL; ++k) {
-    const int i = tid + k * THREADS;
-    if (i < ROWS * C::CH) {
-      const int r = i / C::CH, ch = i - r * C::CH;
-      const int rr = min(r, R - 1);
-      const int q = d.q0 + rr / a.G;
-      const int head = d.h * a.G + rr % a.G;
-      ld.qreg[k] = *((const u32x4*)a.q + ((long)q * a.kv.num_q_heads + head) * C::CH + ch);
-    }
-  }
-  ld.d_slot = 0;
-  ld.d_branch = -1;
-  if (tid < ROWS) {
-    const int rr = min(tid, R - 1);
-    const int q = d.q0 + rr / a.G;
-    ld.d_slot = a.logical_slot[q];
-    ld.d_branch = a.q_branch[q];
-  }
-  // Owner tags travel with the pair whenever the call has any (the rows that need them are not known yet).
-  // A call without tags loads two words it never looks at instead of branching: with the same loads in
-  // flight on every path the compiler's wait counts stay exact (a branch here made the page loads below
-  // wait for every load above).
-  const uint8_t* own_p0 = owner_row ? owner_row + P0 * ASPD_BLOCK + 4 * g : (const uint8_t*)a.logical_slot;
-  const int own_step = owner_row ? min(ASPD_BLOCK, a.owner_stride - 4 - (P0 * ASPD_BLOCK + 4 * g)) : 0;  // stays inside the owner row
-  ld.first.own[0] = *(const uint32_t*)own_p0;
-  ld.first.own[1] = *(const uint32_t*)(own_p0 + own_step);
-}
-// ... and the pages of the wave's first pair, from two block ids: those the plan carries for a
-// workgroup's first segment (one round trip after the kernel starts), or those just loaded from the
-// block table.  Any two blocks of the pool are safe to read; the segment compares them with the block
-// table before it uses the pages.
-template <int D, int NT, int NW, bool STREAM>
-__device__ __forceinline__ void segment_issue_pair(const AttnArgs& a, const Seg& d, SegLoads<D, NT, NW>& ld, int b0,
-                                                   int b1) {
-  ld.used0 = min(max(__builtin_amdgcn_readfirstlane(b0), 0), a.kv.num_blocks - 1);
-  ld.used1 = min(max(__builtin_amdgcn_readfirstlane(b1), 0), a.kv.num_blocks - 1);
-  issue_pair<D, STREAM>(ld.first, a, d.h, ld.used0, ld.used1, threadIdx.x & 63, nullptr, 0);
-}
+// Largest weight sum of a lane's four keys before the row's reference is raised (see segment_stream).  With 20, and with
+// the references raised at a wave's second page in any case, the error against float64 is 1 to 14 % below that of
+// references raised at a score 2^6 above (as with pairs of pages), for queries ~ N(0, 1), N(0, 4) and N(0, 36).
+constexpr float STREAM_SUM_MAX = 20.f;
 
-// Segment start-up, part two, the stream and the epilogue.  `ld` holds the loads made for this very
-// segment.
-template <int D, int NT, int NW, int PF, bool STREAM>
-__device__ void segment_bf16(const AttnArgs& a, char* smem, const Seg& it, bool complete, float* pslot,
-                             const SegLoads<D, NT, NW>& ld) {
-  using C = Bf16Cfg<D>;
-  using LD = SegLoads<D, NT, NW>;
-  constexpr int ROWS = 16 * NT;
-  constexpr int THREADS = NW * 64;
+template <int D, int NT, bool STREAM>
+__device__ __forceinline__ void segment_stream(const AttnArgs& a, char* smem, const Seg& it, bool complete, float* pslot,
+                                               int id0, int id1 /* blocks of the wave's first two pages, or what was
+                                               thought to be: compared with the block table before the pages count */) {
+  using C = StreamLds<D, NT>;
+  constexpr int NW = C::NW, THREADS = NW * 64;
+  constexpr int KSTEPS = D / 32, MT = D / 16, CH = C::CH;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15;
   const int g = lane >> 4;
   const int R = it.nq * a.G;
-  const int page0 = it.page0, page1 = it.page1, L = it.L;
+  const int page0 = it.page0, np = it.page1 - it.page0, L = it.L;
+  const uint32_t lds0 = lds_address(smem);
+  const uint32_t stage0 = lds0 + wave * C::WAVE_B;
 
-  u32x4* stage = (u32x4*)(smem + wave * C::STAGE_BYTES);                // this wave's K0 K1 V0 V1
-  u32x4* qtile = (u32x4*)(smem + NW * C::STAGE_BYTES);                  // [ROWS][LROW]
-  int* rowslot = (int*)(smem + NW * C::STAGE_BYTES + ROWS * C::LROW * 16);
-  int* rowtag = rowslot + ROWS;
-  float* wm = (float*)(rowtag + ROWS);                                  // [NW][ROWS]
-  float* wl = wm + NW * ROWS;
-  int* blk_lds = (int*)(wl + NW * ROWS);                                // [BLK_WIN] block ids of the window
-  int* pair_counter = blk_lds + BLK_WIN;                                // next pair nobody has taken yet
-
-  const int* bt = a.kv.block_tables + (long)it.s * a.kv.max_blocks_per_seq;
-  const uint8_t* owner_row = a.slot_owner ? a.slot_owner + (long)it.s * a.owner_stride : nullptr;
-
-  __syncthreads();  // LDS of the previous segment is free
+  // ---- loads of the segment's start; the small ones first, loads return in order
+  // lane offsets of a page's loads: load k brings rows k * 64 / CH ...
+  uint32_t koff[C::LPP], voff[C::LPP];
 #pragma unroll
-  for (int k = 0; k < LD::BPT; ++k) blk_lds[tid + k * THREADS] = min(max(ld.blkreg[k], 0), a.kv.num_blocks - 1);
-  if (tid == 0) *pair_counter = NW;  // pairs 0 .. NW - 1 of the first window are on their way already
+  for (int k = 0; k < C::LPP; ++k) {
+    const int row = lane / CH + k * (64 / CH);
+    koff[k] = (lane / CH) * (D * 2) + ((lane % CH ^ C::kswz(row)) << 4);
+    voff[k] = (lane / CH) * (D * 2) + ((lane % CH ^ C::vswz(row)) << 4);
+  }
+  const int32_t* bt = a.kv.block_tables + (long)it.s * a.kv.max_blocks_per_seq + page0;
+  {
+    // query rows: 1024 bytes of the tile per wave and round
+    const char* qsrc = (const char*)a.q + ((long)it.q0 * a.kv.num_q_heads + it.h * a.G) * (D * 2);
 #pragma unroll
-  for (int k = 0; k < LD::QL; ++k) {
-    const int i = tid + k * THREADS;
-    if (i < ROWS * C::CH) {
-      const int r = i / C::CH, ch = i - r * C::CH;
-      qtile[lds_pos<D>(r, ch)] = ld.qreg[k];
+    for (int j0 = 0; j0 < NT * C::LPP; j0 += NW) {
+      const int j = j0 + wave;
+      if (j < NT * C::LPP) {
+        const int row = j * (64 / CH) + lane / CH;
+        const int rr = min(row, R - 1);
+        const int qi = div_by_g(a, rr);
+        load_to_lds(qsrc, (uint32_t)((qi * a.kv.num_q_heads + rr - qi * a.G) * (D * 2) + ((lane % CH ^ C::kswz(row)) << 4)),
+                    lds0 + C::Q + j * 1024);
+      }
     }
+    if (wave == NW - 1) load4_to_lds(a.logical_slot + it.q0, 4 * min(lane, it.nq - 1), lds0 + C::SLOT);
+    if (wave == NW - 2) load4_to_lds(a.q_branch + it.q0, 4 * min(lane, it.nq - 1), lds0 + C::BRANCH);
+    load4_to_lds(bt, 4 * min(tid, np - 1), lds0 + C::BLK + wave * 256);
   }
-  if (tid < ROWS) {
-    rowslot[tid] = ld.d_slot;
-    rowtag[tid] = (ld.d_branch < 0 || !a.cu_branches) ? 0 : ld.d_branch - ld.first_branch + 1;
+  const char* const own_row = a.slot_owner ? (const char*)(a.slot_owner + (long)it.s * a.owner_stride)
+                                           : (const char*)a.logical_slot;  // (no tags: four bytes nobody looks at)
+  const uint32_t own_off = a.slot_owner ? 4 * (lane & 3) : 0;
+  const int own_step = a.slot_owner ? ASPD_BLOCK : 0;
+  auto issue = [&](int page /* of the segment */, int id, uint32_t at) {
+    const long block = min(max(id, 0), a.kv.num_blocks - 1);
+    const long from = (block * a.kv.num_kv_heads + it.h) * C::PAGE_B;
+    page_to_lds<D, STREAM>((const char*)a.kv.k + from, koff, at);
+    page_to_lds<D, STREAM>((const char*)a.kv.v + from, voff, at + C::PAGE_B);
+    load4_to_lds(own_row + (long)(page0 + page) * own_step, own_off, at + 2 * C::PAGE_B);
+  };
+  int cur = wave, nxt = wave + NW;  // pages are numbered from the segment's first; past the end: none
+  if (cur < np) issue(cur, id0, stage0);
+  if (nxt < np) issue(nxt, id1, stage0 + C::STAGE_B);
+  // the first two pages of a wave are its own, the others go to whoever is free first
+  if (tid == 0) *(__attribute__((address_space(3))) int*)(uintptr_t)(lds0 + C::TAKE) = 3 * NW;
+  int ahead = wave + 2 * NW;
+  const int first_branch = a.cu_branches ? load_word_uniform(a.cu_branches + it.s) : 0;
+  // The rows of a group are packed in the order of their slots.
+  const int first_slot = load_word_uniform(a.logical_slot + it.q0);
+  const int last_slot = load_word_uniform(a.logical_slot + it.q0 + it.nq - 1);
+  const int mask_from = min(L, first_slot);  // keys below this slot are visible to every row of the group
+
+  // what does not depend on the loads: LDS addresses of the lane's operands, per stage a constant further on
+  uint32_t ka[KSTEPS], va[MT];
+#pragma unroll
+  for (int t = 0; t < KSTEPS; ++t) ka[t] = c * (D * 2) + (((4 * t + g) ^ C::kswz(c)) << 4);
+  {
+    const int key = 4 * g + (c >> 2);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      va[mt] = stage0 + C::PAGE_B + key * (D * 2) + (((2 * mt + ((c & 3) >> 1)) ^ C::vswz(key)) << 4) + 8 * (c & 1);
   }
+  int query[NT];  // of the lane's row, within the group
+#pragma unroll
+  for (int n = 0; n < NT; ++n) query[n] = div_by_g(a, min(16 * n + c, R - 1));
+  if (nxt < np) wait_loads<2 * C::LOADS>();
+  else if (cur < np) wait_loads<C::LOADS>();
+  else wait_loads<0>();
   __syncthreads();
 
-  RowState<D, NT> ts;
-  int mask_from = L;  // keys below this slot are visible to every row of the group
-  int last_slot = 0;  // keys above this slot are visible to none
+  // ---- the rows: queries as operands, and what each row may see
+  auto lds_int = [&](uint32_t at) -> int { return *(const __attribute__((address_space(3))) int*)(uintptr_t)at; };
+  constexpr bool Q_HELD = NT * D <= 256;  // in registers (more of them would spill)
+  bf16x8 qf[NT][KSTEPS];
+  const uint32_t q_back = lds0 + C::Q - stage0;
+  int slot[NT], tag[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
-    ts.slot[n] = rowslot[16 * n + c];
-    ts.tag[n] = rowtag[16 * n + c];
-    mask_from = min(mask_from, ts.slot[n]);
-    last_slot = max(last_slot, ts.slot[n]);
+#pragma unroll
+    for (int t = 0; t < KSTEPS; ++t)
+      if (Q_HELD) qf[n][t] = lds_operand(lds0 + C::Q + n * C::PAGE_B + ka[t]);
+    slot[n] = lds_int(lds0 + C::SLOT + 4 * query[n]);
+    const int b = lds_int(lds0 + C::BRANCH + 4 * query[n]);
+    tag[n] = (b < 0 || !a.cu_branches) ? 0 : b - first_branch + 1;
   }
 #pragma unroll
-  for (int off = 1; off < 16; off <<= 1) {
-    mask_from = min(mask_from, __shfl_xor(mask_from, off));
-    last_slot = max(last_slot, __shfl_xor(last_slot, off));
-  }
-  mask_from = __builtin_amdgcn_readfirstlane(mask_from);
-  last_slot = __builtin_amdgcn_readfirstlane(last_slot);
-
-  // LDS addressing: every position used in the loop is one of a few lane-dependent bases
-  // plus a compile-time offset (which the LDS instructions carry as an immediate).
-  //   stage writes: lane owns 16-byte chunk (lane % CH) of row (lane / CH) + i * RPL
-  const int wrow = lane / C::CH, wch = lane % C::CH;
-  const int kw = lds_pos<D>(wrow, wch);
-  //   K / Q operand reads: row c, chunk 4t + g; t even and t odd differ in bit 2 of the chunk
-  const int kr_even = lds_pos<D>(c, g);
-  const int kr_odd = lds_pos<D>(c, 4 + g);
-  //   V transpose reads in 8-byte units: key 4g + c/4, d-tile mt at units 4 mt .. 4 mt + 3 of the row
-  const int vkey = 4 * g + (c >> 2);
-  int vu[4];
-#pragma unroll
-  for (int b = 0; b < 4; ++b) vu[b] = vkey * (2 * C::LROW) + 4 * b + (c & 3);
-
+  for (int t = 0; t < KSTEPS; ++t) ka[t] += stage0;
+  f32x4 acc[NT][MT];
+  float m_run[NT], l_run[NT], neg_ref[NT], limit[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
-    ts.m_run[n] = -INFINITY;
-    ts.l_run[n] = 0.f;
+    m_run[n] = -INFINITY;
+    l_run[n] = 0.f;
+    neg_ref[n] = 0.f;
+    limit[n] = -2.f;
 #pragma unroll
-    for (int mt = 0; mt < C::MT; ++mt) ts.acc[n][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MT; ++mt) acc[n][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  // ---- the stream.  Pairs of pages are handed out dynamically: a wave that gets its data sooner
-  // takes the next pair sooner, so the waves of the workgroup finish together whatever the memory
-  // system does to each of them.  A wave keeps PF pairs in flight in a ring of register sets (the
-  // ring is unrolled so that every set has fixed registers); the set it has just emptied into its
-  // LDS stage is refilled at once, before the pair is computed.
-  PairRegs<D> pr[PF];
-  int idx[PF];
-  // owner tags are needed (and fetched) only for pairs that reach past mask_from
-  auto own_ptr = [&](int P0) -> const uint8_t* {
-    return (owner_row && (P0 + 2) * ASPD_BLOCK > mask_from) ? owner_row + P0 * ASPD_BLOCK + 4 * g : nullptr;
+  // Next page nobody has taken (may be past the end).  Every lane adds to a word of its own and lane 0's counts: without
+  // a branch around the addition.
+  auto take = [&]() -> int {
+    return __hip_atomic_fetch_add((__attribute__((address_space(3))) int*)(uintptr_t)(lds0 + C::TAKE + 4 * lane), 1,
+                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   };
-  auto own_step = [&](int P0) -> int {
-    return min(ASPD_BLOCK, a.owner_stride - 4 - (P0 * ASPD_BLOCK + 4 * g));  // stays inside the owner row
-  };
-  for (int wbase = page0; wbase < page1; wbase += BLK_WIN) {  // windows of block ids; normally one
-    const int wend = min(page1, wbase + BLK_WIN);
-    const int wpages = wend - wbase;
-    const int npairs = (wpages + 1) >> 1;
-    if (wbase != page0) {
-      __syncthreads();  // every wave is done with the previous window's ids and counter
-#pragma unroll
-      for (int k = 0; k < LD::BPT; ++k) {
-        const int P = min(wbase + tid + k * THREADS, page1 - 1);
-        blk_lds[tid + k * THREADS] = min(max(bt[P], 0), a.kv.num_blocks - 1);
-      }
-      if (tid == 0) *pair_counter = 0;
-      __syncthreads();
-    }
-    auto take = [&]() -> int {  // next pair nobody has taken (may be past the end)
-      int v = 0;
-      if (lane == 0) v = atomicAdd(pair_counter, 1);
-      return __builtin_amdgcn_readfirstlane(v);
-    };
-#pragma unroll
-    for (int sl = 0; sl < PF; ++sl) {
-      if (sl == 0 && wbase == page0) {  // fetched at start-up
-        idx[0] = wave;
-        pr[0] = ld.first;
-        // ... with block ids that may have come from the plan: fetched again if the block table the
-        // call was given says otherwise
-        const int a0 = __builtin_amdgcn_readfirstlane(blk_lds[min(2 * wave, wpages - 1)]);
-        const int a1 = __builtin_amdgcn_readfirstlane(blk_lds[min(2 * wave + 1, wpages - 1)]);
-        if (a0 != ld.used0 || a1 != ld.used1) issue_pair<D, STREAM>(pr[0], a, it.h, a0, a1, lane, nullptr, 0);
-        continue;
-      }
-      idx[sl] = take();
-      if (idx[sl] < npairs) {
-        const int b0 = __builtin_amdgcn_readfirstlane(blk_lds[2 * idx[sl]]);
-        const int b1 = __builtin_amdgcn_readfirstlane(blk_lds[min(2 * idx[sl] + 1, wpages - 1)]);
-        issue_pair<D, STREAM>(pr[sl], a, it.h, b0, b1, lane, own_ptr(wbase + 2 * idx[sl]), own_step(wbase + 2 * idx[sl]));
-      }
-    }
-    int ahead = take();  // always one hand-out ahead, so that a refill never waits for the counter
-    bool more = true;
-    while (more) {
-#pragma unroll
-      for (int sl = 0; sl < PF; ++sl) {
-        // pairs are handed out in increasing order: once the oldest outstanding one is past the end,
-        // all are
-        if (idx[sl] >= npairs) {
-          more = false;
-          break;
-        }
-        const int pair = idx[sl];
-        const int P0 = wbase + 2 * pair;
-        // Slots past the last row's own slot have never been written (the tail of the last page) and may
-        // hold anything: their V rows enter the second product with weight zero, and zero times a NaN
-        // is a NaN, so they are cleared on the way into LDS.  (Their K rows only reach scores that the
-        // mask replaces.)
-        if ((P0 + 2) * ASPD_BLOCK > last_slot + 1) {
-#pragma unroll
-          for (int i = 0; i < C::LPP; ++i) {
-            const int key = P0 * ASPD_BLOCK + wrow + i * C::RPL;
-            if (key > last_slot) pr[sl].r[2][i] = u32x4{0u, 0u, 0u, 0u};
-            if (key + ASPD_BLOCK > last_slot) pr[sl].r[3][i] = u32x4{0u, 0u, 0u, 0u};
-          }
-        }
-        // ---- registers -> this wave's LDS stage
-#pragma unroll
-        for (int i = 0; i < C::LPP; ++i) {
-          // the position is a lane-dependent base plus a compile-time offset
-          constexpr int STEP = C::RPL * C::LROW;  // load i of a page is rows i * RPL .. of it
-          stage[0 * C::LPAGE_U4 + i * STEP + kw] = pr[sl].r[0][i];
-          stage[1 * C::LPAGE_U4 + i * STEP + kw] = pr[sl].r[1][i];
-          stage[2 * C::LPAGE_U4 + i * STEP + kw] = pr[sl].r[2][i];
-          stage[3 * C::LPAGE_U4 + i * STEP + kw] = pr[sl].r[3][i];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // ---- refill the set: the next pair streams in while this one is computed
-        idx[sl] = ahead;
-        const uint32_t own0 = pr[sl].own[0], own1 = pr[sl].own[1];  // of the pair about to be computed
-        if (ahead < npairs) {
-          const int b0 = __builtin_amdgcn_readfirstlane(blk_lds[2 * ahead]);
-          const int b1 = __builtin_amdgcn_readfirstlane(blk_lds[min(2 * ahead + 1, wpages - 1)]);
-          issue_pair<D, STREAM>(pr[sl], a, it.h, b0, b1, lane, own_ptr(wbase + 2 * ahead), own_step(wbase + 2 * ahead));
-        }
-        ahead = take();
+  auto block_of = [&](int page, int wpages) -> int { return lds_int(lds0 + C::BLK + 4 * min(page, wpages - 1)); };
 
-        const bool second_valid = (P0 + 1) < wend;
-
-        constexpr bool ROOMY = (NW <= 4);  // one wave per SIMD: 512 registers
-        constexpr int KB = (NT == 1 || ROOMY) ? C::KSTEPS : (NT == 2 ? 2 : 1);
-        constexpr int VB = (NT == 1 || ROOMY) ? C::MT : (NT == 2 ? 4 : 2);
-        pair_compute<D, NT, KB, VB>(stage, qtile, ts, kr_even, kr_odd, vu, g, L, mask_from, P0, second_valid, own0,
-                                    own1, a.scale_log2);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+  // One page, from stage S of the wave.
+  auto compute = [&](auto S, int page) {
+    constexpr uint32_t at = decltype(S)::value * C::STAGE_B;
+    const int k_first = (page0 + page) * ASPD_BLOCK;
+    // Slots past the last row's own have never been written (the tail of the last page) and may hold anything: their V
+    // rows enter the second product with weight zero, and zero times a NaN is a NaN, so they are cleared.  (Their K rows
+    // only reach scores that the mask replaces.)
+    if (k_first + ASPD_BLOCK > last_slot + 1) {
+#pragma unroll
+      for (int k = 0; k < C::LPP; ++k)
+        if (k_first + lane / CH + k * (64 / CH) > last_slot)
+          *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(stage0 + at + C::PAGE_B + k * 1024 + lane * 16) =
+              u32x4{0u, 0u, 0u, 0u};
+    }
+    bf16x8 kf[KSTEPS];
+#pragma unroll
+    for (int t = 0; t < KSTEPS; ++t) kf[t] = lds_operand(ka[t] + at);
+    s16x4 vf[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) vf[mt] = lds_operand_transposed(va[mt] + at);
+    f32x4 s[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) s[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (!Q_HELD) {
+#pragma unroll
+      for (int t = 0; t < KSTEPS; ++t) {
+        const uint32_t q_at = ka[t] + q_back;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) qf[n][t] = lds_operand(q_at + n * C::PAGE_B);
       }
     }
-  }
-
-  // ---- combine the waves of the workgroup
 #pragma unroll
-  for (int n = 0; n < NT; ++n) {
-    ts.l_run[n] += __shfl_xor(ts.l_run[n], 16);
-    ts.l_run[n] += __shfl_xor(ts.l_run[n], 32);
-    if (g == 0) {
-      wm[wave * ROWS + 16 * n + c] = ts.m_run[n];
-      wl[wave * ROWS + 16 * n + c] = ts.l_run[n];
-    }
-  }
-  __syncthreads();  // also: every wave is done with its stage, which `red` aliases from here on
-  float* red = (float*)smem;  // [NW][16][D + 4]: rows padded by four banks so that the 16 rows a wave
-                              // writes at once fall on different banks
-  constexpr int RS = D + 4;
+    for (int t = 0; t < KSTEPS; ++t)
 #pragma unroll
-  for (int n = 0; n < NT; ++n) {
-    {
-      float mg = -INFINITY;
+      for (int n = 0; n < NT; ++n) s[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t], qf[n][t], s[n], 0, 0, 0);
+    if (k_first + ASPD_BLOCK > mask_from) {  // (only pages that reach into the branch region or past a row's slot)
+      const uint32_t own = (uint32_t)lds_int(stage0 + at + 2 * C::PAGE_B + 4 * g);
+      const int k0 = k_first + 4 * g;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) mg = fmaxf(mg, wm[w * ROWS + 16 * n + c]);
-      const float f = __builtin_amdgcn_exp2f(ts.m_run[n] - exp2_safe_ref(mg));
+      for (int n = 0; n < NT; ++n) {
+        // (no short-circuits: they become branches on the execution mask)
+        const int n_end = slot[n] - k0, n_base = (tag[n] == 0 ? 0x7fffffff : L) - k0;
 #pragma unroll
-      for (int mt = 0; mt < C::MT; ++mt) {
-        f32x4 v = ts.acc[n][mt] * f;
-        *(f32x4*)&red[(wave * 16 + c) * RS + 16 * mt + 4 * g] = v;
+        for (int e = 0; e < 4; ++e) {
+          const int o = (int)((own >> (8 * e)) & 0xff);
+          const int vis = (int)(e <= n_end) & ((int)(e < n_base) | (int)(o == tag[n]));
+          s[n][e] = vis ? s[n][e] : -INFINITY;
+        }
       }
     }
-    __syncthreads();
-    {
-      // Consecutive lanes take consecutive 16-byte chunks of the tile: every store fills whole lines.
-      constexpr int CPR = D / 4;  // chunks per row
-      constexpr int PASSES = (16 * CPR + THREADS - 1) / THREADS;
-      auto row_stats = [&](int r, float* mg_out, float* lg_out) {
-        float mg = -INFINITY;
+    // Running softmax with a lazily raised reference per row (log2 domain, scaled scores; not necessarily the row's
+    // maximum; the same in the four lanes of a row).  The weights are formed first, and their sum, which the row needs
+    // anyway, tells whether the reference has to go up: while no lane's four weights sum to more than STREAM_SUM_MAX none
+    // of them exceeds it.
+    s16x4 p[NT];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) mg = fmaxf(mg, wm[w * ROWS + r]);
-        const float mref = exp2_safe_ref(mg);
-        float lg = 0.f;
+    for (int n = 0; n < NT; ++n) {
+      auto weights = [&]() -> float {
+        float sum = 0.f;
+        typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+        bf16x4 w4;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) lg += wl[w * ROWS + r] * __builtin_amdgcn_exp2f(wm[w * ROWS + r] - mref);
-        *mg_out = mg;
-        *lg_out = lg;
+        for (int e = 0; e < 4; ++e) {
+          const float w = __builtin_amdgcn_exp2f(fmaf(s[n][e], a.scale_log2, neg_ref[n]));
+          sum += w;
+          w4[e] = (__bf16)w;
+        }
+        p[n] = __builtin_bit_cast(s16x4, w4);
+        return sum;
       };
-      // The index arithmetic below (divisions by G among it) depends on nothing the main loop produces;
-      // tying it to a value defined here keeps it, and the registers it needs, out of that loop.
-      int tid_here = tid;
-      asm volatile("" : "+v"(tid_here)::"memory");
+      float sum = weights();
+      if (__any(sum > limit[n])) {
+        float mx = fmaxf(fmaxf(s[n][0], s[n][1]), fmaxf(s[n][2], s[n][3]));
+        mx = over_quarters(mx, [](float x, float y) { return fmaxf(x, y); }) * a.scale_log2;  // scale > 0
+        const float m_new = fmaxf(m_run[n], mx);
+        const float ref = exp2_safe_ref(m_new);
+        const float alpha = __builtin_amdgcn_exp2f(m_run[n] - ref);
+        m_run[n] = m_new;
+        neg_ref[n] = -ref;
+        l_run[n] *= alpha;
 #pragma unroll
-      for (int k = 0; k < PASSES; ++k) {
-        const int ci = tid_here + k * THREADS;
-        if ((16 * CPR) % THREADS != 0 && ci >= 16 * CPR) break;
-        const int row = ci / CPR;
-        const int d0 = 4 * (ci % CPR);
-        const int r = 16 * n + row;
-        f32x4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int w = 0; w < NW; ++w) o += *(const f32x4*)&red[(w * 16 + row) * RS + d0];
-        if (r >= R) continue;
-        if (complete) {
-          float mg, lg;
-          row_stats(r, &mg, &lg);
-          const int q = it.q0 + r / a.G;
-          const int head = it.h * a.G + r % a.G;
-          const float inv = 1.f / lg;
-          __bf16* dst = (__bf16*)a.out + ((long)q * a.kv.num_q_heads + head) * D + d0;
-          typedef __attribute__((ext_vector_type(4))) __bf16 out_vec;
-          out_vec ov;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(o[e] * inv);
-          *(out_vec*)dst = ov;
-          if (a.lse && d0 == 0) a.lse[(long)q * a.kv.num_q_heads + head] = (mg + log2f(lg)) * LN2;
-        } else {
-          store_device_scope_x4(partial_acc(pslot, r, D) + d0, o);
-        }
+        for (int mt = 0; mt < MT; ++mt) acc[n][mt] *= alpha;
+        limit[n] = __any(m_new == -INFINITY) ? -2.f : (limit[n] < -1.f ? -1.f : STREAM_SUM_MAX);
+        sum = weights();
       }
-      if (!complete && tid_here < 16 && 16 * n + tid_here < R) {
-        float mg, lg;
-        row_stats(16 * n + tid_here, &mg, &lg);
-        store_device_scope_x4(partial_stat(a, pslot, 16 * n + tid_here, D), f32x4{mg, lg, 0.f, 0.f});
+      l_run[n] += sum;
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+        acc[n][mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vf[mt], p[n], acc[n][mt], 0, 0, 0);
+  };
+
+  // ---- the stream, in windows of block ids (normally one).  Pages are handed out dynamically, two hand-outs ahead: a
+  // wave that gets its data sooner takes the next page sooner, so that the waves finish together whatever the memory
+  // system does to each of them.
+  for (int w0 = 0;;) {  // w0: first page of the window; cur, nxt and ahead count from it
+    const int wpages = min(np - w0, BLK_WIN);
+    if (w0 > 0) {
+      __syncthreads();  // every wave is done with the previous window's ids and counter
+      load4_to_lds(bt + w0, 4 * min(tid, wpages - 1), lds0 + C::BLK + wave * 256);
+      if (tid == 0) *(__attribute__((address_space(3))) int*)(uintptr_t)(lds0 + C::TAKE) = 3 * NW;
+      wait_loads<0>();
+      __syncthreads();
+      cur = wave;
+      nxt = wave + NW;
+      ahead = wave + 2 * NW;
+    }
+    {
+      const int b0 = __builtin_amdgcn_readfirstlane(block_of(cur, wpages));
+      const int b1 = __builtin_amdgcn_readfirstlane(block_of(nxt, wpages));
+      if (w0 > 0 || (cur < wpages && b0 != id0) || (nxt < wpages && b1 != id1)) {
+        wait_loads<0>();  // (pages of other blocks are on their way to the same place)
+        if (cur < wpages) issue(w0 + cur, b0, stage0);
+        if (nxt < wpages) issue(w0 + nxt, b1, stage0 + C::STAGE_B);
       }
     }
+    auto turn = [&](auto S) {
+      const int id_v = block_of(ahead, wpages), taken_v = take();
+      if (nxt < wpages) wait_loads<C::LOADS>();
+      else wait_loads<0>();
+      compute(S, w0 + cur);
+      const int id = __builtin_amdgcn_readfirstlane(id_v);
+      // the stage has been read; it is refilled at once
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (ahead < wpages) issue(w0 + ahead, id, stage0 + decltype(S)::value * C::STAGE_B);
+      cur = nxt;
+      nxt = ahead;
+      ahead = __builtin_amdgcn_readfirstlane(taken_v);
+    };
+    // pages are handed out in increasing order: once one is past the end, all later ones are
+    while (cur < wpages) {
+      turn(std::integral_constant<int, 0>{});
+      if (cur >= wpages) break;
+      turn(std::integral_constant<int, 1>{});
+    }
+    w0 += BLK_WIN;
+    if (w0 >= np) break;
+  }
+
+  // ---- combine the waves.  Every wave puts its accumulators, as they are, where its stages were and its statistics
+  // beside them; behind a barrier a thread takes a 16-byte chunk of a row and weighs the waves' parts itself.
+  const float* const wm = (const float*)(smem + C::M);
+  const float* const wl = (const float*)(smem + C::L);
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const float l = over_quarters(l_run[n], [](float x, float y) { return x + y; });
+    if (g == 0) {
+      ((float*)wm)[(16 * n + c) * NW + wave] = m_run[n];
+      ((float*)wl)[(16 * n + c) * NW + wave] = l;
+    }
+  }
+  constexpr int CPR = D / 4;                     // chunks per row
+  constexpr int TPP = THREADS / (16 * CPR) > 1 ? THREADS / (16 * CPR) : 1;  // tiles the threads cover at once
+  static_assert(THREADS == TPP * 16 * CPR && TPP <= 2, "one chunk per thread");
+  float* const red = (float*)(smem + wave * C::WAVE_B);
+  const float* const red0 = (const float*)smem;
+#pragma unroll
+  for (int n0 = 0; n0 < NT; n0 += 2) {           // two tiles a round
+    if (16 * n0 >= R) break;
+    if (n0 > 0) __syncthreads();
+#pragma unroll
+    for (int n = n0; n < n0 + 2 && n < NT; ++n)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        *(f32x4*)&red[(16 * (n - n0) + c) * C::RED_ROW + 16 * mt + 4 * g] = acc[n][mt];
     __syncthreads();
+    // (the index arithmetic below depends on nothing the main loop produces; tying it to a value defined here keeps it,
+    // and the registers it needs, out of that loop)
+    int tid_here = tid;
+    asm volatile("" : "+v"(tid_here)::"memory");
+#pragma unroll
+    for (int n = n0; n < n0 + 2 && n < NT; n += TPP) {
+      const int rl = 16 * (n - n0) + tid_here / CPR;  // row of the round
+      const int r = 16 * n0 + rl;
+      const int d0 = 4 * (tid_here % CPR);
+      if (r >= R || r >= 16 * NT) continue;
+      float m8[NW], mg = -INFINITY, lg = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) m8[w] = wm[r * NW + w];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) mg = fmaxf(mg, m8[w]);
+      const float mref = exp2_safe_ref(mg);
+      f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float f = __builtin_amdgcn_exp2f(m8[w] - mref);
+        lg += wl[r * NW + w] * f;
+        o += *(const f32x4*)&red0[w * (C::WAVE_B / 4) + rl * C::RED_ROW + d0] * f;
+      }
+      if (complete) {
+        const int qi = div_by_g(a, r);
+        const long row = (long)(it.q0 + qi) * a.kv.num_q_heads + it.h * a.G + r - qi * a.G;
+        const float inv = 1.f / lg;
+        typedef __attribute__((ext_vector_type(4))) __bf16 out_vec;
+        out_vec ov;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(o[e] * inv);
+        *(out_vec*)((__bf16*)a.out + row * D + d0) = ov;
+        if (a.lse && d0 == 0) a.lse[row] = (mg + log2f(lg)) * LN2;
+      } else {
+        store_device_scope_x4(partial_acc(pslot, r, D) + d0, o);
+        if (d0 == 0) store_device_scope_x4(partial_stat(a, pslot, r, D), f32x4{mg, lg, 0.f, 0.f});
+      }
+    }
   }
 }
 
-
-template <int D, int NT, int NW>
-size_t bf16_smem_bytes() {
-  return NW * Bf16Cfg<D>::STAGE_BYTES + 16 * NT * Bf16Cfg<D>::LROW * 16 + 2 * 16 * NT * 4 + 2 * NW * 16 * NT * 4 +
-         (BLK_WIN + 4) * 4;
-}
-
-template <int D, int NT, int NW, int PF, bool STREAM>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void attn_bf16_kernel(
-    AttnArgs a) {
+template <int D, int NT, bool STREAM>
+__global__ __launch_bounds__(STREAM_NW * 64) __attribute__((amdgpu_waves_per_eu(STREAM_NW / 4, STREAM_NW / 4))) void
+attn_bf16_kernel(AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ int merge_flag;
-  constexpr int THREADS = NW * 64;
+  constexpr int NW = STREAM_NW;
+  constexpr int MERGE = D == 128 ? (NT < 3 ? NT : 4) : (NT < 3 ? 1 : 2);  // the rows of a group in one round
   static_assert(2 * NW <= PLAN_IDS, "the plan carries two block ids per wave");
   // One memory round trip after the kernel starts the workgroup knows its first segment and the blocks
-  // of each wave's first pair of pages (scalar loads of the plan header), and the pages, the block ids of
+  // of each wave's first two pages (scalar loads of the plan header), and the pages, the block ids of
   // the whole segment, the Q rows and the row descriptors all leave together.
   Seg seg;
   int next;
-  i32x2 ids;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nseg = plan_begin(a, &seg, &next, 2 * wave, &ids);
+  const int32_t* ids = a.plan + (long)PLAN_HDR * blockIdx.x + PLAN_HDR_IDS + wave;
+  int id0 = load_word_uniform(ids), id1 = load_word_uniform(ids + NW);
+  const int nseg = plan_begin(a, &seg, &next);
   if (nseg == 0) return;
-  SegLoads<D, NT, NW> ld;
-  // (loads return in order: the small ones first, the LDS set-up waits for them and not for the pages)
-  segment_issue_ids<D, NT, NW>(a, seg, ld);
-  segment_issue_pair<D, NT, NW, STREAM>(a, seg, ld, ids[0], ids[1]);
-  asm volatile("" ::: "memory");  // the loads leave here, not where their results are first used
   for (int i = 0;;) {
     // the next segment's words are on their way while this one streams
     Seg after = seg;
     if (i + 1 < nseg) after = plan_segment(a, next + i);
     const bool complete = seg_complete(seg);
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
-    segment_bf16<D, NT, NW, PF, STREAM>(a, smem, seg, complete, pslot, ld);
-    // the merging workgroup has 16 * NT rows of D / 4 chunks to combine: one pass of its 64 * NW threads
-    if (!complete) announce_partial<D, true, THREADS, (NT == 1 ? 2 : 3)>(a, seg, &merge_flag);
+    segment_stream<D, NT, STREAM>(a, smem, seg, complete, pslot, id0, id1);
+    if (!complete) announce_partial<D, true, NW * 64, MERGE, (MERGE == 4 ? 6 : 16 / MERGE)>(a, seg, &merge_flag);
     if (++i >= nseg) break;
     seg = after;
     if (!seg_ok(a, seg)) break;
-    segment_issue_ids<D, NT, NW>(a, seg, ld);
-    segment_issue_pair<D, NT, NW, STREAM>(a, seg, ld, ld.b0, ld.b1);
+    const int32_t* bt = a.kv.block_tables + (long)seg.s * a.kv.max_blocks_per_seq;
+    id0 = load_word_uniform(bt + min(seg.page0 + wave, seg.page1 - 1));
+    id1 = load_word_uniform(bt + min(seg.page0 + wave + NW, seg.page1 - 1));
+    __syncthreads();  // LDS of the segment before is free
   }
 }
 

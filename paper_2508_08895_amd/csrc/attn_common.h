@@ -8,22 +8,18 @@ namespace {
 
 constexpr int NW = 4;                 // waves per workgroup, fp32 kernel
 constexpr int THREADS = NW * 64;
-// bf16 streaming kernel: one workgroup of 4 waves per compute unit (one wave per SIMD, so up to 512
-// registers each) and one pair of pages in flight per wave, 64 KB per compute unit.  Measured: deeper
-// prefetch (rings of 2 or 3 pairs per wave) and 8 waves both lower the read rate of the whole device
-// and make it uneven between the XCDs; the ring depth stays a template parameter.
-constexpr int STREAM_NW = 4;
-constexpr int STREAM_PF = 1;
-constexpr int BF16_ROWS = 16 * NT_MAX;
+// bf16 streaming kernel: one workgroup of eight waves per compute unit, each with one page of K and V in flight beside
+// the one it computes, 64 KB per compute unit.
+constexpr int STREAM_NW = 8;
 constexpr int ROWS_PPS = 2;           // pairs of pages it stages (and computes) between two barriers
 constexpr int COUNTER_BYTES = 4096;   // MAX_WG arrival counters at the head of the workspace
 static_assert(COUNTER_BYTES == MAX_WG * 4, "workspace head");
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
-constexpr float LAZY = 6.f;           // log2 slack of the running softmax reference (bf16 path)
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;  // 16 bytes in registers (a native
@@ -49,10 +45,16 @@ struct AttnArgs {
   int*           counters;      // [nwg] arrivals per split item, zero between calls
   float          scale_log2;    // sm_scale * log2(e)
   int            G;             // query heads per KV head
+  float          inv_G;         // 1 / G, see div_by_g
   int            rows_cap;      // rows per row group the partial slots are sized for
   const int32_t* row_base;      // whole-sequence launches: per packed row, the first slot of the row's stage
   const int32_t* row_lo;        // ... and the first slot of its own branch there
 };
+
+// r / G for a row of a row group.  Exact: (r + 1/2) / G is at least 1 / (2 G) away from a whole number, and r < 768.
+// (An integer division by a value the compiler does not know is forty instructions, and with few waves on a SIMD every
+// instruction of a start or an end counts: one wave alone issues one in eight to nine cycles.)
+__device__ __forceinline__ int div_by_g(const AttnArgs& a, int r) { return (int)(((float)r + 0.5f) * a.inv_G); }
 
 // ---------------------------------------------------------------------------------------------
 // The plan, as the kernels read it.
@@ -112,8 +114,8 @@ __device__ __forceinline__ bool seg_complete(const Seg& g) { return g.page0 == 0
 
 // Called by every thread of a workgroup that has written a partial of the item of `g` (defined after
 // the kernels: it needs the merge).
-template <int D, bool BF16, int THREADS, int ELEMS>
-__device__ void announce_partial(const AttnArgs& a, const Seg& g, int* flag /* LDS */);
+template <int D, bool BF16, int THREADS, int ELEMS, int BATCH>
+__device__ __forceinline__ void announce_partial(const AttnArgs& a, const Seg& g, int* flag /* LDS */);
 
 __device__ __forceinline__ float* partial_slot(const AttnArgs& a, int wg, int starts_item, int D) {
   return a.partial + ((long)(2 * wg + starts_item)) * a.rows_cap * (D + 4);

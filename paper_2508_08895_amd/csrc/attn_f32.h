@@ -173,8 +173,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
     const bool complete = seg_complete(seg);
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
     segment_f32<D>(a, smem, seg, complete, pslot);
-    // F32_ROWS rows of D / 4 chunks never exceed the workgroup's threads: one element per thread
-    if (!complete) announce_partial<D, false, THREADS, 1>(a, seg, &merge_flag);
+    if (!complete) announce_partial<D, false, THREADS, 1, 16>(a, seg, &merge_flag);
   }
 }
 

@@ -12,103 +12,105 @@ namespace {
 // another.  The partials are the "starts item" slot of the first workgroup and the "continues
 // item" slots of the following ones.
 // ---------------------------------------------------------------------------------------------
+// A thread combines ELEMS 16-byte chunks of one row at a time, BATCH parts of each: all their loads and those of the row's
+// statistics are on their way at once, and nothing goes through LDS.  Bound by the instructions issued, so a row's weights
+// are worked out once for all chunks of a thread (chunks of different rows before: 10 parts of 16 rows took 4.7 us of a
+// launch of 14.8; stage openings over 12 sequences, three parts of 180 rows 63.1 -> 59.9 us a layer).
 template <int D, bool BF16, int THREADS, int ELEMS, int BATCH>
-__device__ void merge_parts(const AttnArgs& a, const Seg& it, int owner, int w_last) {
-  constexpr int CPR = D / 4;  // float4 chunks per row
-  // ELEMS: (row, chunk) elements a thread combines concurrently; BATCH: partials fetched at once, per
-  // element.
-  const int R = it.nq * a.G;
-  const long stride = (long)a.rows_cap * (D + 4);
+__device__ __forceinline__ void merge_parts(const AttnArgs& a, const Seg& it, int owner, int w_last) {
+  constexpr int LPR = D / 4 / ELEMS;     // threads per row
+  constexpr int ROWS = THREADS / LPR;    // rows of a round
+  // (defined here, so that nothing that is worked out from it lives in registers across the main loop)
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int c0 = tid % LPR;              // the thread's chunks: c0, c0 + LPR ..
+  const long stride = (long)a.rows_cap * (D + 4) * sizeof(float);
   const int nparts = w_last - owner + 1;
-  const int total = R * CPR;
-  // The loads miss the caches and are latency-bound: a thread keeps the loads of up to ELEMS
-  // elements x BATCH partials in flight at once.
-  for (int i0 = threadIdx.x; i0 < total; i0 += ELEMS * THREADS) {
-    int r[ELEMS], cc[ELEMS];
-    float m[ELEMS], l[ELEMS];
+  const int R = it.nq * a.G;
+  const char* const first = (const char*)(a.partial) + 2 * owner * stride;
+  for (int r0 = 0; r0 < R; r0 += ROWS) {
+    const int r = r0 + tid / LPR;
+    const uint32_t row_at = (uint32_t)min(r, R - 1);  // (rows past the last are the last again and not stored)
+    const uint32_t at = row_at * (D * 4) + c0 * 16;
+    float m = -INFINITY, l = 0.f;
     f32x4 o[ELEMS];
 #pragma unroll
-    for (int x = 0; x < ELEMS; ++x) {
-      const int i = min(i0 + x * THREADS, total - 1);  // a clamped duplicate is computed and not stored
-      r[x] = i / CPR;
-      cc[x] = i - r[x] * CPR;
-      m[x] = -INFINITY;
-      l[x] = 0.f;
-      o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int x = 0; x < ELEMS; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int p0 = 0; p0 < nparts; p0 += BATCH) {
-      float pm[ELEMS][BATCH], pl[ELEMS][BATCH];
+      f32x2 ml[BATCH];
       f32x4 po[ELEMS][BATCH];
 #pragma unroll
-      for (int x = 0; x < ELEMS; ++x) {
+      for (int k = 0; k < BATCH; ++k) {
+        const int kk = min(p0 + k, nparts - 1);  // (parts past the last are the last again and weigh nothing)
+        // the first part starts the item, the others continue it
+        const char* slot = first + (kk == 0 ? 1 : 2 * kk) * stride;
+        ml[k] = *(const f32x2*)(slot + (long)a.rows_cap * D * sizeof(float) + row_at * 16);  // reference, sum
 #pragma unroll
-        for (int k = 0; k < BATCH; ++k) {
-          const int ww = owner + min(p0 + k, nparts - 1);
-          const float* slot = a.partial + (long)(2 * ww + (ww == owner ? 1 : 0)) * stride;
-          const f32x4 ml = *(const f32x4*)(slot + (long)a.rows_cap * D + 4 * r[x]);  // reference, sum, padding
-          pm[x][k] = ml[0];
-          pl[x][k] = ml[1];
-          po[x][k] = *(const f32x4*)(slot + (long)r[x] * D + 4 * cc[x]);
-        }
+        for (int x = 0; x < ELEMS; ++x) po[x][k] = *(const f32x4*)(slot + at + x * LPR * 16);
+      }
+      float mb = m;
+#pragma unroll
+      for (int k = 0; k < BATCH; ++k) mb = fmaxf(mb, ml[k][0]);
+      const float mref = exp2_safe_ref(mb);
+      if (p0 > 0) {
+        const float f0 = __builtin_amdgcn_exp2f(m - mref);
+        l *= f0;
+#pragma unroll
+        for (int x = 0; x < ELEMS; ++x) o[x] *= f0;
       }
 #pragma unroll
-      for (int x = 0; x < ELEMS; ++x) {
-        float mb = m[x];
+      for (int k = 0; k < BATCH; ++k) {
+        if (p0 + k < nparts) {
+          const float f = __builtin_amdgcn_exp2f(ml[k][0] - mref);
+          l += ml[k][1] * f;
 #pragma unroll
-        for (int k = 0; k < BATCH; ++k)
-          if (p0 + k < nparts) mb = fmaxf(mb, pm[x][k]);
-        const float mref = exp2_safe_ref(mb);
-        const float f0 = __builtin_amdgcn_exp2f(m[x] - mref);
-        l[x] *= f0;
-        o[x] *= f0;
-#pragma unroll
-        for (int k = 0; k < BATCH; ++k) {
-          if (p0 + k < nparts) {
-            const float f = __builtin_amdgcn_exp2f(pm[x][k] - mref);
-            l[x] += pl[x][k] * f;
-            o[x] += po[x][k] * f;
-          }
+          for (int x = 0; x < ELEMS; ++x) o[x] += po[x][k] * f;
         }
-        m[x] = mb;
       }
+      m = mb;
     }
+    if (r < R) {
+      const int qi = div_by_g(a, r);
+      const long row = (long)(it.q0 + qi) * a.kv.num_q_heads + it.h * a.G + r - qi * a.G;
+      const float inv = 1.f / l;
 #pragma unroll
-    for (int x = 0; x < ELEMS; ++x) {
-      if (i0 + x * THREADS >= total) continue;
-      const int q = it.q0 + r[x] / a.G;
-      const int head = it.h * a.G + r[x] % a.G;
-      const long oi = ((long)q * a.kv.num_q_heads + head) * D + 4 * cc[x];
-      const float inv = 1.f / l[x];
-      if (BF16) {
-        typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-        bf16x4 ov;
+      for (int x = 0; x < ELEMS; ++x) {
+        const long to = row * D + 4 * (c0 + x * LPR);
+        if (BF16) {
+          typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+          bf16x4 ov;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(o[x][e] * inv);
-        *(bf16x4*)((__bf16*)a.out + oi) = ov;
-      } else {
-        *(f32x4*)((float*)a.out + oi) = o[x] * inv;
+          for (int e = 0; e < 4; ++e) ov[e] = (__bf16)(o[x][e] * inv);
+          *(bf16x4*)((__bf16*)a.out + to) = ov;
+        } else {
+          *(f32x4*)((float*)a.out + to) = o[x] * inv;
+        }
       }
-      if (a.lse && cc[x] == 0) a.lse[(long)q * a.kv.num_q_heads + head] = (m[x] + log2f(l[x])) * LN2;
+      if (a.lse && c0 == 0) a.lse[row] = (m + log2f(l)) * LN2;
     }
   }
+  // Every load has been used or not wanted: said here, so that the compiler does not wait for one of the latter, and with
+  // it for all loads it does not know of, where its register is written next.
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 }
 
-// A second batch costs a second round trip to memory, so the batch is as large as the registers allow
-// (sixteen in the one-tile streaming kernel, one wave per SIMD) - but no larger than the parts there are:
-// with one wave per SIMD the merge is bound by the instructions it issues, and every slot of a batch costs
-// its loads and its arithmetic whether a part stands behind it or not.
-template <int D, bool BF16, int THREADS, int ELEMS>
-__device__ void merge_item(const AttnArgs& a, const Seg& it, int owner, int w_last) {
-  constexpr bool WIDE = BF16 && ELEMS == 2 && THREADS == 256;
+// A second batch costs a second round trip to memory, so the batch is as large as the registers allow, but no larger than
+// the parts there are: with two waves per SIMD the merge is bound by the instructions it issues, and every slot of a batch
+// costs its loads and its arithmetic whether a part stands behind it or not.
+template <int D, bool BF16, int THREADS, int ELEMS, int BATCH>
+__device__ __forceinline__ void merge_item(const AttnArgs& a, const Seg& it, int owner, int w_last) {
   const int nparts = w_last - owner + 1;
-  if (nparts <= 4) merge_parts<D, BF16, THREADS, ELEMS, 4>(a, it, owner, w_last);
-  else if (!WIDE || nparts <= 8) merge_parts<D, BF16, THREADS, ELEMS, 8>(a, it, owner, w_last);
-  else merge_parts<D, BF16, THREADS, ELEMS, WIDE ? 16 : 8>(a, it, owner, w_last);
+  if (nparts <= 2) merge_parts<D, BF16, THREADS, ELEMS, 2>(a, it, owner, w_last);
+  else if (BATCH > 3 && nparts <= 3) merge_parts<D, BF16, THREADS, ELEMS, 3>(a, it, owner, w_last);
+  else if (BATCH > 4 && nparts <= 4) merge_parts<D, BF16, THREADS, ELEMS, 4>(a, it, owner, w_last);
+  else if (BATCH > 6 && nparts <= 6) merge_parts<D, BF16, THREADS, ELEMS, 6>(a, it, owner, w_last);
+  else if (BATCH > 8 && nparts <= 8) merge_parts<D, BF16, THREADS, ELEMS, 8>(a, it, owner, w_last);
+  else if (BATCH > 12 && nparts <= 12) merge_parts<D, BF16, THREADS, ELEMS, 12>(a, it, owner, w_last);
+  else merge_parts<D, BF16, THREADS, ELEMS, BATCH>(a, it, owner, w_last);
 }
 
-// Called by every thread of the workgroup after it has written a partial of the item of `it`.
-template <int D, bool BF16, int THREADS, int ELEMS>
-__device__ void announce_partial(const AttnArgs& a, const Seg& it, int* flag /* LDS */) {
+template <int D, bool BF16, int THREADS, int ELEMS, int BATCH>
+__device__ __forceinline__ void announce_partial(const AttnArgs& a, const Seg& it, int* flag /* LDS */) {
   const int owner = it.owner, w_last = it.w_last;
   // the write-through stores of the partial have completed before the arrival is counted
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -128,7 +130,7 @@ __device__ void announce_partial(const AttnArgs& a, const Seg& it, int* flag /* 
   // which all waves of the workgroup share.
   if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   __syncthreads();
-  merge_item<D, BF16, THREADS, ELEMS>(a, it, owner, w_last);
+  merge_item<D, BF16, THREADS, ELEMS, BATCH>(a, it, owner, w_last);
 }
 
 }  // namespace

@@ -290,6 +290,37 @@ def test_capped_grid_and_long_segments(A):
     _compare_attention(A, gb, tt, wl, step, meta, A.aspd_attn_serial_decode, label="uncapped serial")
 
 
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("branches", [1, 3, 6, 11], ids=["part_of_a_tile", "one_tile", "two_tiles", "three_tiles"])
+def test_segments_of_few_pages_and_items_of_many_parts(A, hd, branches):
+    """The decode kernel at the edges of its stream and of the merge: segments with fewer pages than a workgroup has
+    waves, with exactly as many, with one or two rounds and a page more (one workgroup takes each item whole), and items
+    cut into as many parts as a batch of the merge holds, one more, and more than one batch."""
+    def decode(gb, tt, wl, cap, label):
+        ones = np.ones(wl.NB, dtype=np.int32)
+        meta = tt.append_parallel(ones)
+        step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_PARALLEL, gb._dev_i32(ones), NQ=int(ones.sum()),
+                                        max_new_per_seq=branches, max_workgroups=cap)
+        _compare_attention(A, gb, tt, wl, step, meta, A.aspd_attn_parallel_decode, label=label)
+
+    heads = dict(dtype="bf16", head_dim=hd, num_q_heads=8, num_kv_heads=2)
+    for pages in (1, 2, 7, 8, 9, 15, 16, 17, 24, 25, 33):
+        # (branches of one token each, so that the pages are the prefix's but for the last one or two)
+        tokens = max(0, 16 * pages - 2 * branches)
+        wl = W.random_small(seed=500 + pages, batch=2, prefix_range=(tokens, tokens), branches_range=(branches, branches),
+                            branch_len_range=(1, 1), extra_tokens_per_branch=4, **heads)
+        gb, tt = _grow_both(A, wl, wl.branch_len, False)
+        decode(gb, tt, wl, 1, f"{pages} pages, one workgroup")
+        decode(gb, tt, wl, 0, f"{pages} pages")
+    heads["num_kv_heads"] = 1
+    heads["num_q_heads"] = 4
+    wl = W.random_small(seed=560, batch=1, prefix_range=(5500, 5500), branches_range=(branches, branches),
+                        branch_len_range=(1, 1), extra_tokens_per_branch=15, **heads)
+    gb, tt = _grow_both(A, wl, wl.branch_len, False)
+    for parts in (2, 3, 4, 5, 6, 7, 8, 9, 12, 13, 16, 17, 20):
+        decode(gb, tt, wl, parts, f"{parts} parts")
+
+
 @pytest.mark.parametrize("branches", [3, 6], ids=["one_tile", "two_tiles"])
 def test_decode_loop_on_one_workspace(A, branches):
     """Forty consecutive decode launches on ONE workspace, with the hints a decoding loop gives (so the
