@@ -13,7 +13,9 @@
 //   [32 nwg, 32 nwg + 8 nsegs)     the segments that are not the first of their workgroup, in the
 //                                  order the workgroups walk them
 // Header: words 0-7 the workgroup's first segment, 8 the number of its segments (0: nothing to do),
-//   9 the index of its second segment in the list above, 16-31 the block ids of the first sixteen
+//   9 the index of its second segment in the list above, 10 in a plan whose items are taken from a queue the number of
+//   items that are not the first of a workgroup (0 in other plans; the kernel's order of them is that of their index in
+//   their workgroup, then of the workgroups), 16-31 the block ids of the first sixteen
 //   pages of its first segment (read again from the block table before they count, see the kernels).
 // Segment: a run of pages [page0, page1) of one item, for all rows of the item's row group:
 //   0  sequence | KV head << 16        1  first packed query row of the row group
@@ -29,8 +31,12 @@ constexpr int PLAN_HDR = 32;         // words per workgroup header
 constexpr int PLAN_SEG = 8;          // words per segment
 constexpr int PLAN_HDR_NSEG = 8;
 constexpr int PLAN_HDR_NEXT = 9;
+constexpr int PLAN_HDR_QUEUE = 10;
 constexpr int PLAN_HDR_IDS = 16;
 constexpr int PLAN_IDS = 16;
+
+// Words of the arrival counters that the queue uses (the row-splitting kernel, whose grid is smaller, has the others).
+constexpr int QUEUE_NEXT = 1022, QUEUE_DONE = 1023;
 
 constexpr int MAX_WG = 1024;         // upper bound of any attention grid
 constexpr int NT_MAX = 3;            // 16-row MFMA tiles per row group of the streaming bf16 kernel
@@ -45,6 +51,9 @@ constexpr int PAD_ROWS = 32;         // and for the row-splitting kernel: a segm
                                      // merge), 25-40 pages' worth; steps with 16 / 32 / 48, us: 64-sequence chunk
                                      // 1830 / 1750 / 1690, eight prompts 437 / 435 / 442, stage opening over 12
                                      // sequences 317 each time
+
+constexpr int ROWS_PAGE_COST = 4;    // row-splitting kernel: a page takes 0.14 us + 0.038 us per wave that has rows
+static_assert(MAX_WG_ROWS <= 1022 && MAX_WG == 1024, "queue words");
 
 enum AttnKernel { KERNEL_F32 = 0, KERNEL_BF16_STREAM = 1, KERNEL_BF16_ROWS = 2 };
 

@@ -23,6 +23,9 @@ struct PlanArgs {
   int32_t*       plan;
   int            B, nwg, qpg, pad, num_kv_heads, max_blocks_per_seq, num_blocks;
   int            has_owner;
+  int            w_page, w_wave;  // what a page costs: w_page + w_wave for every 32 rows of its row group
+  int            rows_per_query;  // query heads per KV head
+  int            queue;           // the kernel can take whole items from a queue
 };
 
 struct Item {
@@ -89,6 +92,13 @@ __device__ __forceinline__ Groups groups_at(const PlanArgs& a, int T, int rows, 
   return g;
 }
 
+// Cost of a page of a row group of nq queries.
+__device__ __forceinline__ int page_cost(const PlanArgs& a, int nq) {
+  return a.w_page + a.w_wave * ((nq * a.rows_per_query + 31) / 32);
+}
+// Queries of the last of a sequence's row groups.
+__device__ __forceinline__ int last_group(const PlanArgs& a, int rows, int n) { return rows - (n - 1) * a.qpg; }
+
 __device__ __forceinline__ Groups groups_of(const PlanArgs& a, const Sched& sc, int s) {
   return groups_at(a, sc.T[s], sc.q0[s + 1] - sc.q0[s], sc.ng[s]);
 }
@@ -104,6 +114,19 @@ __device__ __forceinline__ Groups groups_of(const PlanArgs& a, const Sched& sc, 
 // all items fit the grid.  A workgroup pays a segment's fixed cost once, and an item that fits one piece
 // needs no merge.
 //
+// What a page costs depends, for the row-splitting kernel, on how many of its waves have rows (page_cost), so the
+// lengths compared are costs there (a stage opening over 12 sequences, where row groups have two to eight waves: the
+// workgroups end between 27 and 65 us with pieces of equal pages, between 26 and 59 with pieces of equal cost).
+//
+// QUEUE (row-splitting kernel, more items than workgroups, none of them long against a share).  Every workgroup takes
+// whole items, longest first: the first is given, after that whichever is next when the workgroup gets free.  Nothing is
+// split or merged, and no share has to be guessed from costs.  The plan lists the items dealt round in that order,
+// which is what a workgroup's header and the list say; the kernel takes them out of the list by its own counter.
+// Shares of equal pages (RAGGED) ended between 457 and 804 us in a 64-sequence chunk, this between 637 and 685 (median
+// 647); in eight prompts between 87 and 149, this between 121 and 135.  Launches, us: chunk 821 -> 676, prompts 154 ->
+// 136.  The line: the costliest item is no more than 1.25 of a share (the longest go first, so it is alone on its workgroup
+// at worst); beyond it a launch would wait for that item, and RAGGED splits it.
+//
 // RAGGED.  Workgroup w nominally takes [w * total / n, (w + 1) * total / n); a boundary inside an
 // item's padding, or within `tol` units after it or before the item's end, is moved onto the item
 // boundary: a sliver of a neighbouring item would cost a whole extra segment for a few pages.  The
@@ -111,7 +134,10 @@ __device__ __forceinline__ Groups groups_of(const PlanArgs& a, const Sched& sc, 
 struct Shares {
   int total, n, tol, pad;
   bool even;
-  int piece;        // EVEN: p, the length no piece exceeds
+  bool queue;
+  int longest;      // QUEUE: cost of the costliest item
+  int items;
+  int piece;        // EVEN: p, the cost no piece exceeds
   double share;     // RAGGED: total / n, units per workgroup
   __device__ __forceinline__ int nominal_begin(int w) const { return min(total, (int)((double)w * share)); }
 };
@@ -205,14 +231,32 @@ __device__ int share_begin(const PlanArgs& a, const Sched& sc, const Shares& sh,
   return nominal;
 }
 
+// EVEN: pieces of an item of np pages at page cost w, none of more than p (a piece is not shorter than
+// MIN_PAGES_PER_WG pages, as far as the item allows).
+__device__ __forceinline__ int even_pieces(int np, int w, int p, float rp /* 1 / p */) {
+  // ceil(np w / p) by a float reciprocal, made exact by one correction (np w + p < 2^24, the estimate is off by one at
+  // most)
+  const int x = np * w + p - 1;
+  int q = (int)((float)x * rp);
+  if ((q + 1) * p <= x) ++q;
+  else if (q * p > x) --q;
+  return min(q, (np + MIN_PAGES_PER_WG - 1) / MIN_PAGES_PER_WG);
+}
+// Workgroups for one KV head of a sequence: n - 1 full row groups and a last one.
+__device__ __forceinline__ int even_per_head(const PlanArgs& a, int np, int n, int nq_last, int p, float rp) {
+  return (n - 1) * even_pieces(np, page_cost(a, a.qpg), p, rp) + even_pieces(np, page_cost(a, nq_last), p, rp);
+}
+
 // Fills the LDS tables and returns the shares.  All threads of the workgroup call it.
-__device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratch /* 3 * PLAN_THREADS / 64 + 2 ints */) {
+__device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratch /* 5 * PLAN_THREADS / 64 + 2 ints */) {
   constexpr int PER = (ASPD_MAX_BATCH + PLAN_THREADS - 1) / PLAN_THREADS;  // sequences per thread
   constexpr int NWV = PLAN_THREADS / 64;
   const int tid = threadIdx.x;
   int mine_p[PER], mine_i[PER];
   int sum_p = 0, sum_i = 0;
-  int longest = 0;
+  int longest = 0;       // cost of the costliest item in the even regime (all pages of its sequence)
+  int longest_q = 0;     // ... and whole (its row group's pages)
+  long cost = 0;         // of all items, whole
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int s = tid * PER + j;
@@ -232,17 +276,23 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
       if (np > 0 && g.n > 0) {
         mine_i[j] = g.n * a.num_kv_heads;
         mine_p[j] = g.before(g.n, 0) * a.num_kv_heads;
-        longest = max(longest, np);
+        const int w_full = page_cost(a, a.qpg), w_last = page_cost(a, last_group(a, q1 - q0, g.n));
+        longest = max(longest, np * (g.n > 1 ? w_full : w_last));
+        longest_q = max(longest_q, max(g.n > 1 ? g.pages(g.n - 2) * w_full : 0, np * w_last));
+        cost += (long)(g.before(g.n - 1, 0) * (long)w_full + (long)np * w_last) * a.num_kv_heads;
       }
-      // (for the search below; both tables are filled in for good later)
-      sc.cu_units[s] = mine_i[j];
+      // (for the search below; the table is filled in for good later)
       sc.wgb[s] = mine_i[j] > 0 ? np : 0;
     }
     sum_p += mine_p[j];
     sum_i += mine_i[j];
   }
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
+  for (int off = 32; off > 0; off >>= 1) {
+    longest = max(longest, __shfl_xor(longest, off));
+    longest_q = max(longest_q, __shfl_xor(longest_q, off));
+    cost += __shfl_xor(cost, off);
+  }
   // scans: inside the wave by shuffles, across the waves through LDS (one barrier)
   int incl_p = sum_p, incl_i = sum_i;
 #pragma unroll
@@ -258,11 +308,14 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
     scratch[tid >> 6] = incl_p;
     scratch[NWV + (tid >> 6)] = incl_i;
     scratch[2 * NWV + (tid >> 6)] = longest;
+    scratch[3 * NWV + (tid >> 6)] = longest_q;
+    ((unsigned*)scratch)[4 * NWV + (tid >> 6)] = (unsigned)(cost >> 4);  // (16 cost units: less than 2^32 of them)
   }
   __syncthreads();
   int run_p = incl_p - sum_p, run_i = incl_i - sum_i;  // exclusive within the wave
   int pages = 0, items = 0;
-  longest = 0;
+  longest = longest_q = 0;
+  cost = 0;
 #pragma unroll
   for (int w = 0; w < NWV; ++w) {
     const int tp = scratch[w], ti = scratch[NWV + w];
@@ -273,30 +326,32 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
     pages += tp;
     items += ti;
     longest = max(longest, scratch[2 * NWV + w]);
+    longest_q = max(longest_q, scratch[3 * NWV + w]);
+    cost += (long)((unsigned*)scratch)[4 * NWV + w] << 4;
   }
   Shares sh;
   sh.pad = a.pad;
   sh.piece = 0;
   sh.even = false;
-  // ---- EVEN regime?  Thread t tries piece length p_t; the smallest that fits the grid wins.
-  int* best = scratch + 3 * NWV;  // [2]: smallest piece length that fits; workgroups it takes
+  sh.queue = false;
+  sh.items = items;
+  sh.longest = longest_q;
+  const int w_full = page_cost(a, a.qpg);
+  // ---- EVEN regime?  Thread t tries piece cost p_t; the smallest that fits the grid wins.
+  int* best = scratch + 5 * NWV;  // [2]: smallest piece cost that fits; workgroups it takes
   if (tid == 0) best[0] = 0x7fffffff;
   __syncthreads();
   if (items > 0 && items <= a.nwg) {
-    const int span = max(longest - MIN_PAGES_PER_WG, 0);
+    const int least = MIN_PAGES_PER_WG * page_cost(a, 1);
+    const int span = max(longest - least, 0);
     const int step = span / PLAN_THREADS + 1;
-    const int p = min(max(longest, 1), MIN_PAGES_PER_WG + tid * step);
-    // pieces of all items at this length: ceil(np / p) by a float reciprocal, made exact by one correction
-    // (np + p < 2^24, the estimate is off by one at most)
+    const int p = min(max(longest, 1), least + tid * step);
     const float rp = __builtin_amdgcn_rcpf((float)p);
     long need = 0;
-    for (int s = 0; s < a.B; ++s) {
-      const int x = sc.wgb[s] + p - 1;
-      int q = (int)((float)x * rp);
-      if ((q + 1) * p <= x) ++q;
-      else if (q * p > x) --q;
-      need += (long)sc.cu_units[s] * q;
-    }
+    for (int s = 0; s < a.B; ++s)
+      if (sc.wgb[s] > 0)
+        need += (long)a.num_kv_heads *
+                even_per_head(a, sc.wgb[s], sc.ng[s], last_group(a, sc.q0[s + 1] - sc.q0[s], sc.ng[s]), p, rp);
     int mine = need <= a.nwg ? p : 0x7fffffff;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mine = min(mine, __shfl_xor(mine, off));
@@ -304,10 +359,10 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
   }
   __syncthreads();
   if (best[0] != 0x7fffffff) {
-    // pieces of this length against what the ragged regime's longest workgroups would carry (a share and two
+    // pieces of this cost against what the ragged regime's longest workgroups would carry (a share and two
     // segment starts)
     sh.piece = best[0];
-    sh.even = (long)sh.piece + a.pad <= (long)pages / a.nwg + 2L * a.pad;
+    sh.even = (long)sh.piece + a.pad * w_full <= (a.w_wave ? cost : (long)pages) / a.nwg + 2L * a.pad * w_full;
   }
   __syncthreads();  // (best is read by all before anyone reuses scratch)
   if (sh.even) {
@@ -318,7 +373,9 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
     for (int j = 0; j < PER; ++j) {
       const int s = tid * PER + j;
       mine_w[j] = 0;
-      if (s < a.B && mine_i[j] > 0) mine_w[j] = mine_i[j] * ((sc.wgb[s] + sh.piece - 1) / sh.piece);
+      if (s < a.B && mine_i[j] > 0)
+        mine_w[j] = a.num_kv_heads * even_per_head(a, sc.wgb[s], sc.ng[s], last_group(a, sc.q0[s + 1] - sc.q0[s], sc.ng[s]),
+                                                   sh.piece, __builtin_amdgcn_rcpf((float)sh.piece));
       sum_w += mine_w[j];
     }
     int incl_w = sum_w;
@@ -346,6 +403,21 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
     sh.n = total_w;
     sh.tol = 0;
     sh.share = 1.0;
+    __syncthreads();
+    return sh;
+  }
+  // ---- QUEUE regime?
+  if (a.queue && items > a.nwg && 4L * sh.longest <= 5L * cost / a.nwg) {
+    sh.queue = true;
+    sh.n = a.nwg;
+    // cu_units[s]: row groups of the sequences before s
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int s = tid * PER + j;
+      if (s < a.B) sc.cu_units[s] = run_i / a.num_kv_heads;
+      run_i += mine_i[j];
+    }
+    if (tid == 0) sc.cu_units[a.B] = items / a.num_kv_heads;
     __syncthreads();
     return sh;
   }
@@ -397,12 +469,18 @@ __device__ bool even_share(const PlanArgs& a, const Sched& sc, const Shares& sh,
   Item it;
   it.s = lo;
   it.np = pages_of(a, sc, lo);
-  const int k = (it.np + sh.piece - 1) / sh.piece;  // workgroups per item of this sequence
+  const int ngroups = sc.ng[lo], rows = sc.q0[lo + 1] - sc.q0[lo];
+  const float rp = __builtin_amdgcn_rcpf((float)sh.piece);
+  // workgroups per item: of a full row group, of the last
+  const int k_full = even_pieces(it.np, page_cost(a, a.qpg), sh.piece, rp);
+  const int k_last = even_pieces(it.np, page_cost(a, last_group(a, rows, ngroups)), sh.piece, rp);
+  const int per_head = (ngroups - 1) * k_full + k_last;
   const int local = w - sc.cu_units[lo];
-  const int idx = local / k, j = local - idx * k;
-  const int ngroups = sc.ng[lo];
-  it.h = idx / ngroups;       // row groups of one KV head are neighbours: they read the same pages
-  it.rg = idx - it.h * ngroups;
+  it.h = local / per_head;    // row groups of one KV head are neighbours: they read the same pages
+  const int in_head = local - it.h * per_head;
+  it.rg = min(in_head / k_full, ngroups - 1);
+  const int j = in_head - it.rg * k_full;
+  const int k = it.rg == ngroups - 1 ? k_last : k_full;
   it.first_unit = 0;
   it.lp = a.has_owner ? min(it.np, sc.L[lo] / ASPD_BLOCK) : it.np;
   const int qs = sc.q0[lo];
@@ -467,19 +545,102 @@ __device__ __forceinline__ bool walk_next(const PlanArgs& a, const Sched& sc, co
 // on from where pass 1 stood when the room ran out.
 __host__ __device__ constexpr int plan_cached_segments(int nwg) { return nwg <= 256 ? 4 : (nwg <= 512 ? 2 : 1); }
 
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+// Block ids of the first sixteen pages of a run, for a workgroup's header.
+__device__ __forceinline__ void load_ids(const PlanArgs& a, int s, int p0, int p1, int (&ids)[PLAN_IDS]) {
+  const int32_t* bt = a.block_tables + (long)s * a.max_blocks_per_seq;
+#pragma unroll
+  for (int k = 0; k < PLAN_IDS; ++k) ids[k] = bt[min(p0 + k, p1 - 1)];  // all on their way at once
+#pragma unroll
+  for (int k = 0; k < PLAN_IDS; ++k) ids[k] = min(max(ids[k], 0), a.num_blocks - 1);
+}
+__device__ __forceinline__ void store_ids(int32_t* hdr, const int (&ids)[PLAN_IDS]) {
+#pragma unroll
+  for (int k = 0; k < PLAN_IDS; k += 4)
+    *(i32x4*)(hdr + PLAN_HDR_IDS + k) = i32x4{ids[k], ids[k + 1], ids[k + 2], ids[k + 3]};
+}
+
+// QUEUE: sorts the row groups by cost (longest first, into QUEUE_BINS classes of it) and writes headers and list.  Item r
+// in that order is the first of workgroup r, and the (r / nwg)-th of workgroup r % nwg.
+constexpr int QUEUE_BINS = 1024;
+__device__ void write_queue(const PlanArgs& a, const Sched& sc, const Shares& sh, int* bins /* QUEUE_BINS */) {
+  const int tid = threadIdx.x;
+  const int groups = sc.cu_units[a.B];
+  static_assert(QUEUE_BINS == PLAN_THREADS, "a thread per bin");
+  bins[tid] = 0;
+  __syncthreads();
+  const float scale = (float)(QUEUE_BINS - 1) / (float)sh.longest;
+  auto group_at = [&](int e, int* s_out, int* rg_out, Groups* g) -> int {  // row group e; its bin
+    int lo = 0, hi = a.B - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (sc.cu_units[mid] <= e) lo = mid; else hi = mid - 1;
+    }
+    *s_out = lo;
+    *rg_out = e - sc.cu_units[lo];
+    *g = groups_of(a, sc, lo);
+    const int rows = sc.q0[lo + 1] - sc.q0[lo];
+    const int cost = g->pages(*rg_out) * page_cost(a, *rg_out < g->n - 1 ? a.qpg : last_group(a, rows, g->n));
+    return QUEUE_BINS - 1 - min(QUEUE_BINS - 1, (int)((float)cost * scale));
+  };
+  int s, rg;
+  Groups g;
+  for (int e = tid; e < groups; e += PLAN_THREADS) atomicAdd(&bins[group_at(e, &s, &rg, &g)], 1);
+  __syncthreads();
+  // exclusive scan of the bins
+  const int mine = bins[tid];
+  int incl = mine;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int v = __shfl_up(incl, off);
+    if ((tid & 63) >= off) incl += v;
+  }
+  __shared__ int tot[PLAN_THREADS / 64];
+  if ((tid & 63) == 63) tot[tid >> 6] = incl;
+  __syncthreads();
+  int run = incl - mine;
+  for (int w = 0; w < (tid >> 6); ++w) run += tot[w];
+  bins[tid] = run;
+  __syncthreads();
+  const int extra = sh.items - a.nwg, each = extra / a.nwg, rest = extra - each * a.nwg;
+  int32_t* list = a.plan + PLAN_HDR * a.nwg;
+  for (int e = tid; e < groups; e += PLAN_THREADS) {
+    const int bin = group_at(e, &s, &rg, &g);
+    const int rank = atomicAdd(&bins[bin], 1) * a.num_kv_heads;
+    const int q0 = sc.q0[s] + rg * a.qpg, np = g.pages(rg), nq = min(a.qpg, sc.q0[s + 1] - q0);
+    int ids[PLAN_IDS];
+    if (rank < a.nwg) load_ids(a, s, 0, np, ids);
+    for (int h = 0; h < a.num_kv_heads; ++h) {
+      const int r = rank + h, w = r % a.nwg, next = w * each + min(w, rest);
+      int32_t* d = r < a.nwg ? a.plan + PLAN_HDR * w : list + PLAN_SEG * (next + r / a.nwg - 1);
+      *(i32x4*)d = i32x4{s | (h << 16), q0, nq, 0};
+      *(i32x4*)(d + 4) = i32x4{np, np, w | (w << 16), sc.L[s]};
+      if (r < a.nwg) {
+        d[PLAN_HDR_NSEG] = 1 + each + (w < rest ? 1 : 0);
+        d[PLAN_HDR_NEXT] = next;
+        d[PLAN_HDR_QUEUE] = extra;
+        store_ids(d, ids);
+      }
+    }
+  }
+}
+
 __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(PlanArgs a) {
   extern __shared__ int lds[];
-  __shared__ int scratch[3 * PLAN_THREADS / 64 + 2];
+  __shared__ int scratch[5 * PLAN_THREADS / 64 + 2];
   __shared__ int wave_tot[PLAN_THREADS / 64];
   const Sched sc = sched_at(lds, a.B);
   int* seg_cache = lds + sched_ints(a.B);
   const int CS = plan_cached_segments(a.nwg);
   const int tid = threadIdx.x;
   const Shares sh = build_schedule(a, sc, scratch);
+  if (sh.queue) {
+    write_queue(a, sc, sh, seg_cache);
+    return;
+  }
 
   // ---- pass 1: the segments of each workgroup (thread w: workgroup w); the first few are kept in LDS
   static_assert(PLAN_THREADS >= MAX_WG, "a thread per workgroup");
-  typedef int i32x4 __attribute__((ext_vector_type(4)));
   const int w = tid;
   int cnt = 0;
   Walk resume;  // where the walk stood after the cached segments
@@ -518,6 +679,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(PlanArgs a) {
   int32_t* hdr = a.plan + PLAN_HDR * w;
   hdr[PLAN_HDR_NSEG] = cnt;
   hdr[PLAN_HDR_NEXT] = run;
+  hdr[PLAN_HDR_QUEUE] = 0;
   const int cached = min(cnt, CS);
   for (int i = 0; i < cached; ++i) {
     const int* c = seg_cache + (w * CS + i) * PLAN_SEG;
@@ -526,16 +688,9 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(PlanArgs a) {
     *(i32x4*)d = lo;
     *(i32x4*)(d + 4) = hi;
     if (i == 0) {
-      const int p0 = lo[3], p1 = hi[0];
-      const int32_t* bt = a.block_tables + (long)(lo[0] & 0xffff) * a.max_blocks_per_seq;
       int ids[PLAN_IDS];
-#pragma unroll
-      for (int k = 0; k < PLAN_IDS; ++k) ids[k] = bt[min(p0 + k, p1 - 1)];  // all on their way at once
-#pragma unroll
-      for (int k = 0; k < PLAN_IDS; k += 4)
-        *(i32x4*)(hdr + PLAN_HDR_IDS + k) =
-            i32x4{min(max(ids[k], 0), a.num_blocks - 1), min(max(ids[k + 1], 0), a.num_blocks - 1),
-                  min(max(ids[k + 2], 0), a.num_blocks - 1), min(max(ids[k + 3], 0), a.num_blocks - 1)};
+      load_ids(a, lo[0] & 0xffff, lo[3], hi[0], ids);
+      store_ids(hdr, ids);
     }
   }
   if (cnt > CS) {
@@ -644,7 +799,11 @@ int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, const i
   a.max_blocks_per_seq = kv->max_blocks_per_seq;
   a.num_blocks = kv->num_blocks;
   a.has_owner = v.has_owner ? 1 : 0;
-  const size_t lds = (size_t)(sched_ints(B) + v.nwg * plan_cached_segments(v.nwg) * PLAN_SEG) * sizeof(int);
+  a.queue = v.kernel == KERNEL_BF16_ROWS ? 1 : 0;
+  a.w_page = v.kernel == KERNEL_BF16_ROWS ? ROWS_PAGE_COST : 1;
+  a.w_wave = v.kernel == KERNEL_BF16_ROWS ? 1 : 0;
+  a.rows_per_query = kv->num_q_heads / kv->num_kv_heads;
+  const size_t lds = (size_t)(sched_ints(B) + std::max(v.nwg * plan_cached_segments(v.nwg) * PLAN_SEG, QUEUE_BINS)) * sizeof(int);
   hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(PLAN_THREADS), lds, stream, a);
   ASPD_HIP_CHECK(hipGetLastError());
   return ASPD_OK;

@@ -569,16 +569,40 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
   constexpr int THREADS = NW * 64;
   Seg seg;
   int next;
+  const int queue = load_word_uniform(a.plan + (long)PLAN_HDR * blockIdx.x + PLAN_HDR_QUEUE);
   const int nseg = plan_begin(a, &seg, &next);
-  for (int i = 0; i < nseg; ++i) {
-    if (i > 0) {
-      seg = plan_segment(a, next + i - 1);
-      if (!seg_ok(a, seg)) break;
-    }
+  // In a plan with a queue the d-th item that is no workgroup's first is item d / nwg + 1 of workgroup d % nwg, whose
+  // items stand one behind the other in the list.
+  const int each = queue / a.nwg, rest = queue - each * a.nwg;
+  for (int i = 1; nseg > 0;) {
     const bool complete = seg_complete(seg);
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
     segment_rows<D, NW>(a, smem, seg, complete, pslot);
     if (!complete) announce_partial<D, true, THREADS, 4, 4>(a, seg, &merge_flag);
+    int at;
+    if (queue == 0) {
+      if (i >= nseg) break;
+      at = next + i - 1;
+      ++i;
+    } else {
+      if (threadIdx.x == 0) merge_flag = atomicAdd(a.counters + QUEUE_NEXT, 1);
+      __syncthreads();
+      const int d = __builtin_amdgcn_readfirstlane(merge_flag);
+      if (d >= queue) break;
+      at = d % a.nwg * each + min(d % a.nwg, rest) + d / a.nwg;
+    }
+    seg = plan_segment(a, at);
+    if (queue > 0) seg.owner = seg.w_last = seg.page0 == 0 && seg.page1 == seg.np ? (int)blockIdx.x : -1;  // whole items only
+    if (!seg_ok(a, seg)) break;
+  }
+  if (queue == 0) return;
+  // the last workgroup to leave puts the queue's words back to zero for the next launch
+  if (threadIdx.x == 0) {
+    const int gone = atomicAdd(a.counters + QUEUE_DONE, 1);
+    if (gone == a.nwg - 1) {
+      atomicExch(a.counters + QUEUE_NEXT, 0);
+      atomicExch(a.counters + QUEUE_DONE, 0);
+    }
   }
 }
 

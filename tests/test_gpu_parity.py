@@ -321,6 +321,33 @@ def test_segments_of_few_pages_and_items_of_many_parts(A, hd, branches):
         decode(gb, tt, wl, parts, f"{parts} parts")
 
 
+@pytest.mark.parametrize("hq,hkv,hd", [(32, 8, 128), (8, 8, 128), (16, 4, 64)])
+def test_whole_items_from_a_queue(A, hq, hkv, hd):
+    """Chunks and prompts with more items than workgroups: the row-splitting kernel takes whole items from a queue
+    (plan word 10 says so).  Three launches in a row on one workspace, then one whose items are split: the queue and the
+    arrival counters are left as they were found."""
+    from gpu_drive import GpuBatch
+    wl = W.random_small(seed=77, dtype="bf16", num_q_heads=hq, num_kv_heads=hkv, head_dim=hd, batch=7,
+                        prefix_range=(30, 700), branches_range=(2, 6), branch_len_range=(1, 9),
+                        extra_tokens_per_branch=30, extra_tokens_per_seq=4)
+    gb, tt = _grow_both(A, wl, wl.branch_len, False)
+    rng = np.random.default_rng(77)
+    for cap in (3, 5, 16):
+        new = rng.integers(6, 25, size=wl.NB).astype(np.int32) if cap == 3 else np.full(wl.NB, 2, dtype=np.int32)
+        meta = tt.append_parallel(new)
+        hint = max(64 * 8, int(new.sum()))  # (a bound that makes the launch split rows)
+        step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_PARALLEL, gb._dev_i32(new), NQ=int(new.sum()),
+                                        max_new_per_seq=hint, max_workgroups=cap)
+        plan = step.plan.cpu().numpy().view(np.int32)
+        assert plan[10] > 0 and plan[10] == plan[32 + 10], "a plan with a queue"
+        for rep in range(3):
+            _compare_attention(A, gb, tt, wl, step, meta, A.aspd_attn_branch_chunk, label=f"cap {cap} launch {rep}")
+    assert int(gb.workspace[:4096].count_nonzero()) == 0
+    ones = np.ones(wl.NB, dtype=np.int32)
+    meta = tt.append_parallel(ones)
+    _compare_attention(A, gb, tt, wl, gb.parallel(ones), meta, A.aspd_attn_parallel_decode, label="decode behind it")
+
+
 @pytest.mark.parametrize("branches", [3, 6], ids=["one_tile", "two_tiles"])
 def test_decode_loop_on_one_workspace(A, branches):
     """Forty consecutive decode launches on ONE workspace, with the hints a decoding loop gives (so the
