@@ -127,8 +127,11 @@ __device__ __forceinline__ float rows_raise(const f32x16& s, Rows32<D>& rs, bf16
 // slot of its own stage (a.row_base) and the first slot of its own branch there (a.row_lo), which are all of
 // what it sees: [0, base) and [lo, slot].  Otherwise all rows belong to the sequence's running stage, which
 // starts at it.L, and owner tags tell whose a slot of that stage is.
+// take_from: a counter that thread 0 adds one to before it writes its rows (so that the answer, which it returns, does not
+// have to be waited for), or null.
 template <int D, int NW, bool SEQ = false>
-__device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool complete, float* pslot) {
+__device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool complete, float* pslot,
+                                            int* take_from) {
   using C = RowsCfg<D>;
   constexpr int PPS = ROWS_PPS;
   static_assert(PPS == 2 && NW == 4 * PPS, "one wave per page of a group");
@@ -150,7 +153,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   // The rows of a group are packed in the order of their slots: the last row's slot bounds what any row
   // of the group may see.  Slots past it have never been written (the tail of the last page) and may hold
   // anything; their V rows are cleared on the way into LDS (zero weight times a NaN would be a NaN).
-  const int last_slot = __builtin_amdgcn_readfirstlane(a.logical_slot[it.q0 + it.nq - 1]);
+  const int last_slot = load_word_uniform(a.logical_slot + it.q0 + it.nq - 1);
 
   // Pairs of pages of the segment, numbered without the ones no row of the group sees: whole sequences lay a
   // stage's branches one after the other, so between the start of a stage and the first branch that the group
@@ -158,38 +161,94 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   int npairs = (page1 - page0 + 1) >> 1;
   int hole_at = npairs, hole = 0;
   if (SEQ && a.slot_owner) {
-    const int b0 = a.row_base[it.q0], b1 = a.row_base[it.q0 + it.nq - 1], lo0 = a.row_lo[it.q0];
-    if (b0 == b1) {
-      const int from = (b0 + 31) >> 5, to = min(lo0 >> 5, npairs);
-      if (to > from) {
-        hole_at = __builtin_amdgcn_readfirstlane(from);
-        hole = __builtin_amdgcn_readfirstlane(to - from);
-      }
+    const int b0 = load_word_uniform(a.row_base + it.q0), b1 = load_word_uniform(a.row_base + it.q0 + it.nq - 1);
+    const int lo0 = load_word_uniform(a.row_lo + it.q0);
+    const int from = (b0 + 31) >> 5, to = min(lo0 >> 5, npairs);
+    if (b0 == b1 && to > from) {
+      hole_at = from;
+      hole = to - from;
     }
     npairs -= hole;
   }
   auto page_of_pair = [&](int p) -> int { return page0 + 2 * (p < hole_at ? p : p + hole); };
 
-  // ---- this wave's Q operands and row descriptors go straight to registers
+  // ---- the loads of the start: this wave's row descriptors and Q operands, which go straight to registers, then its pages
+  // of the first two groups.  They return in that order, and a wait for a descriptor, which the compiler counts without
+  // the pages it does not know of, ends when the Q operands are there at the latest: what the rows have in common is
+  // worked out while the pages are on their way (first scores 7.1 -> 5.3 us after the launch's start; launches, us: stage
+  // opening over 12 sequences 59.6 -> 58.9, eight prompts 138.3 -> 137.3, three whole sequences 45.5 -> 45.1).
+  __syncthreads();  // LDS of the previous segment is free
   bf16x8 qr[C::KSTEPS];
-  int slot, tag = 0, base, lo = 0;
+  int slot, branch = 0, base = it.L, lo = 0;
   {
     const int rr = min(wave * 32 + c, R - 1);  // padding rows (and idle waves) repeat the last row
-    const int q = it.q0 + rr / a.G;
-    const int head = it.h * a.G + rr % a.G;
-    const u32x4* qsrc = (const u32x4*)a.q + ((long)q * a.kv.num_q_heads + head) * C::CH + h;
-#pragma unroll
-    for (int t = 0; t < C::KSTEPS; ++t) qr[t] = __builtin_bit_cast(bf16x8, qsrc[2 * t]);
+    const int qi = div_by_g(a, rr), q = it.q0 + qi;
+    const int head = it.h * a.G + rr - qi * a.G;
     slot = a.logical_slot[q];
     if (SEQ) {
       // (no owner tags: the shared mask, every row is treated like a main-branch row)
-      base = a.slot_owner ? a.row_base[q] : slot;
-      lo = a.slot_owner ? a.row_lo[q] : slot;
+      base = a.slot_owner ? a.row_base[q] : -1;
+      lo = a.slot_owner ? a.row_lo[q] : -1;
     } else {
-      const int qb = a.q_branch[q];
-      tag = (qb < 0 || !a.cu_branches) ? 0 : qb - a.cu_branches[it.s] + 1;
-      base = it.L;
+      branch = a.q_branch[q];
     }
+    const u32x4* qsrc = (const u32x4*)a.q + ((long)q * a.kv.num_q_heads + head) * C::CH + h;
+#pragma unroll
+    for (int t = 0; t < C::KSTEPS; ++t) qr[t] = __builtin_bit_cast(bf16x8, qsrc[2 * t]);
+  }
+  // ---- staging.  Group i holds the K pages of pairs 2 i + 1 and 2 i + 2 and the V pages of pairs 2 i - 1 and
+  // 2 i (what the two steps of the group multiply); wave w fetches one page of it.  Pages outside the segment
+  // are fetched as the nearest one inside.  Their scores are not used; V pages that a step multiplies all the same, with
+  // weight zero (pair -1 by the first full step, the second page of an odd last pair), are zeros in LDS.
+  const bool l_is_k = wave < 4;
+  const int l_pair = (wave >> 1) & 1;
+  const int n_last = npairs - 1;
+  auto page_of_group = [&](int i) -> int {
+    const int p = min(max(2 * i + l_pair + (l_is_k ? 1 : -1), 0), n_last);
+    return min(page_of_pair(p) + (wave & 1), page1 - 1);
+  };
+  const char* const pool = (const char*)(l_is_k ? a.kv.k : a.kv.v) + (long)it.h * C::PAGE_B;
+  const uint32_t l_at = lds0 + (l_is_k ? 0 : PPS * C::PAIR_B) + l_pair * C::PAIR_B + (wave & 1) * C::PAGE_B;
+  // Which 16 bytes of its page the lane fetches with the first load; with the k-th, 1024 k bytes on, and with the
+  // chunk order of the rows there (bit 2 of a K row's order changes with every load).
+  uint32_t goff;
+  {
+    const int row = lane / C::CH;
+    goff = row * (D * 2) + ((lane % C::CH ^ (l_is_k ? C::kswz(row) : C::vswz(row))) << 4);
+  }
+  const uint32_t goff_flip = l_is_k ? 64 : 0;
+
+  auto buffer_of = [&](int i) -> int { return i & (ROWS_BUFS - 1); };
+  const int i_last = npairs >> 1;
+  int block = 0;  // block id of the group that is sent for next
+  auto send = [&](int i) {
+    if (i > i_last) return;
+    const char* src = pool + (long)min(max(block, 0), a.kv.num_blocks - 1) * a.kv.num_kv_heads * C::PAGE_B;
+#pragma unroll
+    for (int k = 0; k < LPT; ++k) load_to_lds(src + k * 1024, goff ^ (k * goff_flip), l_at + buffer_of(i) * C::STAGE_B + k * 1024);
+    block = bt[page_of_group(i + 1)];
+  };
+  auto clear_v = [&](int i, int k) {
+    *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(l_at + buffer_of(i) * C::STAGE_B + k * 1024 + lane * 16) =
+        u32x4{0u, 0u, 0u, 0u};
+  };
+  const int first_branch = !SEQ && a.cu_branches ? load_word_uniform(a.cu_branches + it.s) : 0;
+  block = bt[page_of_group(-1)];
+  send(-1);
+  if (!l_is_k && l_pair == 0) {  // V of pair -1, which the first full step multiplies with weights zero
+#pragma unroll
+    for (int k = 0; k < LPT; ++k) clear_v(0, k);
+    // (no load in flight for group 0 here: this wave's wait for group -1, whose V pages nobody reads, may come up early)
+    block = bt[page_of_group(1)];
+  } else {
+    send(0);
+  }
+
+  int tag = 0;
+  if (SEQ) {
+    if (base < 0) base = lo = slot;
+  } else {
+    tag = (branch < 0 || !a.cu_branches) ? 0 : branch - first_branch + 1;
   }
   // What the wave's rows have in common decides which pairs need a mask and which can be left out:
   //   mask_from  every key below this slot is visible to every row (below every row's stage and slot);
@@ -242,7 +301,6 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
       va[mt] = first + PPS * C::PAIR_B + key * (D * 2) +
                (((4 * mt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ C::vswz(key)) << 4) + 8 * (lane & 1);
   }
-  auto buffer_of = [&](int i) -> int { return i & (ROWS_BUFS - 1); };
   auto next_group = [&](int i) {  // from group i's stage to the next
     const int d = buffer_of(i) == ROWS_BUFS - 1 ? -(ROWS_BUFS - 1) * C::STAGE_B : C::STAGE_B;
 #pragma unroll
@@ -252,28 +310,6 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   };
   auto k_operand = [&](int u, int t) { return lds_operand(ka[t] + u * C::PAIR_B); };
   auto v_operand = [&](int u, int j) { return rows_v_operand<D>(va[j % C::MT] + u * C::PAIR_B + (j / C::MT) * C::PAGE_B); };
-
-  // ---- staging.  Group i holds the K pages of pairs 2 i + 1 and 2 i + 2 and the V pages of pairs 2 i - 1 and
-  // 2 i (what the two steps of the group multiply); wave w fetches one page of it.  Pages outside the segment
-  // are fetched as the nearest one inside.  Their scores are not used; V pages that a step multiplies all the same, with
-  // weight zero (pair -1 by the first full step, the second page of an odd last pair), are zeros in LDS.
-  const bool l_is_k = wave < 4;
-  const int l_pair = (wave >> 1) & 1;
-  const int n_last = npairs - 1;
-  auto page_of_group = [&](int i) -> int {
-    const int p = min(max(2 * i + l_pair + (l_is_k ? 1 : -1), 0), n_last);
-    return min(page_of_pair(p) + (wave & 1), page1 - 1);
-  };
-  const char* const pool = (const char*)(l_is_k ? a.kv.k : a.kv.v) + (long)it.h * C::PAGE_B;
-  const uint32_t l_at = lds0 + (l_is_k ? 0 : PPS * C::PAIR_B) + l_pair * C::PAIR_B + (wave & 1) * C::PAGE_B;
-  // Which 16 bytes of its page the lane fetches with the first load; with the k-th, 1024 k bytes on, and with the
-  // chunk order of the rows there (bit 2 of a K row's order changes with every load).
-  uint32_t goff;
-  {
-    const int row = lane / C::CH;
-    goff = row * (D * 2) + ((lane % C::CH ^ (l_is_k ? C::kswz(row) : C::vswz(row))) << 4);
-  }
-  const uint32_t goff_flip = l_is_k ? 64 : 0;
 
   // owner tags of a group's K pairs that reach into the branch region
   auto tags_of = [&](int i, u32x4 (&t)[PPS][2]) {
@@ -434,20 +470,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   // One barrier per group: every wave has its page of the group in LDS, and is done with the stage that the group two
   // further on goes to.  The V rows of slots past the last row's or past the segment are cleared before it: they may
   // hold anything, or an infinity that belongs to another slot, and zero times either would be a NaN.
-  const int i_last = npairs >> 1;
-  int block = 0;  // block id of the group that is sent for next
-  auto send = [&](int i) {
-    if (i > i_last) return;
-    const char* src = pool + (long)min(max(block, 0), a.kv.num_blocks - 1) * a.kv.num_kv_heads * C::PAGE_B;
-#pragma unroll
-    for (int k = 0; k < LPT; ++k) load_to_lds(src + k * 1024, goff ^ (k * goff_flip), l_at + buffer_of(i) * C::STAGE_B + k * 1024);
-    block = bt[page_of_group(i + 1)];
-  };
   const int v_last = min(last_slot, page1 * ASPD_BLOCK - 1);
-  auto clear_v = [&](int i, int k) {
-    *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(l_at + buffer_of(i) * C::STAGE_B + k * 1024 + lane * 16) =
-        u32x4{0u, 0u, 0u, 0u};
-  };
   auto arrive = [&](int i, bool tail) {
     if (i + 1 <= i_last) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPT) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -478,17 +501,11 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   // costs one barrier and is staged the same way in either kind of step.
   const int open_pairs = min(hole_at, (min(page1, mask_from / ASPD_BLOCK) - page0) >> 1);
   const int i_open = wave_active ? (open_pairs - 1) >> 1 : 0;  // 2 i + 2 <= open_pairs - 1
-  __syncthreads();  // LDS of the previous segment is free
-  block = bt[page_of_group(-1)];
-  send(-1);
-  if (!l_is_k && l_pair == 0) {  // V of pair -1, which the first full step multiplies with weights zero
+  // The Q operands are there since the first descriptor was; the compiler would wait for them where they are first used,
+  // and with them for the group that is sent for in between.
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 0; k < LPT; ++k) clear_v(0, k);
-    // (no load in flight for group 0 here: this wave's wait for group -1, whose V pages nobody reads, may come up early)
-    block = bt[page_of_group(1)];
-  } else {
-    send(0);
-  }
+  for (int t = 0; t < C::KSTEPS; ++t) asm volatile("" : "+v"(qr[t]));
   general_groups(-1, 0);  // (the scores of pair 0)
   int i = 0;
   if (i_open > 0) {
@@ -512,11 +529,13 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
   general_groups(i, i_last + 1);
 
   // ---- every wave writes its own rows
-  if (!wave_active) return;
+  int taken = 0;
+  if (take_from && tid == 0) taken = atomicAdd(take_from, 1);
+  if (!wave_active) return taken;
   rs.l_run += __shfl_xor(rs.l_run, 32);
   const int r = wave * 32 + c;  // row inside the row group
   if (complete) {
-    if (c >= Rw) return;
+    if (c >= Rw) return taken;
     const int q = it.q0 + r / a.G;
     const int head = it.h * a.G + r % a.G;
     const float inv = 1.f / rs.l_run;
@@ -559,6 +578,7 @@ __device__ void segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool 
     }
     if (h == 0 && c < Rw) store_device_scope_x4(partial_stat(a, pslot, r, D), f32x4{rs.m_run, rs.l_run, 0.f, 0.f});
   }
+  return taken;
 }
 
 template <int D, int NW>
@@ -577,15 +597,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
   for (int i = 1; nseg > 0;) {
     const bool complete = seg_complete(seg);
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
-    segment_rows<D, NW>(a, smem, seg, complete, pslot);
-    if (!complete) announce_partial<D, true, THREADS, 4, 4>(a, seg, &merge_flag);
+    const int taken = segment_rows<D, NW>(a, smem, seg, complete, pslot, queue > 0 ? a.counters + QUEUE_NEXT : nullptr);
+    if (!complete) announce_partial<D, true, THREADS, D / 16, 4>(a, seg, &merge_flag);
     int at;
     if (queue == 0) {
       if (i >= nseg) break;
       at = next + i - 1;
       ++i;
     } else {
-      if (threadIdx.x == 0) merge_flag = atomicAdd(a.counters + QUEUE_NEXT, 1);
+      if (threadIdx.x == 0) merge_flag = taken;
       __syncthreads();
       const int d = __builtin_amdgcn_readfirstlane(merge_flag);
       if (d >= queue) break;
@@ -623,11 +643,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
   const int32_t* items = a.plan + SEQ_PLAN_HDR + ((a.NQ + 3) & ~3);
   const int Hkv = a.kv.num_kv_heads;
   const long total = (long)n_groups * Hkv;
+  int taken = 0;
+  if (threadIdx.x == 0) taken = atomicAdd(a.counters, 1);
   for (;;) {
-    if (threadIdx.x == 0) next_item = atomicAdd(a.counters, 1);
+    if (threadIdx.x == 0) next_item = taken;
     __syncthreads();
-    const int e = next_item;
-    __syncthreads();  // everyone has read it before the next round overwrites it
+    const int e = __builtin_amdgcn_readfirstlane(next_item);
     if (e >= total) break;
     const i32x4 w = *(const i32x4*)(items + 4 * (e / Hkv));
     Seg seg;
@@ -644,8 +665,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
     const bool ok = (int)(seg.s >= 0) & (int)(seg.s < a.B) & (int)(seg.q0 >= 0) & (int)(seg.nq >= 1) &
                     (int)(seg.nq <= a.qpg) & (int)(seg.q0 <= a.NQ - seg.nq) & (int)(seg.np >= 1) &
                     (int)(seg.np <= a.kv.max_blocks_per_seq);
-    if (!ok) continue;
-    segment_rows<D, NW, true>(a, smem, seg, true, nullptr);
+    if (!ok) {
+      __syncthreads();  // everyone has read next_item
+      if (threadIdx.x == 0) taken = atomicAdd(a.counters, 1);
+      continue;
+    }
+    taken = segment_rows<D, NW, true>(a, smem, seg, true, nullptr, a.counters);
   }
   // the last workgroup to leave puts the two counters back to zero for the next launch
   if (threadIdx.x == 0) {
