@@ -1,4 +1,5 @@
-"""ctypes binding of libaspd.so: argument marshalling only.
+"""Binding of libaspd.so: argument marshalling only, by ctypes; for the calls of every step by compiled code
+(csrc/aspd_pycalls.cpp), because their arguments cost more time in Python than the smallest steps take on the GPU.
 
 Every operation runs in the library's HIP kernels.  PyTorch is used for device memory
 and for the current stream, nothing else.  There is no fallback: if the shared library is
@@ -117,9 +118,23 @@ def status_string(code: int) -> str:
     return lib().aspd_status_string(int(code)).decode()
 
 
-# Small steps are bound by the host: an append and an attention call take some thirty addresses.  They go to ctypes
-# as plain ints, which fields and argument types of type c_void_p take as they are; an object around each took 4 of the
-# 20 us that the two calls' arguments cost (a step of four layers over one sequence: 120 -> 114 us).
+_pycalls = None
+
+
+def _calls():
+    """The compiled half of the binding, loaded with the library."""
+    global _pycalls
+    if _pycalls is None:
+        lib()
+        if not os.path.exists(os.path.join(_HERE, "_pycalls.so")):
+            raise FileNotFoundError(f"{_HERE}/_pycalls.so not built: run `python -m paper_2508_08895_amd.build`")
+        from paper_2508_08895_amd import _pycalls as m
+        m.init(KVCache, BatchState, Step)
+        _pycalls = m
+    return _pycalls
+
+
+# Addresses go to ctypes as plain ints, which fields and argument types of type c_void_p take as they are.
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -212,10 +227,8 @@ def aspd_build_branch_meta(kv: KVCache, state: BatchState, stage: int, new_len: 
     """See aspd.h.  `NQ` = sum of new_len, known to the caller.  Returns the Step (None for MERGE,
     where new_len, if given, says per sequence whether its stage ends).  `plan`: give the step a plan
     buffer (allocated here on the step's first use) so that the attention calls start from the plan."""
-    kvs, sts = kv.struct(), state.struct()
     if stage == STAGE_MERGE:
-        rc = lib().aspd_build_branch_meta(C.byref(kvs), C.byref(sts), stage, state.pos_mode, _ptr(new_len), None,
-                                          _stream(stream))
+        rc = _calls().build_branch_meta(kv, state, stage, new_len, None, stream)
         if rc != OK:
             raise AspdError(rc, "aspd_build_branch_meta")
         return None
@@ -224,12 +237,9 @@ def aspd_build_branch_meta(kv: KVCache, state: BatchState, stage: int, new_len: 
                     max_new_per_seq, max_workgroups)
     if plan and step.plan is None and step.NQ > 0:
         step.plan = torch.empty(aspd_plan_bytes(kv, state.B, step.NQ), dtype=torch.uint8, device=state.device)
-    sps = step.struct()
-    rc = lib().aspd_build_branch_meta(C.byref(kvs), C.byref(sts), stage, state.pos_mode, _ptr(new_len),
-                                      C.byref(sps), _stream(stream))
+    rc = _calls().build_branch_meta(kv, state, stage, new_len, step, stream)   # (sets step.plan_key)
     if rc != OK:
         raise AspdError(rc, "aspd_build_branch_meta")
-    step.plan_key = int(sps.plan_key)   # the one host field the library writes
     return step
 
 
@@ -253,9 +263,7 @@ def aspd_renumber_branches(state: BatchState, new_cu_branches: torch.Tensor, str
 def aspd_rope_append(kv: KVCache, step: Step, q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor,
                      rope_theta: float, stream=None) -> torch.Tensor:
     """See aspd.h: rotates q in place, writes rotated k_new and plain v_new into the cache.  Returns q."""
-    kvs, sps = kv.struct(), step.struct()
-    rc = lib().aspd_rope_append(C.byref(kvs), C.byref(sps), _ptr(q), _ptr(k_new), _ptr(v_new),
-                                C.c_float(rope_theta), _stream(stream))
+    rc = _calls().rope_append(kv, step, q, k_new, v_new, rope_theta, stream)
     if rc != OK:
         raise AspdError(rc, "aspd_rope_append")
     return q
@@ -271,28 +279,30 @@ def aspd_plan_bytes(kv: KVCache, B: int, NQ: int) -> int:
     return int(lib().aspd_plan_bytes(C.byref(kvs), B, NQ))
 
 
-def _attn(name, kv, state, step, q, out, lse, sm_scale, workspace, stream):
-    kvs, sts, sps = kv.struct(), state.struct(), step.struct()
-    if out is None:
+# the attention calls by their number there
+_ATTN = ("aspd_attn_parallel_decode", "aspd_attn_branch_chunk", "aspd_attn_serial_decode", "aspd_attn_full_sequence",
+         "aspd_attn_parallel_decode_static")
+
+
+def _attn(which, kv, state, step, q, out, lse, sm_scale, workspace, stream):
+    if out is None and which != 4:   # (the static call allocates nothing and refuses to go without)
         out = torch.empty_like(q)
-    nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    rc = getattr(lib(), name)(C.byref(kvs), C.byref(sts), C.byref(sps), _ptr(q), _ptr(out), _ptr(lse),
-                              C.c_float(sm_scale), _ptr(workspace), nbytes, _stream(stream))
+    rc = _calls().attn(which, kv, state, step, q, out, lse, sm_scale, workspace, stream)
     if rc != OK:
-        raise AspdError(rc, name)
+        raise AspdError(rc, _ATTN[which])
     return out
 
 
 def aspd_attn_parallel_decode(kv, state, step, q, workspace, out=None, lse=None, sm_scale=0.0, stream=None):
-    return _attn("aspd_attn_parallel_decode", kv, state, step, q, out, lse, sm_scale, workspace, stream)
+    return _attn(0, kv, state, step, q, out, lse, sm_scale, workspace, stream)
 
 
 def aspd_attn_branch_chunk(kv, state, step, q, workspace, out=None, lse=None, sm_scale=0.0, stream=None):
-    return _attn("aspd_attn_branch_chunk", kv, state, step, q, out, lse, sm_scale, workspace, stream)
+    return _attn(1, kv, state, step, q, out, lse, sm_scale, workspace, stream)
 
 
 def aspd_attn_serial_decode(kv, state, step, q, workspace, out=None, lse=None, sm_scale=0.0, stream=None):
-    return _attn("aspd_attn_serial_decode", kv, state, step, q, out, lse, sm_scale, workspace, stream)
+    return _attn(2, kv, state, step, q, out, lse, sm_scale, workspace, stream)
 
 
 def aspd_sequence_plan_bytes(kv: KVCache, B: int, NQ: int) -> int:
@@ -305,35 +315,25 @@ def aspd_build_sequence_meta(kv: KVCache, state: BatchState, cu_runs: torch.Tens
                              max_workgroups: int = 0) -> Step:
     """See aspd.h: the metadata of every token of a batch of whole multi-stage sequences.  The three int32
     device arrays describe the layout; `NQ` = sum of run_len, known to the caller."""
-    kvs, sts = kv.struct(), state.struct()
     if step is None:
         step = Step(NQ, 0, state.B, state.device, 0, max_workgroups)
-    need = aspd_sequence_plan_bytes(kv, state.B, step.NQ)
+    need = _calls().sequence_plan_bytes(kv, state.B, step.NQ)
     if step.plan is None or step.plan.numel() < need:
         step.plan = torch.empty(max(need, 256), dtype=torch.uint8, device=state.device)
-    lay = aspd_layout(int(run_branch.numel()), _ptr(cu_runs), _ptr(run_branch), _ptr(run_len))
-    sps = step.struct()
-    rc = lib().aspd_build_sequence_meta(C.byref(kvs), C.byref(sts), C.byref(lay), state.pos_mode, C.byref(sps),
-                                        _stream(stream))
-    if rc != OK:
+    rc = _calls().build_sequence_meta(kv, state, int(run_branch.numel()), cu_runs, run_branch, run_len, step, stream)
+    if rc != OK:   # (a call that succeeds has set step.plan_key)
         raise AspdError(rc, "aspd_build_sequence_meta")
-    step.plan_key = int(sps.plan_key)
     return step
 
 
 def aspd_attn_full_sequence(kv, state, step, q, workspace, out=None, lse=None, sm_scale=0.0, stream=None):
-    return _attn("aspd_attn_full_sequence", kv, state, step, q, out, lse, sm_scale, workspace, stream)
+    return _attn(3, kv, state, step, q, out, lse, sm_scale, workspace, stream)
 
 
 def aspd_attn_parallel_decode_static(kv, state, step, q, out, lse=None, sm_scale=0.0, stream=None):
     """See aspd.h: parallel decode on the library's own static scratch.  `out` is the caller's (nothing is
     allocated here either)."""
-    kvs, sts, sps = kv.struct(), state.struct(), step.struct()
-    rc = lib().aspd_attn_parallel_decode_static(C.byref(kvs), C.byref(sts), C.byref(sps), _ptr(q), _ptr(out), _ptr(lse),
-                                                C.c_float(sm_scale), _stream(stream))
-    if rc != OK:
-        raise AspdError(rc, "aspd_attn_parallel_decode_static")
-    return out
+    return _attn(4, kv, state, step, q, out, lse, sm_scale, None, stream)
 
 
 def aspd_workspace_init(workspace: torch.Tensor, stream=None) -> None:

@@ -1,14 +1,17 @@
-"""Builds libaspd.so (HIP, gfx950) in-tree.  `python -m paper_2508_08895_amd.build`."""
+"""Builds libaspd.so (HIP, gfx950) and the binding's _pycalls.so (host code over it) in-tree.
+`python -m paper_2508_08895_amd.build`."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libaspd.so")
+CALLS = os.path.join(HERE, "_pycalls.so")
 SOURCES = ["aspd_meta.hip", "aspd_seq_meta.hip", "aspd_plan.hip", "aspd_attn.hip", "aspd_rope.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -21,7 +24,26 @@ def build(verbose: bool = False, extra=()) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    build_calls(verbose)
     return LIB
+
+
+def build_calls(verbose: bool = False) -> str:
+    """The compiled half of the binding, against the libraries of the torch it runs beside."""
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    dirs = [*include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[x for d in dirs for x in ("-isystem" if d != dirs[-1] else "-I", d)],
+           os.path.join(CSRC, "aspd_pycalls.cpp"), "-o", CALLS, "-L", HERE, "-l:libaspd.so", "-L", torch_lib,
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALLS
 
 
 if __name__ == "__main__":
