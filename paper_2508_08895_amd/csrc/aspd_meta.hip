@@ -108,7 +108,18 @@ __global__ __launch_bounds__(META_THREADS) void meta_parallel_kernel(KvView kv, 
     return;
   }
   if (c_main != 0) {  // main-branch tokens while branches are open: refuse the sequence
-    if (tid == 0) raise_fault(st.fault, ASPD_FAULT_STAGE);
+    // Its rows stay unwritten, but where they would lie is written like that of every refused sequence: the plan takes the
+    // number of a sequence's rows from its neighbours' entries, and an entry left from an earlier step made it thousands.
+    if (tid == 0) {
+      raise_fault(st.fault, ASPD_FAULT_STAGE);
+      sp.cu_seq_new[s] = base;
+    }
+    if (s == st.B - 1) {
+      part = 0;
+      for (int i = b0 + tid; i < b1; i += META_THREADS) part += new_len[i];
+      const int own = block_sum(part, red);
+      if (tid == 0) sp.cu_seq_new[st.B] = base + own + c_main;
+    }
     return;
   }
   if (tid == 0 && st.stage_open) st.stage_open[s] = 1;  // named with branches: in a parallel stage, tokens or not
@@ -348,7 +359,7 @@ extern "C" int aspd_build_branch_meta(const aspd_kv* kv, aspd_state* state, int3
   }
   ASPD_HIP_CHECK(hipGetLastError());
   if (with_plan) {
-    rc = aspd_plan_launch(kv, variant, state->B, state->stage_base_d, state->seq_len_d, out->cu_seq_new_d,
+    rc = aspd_plan_launch(kv, variant, state->B, out->NQ, state->stage_base_d, state->seq_len_d, out->cu_seq_new_d,
                           out->plan_d, hs);
     if (rc != ASPD_OK) return rc;
     out->plan_key = aspd_plan_key(variant, state->B);

@@ -83,7 +83,7 @@ uint64_t aspd_plan_key(const AttnVariant& v, int32_t B);
 size_t aspd_plan_words(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t NQ);
 
 // Enqueues the kernel that writes the plan of the step for launch shape `v` to plan_d.
-int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, const int32_t* stage_base_d,
+int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t NQ, const int32_t* stage_base_d,
                      const int32_t* seq_len_d, const int32_t* cu_seq_new_d, int32_t* plan_d, hipStream_t stream);
 
 // ---- The plan of a whole-sequence step (aspd_build_sequence_meta / aspd_attn_full_sequence) -------

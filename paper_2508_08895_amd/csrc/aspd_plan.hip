@@ -26,7 +26,14 @@ struct PlanArgs {
   int            w_page, w_wave;  // what a page costs: w_page + w_wave for every 32 rows of its row group
   int            rows_per_query;  // query heads per KV head
   int            queue;           // the kernel can take whole items from a queue
+  int            NQ, max_items;   // rows of the step, and the items the plan has room for
 };
+
+// Rows of a sequence whose rows are [q0, q1) of the step; none where they are not rows of the step (more new tokens than the
+// caller said: the metadata refuses those sequences, and a plan is sized for the rows that the caller said).
+__device__ __forceinline__ int rows_between(const PlanArgs& a, int q0, int q1) {
+  return (int)(q0 >= 0) & (int)(q0 <= q1) & (int)(q1 <= a.NQ) ? q1 - q0 : 0;
+}
 
 struct Item {
   int s, rg, h;     // sequence, row group, KV head
@@ -270,7 +277,7 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
       sc.L[s] = a.stage_base[s];
       sc.q0[s] = q0;
       if (s == a.B - 1) sc.q0[a.B] = q1;
-      const Groups g = groups_at(a, T, q1 - q0, (q1 - q0 + a.qpg - 1) / a.qpg);
+      const Groups g = groups_at(a, T, q1 - q0, (rows_between(a, q0, q1) + a.qpg - 1) / a.qpg);
       sc.ng[s] = g.n;
       const int np = g.np;
       if (np > 0 && g.n > 0) {
@@ -329,6 +336,7 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
     longest_q = max(longest_q, scratch[3 * NWV + w]);
     cost += (long)((unsigned*)scratch)[4 * NWV + w] << 4;
   }
+  if (items > a.max_items) items = pages = 0;  // rows that no metadata call has written: nothing is planned
   Shares sh;
   sh.pad = a.pad;
   sh.piece = 0;
@@ -783,7 +791,7 @@ size_t aspd_plan_words(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32
   return (size_t)PLAN_HDR * v.nwg + (size_t)PLAN_SEG * (items + v.nwg);
 }
 
-int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, const int32_t* stage_base_d,
+int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t NQ, const int32_t* stage_base_d,
                      const int32_t* seq_len_d, const int32_t* cu_seq_new_d, int32_t* plan_d, hipStream_t stream) {
   PlanArgs a;
   a.stage_base = stage_base_d;
@@ -803,6 +811,8 @@ int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, const i
   a.w_page = v.kernel == KERNEL_BF16_ROWS ? ROWS_PAGE_COST : 1;
   a.w_wave = v.kernel == KERNEL_BF16_ROWS ? 1 : 0;
   a.rows_per_query = kv->num_q_heads / kv->num_kv_heads;
+  a.NQ = NQ;
+  a.max_items = (int)((B + (long)NQ / v.qpg) * kv->num_kv_heads);
   const size_t lds = (size_t)(sched_ints(B) + std::max(v.nwg * plan_cached_segments(v.nwg) * PLAN_SEG, QUEUE_BINS)) * sizeof(int);
   hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(PLAN_THREADS), lds, stream, a);
   ASPD_HIP_CHECK(hipGetLastError());
