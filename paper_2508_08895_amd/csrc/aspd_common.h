@@ -63,3 +63,50 @@ static inline StepView make_view(const aspd_step* sp) {
 
 // Host-side validation of the cache descriptor; returns an ASPD_* code.
 int aspd_check_kv(const aspd_kv* kv);
+
+#ifdef __HIP__
+// Inclusive scans over a row of 16 lanes and over the 64 lanes of a wave by data-parallel moves: four and six instructions a
+// value, where shuffles go through LDS, three instructions and a wait each.  The last lane has the result over all
+// of them.  Lanes without a source see 0.
+template <typename Op>
+__device__ __forceinline__ int row_scan(int v, Op op) {
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));  // one lane up
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));  // two
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));  // four
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));  // eight
+  return v;
+}
+template <typename Op>
+__device__ __forceinline__ int wave_scan(int v, Op op) {
+  v = row_scan(v, op);
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));  // last lane of rows 0 and 2 to rows 1 and 3
+  v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));  // lane 31 to rows 2 and 3
+  return v;
+}
+__device__ __forceinline__ int row_scan_add(int v) {
+  return row_scan(v, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int wave_scan_add(int v) {
+  return wave_scan(v, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int wave_scan_max(int v) {  // of values that are not negative
+  return wave_scan(v, [](int a, int b) { return a > b ? a : b; });
+}
+
+// x / d for x >= 0, d > 0 by a float reciprocal rd of d, made exact (the loops run once at most while the quotient is below
+// 2^20; an integer division by a value the compiler does not know is thirty to forty instructions).
+__device__ __forceinline__ int quotient(int x, int d, float rd) {
+  int q = (int)((float)x * rd);
+  int r = x - q * d;
+  while (r < 0) {
+    --q;
+    r += d;
+  }
+  while (r >= d) {
+    ++q;
+    r -= d;
+  }
+  return q;
+}
+__device__ __forceinline__ int quotient(int x, int d) { return quotient(x, d, __builtin_amdgcn_rcpf((float)d)); }
+#endif

@@ -11,17 +11,11 @@ namespace {
 
 constexpr int META_THREADS = 256;
 
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
-}
-
 // Sum over the workgroup; every thread gets the total.  `red` holds META_THREADS/64 ints.
 __device__ int block_sum(int v, int* red) {
-  v = wave_sum(v);
+  v = wave_scan_add(v);
   __syncthreads();  // red may still be read from an earlier call
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
   __syncthreads();
   int tot = 0;
 #pragma unroll
@@ -45,7 +39,7 @@ __global__ __launch_bounds__(META_THREADS) void meta_parallel_kernel(KvView kv, 
                                                                      const int32_t* __restrict__ new_len,
                                                                      const int32_t* __restrict__ main_len,
                                                                      bool same_seq, int fix_n) {
-  __shared__ int red[META_THREADS / 64];
+  __shared__ int red[2 * META_THREADS / 64];
   __shared__ int off[ASPD_MAX_BRANCHES_PER_SEQ + 2];  // exclusive scan of this sequence's new_len
   __shared__ int held[ASPD_MAX_BRANCHES_PER_SEQ + 1]; // tokens each branch already holds
   const int s = blockIdx.x;
@@ -68,8 +62,23 @@ __global__ __launch_bounds__(META_THREADS) void meta_parallel_kernel(KvView kv, 
   for (int i = tid; i < b0; i += META_THREADS) part += new_len[i];
   if (main_len)
     for (int i = tid; i < s; i += META_THREADS) part += main_len[i];
-  const int base = block_sum(part, red);
   const int c_main = main_len ? main_len[s] : 0;
+  // and the sequence's own branches (K <= 255: one per thread), whose scan goes over the waves together with that sum
+  const int c_mine = (tid < K) ? new_len[b0 + tid] : 0;
+  const int held_mine = (tid < K) ? st.branch_len[b0 + tid] : 0;
+  int before = wave_scan_add(c_mine);
+  part = wave_scan_add(part);
+  if ((tid & 63) == 63) {
+    red[tid >> 6] = part;
+    red[META_THREADS / 64 + (tid >> 6)] = before;
+  }
+  __syncthreads();
+  int base = 0;
+#pragma unroll
+  for (int w = 0; w < META_THREADS / 64; ++w) {
+    base += red[w];
+    if (w < (tid >> 6)) before += red[META_THREADS / 64 + w];
+  }
 
   if (K == 0) {
     // no open branch: the sequence is serial and takes main-branch tokens (or none)
@@ -124,26 +133,12 @@ __global__ __launch_bounds__(META_THREADS) void meta_parallel_kernel(KvView kv, 
   }
   if (tid == 0 && st.stage_open) st.stage_open[s] = 1;  // named with branches: in a parallel stage, tokens or not
 
-  // scan over the sequence's own branches (K <= 255: one branch per thread, serial scan by thread 0
-  // would do, but a log-step scan keeps the launch short for wide stages)
-  const int c_mine = (tid < K) ? new_len[b0 + tid] : 0;
-  if (tid < K) held[tid] = st.branch_len[b0 + tid];
-  if (tid <= K) off[tid] = 0;
-  __syncthreads();
-  {
-    // inclusive Hillis-Steele in registers + LDS over the first 256 threads
-    __shared__ int scan[META_THREADS];
-    scan[tid] = c_mine;
-    __syncthreads();
-    for (int d = 1; d < META_THREADS; d <<= 1) {
-      int v = (tid >= d) ? scan[tid - d] : 0;
-      __syncthreads();
-      scan[tid] += v;
-      __syncthreads();
-    }
-    if (tid < K) off[tid + 1] = scan[tid];
-    __syncthreads();
+  if (tid < K) {
+    held[tid] = held_mine;
+    off[tid + 1] = before;
   }
+  if (tid == 0) off[0] = 0;
+  __syncthreads();
   const int total = off[K];
 
   if (tid < K) sp.cu_new[b0 + tid] = base + off[tid];

@@ -38,7 +38,7 @@ constexpr int PLAN_IDS = 16;
 // Words of the arrival counters that the queue uses (the row-splitting kernel, whose grid is smaller, has the others).
 constexpr int QUEUE_NEXT = 1022, QUEUE_DONE = 1023;
 
-constexpr int MAX_WG = 1024;         // upper bound of any attention grid
+constexpr int MAX_WG = 512;          // upper bound of any attention grid
 constexpr int NT_MAX = 3;            // 16-row MFMA tiles per row group of the streaming bf16 kernel
 constexpr int F32_ROWS = 4;          // rows per row group of the fp32 kernel
 constexpr int ROWS_NW = 8;           // waves per workgroup of the row-splitting (chunk) kernel, 32 rows each
@@ -53,7 +53,7 @@ constexpr int PAD_ROWS = 32;         // and for the row-splitting kernel: a segm
                                      // sequences 317 each time
 
 constexpr int ROWS_PAGE_COST = 4;    // row-splitting kernel: a page takes 0.14 us + 0.038 us per wave that has rows
-static_assert(MAX_WG_ROWS <= 1022 && MAX_WG == 1024, "queue words");
+static_assert(MAX_WG <= QUEUE_NEXT, "queue words");
 
 enum AttnKernel { KERNEL_F32 = 0, KERNEL_BF16_STREAM = 1, KERNEL_BF16_ROWS = 2 };
 

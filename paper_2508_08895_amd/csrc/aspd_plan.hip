@@ -13,7 +13,13 @@
 
 namespace {
 
-constexpr int PLAN_THREADS = 1024;  // one workgroup; a thread per workgroup of the largest attention grid
+// One workgroup; a thread per workgroup of the largest attention grid and per sequence of the largest batch.  Not more waves than
+// that, and few instructions on the way of all: a wave by itself issues one in eight to nine cycles, and what every wave does
+// alike (sums across the waves, the choice of a regime) was most of the kernel whatever the batch.  With sixteen waves,
+// shuffles, integer and 64-bit divisions the plan of one sequence took 18 400 cycles, of 16 sequences 21 100, of 64 35 100;
+// with eight, data-parallel moves and reciprocals 10 700, 14 300 and 28 100.
+constexpr int PLAN_THREADS = 512;
+static_assert(PLAN_THREADS >= MAX_WG && PLAN_THREADS >= ASPD_MAX_BATCH, "a thread per workgroup and per sequence");
 
 struct PlanArgs {
   const int32_t* stage_base;
@@ -171,11 +177,11 @@ __device__ Item locate(const PlanArgs& a, const Sched& sc, int pad, int u, Group
   const Groups g = groups_of(a, sc, lo);
   const int per_head = g.before(g.n, pad);
   int rel = u - sc.cu_units[lo];
-  it.h = rel / per_head;      // row groups of one KV head are neighbours: they read the same pages
+  it.h = quotient(rel, per_head);  // row groups of one KV head are neighbours: they read the same pages
   rel -= it.h * per_head;
   int rg = 0;
   if (g.step == 0) {
-    if (g.n > 1) rg = rel / (g.np + pad);
+    if (g.n > 1) rg = quotient(rel, g.np + pad);
   } else {
     int hi_rg = g.n - 1;  // the last group that starts at or before rel
     while (rg < hi_rg) {
@@ -193,7 +199,7 @@ __device__ Item locate(const PlanArgs& a, const Sched& sc, int pad, int u, Group
 
 // The item after `it`; there has to be one.  (The kernel is one workgroup whose threads each walk a workgroup's share, so
 // what a step of the walk takes adds up: with a look-up of every item, three divisions and two searches, the plan of a
-// 64-sequence chunk took 38.0 us, 28.0 now; of eight prompts 21.7 -> 15.4, of 64 decoding sequences 22.0 -> 18.9.)
+// 64-sequence chunk took 38.0 us, 28.0 without; of eight prompts 21.7 -> 15.4, of 64 decoding sequences 22.0 -> 18.9.)
 __device__ __forceinline__ void advance(const PlanArgs& a, const Sched& sc, int pad, Item* it, Groups* g) {
   it->first_unit += it->np + pad;
   int rg = it->rg + 1;
@@ -212,19 +218,12 @@ __device__ __forceinline__ void advance(const PlanArgs& a, const Sched& sc, int 
 // Cutting one item among its k workgroups (even regime).  A page of the branch region costs a wave
 // more than a page before it (owner tags, masking, scores that are thrown away): measured between 1.1
 // and 1.5 times, taken as 1.25.  The cut is therefore even in cost(p) = 4p + max(0, p - lp) rather than
-// in pages: piece j starts at the first page p with cost(p) * k >= j * cost(np), and page p belongs to
-// piece cost(p) * k / cost(np).
+// in pages: piece j starts at the first page p with cost(p) * k >= j * cost(np).
 __device__ __forceinline__ int item_cut(const Item& it, int j, int k) {
   const int total = 4 * it.np + (it.np - it.lp);
-  const int t = (int)(((unsigned)j * (unsigned)total + (unsigned)k - 1u) / (unsigned)k);
+  const int t = quotient(j * total + k - 1, k);
   return t <= 4 * it.lp ? (t + 3) >> 2 : it.lp + (t - 4 * it.lp + 4) / 5;
 }
-__device__ __forceinline__ int item_piece(const Item& it, int page, int k) {
-  const int total = 4 * it.np + (it.np - it.lp);
-  const int cost = 4 * page + max(0, page - it.lp);
-  return min(k - 1, (int)((unsigned)cost * (unsigned)k / (unsigned)total));
-}
-
 __device__ int share_begin(const PlanArgs& a, const Sched& sc, const Shares& sh, int w) {
   if (w <= 0) return 0;
   if (w >= sh.n) return sh.total;
@@ -251,11 +250,12 @@ __device__ __forceinline__ int even_pieces(int np, int w, int p, float rp /* 1 /
 }
 // Workgroups for one KV head of a sequence: n - 1 full row groups and a last one.
 __device__ __forceinline__ int even_per_head(const PlanArgs& a, int np, int n, int nq_last, int p, float rp) {
-  return (n - 1) * even_pieces(np, page_cost(a, a.qpg), p, rp) + even_pieces(np, page_cost(a, nq_last), p, rp);
+  const int last = even_pieces(np, page_cost(a, nq_last), p, rp);
+  return n > 1 ? (n - 1) * even_pieces(np, page_cost(a, a.qpg), p, rp) + last : last;
 }
 
 // Fills the LDS tables and returns the shares.  All threads of the workgroup call it.
-__device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratch /* 5 * PLAN_THREADS / 64 + 2 ints */) {
+__device__ __forceinline__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratch /* 5 * PLAN_THREADS / 64 + 2 ints */) {
   constexpr int PER = (ASPD_MAX_BATCH + PLAN_THREADS - 1) / PLAN_THREADS;  // sequences per thread
   constexpr int NWV = PLAN_THREADS / 64;
   const int tid = threadIdx.x;
@@ -263,7 +263,7 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
   int sum_p = 0, sum_i = 0;
   int longest = 0;       // cost of the costliest item in the even regime (all pages of its sequence)
   int longest_q = 0;     // ... and whole (its row group's pages)
-  long cost = 0;         // of all items, whole
+  unsigned cost16 = 0;   // of all items, whole, in units of 16 (less than 2^32 of them)
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int s = tid * PER + j;
@@ -277,7 +277,7 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
       sc.L[s] = a.stage_base[s];
       sc.q0[s] = q0;
       if (s == a.B - 1) sc.q0[a.B] = q1;
-      const Groups g = groups_at(a, T, q1 - q0, (rows_between(a, q0, q1) + a.qpg - 1) / a.qpg);
+      const Groups g = groups_at(a, T, q1 - q0, quotient(rows_between(a, q0, q1) + a.qpg - 1, a.qpg));
       sc.ng[s] = g.n;
       const int np = g.np;
       if (np > 0 && g.n > 0) {
@@ -286,7 +286,7 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
         const int w_full = page_cost(a, a.qpg), w_last = page_cost(a, last_group(a, q1 - q0, g.n));
         longest = max(longest, np * (g.n > 1 ? w_full : w_last));
         longest_q = max(longest_q, max(g.n > 1 ? g.pages(g.n - 2) * w_full : 0, np * w_last));
-        cost += (long)(g.before(g.n - 1, 0) * (long)w_full + (long)np * w_last) * a.num_kv_heads;
+        cost16 += (unsigned)(((long)g.before(g.n - 1, 0) * w_full + (long)np * w_last) * a.num_kv_heads >> 4);
       }
       // (for the search below; the table is filled in for good later)
       sc.wgb[s] = mine_i[j] > 0 ? np : 0;
@@ -294,37 +294,26 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
     sum_p += mine_p[j];
     sum_i += mine_i[j];
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    longest = max(longest, __shfl_xor(longest, off));
-    longest_q = max(longest_q, __shfl_xor(longest_q, off));
-    cost += __shfl_xor(cost, off);
-  }
-  // scans: inside the wave by shuffles, across the waves through LDS (one barrier)
-  int incl_p = sum_p, incl_i = sum_i;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int vp = __shfl_up(incl_p, off);
-    const int vi = __shfl_up(incl_i, off);
-    if ((tid & 63) >= off) {
-      incl_p += vp;
-      incl_i += vi;
-    }
-  }
+  // scans: inside the wave without LDS, across the waves through LDS (one barrier)
+  const int incl_p = wave_scan_add(sum_p), incl_i = wave_scan_add(sum_i);
+  longest = wave_scan_max(longest);
+  longest_q = wave_scan_max(longest_q);
+  cost16 = (unsigned)wave_scan_add((int)cost16);
   if ((tid & 63) == 63) {
     scratch[tid >> 6] = incl_p;
     scratch[NWV + (tid >> 6)] = incl_i;
     scratch[2 * NWV + (tid >> 6)] = longest;
     scratch[3 * NWV + (tid >> 6)] = longest_q;
-    ((unsigned*)scratch)[4 * NWV + (tid >> 6)] = (unsigned)(cost >> 4);  // (16 cost units: less than 2^32 of them)
+    ((unsigned*)scratch)[4 * NWV + (tid >> 6)] = cost16;
   }
   __syncthreads();
   int run_p = incl_p - sum_p, run_i = incl_i - sum_i;  // exclusive within the wave
   int pages = 0, items = 0;
   longest = longest_q = 0;
-  cost = 0;
-#pragma unroll
-  for (int w = 0; w < NWV; ++w) {
+  long cost = 0;
+  const int used = (a.B + 64 * PER - 1) / (64 * PER);  // waves that hold sequences
+#pragma unroll 1
+  for (int w = 0; w < used; ++w) {
     const int tp = scratch[w], ti = scratch[NWV + w];
     if (w < (tid >> 6)) {
       run_p += tp;
@@ -345,32 +334,43 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
   sh.items = items;
   sh.longest = longest_q;
   const int w_full = page_cost(a, a.qpg);
-  // ---- EVEN regime?  Thread t tries piece cost p_t; the smallest that fits the grid wins.
-  int* best = scratch + 5 * NWV;  // [2]: smallest piece cost that fits; workgroups it takes
-  if (tid == 0) best[0] = 0x7fffffff;
+  // ---- EVEN regime?  The smallest of 1 024 piece costs whose pieces fit the grid.  Fewer pieces come of a larger cost, so
+  // it is found in two rounds of 32 candidates each: the first tries the largest cost of every 32, the second those of the
+  // 32 that hold the answer.  16 threads share a candidate, each with its part of the sequences.  (All candidates in one
+  // round, every thread with all sequences: the step of 27 mixed sequences took 7 us longer.)
+  constexpr int CANDIDATES = 32;
+  constexpr int SHARE = PLAN_THREADS / CANDIDATES;
+  int* best = scratch + 5 * NWV;  // [2]: per round, the first candidate that fits
+  if (tid < 2) best[tid] = 0x7fffffff;
+  const int least = MIN_PAGES_PER_WG * page_cost(a, 1);
+  const int step = max(longest - least, 0) / (CANDIDATES * CANDIDATES) + 1;
+  auto candidate = [&](int t) -> int { return min(max(longest, 1), least + t * step); };
   __syncthreads();
   if (items > 0 && items <= a.nwg) {
-    const int least = MIN_PAGES_PER_WG * page_cost(a, 1);
-    const int span = max(longest - least, 0);
-    const int step = span / PLAN_THREADS + 1;
-    const int p = min(max(longest, 1), least + tid * step);
-    const float rp = __builtin_amdgcn_rcpf((float)p);
-    long need = 0;
-    for (int s = 0; s < a.B; ++s)
-      if (sc.wgb[s] > 0)
-        need += (long)a.num_kv_heads *
-                even_per_head(a, sc.wgb[s], sc.ng[s], last_group(a, sc.q0[s + 1] - sc.q0[s], sc.ng[s]), p, rp);
-    int mine = need <= a.nwg ? p : 0x7fffffff;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mine = min(mine, __shfl_xor(mine, off));
-    if ((tid & 63) == 0 && mine != 0x7fffffff) atomicMin(best, mine);
+#pragma unroll 1
+    for (int round = 0; round < 2; ++round) {
+      const int t = round == 0 ? (tid / SHARE + 1) * CANDIDATES - 1 : best[0] - (CANDIDATES - 1) + tid / SHARE;
+      if (round == 1 && best[0] == 0x7fffffff) break;
+      const int p = candidate(t);
+      const float rp = __builtin_amdgcn_rcpf((float)p);
+      int need = 0;  // (at most items * pages / MIN_PAGES_PER_WG, with no more items than workgroups)
+#pragma unroll 1
+      for (int s = tid % SHARE; s < a.B; s += SHARE)
+        if (sc.wgb[s] > 0)
+          need += a.num_kv_heads *
+                  even_per_head(a, sc.wgb[s], sc.ng[s], last_group(a, sc.q0[s + 1] - sc.q0[s], sc.ng[s]), p, rp);
+      static_assert(SHARE == 16, "a row of lanes");
+      need = row_scan_add(need);
+      if (tid % SHARE == SHARE - 1 && need <= a.nwg) atomicMin(best + round, t);
+      __syncthreads();
+    }
   }
-  __syncthreads();
-  if (best[0] != 0x7fffffff) {
+  if (best[1] != 0x7fffffff) {
     // pieces of this cost against what the ragged regime's longest workgroups would carry (a share and two
     // segment starts)
-    sh.piece = best[0];
-    sh.even = (long)sh.piece + a.pad * w_full <= (a.w_wave ? cost : (long)pages) / a.nwg + 2L * a.pad * w_full;
+    sh.piece = candidate(best[1]);
+    // (x <= y / n for whole numbers as x n <= y: 64-bit divisions took longer than the whole search)
+    sh.even = ((long)sh.piece - a.pad * w_full) * a.nwg <= (a.w_wave ? cost : (long)pages);
   }
   __syncthreads();  // (best is read by all before anyone reuses scratch)
   if (sh.even) {
@@ -386,17 +386,12 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
                                                    sh.piece, __builtin_amdgcn_rcpf((float)sh.piece));
       sum_w += mine_w[j];
     }
-    int incl_w = sum_w;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int v = __shfl_up(incl_w, off);
-      if ((tid & 63) >= off) incl_w += v;
-    }
+    const int incl_w = wave_scan_add(sum_w);
     if ((tid & 63) == 63) scratch[tid >> 6] = incl_w;
     __syncthreads();
     int run_w = incl_w - sum_w, total_w = 0;
-#pragma unroll
-    for (int w = 0; w < NWV; ++w) {
+#pragma unroll 1
+    for (int w = 0; w < used; ++w) {
       if (w < (tid >> 6)) run_w += scratch[w];
       total_w += scratch[w];
     }
@@ -415,7 +410,7 @@ __device__ Shares build_schedule(const PlanArgs& a, const Sched& sc, int* scratc
     return sh;
   }
   // ---- QUEUE regime?
-  if (a.queue && items > a.nwg && 4L * sh.longest <= 5L * cost / a.nwg) {
+  if (a.queue && items > a.nwg && 4L * sh.longest * a.nwg <= 5L * cost) {
     sh.queue = true;
     sh.n = a.nwg;
     // cu_units[s]: row groups of the sequences before s
@@ -484,9 +479,9 @@ __device__ bool even_share(const PlanArgs& a, const Sched& sc, const Shares& sh,
   const int k_last = even_pieces(it.np, page_cost(a, last_group(a, rows, ngroups)), sh.piece, rp);
   const int per_head = (ngroups - 1) * k_full + k_last;
   const int local = w - sc.cu_units[lo];
-  it.h = local / per_head;    // row groups of one KV head are neighbours: they read the same pages
+  it.h = quotient(local, per_head);    // row groups of one KV head are neighbours: they read the same pages
   const int in_head = local - it.h * per_head;
-  it.rg = min(in_head / k_full, ngroups - 1);
+  it.rg = min(quotient(in_head, k_full), ngroups - 1);
   const int j = in_head - it.rg * k_full;
   const int k = it.rg == ngroups - 1 ? k_last : k_full;
   it.first_unit = 0;
@@ -574,8 +569,8 @@ constexpr int QUEUE_BINS = 1024;
 __device__ void write_queue(const PlanArgs& a, const Sched& sc, const Shares& sh, int* bins /* QUEUE_BINS */) {
   const int tid = threadIdx.x;
   const int groups = sc.cu_units[a.B];
-  static_assert(QUEUE_BINS == PLAN_THREADS, "a thread per bin");
-  bins[tid] = 0;
+  static_assert(QUEUE_BINS == 2 * PLAN_THREADS, "two bins per thread");
+  bins[2 * tid] = bins[2 * tid + 1] = 0;
   __syncthreads();
   const float scale = (float)(QUEUE_BINS - 1) / (float)sh.longest;
   auto group_at = [&](int e, int* s_out, int* rg_out, Groups* g) -> int {  // row group e; its bin
@@ -596,19 +591,15 @@ __device__ void write_queue(const PlanArgs& a, const Sched& sc, const Shares& sh
   for (int e = tid; e < groups; e += PLAN_THREADS) atomicAdd(&bins[group_at(e, &s, &rg, &g)], 1);
   __syncthreads();
   // exclusive scan of the bins
-  const int mine = bins[tid];
-  int incl = mine;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int v = __shfl_up(incl, off);
-    if ((tid & 63) >= off) incl += v;
-  }
+  const int mine0 = bins[2 * tid], mine = mine0 + bins[2 * tid + 1];
+  const int incl = wave_scan_add(mine);
   __shared__ int tot[PLAN_THREADS / 64];
   if ((tid & 63) == 63) tot[tid >> 6] = incl;
   __syncthreads();
   int run = incl - mine;
   for (int w = 0; w < (tid >> 6); ++w) run += tot[w];
-  bins[tid] = run;
+  bins[2 * tid] = run;
+  bins[2 * tid + 1] = run + mine0;
   __syncthreads();
   const int extra = sh.items - a.nwg, each = extra / a.nwg, rest = extra - each * a.nwg;
   int32_t* list = a.plan + PLAN_HDR * a.nwg;
@@ -618,71 +609,35 @@ __device__ void write_queue(const PlanArgs& a, const Sched& sc, const Shares& sh
     const int q0 = sc.q0[s] + rg * a.qpg, np = g.pages(rg), nq = min(a.qpg, sc.q0[s + 1] - q0);
     int ids[PLAN_IDS];
     if (rank < a.nwg) load_ids(a, s, 0, np, ids);
+    int turn = quotient(rank, a.nwg), w = rank - turn * a.nwg;
     for (int h = 0; h < a.num_kv_heads; ++h) {
-      const int r = rank + h, w = r % a.nwg, next = w * each + min(w, rest);
-      int32_t* d = r < a.nwg ? a.plan + PLAN_HDR * w : list + PLAN_SEG * (next + r / a.nwg - 1);
+      const int next = w * each + min(w, rest);
+      int32_t* d = turn == 0 ? a.plan + PLAN_HDR * w : list + PLAN_SEG * (next + turn - 1);
       *(i32x4*)d = i32x4{s | (h << 16), q0, nq, 0};
       *(i32x4*)(d + 4) = i32x4{np, np, w | (w << 16), sc.L[s]};
-      if (r < a.nwg) {
+      if (turn == 0) {
         d[PLAN_HDR_NSEG] = 1 + each + (w < rest ? 1 : 0);
         d[PLAN_HDR_NEXT] = next;
         d[PLAN_HDR_QUEUE] = extra;
         store_ids(d, ids);
       }
+      if (++w == a.nwg) {
+        w = 0;
+        ++turn;
+      }
     }
   }
 }
 
-__global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(PlanArgs a) {
-  extern __shared__ int lds[];
-  __shared__ int scratch[5 * PLAN_THREADS / 64 + 2];
-  __shared__ int wave_tot[PLAN_THREADS / 64];
-  const Sched sc = sched_at(lds, a.B);
-  int* seg_cache = lds + sched_ints(a.B);
-  const int CS = plan_cached_segments(a.nwg);
-  const int tid = threadIdx.x;
-  const Shares sh = build_schedule(a, sc, scratch);
-  if (sh.queue) {
-    write_queue(a, sc, sh, seg_cache);
-    return;
-  }
+// LDS of the plan behind the tables of the schedule.
+__host__ __device__ constexpr int plan_work_ints(int nwg) {
+  const int cached = nwg * plan_cached_segments(nwg) * PLAN_SEG;
+  return cached > QUEUE_BINS ? cached : QUEUE_BINS;
+}
 
-  // ---- pass 1: the segments of each workgroup (thread w: workgroup w); the first few are kept in LDS
-  static_assert(PLAN_THREADS >= MAX_WG, "a thread per workgroup");
-  const int w = tid;
-  int cnt = 0;
-  Walk resume;  // where the walk stood after the cached segments
-  if (w < a.nwg) {
-    Walk wk = walk_begin(a, sc, sh, w);
-    resume = wk;
-    Item it;
-    int p0, p1, owner, w_last;
-    while (cnt < CS && walk_next(a, sc, sh, w, &wk, &it, &p0, &p1, &owner, &w_last)) {
-      int* c = seg_cache + (w * CS + cnt) * PLAN_SEG;
-      *(i32x4*)c = i32x4{it.s | (it.h << 16), it.q0, it.nq, p0};
-      *(i32x4*)(c + 4) = i32x4{p1, it.np, owner | (w_last << 16), sc.L[it.s]};
-      ++cnt;
-    }
-    resume = wk;
-    // the rest is only counted here (most of a step of the walk is then dead code)
-    if (cnt == CS)
-      while (walk_next(a, sc, sh, w, &wk, &it, &p0, &p1, &owner, &w_last)) ++cnt;
-  }
-  // exclusive scan, over the workgroups, of the segments beyond the first
-  const int extra = max(cnt - 1, 0);
-  int incl = extra;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int v = __shfl_up(incl, off);
-    if ((tid & 63) >= off) incl += v;
-  }
-  if ((tid & 63) == 63) wave_tot[tid >> 6] = incl;
-  __syncthreads();
-  int run = incl - extra;
-  for (int wv = 0; wv < (tid >> 6); ++wv) run += wave_tot[wv];
-
-  // ---- pass 2: headers and segments
-  if (w >= a.nwg) return;
+// Pass 2: header and segments of workgroup w (`cnt` of them, those beyond the first from place `run` of the list on).
+__device__ __forceinline__ void plan_write(const PlanArgs& a, const Sched& sc, const Shares& sh, int w, int cnt, int run,
+                                           int CS, const int* seg_cache, const Walk& resume) {
   int32_t* seg_list = a.plan + PLAN_HDR * a.nwg;
   int32_t* hdr = a.plan + PLAN_HDR * w;
   hdr[PLAN_HDR_NSEG] = cnt;
@@ -713,6 +668,54 @@ __global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(PlanArgs a) {
       ++i;
     }
   }
+}
+
+__global__ __launch_bounds__(PLAN_THREADS) void plan_kernel(PlanArgs a) {
+  extern __shared__ int lds[];
+  __shared__ int scratch[5 * PLAN_THREADS / 64 + 2];
+  __shared__ int wave_tot[PLAN_THREADS / 64];
+  const Sched sc = sched_at(lds, a.B);
+  int* seg_cache = lds + sched_ints(a.B);
+  const int CS = plan_cached_segments(a.nwg);
+  const int tid = threadIdx.x;
+  const Shares sh = build_schedule(a, sc, scratch);
+  if (sh.queue) {
+    write_queue(a, sc, sh, seg_cache);
+    return;
+  }
+
+  // ---- pass 1: the segments of each workgroup (thread w: workgroup w); the first few are kept in LDS
+  const int w = tid;
+  int cnt = 0;
+  Walk resume;  // where the walk stood after the cached segments
+  if (w < a.nwg) {
+    Walk wk = walk_begin(a, sc, sh, w);
+    resume = wk;
+    Item it;
+    int p0, p1, owner, w_last;
+    while (cnt < CS && walk_next(a, sc, sh, w, &wk, &it, &p0, &p1, &owner, &w_last)) {
+      int* c = seg_cache + (w * CS + cnt) * PLAN_SEG;
+      *(i32x4*)c = i32x4{it.s | (it.h << 16), it.q0, it.nq, p0};
+      *(i32x4*)(c + 4) = i32x4{p1, it.np, owner | (w_last << 16), sc.L[it.s]};
+      ++cnt;
+    }
+    resume = wk;
+    // the rest is only counted here (most of a step of the walk is then dead code)
+    if (cnt == CS)
+      while (walk_next(a, sc, sh, w, &wk, &it, &p0, &p1, &owner, &w_last)) ++cnt;
+  }
+  // exclusive scan, over the workgroups, of the segments beyond the first
+  int run = 0;
+  if (!sh.even) {  // (a segment each there)
+    const int extra = max(cnt - 1, 0);
+    const int incl = wave_scan_add(extra);
+    if ((tid & 63) == 63) wave_tot[tid >> 6] = incl;
+    __syncthreads();
+    run = incl - extra;
+    for (int wv = 0; wv < (tid >> 6); ++wv) run += wave_tot[wv];
+  }
+
+  if (w < a.nwg) plan_write(a, sc, sh, w, cnt, run, CS, seg_cache, resume);
 }
 
 std::atomic<int> g_cu_count[64];
@@ -813,7 +816,7 @@ int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t
   a.rows_per_query = kv->num_q_heads / kv->num_kv_heads;
   a.NQ = NQ;
   a.max_items = (int)((B + (long)NQ / v.qpg) * kv->num_kv_heads);
-  const size_t lds = (size_t)(sched_ints(B) + std::max(v.nwg * plan_cached_segments(v.nwg) * PLAN_SEG, QUEUE_BINS)) * sizeof(int);
+  const size_t lds = (size_t)(sched_ints(B) + plan_work_ints(v.nwg)) * sizeof(int);
   hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(PLAN_THREADS), lds, stream, a);
   ASPD_HIP_CHECK(hipGetLastError());
   return ASPD_OK;

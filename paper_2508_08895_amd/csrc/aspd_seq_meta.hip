@@ -3,12 +3,17 @@
 // Eq. 4 for the position ids, Eq. 2-3 for what a token sees), for teacher-forced passes and for the
 // re-prefill of a cache (Sec. 4.5.3, "Same-Re").
 //
-// Pure integer work.  One workgroup per sequence: one thread walks the sequence's runs in order (a
+// Pure integer work.  One or more workgroups per sequence: one thread walks the sequence's runs in order (a
 // few hundred at most: the walk carries the stage bookkeeping, which is inherently sequential) and
 // tabulates, per run, its first slot, the position of its first token, the first slot of its stage
 // and its branch number; then all threads emit the tokens, finding a token's run by binary search.
+// The workgroups of a sequence (gridDim.y) all walk it and share its tokens: nothing that is written here is read
+// here, and a token costs its thread three waits for memory, so that with one workgroup the longest sequence
+// decided.
 // A second, one-workgroup kernel lists the row groups of the attention launch, longest key range
 // first, behind the per-row stage bases in the step's plan buffer.
+#include <algorithm>
+
 #include "aspd_plan.h"
 
 namespace {
@@ -42,9 +47,15 @@ __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView 
   // packed row of this sequence's first token: the tokens of all earlier sequences
   int part = 0;
   for (int i = tid; i < r0; i += SEQ_META_THREADS) part += max(lay.run_len[i], 0);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
-  if ((tid & 63) == 0) red[tid >> 6] = part;
+  part = wave_scan_add(part);
+  if ((tid & 63) == 63) red[tid >> 6] = part;
+  // The runs as the layout gives them, for the walk below, which would otherwise wait for memory at every one of them
+  // (its own words of a run take their place).
+  if (nr >= 0 && nr <= ASPD_MAX_RUNS_PER_SEQ)
+    for (int i = tid; i < nr; i += SEQ_META_THREADS) {
+      run_base[i] = lay.run_branch[r0 + i];
+      run_pos0[i] = lay.run_len[r0 + i];
+    }
   __syncthreads();
   int base = 0;
 #pragma unroll
@@ -63,8 +74,8 @@ __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView 
       faults |= ASPD_FAULT_LAYOUT;
     }
     for (int i = 0; ok && i < nr; ++i) {
-      const int b = lay.run_branch[r0 + i];
-      const int n = lay.run_len[r0 + i];
+      const int b = run_base[i];
+      const int n = run_pos0[i];
       if (n < 0 || b < 0 || b > ASPD_MAX_BRANCHES_PER_SEQ || (b > 1 && b != prev + 1)) {
         ok = 0;
         faults |= (b > ASPD_MAX_BRANCHES_PER_SEQ) ? ASPD_FAULT_BRANCHES : ASPD_FAULT_LAYOUT;
@@ -115,20 +126,22 @@ __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView 
       faults |= ASPD_FAULT_ROW_COUNT;  // the sequence's rows are missing from the step
     }
     if (ok) run_slot0[nr] = slot;
-    if (faults) seq_raise_fault(st.fault, faults);
     sh_ok = ok;
-    // state: as after a merge of the last stage
-    st.seq_len[s] = slot;
-    st.stage_base[s] = slot;
-    if (st.main_pos) st.main_pos[s] = main_pos;
-    if (st.stage_open) st.stage_open[s] = 0;
-    sp.cu_seq_new[s] = base;
-    if (s == st.B - 1) sp.cu_seq_new[st.B] = base + slot;
+    if (blockIdx.y == 0) {
+      if (faults) seq_raise_fault(st.fault, faults);
+      // state: as after a merge of the last stage
+      st.seq_len[s] = slot;
+      st.stage_base[s] = slot;
+      if (st.main_pos) st.main_pos[s] = main_pos;
+      if (st.stage_open) st.stage_open[s] = 0;
+      sp.cu_seq_new[s] = base;
+      if (s == st.B - 1) sp.cu_seq_new[st.B] = base + slot;
+    }
   }
   __syncthreads();
   if (!sh_ok) return;
   const int T = run_slot0[nr];
-  for (int j = tid; j < T; j += SEQ_META_THREADS) {
+  for (int j = blockIdx.y * SEQ_META_THREADS + tid; j < T; j += gridDim.y * SEQ_META_THREADS) {
     // the run that holds slot j: the last one whose first slot is <= j and that is not empty
     int lo = 0, hi = nr - 1;
     while (lo < hi) {
@@ -159,22 +172,31 @@ __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView 
 // take groups from the list as they become free, and the list starts with the longest ranges so that
 // the launch does not end on a long one: round t lists, for every sequence that has that many, its
 // t-th group from the end.
-__global__ __launch_bounds__(1024) void sequence_worklist_kernel(const int32_t* __restrict__ cu_seq_new,
+constexpr int WORKLIST_THREADS = 1024;
+__global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(const int32_t* __restrict__ cu_seq_new,
                                                                  const int32_t* __restrict__ seq_len, int B, int NQ,
                                                                  int qpg, int max_items, int32_t* __restrict__ plan) {
   __shared__ int ngr[ASPD_MAX_BATCH];
   __shared__ int first_item[ASPD_MAX_BATCH + 1];
+  __shared__ int wave_tot[WORKLIST_THREADS / 64];
   const int tid = threadIdx.x;
   // (a sequence that was refused holds no token: seq_len, which the kernel before this one wrote, says so,
   // while the packed rows the layout gave it stay where they are, unwritten)
-  for (int s = tid; s < B; s += blockDim.x) ngr[s] = (max(seq_len[s], 0) + qpg - 1) / qpg;
+  static_assert(ASPD_MAX_BATCH <= WORKLIST_THREADS, "a thread per sequence");
+  const int mine = tid < B ? (max(seq_len[tid], 0) + qpg - 1) / qpg : 0;
+  const int incl = wave_scan_add(mine);
+  if ((tid & 63) == 63) wave_tot[tid >> 6] = incl;
   __syncthreads();
+  int first = incl - mine, acc = 0;
+  for (int w = 0; w < (B + 63) >> 6; ++w) {
+    if (w < (tid >> 6)) first += wave_tot[w];
+    acc += wave_tot[w];
+  }
+  if (tid < B) {
+    ngr[tid] = mine;
+    first_item[tid] = first;
+  }
   if (tid == 0) {
-    int acc = 0;
-    for (int s = 0; s < B; ++s) {
-      first_item[s] = acc;
-      acc += ngr[s];
-    }
     first_item[B] = min(acc, max_items);
     plan[0] = first_item[B];
     plan[1] = qpg;
@@ -249,12 +271,15 @@ extern "C" int aspd_build_sequence_meta(const aspd_kv* kv, aspd_state* state, co
   hipStream_t hs = (hipStream_t)stream;
   const int qpg = aspd_sequence_qpg(G);
   LayoutView lay{layout->cu_runs_d, layout->run_branch_d, layout->run_len_d};
-  hipLaunchKernelGGL(meta_sequence_kernel, dim3(state->B), dim3(SEQ_META_THREADS), 0, hs, make_view(kv), make_view(state),
+  // two tokens a thread where the sequences are alike; no more workgroups than eight a compute unit
+  const int share = (int)std::max(1L, std::min({((long)out->NQ / state->B + 2 * SEQ_META_THREADS - 1) / (2 * SEQ_META_THREADS),
+                                                8L * aspd_device_cu_count() / state->B + 1, 32L}));
+  hipLaunchKernelGGL(meta_sequence_kernel, dim3(state->B, share), dim3(SEQ_META_THREADS), 0, hs, make_view(kv), make_view(state),
                      make_view(out), lay, out->plan_d + SEQ_PLAN_HDR,
                      out->plan_d + aspd_sequence_plan_lo(G, state->B, out->NQ), mode == ASPD_POS_SAME_SEQ, mode == ASPD_POS_SAME_MAX, fix_n);
   ASPD_HIP_CHECK(hipGetLastError());
   const int max_items = state->B + out->NQ / qpg;
-  hipLaunchKernelGGL(sequence_worklist_kernel, dim3(1), dim3(1024), 0, hs, out->cu_seq_new_d, state->seq_len_d, state->B,
+  hipLaunchKernelGGL(sequence_worklist_kernel, dim3(1), dim3(WORKLIST_THREADS), 0, hs, out->cu_seq_new_d, state->seq_len_d, state->B,
                      out->NQ, qpg, max_items, out->plan_d);
   ASPD_HIP_CHECK(hipGetLastError());
   out->plan_key = aspd_sequence_plan_key(qpg, state->B);

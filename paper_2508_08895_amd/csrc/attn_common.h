@@ -12,8 +12,8 @@ constexpr int THREADS = NW * 64;
 // the one it computes, 64 KB per compute unit.
 constexpr int STREAM_NW = 8;
 constexpr int ROWS_PPS = 2;           // pairs of pages it stages (and computes) between two barriers
-constexpr int COUNTER_BYTES = 4096;   // MAX_WG arrival counters at the head of the workspace
-static_assert(COUNTER_BYTES == MAX_WG * 4, "workspace head");
+constexpr int COUNTER_BYTES = 4096;   // arrival counters and the queue's words at the head of the workspace
+static_assert(COUNTER_BYTES >= MAX_WG * 4 && COUNTER_BYTES > QUEUE_DONE * 4, "workspace head");
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 

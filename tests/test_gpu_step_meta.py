@@ -1,4 +1,5 @@
-"""The metadata call on steps that it refuses in part: the plan stays inside its buffer and names rows of the step only."""
+"""The metadata calls and the plan where they can go wrong: steps that are refused in part (the plan stays inside its buffer
+and names rows of the step only), batches over several waves of the plan, sequences over several workgroups."""
 import numpy as np
 import pytest
 import torch
@@ -56,3 +57,71 @@ def test_plan_of_a_refused_step_stays_in_its_buffer(B, hint, kind):
         segs += [plan[32 * nwg + 8 * (at + i):32 * nwg + 8 * (at + i + 1)] for i in range(n - 1)]
         for d in segs:
             assert 0 <= d[1] and 1 <= d[2] and d[1] + d[2] <= rows, (w, d)
+
+
+@pytest.mark.parametrize("B,blocks", [(65, 3), (100, 9), (128, 40), (512, 6)])   # sequences in two to eight waves
+@pytest.mark.parametrize("new", [1, 90])                                         # streaming, row-splitting kernel
+def test_plan_of_large_batches_covers_every_page(B, blocks, new):
+    """Even pieces, shares and queue, as the batch and its lengths select them."""
+    rng = np.random.default_rng(B + new)
+    kv, st = _batch(B, np.ones(B, dtype=int), blocks + 8)
+    have = rng.integers(0, 16 * blocks, B).astype(np.int32)
+    have[rng.integers(B)] = 16 * blocks
+    st.stage_base.copy_(torch.from_numpy(have))
+    st.seq_len.copy_(torch.from_numpy(have))
+    lens = rng.integers(0, new + 1, B).astype(np.int32)
+    lens[0] = new
+    step = A.aspd_build_branch_meta(kv, st, A.STAGE_SERIAL, torch.from_numpy(lens).cuda(), NQ=int(lens.sum()),
+                                    max_new_per_seq=new)
+    assert int(st.fault[0]) == 0
+    plan, nwg, qpg = step.plan.cpu().numpy().view(np.int32), step.plan_key >> 27 & 2047, step.plan_key >> 18 & 511
+    first = np.append(0, np.cumsum(lens))
+    total = have + lens
+    read = {}   # (sequence, head, first row): how often each page is read
+    for w in range(nwg):
+        n, at = plan[32 * w + 8], plan[32 * w + 9]
+        segs = [plan[32 * w:32 * w + 8]] if n > 0 else []
+        segs += [plan[32 * nwg + 8 * (at + i):32 * nwg + 8 * (at + i + 1)] for i in range(n - 1)]
+        for d in segs:
+            s, h = int(d[0]) & 0xffff, int(d[0]) >> 16
+            assert first[s] <= d[1] and d[1] + d[2] <= first[s + 1] and (d[1] - first[s]) % qpg == 0
+            assert 0 <= d[3] < d[4] <= d[5] and d[7] == total[s]
+            # no row of the group sees past its last slot; a plan may say more pages, up to the sequence's
+            last = have[s] + d[1] - first[s] + d[2] - 1
+            assert last // 16 + 1 <= d[5] <= (total[s] + 15) // 16
+            pages = read.setdefault((s, h, int(d[1])), np.zeros(d[5], dtype=int))
+            assert len(pages) == d[5]
+            pages[d[3]:d[4]] += 1
+    assert all((p == 1).all() for p in read.values())
+    assert set(read) == {(s, h, q) for s in range(B) for h in range(2) for q in range(first[s], first[s + 1], qpg)}
+
+
+@pytest.mark.parametrize("lengths", [[9001], [1, 513, 0, 2300], [300] * 70, [40, 0, 7] * 60])
+def test_metadata_of_whole_sequences_that_workgroups_share(lengths):
+    """One to sixteen workgroups per sequence, sequences in one to three waves of the row groups' list."""
+    from oracle.sequence_layout import replay_layout
+    rng = np.random.default_rng(len(lengths))
+    blocks = max(lengths) // 16 + 1
+    layouts = []
+    for n in lengths:
+        cut = np.sort(rng.integers(0, n + 1, 4))
+        part = np.diff(np.concatenate([[0], cut, [n]])).tolist()
+        layouts.append([(0, part[0]), (1, part[1]), (2, part[2]), (0, part[3]), (1, part[4])])
+    B = len(lengths)
+    kv, st = _batch(B, np.ones(B, dtype=int), blocks)
+    tt, meta = replay_layout(kv.block_tables.cpu().numpy(), 16, layouts)
+    dev = [torch.from_numpy(np.asarray(x, dtype=np.int32)).cuda() for x in
+           (np.cumsum([0] + [5] * B), [b for r in layouts for b, _ in r], [n for r in layouts for _, n in r])]
+    step = A.aspd_build_sequence_meta(kv, st, *dev, NQ=sum(lengths))
+    assert int(st.fault[0]) == 0 and st.seq_len.cpu().tolist() == lengths
+    assert np.array_equal(step.cu_seq_new.cpu().numpy(), np.append(0, np.cumsum(lengths)))
+    for f in ("q_seq", "q_branch", "position_ids", "logical_slot", "slot_mapping", "kv_len"):
+        assert np.array_equal(getattr(step, f).cpu().numpy(), getattr(meta, f)), f
+    # the row groups: all rows once
+    plan, rows = step.plan.cpu().numpy().view(np.int32), sum(lengths)
+    items = plan[16 + (rows + 3 & ~3):][:4 * plan[0]].reshape(-1, 4)
+    seen = np.zeros(rows, dtype=int)
+    for s, q0, nq, pages in items.tolist():
+        seen[q0:q0 + nq] += 1
+        assert pages == (q0 + nq - int(step.cu_seq_new[s]) + 15) // 16
+    assert (seen == 1).all()
