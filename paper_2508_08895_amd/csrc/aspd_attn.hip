@@ -122,6 +122,8 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
   a.plan = plan;
   a.row_base = nullptr;
   a.row_lo = nullptr;
+  a.pieces = nullptr;
+  a.parts = 0;
   a.NQ = step->NQ;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)kv->head_dim) : sm_scale) * LOG2E;
   a.B = state->B;
@@ -313,7 +315,12 @@ extern "C" int aspd_attn_full_sequence(const aspd_kv* kv, const aspd_state* stat
   a.out = out_d;
   a.lse = lse_d;
   a.counters = (int*)workspace_d;
-  a.partial = nullptr;
+  // room for the partial results of the longest row groups' pieces, as a workspace of the size this library asks for has
+  a.parts = aspd_sequence_parts(kv, state->B, step->NQ);
+  const size_t parts_bytes = (size_t)2 * a.parts * ROWS_NW * 32 * (kv->head_dim + 4) * sizeof(float);
+  if (workspace_bytes < COUNTER_BYTES + parts_bytes) a.parts = 0;
+  a.partial = (float*)((char*)workspace_d + COUNTER_BYTES);
+  a.pieces = step->plan_d + aspd_sequence_plan_pieces(G, state->B, step->NQ);
   a.plan = step->plan_d;
   a.row_base = step->plan_d + SEQ_PLAN_HDR;
   a.row_lo = step->plan_d + aspd_sequence_plan_lo(G, state->B, step->NQ);
@@ -324,23 +331,28 @@ extern "C" int aspd_attn_full_sequence(const aspd_kv* kv, const aspd_state* stat
   a.inv_G = 1.f / (float)G;
   a.qpg = qpg;
   a.rows_cap = ROWS_NW * 32;
-  // one workgroup per compute unit, never more than there are row groups to take
+  // one workgroup per compute unit, never more than there are row groups or pieces to take
   long nwg = aspd_device_cu_count();
-  nwg = std::min(nwg, ((long)state->B + step->NQ / qpg) * kv->num_kv_heads);
+  const bool pieces = a.parts > 0 && aspd_sequence_may_cut(kv, state->B, step->NQ, qpg, aspd_device_cu_count());
+  nwg = std::min(nwg, ((long)state->B + step->NQ / qpg) * kv->num_kv_heads + (pieces ? a.parts : 0));
   if (step->max_workgroups > 0) nwg = std::min(nwg, (long)step->max_workgroups);
   a.nwg = (int)std::max(1L, nwg);
   hipStream_t hs = (hipStream_t)stream;
+#define ASPD_SEQ_LAUNCH(DD, PIECES)                                                                                      \
+  do {                                                                                                                   \
+    rc = allow_big_lds((const void*)attn_bf16_seq_kernel<DD, ROWS_NW, PIECES>);                                          \
+    if (rc != ASPD_OK) return rc;                                                                                        \
+    hipLaunchKernelGGL((attn_bf16_seq_kernel<DD, ROWS_NW, PIECES>), dim3(a.nwg), dim3(ROWS_NW * 64), (rows_smem_bytes<DD>()), \
+                       hs, a);                                                                                           \
+  } while (0)
   if (kv->head_dim == 128) {
-    rc = allow_big_lds((const void*)attn_bf16_seq_kernel<128, ROWS_NW>);
-    if (rc != ASPD_OK) return rc;
-    hipLaunchKernelGGL((attn_bf16_seq_kernel<128, ROWS_NW>), dim3(a.nwg), dim3(ROWS_NW * 64),
-                       (rows_smem_bytes<128>()), hs, a);
+    if (pieces) ASPD_SEQ_LAUNCH(128, true);
+    else ASPD_SEQ_LAUNCH(128, false);
   } else {
-    rc = allow_big_lds((const void*)attn_bf16_seq_kernel<64, ROWS_NW>);
-    if (rc != ASPD_OK) return rc;
-    hipLaunchKernelGGL((attn_bf16_seq_kernel<64, ROWS_NW>), dim3(a.nwg), dim3(ROWS_NW * 64),
-                       (rows_smem_bytes<64>()), hs, a);
+    if (pieces) ASPD_SEQ_LAUNCH(64, true);
+    else ASPD_SEQ_LAUNCH(64, false);
   }
+#undef ASPD_SEQ_LAUNCH
   ASPD_HIP_CHECK(hipGetLastError());
   return ASPD_OK;
 }

@@ -64,7 +64,6 @@ static inline StepView make_view(const aspd_step* sp) {
 // Host-side validation of the cache descriptor; returns an ASPD_* code.
 int aspd_check_kv(const aspd_kv* kv);
 
-#ifdef __HIP__
 // Inclusive scans over a row of 16 lanes and over the 64 lanes of a wave by data-parallel moves: four and six instructions a
 // value, where shuffles go through LDS, three instructions and a wait each.  The last lane has the result over all
 // of them.  Lanes without a source see 0.
@@ -109,4 +108,3 @@ __device__ __forceinline__ int quotient(int x, int d, float rd) {
   return q;
 }
 __device__ __forceinline__ int quotient(int x, int d) { return quotient(x, d, __builtin_amdgcn_rcpf((float)d)); }
-#endif

@@ -88,14 +88,26 @@ int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t
 
 // ---- The plan of a whole-sequence step (aspd_build_sequence_meta / aspd_attn_full_sequence) -------
 // Layout (32-bit words):
-//   [0, 16)                 header: 0 row groups in the list, 1 tokens per row group, 2 NQ, 3 B
+//   [0, 16)                 header: 0 row groups in the list, 1 tokens per row group, 2 NQ, 3 B, 4 entries in the list of
+//                           pieces (0: no row group is cut)
 //   [16, 16 + NQ4)          per packed row, the first slot of the row's own stage (its own slot for a
 //                           main-branch row); NQ4 = NQ rounded up to a multiple of 4
 //   then 4 words per row group, in the order workgroups take them: sequence, first packed row,
 //                           tokens, pages of its key range
 //   then NQ4 words          per packed row, the first slot of the row's own branch in its stage (its own slot
 //                           for a main-branch row): a row sees [0, stage start) and [this, its own slot]
+//   then 2 words per piece  where the longest row groups' key ranges are cut, in the order workgroups take them: row
+//                           group, piece | pieces << 8 | place of its first head's partial results << 16
 constexpr int SEQ_PLAN_HDR = 16;
+constexpr int SEQ_HDR_PIECES = 4;
+constexpr int SEQ_PIECES_MAX = 8;    // of one row group
+constexpr int SEQ_ENTRIES = 1024;    // room in the list of pieces
+constexpr int SEQ_PIECE_MIN = 24;    // pages of a piece, and how many more the longest row group has at least where any
+constexpr int SEQ_PIECE_GAIN = 48;   // is cut
+// Whether row groups may be cut at all, as far as sizes known on the host say.
+static inline bool aspd_sequence_may_cut(const aspd_kv* kv, int32_t B, int32_t NQ, int qpg, int cus) {
+  return kv->max_blocks_per_seq >= SEQ_PIECE_MIN + SEQ_PIECE_GAIN && ((long)B + NQ / qpg) * kv->num_kv_heads <= 2L * cus;
+}
 // Tokens per row group: what the row-splitting kernel holds per workgroup.
 static inline int aspd_sequence_qpg(int G) { return ROWS_NW * 32 / G; }
 // Identifies such a plan; no value aspd_plan_key returns has bit 62 set.
@@ -108,6 +120,12 @@ static inline size_t aspd_sequence_plan_items(int32_t NQ) { return (size_t)SEQ_P
 static inline size_t aspd_sequence_plan_lo(int G, int32_t B, int32_t NQ) {
   return aspd_sequence_plan_items(NQ) + 4 * ((size_t)B + (size_t)NQ / aspd_sequence_qpg(G));
 }
+
+static inline size_t aspd_sequence_plan_pieces(int G, int32_t B, int32_t NQ) {
+  return aspd_sequence_plan_lo(G, B, NQ) + (((size_t)NQ + 3) & ~(size_t)3);
+}
+// Pieces (over all heads) that a workspace of aspd_workspace_bytes has room for the partial results of, two slots each.
+int aspd_sequence_parts(const aspd_kv* kv, int32_t B, int32_t NQ);
 
 // Compute units of the current device (256 when there is none to ask, as on a build host).
 int aspd_device_cu_count();

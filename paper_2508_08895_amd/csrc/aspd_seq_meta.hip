@@ -175,20 +175,30 @@ __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView 
 constexpr int WORKLIST_THREADS = 1024;
 __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(const int32_t* __restrict__ cu_seq_new,
                                                                  const int32_t* __restrict__ seq_len, int B, int NQ,
-                                                                 int qpg, int max_items, int32_t* __restrict__ plan) {
+                                                                 int qpg, int max_items, int num_kv_heads, int nwg,
+                                                                 int parts, int pieces_at, int32_t* __restrict__ plan) {
   __shared__ int ngr[ASPD_MAX_BATCH];
   __shared__ int first_item[ASPD_MAX_BATCH + 1];
-  __shared__ int wave_tot[WORKLIST_THREADS / 64];
+  __shared__ int wave_tot[WORKLIST_THREADS / 64], wave_long[WORKLIST_THREADS / 64], wave_pages[WORKLIST_THREADS / 64];
   const int tid = threadIdx.x;
   // (a sequence that was refused holds no token: seq_len, which the kernel before this one wrote, says so,
   // while the packed rows the layout gave it stay where they are, unwritten)
   static_assert(ASPD_MAX_BATCH <= WORKLIST_THREADS, "a thread per sequence");
   const int mine = tid < B ? (max(seq_len[tid], 0) + qpg - 1) / qpg : 0;
   const int incl = wave_scan_add(mine);
-  if ((tid & 63) == 63) wave_tot[tid >> 6] = incl;
+  // pages of the longest row group, and of all of them (the rule below needs no better than a group's rounded up)
+  const int longest_w = wave_scan_max(tid < B ? (max(seq_len[tid], 0) + ASPD_BLOCK - 1) / ASPD_BLOCK : 0);
+  const int pages_w = parts == 0 ? 0 : wave_scan_add((qpg * (mine * (mine + 1) / 2) + ASPD_BLOCK - 1) / ASPD_BLOCK);
+  if ((tid & 63) == 63) {
+    wave_tot[tid >> 6] = incl;
+    wave_long[tid >> 6] = longest_w;
+    wave_pages[tid >> 6] = pages_w;
+  }
   __syncthreads();
-  int first = incl - mine, acc = 0;
+  int first = incl - mine, acc = 0, longest = 0, total = 0;
   for (int w = 0; w < (B + 63) >> 6; ++w) {
+    longest = max(longest, wave_long[w]);
+    total += wave_pages[w];
     if (w < (tid >> 6)) first += wave_tot[w];
     acc += wave_tot[w];
   }
@@ -202,13 +212,14 @@ __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(con
     plan[1] = qpg;
     plan[2] = NQ;
     plan[3] = B;
-    for (int i = 4; i < SEQ_PLAN_HDR; ++i) plan[i] = 0;
+    for (int i = 4; i < SEQ_PLAN_HDR; ++i) plan[i] = 0;  // (SEQ_HDR_PIECES among them)
   }
   __syncthreads();
   const int n_items = first_item[B];
   int32_t* items = plan + SEQ_PLAN_HDR + ((NQ + 3) & ~3);
   // item (s, t): group ngr[s] - 1 - t of sequence s.  Its place in the list: the items of earlier rounds
   // (min(ngr, t) of every sequence) and, in its own round, the sequences before s that still have a group.
+  int group_place = 0, group_pages = 0;  // of this thread's row group (the first one, see below)
   for (int e = tid; e < n_items; e += blockDim.x) {
     int lo = 0, hi = B - 1;  // sequence of the e-th group in sequence-major order
     while (lo < hi) {
@@ -228,15 +239,93 @@ __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(con
       items[4 * place + 1] = cu_seq_new[s] + tok0;
       items[4 * place + 2] = nq;
       items[4 * place + 3] = (tok0 + nq + ASPD_BLOCK - 1) / ASPD_BLOCK;  // pages up to the group's last slot
+      if (e == tid) {
+        group_place = place;
+        group_pages = (tok0 + nq + ASPD_BLOCK - 1) / ASPD_BLOCK;
+      }
     }
   }
+
+  // ---- Few row groups, some of them long against a workgroup's share of the pages: the launch would wait for the
+  // longest chain of pages, so the longest key ranges are cut into pieces of about a share, whose partial results are merged.
+  // The lines: with more than two row groups per workgroup the queue evens the launch out by itself.  A piece costs its
+  // start, its partial results and its share of a merge, together 40 to 45 pages' worth, so nothing is cut unless the longest
+  // range is SEQ_PIECE_GAIN pages longer than a piece, no piece is shorter than SEQ_PIECE_MIN, and no range is cut that is
+  // not half as long again as a piece.
+  // Two layers, uncut -> cut, us: 8/8 heads of 128, two sequences of 2 000 to 6 000 tokens 268 -> 201, one of 4 000 224 ->
+  // 182, three of 430 to 1 466 112 -> 95; 16/4 of 64, one of 1 500 85 -> 71, one of 4 000 172 -> 148; 32/8 of 128, one of
+  // 1 500 122 -> 115.  On the other side of the line, cut all the same: 32/8, three of 430 to 1 466 (the longest 92 pages,
+  // a share 44) 142 -> 150; 8/8, five of 1 000 (63 and 25) 113 -> 126; one of 700 (44 and 8) 70 -> 72.
+  if (parts == 0 || n_items == 0 || n_items > SEQ_ENTRIES / 2 || n_items * num_kv_heads > 2 * nwg) return;  // (uniform)
+  int target = max(SEQ_PIECE_MIN, quotient(total * num_kv_heads, nwg) + 4);  // pages of a piece
+  if (longest < target + SEQ_PIECE_GAIN) return;
+  static_assert(SEQ_ENTRIES / 2 <= WORKLIST_THREADS, "a row group per thread");
+  __shared__ int sums[2 * (WORKLIST_THREADS / 64)];
+  auto total_of = [&](int v, int* wave) -> int {  // sum over the workgroup, by all of it
+    const int scan = wave_scan_add(v);
+    __syncthreads();
+    if ((tid & 63) == 63) wave[tid >> 6] = scan;
+    __syncthreads();
+    int sum = 0;
+    for (int w = 0; w < (n_items + 63) >> 6; ++w) sum += wave[w];
+    return sum;
+  };
+  int pieces = 1, cut = 0;
+  bool fits = false;
+  for (int attempt = 0; attempt < 16 && !fits; ++attempt) {
+    pieces = 2 * group_pages > 3 * target ? min(SEQ_PIECES_MAX, quotient(group_pages + target - 1, target)) : 1;
+    cut = pieces > 1 ? pieces * num_kv_heads : 0;
+    const int all = total_of(cut, sums);
+    if (all == 0) return;
+    fits = all <= min(parts, 256);
+    if (!fits) target += (target >> 2) + 1;
+  }
+  if (!fits) return;
+  // places of the partial results, and of the pieces in the list: longest first, in classes
+  const int mine_cut = cut, mine_n = tid < n_items ? pieces : 0;
+  const int cut_before = wave_scan_add(mine_cut) - mine_cut;
+  constexpr int BINS = WORKLIST_THREADS;
+  __shared__ int bins[BINS];
+  bins[tid] = 0;
+  __syncthreads();
+  if ((tid & 63) == 63) sums[tid >> 6] = cut_before + mine_cut;
+  const int length = quotient(group_pages + pieces - 1, pieces);
+  const int bin = BINS - 1 - min(BINS - 1, length);
+  if (mine_n > 0) atomicAdd(&bins[bin], mine_n);
+  __syncthreads();
+  int base = cut_before;
+  for (int w = 0; w < (tid >> 6); ++w) base += sums[w];
+  const int in_bin = bins[tid];
+  const int bin_scan = wave_scan_add(in_bin);
+  int* bin_sums = sums + WORKLIST_THREADS / 64;
+  if ((tid & 63) == 63) bin_sums[tid >> 6] = bin_scan;
+  __syncthreads();
+  int first_of_bin = bin_scan - in_bin;
+  for (int w = 0; w < (tid >> 6); ++w) first_of_bin += bin_sums[w];
+  bins[tid] = first_of_bin;
+  __syncthreads();
+  if (mine_n > 0) {
+    const int at = atomicAdd(&bins[bin], mine_n);
+    for (int i = 0; i < mine_n; ++i) {
+      plan[pieces_at + 2 * (at + i)] = group_place;
+      plan[pieces_at + 2 * (at + i) + 1] = i | (mine_n << 8) | (base << 16);
+    }
+  }
+  const int entries = total_of(mine_n, sums);
+  if (tid == 0) plan[SEQ_HDR_PIECES] = entries;
 }
 
 }  // namespace
 
 size_t aspd_sequence_plan_words(const aspd_kv* kv, int32_t B, int32_t NQ) {
   const int G = kv->num_q_heads / kv->num_kv_heads;
-  return aspd_sequence_plan_lo(G, B, NQ) + (((size_t)NQ + 3) & ~(size_t)3);
+  return aspd_sequence_plan_pieces(G, B, NQ) + 2 * SEQ_ENTRIES;
+}
+
+int aspd_sequence_parts(const aspd_kv* kv, int32_t B, int32_t NQ) {
+  AttnVariant v;  // (a chunk of unknown size: one of the launch shapes a workspace is sized for)
+  if (!aspd_choose_variant(kv, B, NQ, 0, 0, true, true, &v) || v.kernel != KERNEL_BF16_ROWS) return 0;
+  return v.nwg;
 }
 
 extern "C" size_t aspd_sequence_plan_bytes(const aspd_kv* kv, int32_t B, int32_t NQ) {
@@ -280,7 +369,12 @@ extern "C" int aspd_build_sequence_meta(const aspd_kv* kv, aspd_state* state, co
   ASPD_HIP_CHECK(hipGetLastError());
   const int max_items = state->B + out->NQ / qpg;
   hipLaunchKernelGGL(sequence_worklist_kernel, dim3(1), dim3(WORKLIST_THREADS), 0, hs, out->cu_seq_new_d, state->seq_len_d, state->B,
-                     out->NQ, qpg, max_items, out->plan_d);
+                     out->NQ, qpg, max_items, kv->num_kv_heads,
+                     out->max_workgroups > 0 ? std::min(out->max_workgroups, aspd_device_cu_count()) : aspd_device_cu_count(),
+                     aspd_sequence_may_cut(kv, state->B, out->NQ, qpg, aspd_device_cu_count())
+                         ? aspd_sequence_parts(kv, state->B, out->NQ) : 0,
+                     (int)aspd_sequence_plan_pieces(G, state->B, out->NQ),
+                     out->plan_d);
   ASPD_HIP_CHECK(hipGetLastError());
   out->plan_key = aspd_sequence_plan_key(qpg, state->B);
   return ASPD_OK;

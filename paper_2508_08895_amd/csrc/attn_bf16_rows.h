@@ -129,8 +129,13 @@ __device__ __forceinline__ float rows_raise(const f32x16& s, Rows32<D>& rs, bf16
 // starts at it.L, and owner tags tell whose a slot of that stage is.
 // take_from: a counter that thread 0 adds one to before it writes its rows (so that the answer, which it returns, does not
 // have to be waited for), or null.
-template <int D, int NW, bool SEQ = false>
-__device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const Seg& it, bool complete, float* pslot,
+// result: asked at the end whether the segment is a whole item, and where its partial result goes otherwise.
+struct Result {
+  bool complete;
+  float* pslot;
+};
+template <int D, int NW, bool SEQ, typename ResultOf>
+__device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const Seg& it, ResultOf result,
                                             int* take_from) {
   using C = RowsCfg<D>;
   constexpr int PPS = ROWS_PPS;
@@ -163,10 +168,12 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
   if (SEQ && a.slot_owner) {
     const int b0 = load_word_uniform(a.row_base + it.q0), b1 = load_word_uniform(a.row_base + it.q0 + it.nq - 1);
     const int lo0 = load_word_uniform(a.row_lo + it.q0);
-    const int from = (b0 + 31) >> 5, to = min(lo0 >> 5, npairs);
+    const int first = page0 >> 1;  // (a piece starts with a whole pair)
+    const int from = max(((b0 + 31) >> 5) - first, 0), to = min((lo0 >> 5) - first, npairs);
     if (b0 == b1 && to > from) {
       hole_at = from;
-      hole = to - from;
+      hole = min(to - from, npairs - 1);  // (a piece that the group sees nothing of keeps one pair, all of it masked)
+      hole_at = min(hole_at, npairs - hole);
     }
     npairs -= hole;
   }
@@ -534,7 +541,8 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
   if (!wave_active) return taken;
   rs.l_run += __shfl_xor(rs.l_run, 32);
   const int r = wave * 32 + c;  // row inside the row group
-  if (complete) {
+  const Result to = result();
+  if (to.complete) {
     if (c >= Rw) return taken;
     const int q = it.q0 + r / a.G;
     const int head = it.h * a.G + r % a.G;
@@ -558,7 +566,7 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
     // of the next, and four lanes hold sixteen consecutive floats of one row (10 sequences of up to 600 tokens, chunks
     // of 2 to 9 tokens per branch, items split over three workgroups: 33.9 -> 31.4 us a layer).
     const int row = lane & 15;
-    float* dst = partial_acc(pslot, wave * 32 + row, D) + 8 * ((lane >> 4) & 1) + 4 * h;
+    float* dst = partial_acc(to.pslot, wave * 32 + row, D) + 8 * ((lane >> 4) & 1) + 4 * h;
 #pragma unroll
     for (int mt = 0; mt < C::MT; ++mt) {
 #pragma unroll
@@ -576,7 +584,7 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
         if (row + 16 < Rw) store_device_scope_x4(dst + 16 * D + 32 * mt + 8 * b, hi);
       }
     }
-    if (h == 0 && c < Rw) store_device_scope_x4(partial_stat(a, pslot, r, D), f32x4{rs.m_run, rs.l_run, 0.f, 0.f});
+    if (h == 0 && c < Rw) store_device_scope_x4(partial_stat(a, to.pslot, r, D), f32x4{rs.m_run, rs.l_run, 0.f, 0.f});
   }
   return taken;
 }
@@ -597,7 +605,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
   for (int i = 1; nseg > 0;) {
     const bool complete = seg_complete(seg);
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
-    const int taken = segment_rows<D, NW>(a, smem, seg, complete, pslot, queue > 0 ? a.counters + QUEUE_NEXT : nullptr);
+    const int taken = segment_rows<D, NW, false>(a, smem, seg, [=]() -> Result { return {complete, pslot}; },
+                                                  queue > 0 ? a.counters + QUEUE_NEXT : nullptr);
     if (!complete) announce_partial<D, true, THREADS, D / 16, 4>(a, seg, &merge_flag);
     int at;
     if (queue == 0) {
@@ -632,52 +641,105 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
 // range first; workgroups take them from the list as they become free (the ranges differ by two orders
 // of magnitude, so no static split would balance), through one counter in the workspace that the last
 // workgroup to finish puts back to zero.  Every group is computed whole by one workgroup with the
-// row-splitting arithmetic above: nothing is split, nothing merged.
+// row-splitting arithmetic above, but for the longest ones of a launch that has few: their key ranges are cut (the plan's
+// list of pieces says where, and is in the order of the pieces' lengths) and the workgroup that brings the last piece
+// merges, as in the row-splitting kernel.  PIECES: there may be such a list, and there is room for partial results;
+// otherwise every group is taken whole.
 // ---------------------------------------------------------------------------------------------
-template <int D, int NW>
+template <int D, int NW, bool PIECES>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void attn_bf16_seq_kernel(
     AttnArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ int next_item;
+  __shared__ int next_item, merge_flag;
+  // Of a piece: slot of its partial result (-1: the item is a whole row group), and what the merge asks for.  In LDS because
+  // the loop over the pages needs the scalar registers.
+  __shared__ int held[5];
   const int n_groups = a.plan[0];
+  const int n_pieces = PIECES ? min(a.plan[SEQ_HDR_PIECES], SEQ_ENTRIES) : 0;
   const int32_t* items = a.plan + SEQ_PLAN_HDR + ((a.NQ + 3) & ~3);
   const int Hkv = a.kv.num_kv_heads;
-  const long total = (long)n_groups * Hkv;
+  const long total = (long)(n_pieces > 0 ? n_pieces : n_groups) * Hkv;
+  int* const take_from = a.counters + QUEUE_NEXT;
+  // Item e of the list; false for one that no plan of the library's own holds (a workgroup that is handed anything else
+  // stays inside the call's arrays).
+  auto item_of = [&](int e, Seg* seg, int* piece, int* pieces) -> bool {
+    int group = e / Hkv, part = 0;
+    *piece = 0;
+    *pieces = 1;
+    if (n_pieces > 0) {
+      const int word = a.pieces[2 * group + 1];
+      group = a.pieces[2 * group];
+      *piece = word & 0xff;
+      *pieces = (word >> 8) & 0xff;
+      part = (int)((unsigned)word >> 16) + e % Hkv * *pieces;
+    }
+    const bool listed = (int)((unsigned)group < (unsigned)n_groups) & (int)(*piece < *pieces) &
+                        (int)(*pieces <= SEQ_PIECES_MAX) & (int)((*pieces == 1) | (part + *pieces <= a.parts));
+    const i32x4 w = *(const i32x4*)(items + 4 * (listed ? group : 0));
+    seg->s = w[0];
+    seg->h = e % Hkv;
+    seg->q0 = w[1];
+    seg->nq = w[2];
+    seg->np = w[3];
+    seg->page0 = 0;
+    seg->page1 = seg->np;
+    if (*pieces > 1) {
+      const int pairs = (seg->np + 1) / 2;
+      const float inv = __builtin_amdgcn_rcpf((float)*pieces);
+      seg->page0 = 2 * quotient(pairs * *piece, *pieces, inv);
+      seg->page1 = min(seg->np, 2 * quotient(pairs * (*piece + 1), *pieces, inv));
+    }
+    seg->owner = part;
+    seg->w_last = part + *pieces - 1;
+    seg->L = 0;
+    return (int)listed & (int)(seg->page0 < seg->page1) & (int)(seg->s >= 0) & (int)(seg->s < a.B) & (int)(seg->q0 >= 0) &
+           (int)(seg->nq >= 1) & (int)(seg->nq <= a.qpg) & (int)(seg->q0 <= a.NQ - seg->nq) & (int)(seg->np >= 1) &
+           (int)(seg->np <= a.kv.max_blocks_per_seq);
+  };
   int taken = 0;
-  if (threadIdx.x == 0) taken = atomicAdd(a.counters, 1);
+  if (threadIdx.x == 0) taken = atomicAdd(take_from, 1);
   for (;;) {
     if (threadIdx.x == 0) next_item = taken;
     __syncthreads();
     const int e = __builtin_amdgcn_readfirstlane(next_item);
     if (e >= total) break;
-    const i32x4 w = *(const i32x4*)(items + 4 * (e / Hkv));
     Seg seg;
-    seg.s = w[0];
-    seg.h = e % Hkv;
-    seg.q0 = w[1];
-    seg.nq = w[2];
-    seg.page0 = 0;
-    seg.page1 = seg.np = w[3];
-    seg.owner = seg.w_last = 0;
-    seg.L = 0;
-    // the list is the library's own; the check keeps a workgroup that is handed anything else inside the
-    // call's arrays
-    const bool ok = (int)(seg.s >= 0) & (int)(seg.s < a.B) & (int)(seg.q0 >= 0) & (int)(seg.nq >= 1) &
-                    (int)(seg.nq <= a.qpg) & (int)(seg.q0 <= a.NQ - seg.nq) & (int)(seg.np >= 1) &
-                    (int)(seg.np <= a.kv.max_blocks_per_seq);
+    int piece, pieces;
+    const bool ok = item_of(e, &seg, &piece, &pieces);
     if (!ok) {
       __syncthreads();  // everyone has read next_item
-      if (threadIdx.x == 0) taken = atomicAdd(a.counters, 1);
+      if (threadIdx.x == 0) taken = atomicAdd(take_from, 1);
       continue;
     }
-    taken = segment_rows<D, NW, true>(a, smem, seg, true, nullptr, a.counters);
+    if (PIECES && threadIdx.x == 0) {
+      held[0] = pieces > 1 ? 2 * (seg.owner + piece) + (piece == 0 ? 1 : 0) : -1;
+      held[1] = seg.owner;
+      held[2] = seg.w_last;
+      held[3] = seg.q0;
+      held[4] = seg.nq | (seg.h << 16);
+    }
+    taken = segment_rows<D, NW, true>(a, smem, seg, [&]() -> Result {
+      if (!PIECES) return {true, nullptr};
+      const int slot = __builtin_amdgcn_readfirstlane(held[0]);
+      return {slot < 0, a.partial + (long)slot * a.rows_cap * (D + 4)};
+    }, take_from);
+    if (PIECES && held[0] >= 0) {
+      Seg seg;
+      seg.owner = __builtin_amdgcn_readfirstlane(held[1]);
+      seg.w_last = __builtin_amdgcn_readfirstlane(held[2]);
+      seg.q0 = __builtin_amdgcn_readfirstlane(held[3]);
+      const int rows = __builtin_amdgcn_readfirstlane(held[4]);
+      seg.nq = rows & 0xffff;
+      seg.h = rows >> 16;
+      announce_partial<D, true, NW * 64, D / 16, 4>(a, seg, &merge_flag);
+    }
   }
   // the last workgroup to leave puts the two counters back to zero for the next launch
   if (threadIdx.x == 0) {
-    const int gone = atomicAdd(a.counters + 1, 1);
+    const int gone = atomicAdd(a.counters + QUEUE_DONE, 1);
     if (gone == (int)gridDim.x - 1) {
-      atomicExch(a.counters, 0);
-      atomicExch(a.counters + 1, 0);
+      atomicExch(a.counters + QUEUE_NEXT, 0);
+      atomicExch(a.counters + QUEUE_DONE, 0);
     }
   }
 }

@@ -49,6 +49,8 @@ struct AttnArgs {
   int            rows_cap;      // rows per row group the partial slots are sized for
   const int32_t* row_base;      // whole-sequence launches: per packed row, the first slot of the row's stage
   const int32_t* row_lo;        // ... and the first slot of its own branch there
+  const int32_t* pieces;        // ... their list of pieces, and how many pieces `partial` (null: none) has slots for
+  int            parts;
 };
 
 // r / G for a row of a row group.  Exact: (r + 1/2) / G is at least 1 / (2 G) away from a whole number, and r < 768.

@@ -523,3 +523,54 @@ def test_re_prefill_with_rotary_append_end_to_end(A):
     err = np.abs(out.double().cpu().numpy() - ref).max()
     print(f"[re-prefill chain] rows={NQ} max|out-ref|={err:.3e}", flush=True)
     assert err <= TOL
+
+
+@pytest.mark.parametrize("heads", [(8, 8, 128), (32, 8, 128), (16, 4, 64), (8, 1, 64)])
+@pytest.mark.parametrize("runs", [
+    [[(0, 1501)]],                                                            # prompts
+    [[(0, 3), (1, 700), (2, 650), (3, 90), (0, 33), (1, 2)]],                 # pieces that whole groups see nothing of
+    [[(0, 700), (1, 31), (2, 33), (0, 1100), (1, 64), (2, 47)], [(0, 17)]],   # a long and a short sequence
+])
+@pytest.mark.parametrize("shared", [0, 1])
+def test_row_groups_cut_into_pieces(A, heads, runs, shared):
+    """Few long sequences: the longest row groups' key ranges are cut and merged.  Against the oracle (under the shared
+    mask against the launch that has no room for partial results and takes every group whole), the same twice."""
+    from gpu_drive import GpuBatch
+    longest = max(sum(n for _, n in r) for r in runs)
+    wl = W.random_small(seed=5500 + len(runs), num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2], batch=len(runs),
+                        prefix_range=(longest, longest), branches_range=(1, 1), branch_len_range=(1, 1))
+    tt, meta = replay_layout(wl.block_tables, wl.block_size, runs)
+    gb = GpuBatch(wl)
+    step = _build(A, gb, runs)
+    _check_meta(A, gb, wl, step, tt, meta, runs)
+    plan = step.plan.cpu().numpy().view(np.int32)
+    G = heads[0] // heads[1]
+    at = HDR + 2 * ((meta.NQ + 3) & ~3) + 4 * (wl.B + meta.NQ // (256 // G))
+    entries = plan[at:at + 2 * plan[4]].reshape(-1, 2)
+    if heads[:2] != (32, 8) or longest > 1900:
+        assert plan[4] > plan[0]
+    # every row group's pieces once, their partial results in places of their own
+    seen, places = set(), []
+    for group, word in entries.tolist():
+        piece, pieces, place = word & 255, word >> 8 & 255, word >> 16
+        assert 0 <= group < plan[0] and piece < pieces <= 8 and (group, piece) not in seen
+        seen.add((group, piece))
+        if pieces > 1 and piece == 0:
+            places += range(place, place + pieces * heads[1])
+    assert len(set(places)) == len(places) and max(places, default=0) < 256
+    assert {g for g, _ in seen} == (set(range(plan[0])) if plan[4] else set())
+    step.shared_mask = shared
+    q = wl.draw_q(meta.NQ).to(gb.dev)
+    def run(ws):
+        lse = torch.full((meta.NQ, wl.num_q_heads), float("nan"), dtype=torch.float32, device=gb.dev)
+        out = torch.full_like(q, float("nan"))
+        A.aspd_attn_full_sequence(gb.kv, gb.state, step, q, ws, out=out, lse=lse)
+        assert not ws[:4096].view(torch.int32).any()       # counters are back at zero
+        return out, lse
+    small = torch.zeros(4096, dtype=torch.uint8, device=gb.dev)
+    cut, again, whole = run(gb.workspace), run(gb.workspace), run(small)
+    assert torch.equal(cut[0], again[0]) and torch.equal(cut[1], again[1])
+    # P and O are rounded to bf16 in both, the weights against other references: two roundings of 2^-9 each way
+    assert float((cut[0].float() - whole[0].float()).abs().max()) <= TOL and float((cut[1] - whole[1]).abs().max()) <= LSE_TOL
+    if not shared:
+        _check_attention(A, gb, wl, step, tt, meta, label=f"cut {heads}")
