@@ -303,7 +303,8 @@ ASPD_API int aspd_build_sequence_meta(const aspd_kv* kv, aspd_state* state, cons
  * rows' latest stage and their first branch there.  With step->shared_mask = 1 every row attends every slot up to and including its
  * own (plain causal attention over the sequence: the "Shared" mask of Sec. 4.5.2, and what a re-prefill of a
  * sequence without parallel stages computes).  Other arguments as aspd_attn_parallel_decode; the workspace needs
- * aspd_workspace_bytes(kv, B, NQ) like any other call (only its counters are used). */
+ * aspd_workspace_bytes(kv, B, NQ) like any other call (with less than that, but room for its counters, row groups are
+ * not cut into pieces, which is slower where they are few). */
 ASPD_API int aspd_attn_full_sequence(const aspd_kv* kv, const aspd_state* state, const aspd_step* step,
                                      const void* q_d, void* out_d, float* lse_d, float sm_scale,
                                      void* workspace_d, size_t workspace_bytes, void* stream);
