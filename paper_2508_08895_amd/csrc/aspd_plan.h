@@ -89,7 +89,9 @@ int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t
 // ---- The plan of a whole-sequence step (aspd_build_sequence_meta / aspd_attn_full_sequence) -------
 // Layout (32-bit words):
 //   [0, 16)                 header: 0 row groups in the list, 1 tokens per row group, 2 NQ, 3 B, 4 entries in the list of
-//                           pieces (0: no row group is cut)
+//                           pieces (0: no row group is cut), 5 the KV heads that list was made for, 6 the places of
+//                           partial results it gives away (an attention call on a cache of another number of KV heads,
+//                           or without room for those places, takes every row group whole)
 //   [16, 16 + NQ4)          per packed row, the first slot of the row's own stage (its own slot for a
 //                           main-branch row); NQ4 = NQ rounded up to a multiple of 4
 //   then 4 words per row group, in the order workgroups take them: sequence, first packed row,
@@ -100,6 +102,8 @@ int aspd_plan_launch(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t
 //                           group, piece | pieces << 8 | place of its first head's partial results << 16
 constexpr int SEQ_PLAN_HDR = 16;
 constexpr int SEQ_HDR_PIECES = 4;
+constexpr int SEQ_HDR_HEADS = 5;
+constexpr int SEQ_HDR_PLACES = 6;
 constexpr int SEQ_PIECES_MAX = 8;    // of one row group
 constexpr int SEQ_ENTRIES = 1024;    // room in the list of pieces
 constexpr int SEQ_PIECE_MIN = 24;    // pages of a piece, and how many more the longest row group has at least where any

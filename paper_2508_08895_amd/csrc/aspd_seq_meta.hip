@@ -270,14 +270,14 @@ __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(con
     for (int w = 0; w < (n_items + 63) >> 6; ++w) sum += wave[w];
     return sum;
   };
-  int pieces = 1, cut = 0;
+  int pieces = 1, cut = 0, places = 0;
   bool fits = false;
   for (int attempt = 0; attempt < 16 && !fits; ++attempt) {
     pieces = 2 * group_pages > 3 * target ? min(SEQ_PIECES_MAX, quotient(group_pages + target - 1, target)) : 1;
     cut = pieces > 1 ? pieces * num_kv_heads : 0;
-    const int all = total_of(cut, sums);
-    if (all == 0) return;
-    fits = all <= min(parts, 256);
+    places = total_of(cut, sums);
+    if (places == 0) return;
+    fits = places <= min(parts, 256);
     if (!fits) target += (target >> 2) + 1;
   }
   if (!fits) return;
@@ -312,7 +312,11 @@ __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(con
     }
   }
   const int entries = total_of(mine_n, sums);
-  if (tid == 0) plan[SEQ_HDR_PIECES] = entries;
+  if (tid == 0) {
+    plan[SEQ_HDR_PIECES] = entries;
+    plan[SEQ_HDR_HEADS] = num_kv_heads;
+    plan[SEQ_HDR_PLACES] = places;
+  }
 }
 
 }  // namespace

@@ -655,9 +655,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
   // the loop over the pages needs the scalar registers.
   __shared__ int held[5];
   const int n_groups = a.plan[0];
-  const int n_pieces = PIECES ? min(a.plan[SEQ_HDR_PIECES], SEQ_ENTRIES) : 0;
-  const int32_t* items = a.plan + SEQ_PLAN_HDR + ((a.NQ + 3) & ~3);
   const int Hkv = a.kv.num_kv_heads;
+  // (places of partial results and arrivals were given away for so many heads: with others, or with fewer places, two row
+  // groups would count on one word)
+  const bool listed = PIECES && a.plan[SEQ_HDR_HEADS] == Hkv && a.plan[SEQ_HDR_PLACES] <= a.parts;
+  const int n_pieces = listed ? min(a.plan[SEQ_HDR_PIECES], SEQ_ENTRIES) : 0;
+  const int32_t* items = a.plan + SEQ_PLAN_HDR + ((a.NQ + 3) & ~3);
   const long total = (long)(n_pieces > 0 ? n_pieces : n_groups) * Hkv;
   int* const take_from = a.counters + QUEUE_NEXT;
   // Item e of the list; false for one that no plan of the library's own holds (a workgroup that is handed anything else
@@ -673,9 +676,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
       *pieces = (word >> 8) & 0xff;
       part = (int)((unsigned)word >> 16) + e % Hkv * *pieces;
     }
-    const bool listed = (int)((unsigned)group < (unsigned)n_groups) & (int)(*piece < *pieces) &
-                        (int)(*pieces <= SEQ_PIECES_MAX) & (int)((*pieces == 1) | (part + *pieces <= a.parts));
-    const i32x4 w = *(const i32x4*)(items + 4 * (listed ? group : 0));
+    const bool in_list = (int)((unsigned)group < (unsigned)n_groups) & (int)(*piece < *pieces) &
+                         (int)(*pieces <= SEQ_PIECES_MAX) & (int)((*pieces == 1) | (part + *pieces <= a.parts));
+    const i32x4 w = *(const i32x4*)(items + 4 * (in_list ? group : 0));
     seg->s = w[0];
     seg->h = e % Hkv;
     seg->q0 = w[1];
@@ -692,7 +695,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
     seg->owner = part;
     seg->w_last = part + *pieces - 1;
     seg->L = 0;
-    return (int)listed & (int)(seg->page0 < seg->page1) & (int)(seg->s >= 0) & (int)(seg->s < a.B) & (int)(seg->q0 >= 0) &
+    return (int)in_list & (int)(seg->page0 < seg->page1) & (int)(seg->s >= 0) & (int)(seg->s < a.B) & (int)(seg->q0 >= 0) &
            (int)(seg->nq >= 1) & (int)(seg->nq <= a.qpg) & (int)(seg->q0 <= a.NQ - seg->nq) & (int)(seg->np >= 1) &
            (int)(seg->np <= a.kv.max_blocks_per_seq);
   };

@@ -574,3 +574,25 @@ def test_row_groups_cut_into_pieces(A, heads, runs, shared):
     assert float((cut[0].float() - whole[0].float()).abs().max()) <= TOL and float((cut[1] - whole[1]).abs().max()) <= LSE_TOL
     if not shared:
         _check_attention(A, gb, wl, step, tt, meta, label=f"cut {heads}")
+
+
+@pytest.mark.parametrize("built,used", [((4, 1), (32, 8)), ((32, 8), (4, 1)), ((8, 8), (3, 3))])
+def test_a_step_serves_caches_of_another_number_of_heads(A, built, used):
+    """A step is made of lengths and block tables, so one built with one cache serves another of the same ratio of heads:
+    the places of the pieces' partial results, which were given away for the heads of the first, are not used then."""
+    from gpu_drive import GpuBatch
+    runs = [[(0, 300), (1, 500), (2, 700), (0, 400)], [(0, 17)]]
+    wl = W.random_small(seed=5600, num_q_heads=used[0], num_kv_heads=used[1], head_dim=64, batch=2, prefix_range=(1900, 1900),
+                        branches_range=(1, 1), branch_len_range=(1, 1))
+    tt, meta = replay_layout(wl.block_tables, wl.block_size, runs)
+    gb = GpuBatch(wl)
+    pool = torch.zeros(1, built[1], 16, 64, dtype=torch.bfloat16, device=gb.dev).expand(wl.num_blocks, -1, -1, -1)
+    own, gb.kv = gb.kv, A.KVCache(pool, pool, gb.kv.block_tables, built[0])
+    step = _build(A, gb, runs)
+    gb.kv = own
+    plan = step.plan.cpu().numpy().view(np.int32)
+    assert plan[4] > plan[0] and plan[5] == built[1]
+    _check_meta(A, gb, wl, step, tt, meta, runs)
+    for _ in range(2):
+        _check_attention(A, gb, wl, step, tt, meta, label=f"built for {built}, used for {used}")
+        assert not gb.workspace[:4096].any()
