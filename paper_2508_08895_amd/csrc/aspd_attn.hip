@@ -100,7 +100,7 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
   // The step's own plan when it was built for this launch shape; otherwise (no plan buffer, a hint that
   // changed since, the other entry point) one is built now, into the workspace, by the same kernel.
   const int32_t* plan = step->plan_d;
-  if (!plan || step->plan_key != aspd_plan_key(v, state->B) || step->plan_bytes < plan_words * sizeof(int32_t)) {
+  if (!plan || step->plan_key != aspd_plan_key(kv, v, state->B) || step->plan_bytes < plan_words * sizeof(int32_t)) {
     int32_t* own = (int32_t*)((char*)workspace_d + COUNTER_BYTES);
     rc = aspd_plan_launch(kv, v, state->B, step->NQ, state->stage_base_d, state->seq_len_d, step->cu_seq_new_d, own, hs);
     if (rc != ASPD_OK) return rc;

@@ -357,7 +357,7 @@ extern "C" int aspd_build_branch_meta(const aspd_kv* kv, aspd_state* state, int3
     rc = aspd_plan_launch(kv, variant, state->B, out->NQ, state->stage_base_d, state->seq_len_d, out->cu_seq_new_d,
                           out->plan_d, hs);
     if (rc != ASPD_OK) return rc;
-    out->plan_key = aspd_plan_key(variant, state->B);
+    out->plan_key = aspd_plan_key(kv, variant, state->B);
   }
   return ASPD_OK;
 }

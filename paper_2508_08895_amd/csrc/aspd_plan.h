@@ -77,7 +77,7 @@ int aspd_choose_variant(const aspd_kv* kv, int32_t B, int32_t NQ, int32_t max_ne
                         bool chunk_call, bool has_owner, AttnVariant* out);
 
 // Identifies the launch a plan was built for; never 0.
-uint64_t aspd_plan_key(const AttnVariant& v, int32_t B);
+uint64_t aspd_plan_key(const aspd_kv* kv, const AttnVariant& v, int32_t B);
 
 // Words a plan for `v` may take.
 size_t aspd_plan_words(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t NQ);

@@ -777,16 +777,18 @@ int aspd_choose_variant(const aspd_kv* kv, int32_t B, int32_t NQ, int32_t max_ne
   return 1;
 }
 
-uint64_t aspd_plan_key(const AttnVariant& v, int32_t B) {
-  // every field the plan kernel's result depends on besides the device arrays
-  uint64_t k = 1;
+uint64_t aspd_plan_key(const aspd_kv* kv, const AttnVariant& v, int32_t B) {
+  // What a plan has to agree on with the call that reads it, besides the device arrays: which items there are and which
+  // kernel takes them.  (The query heads per KV head are in qpg; the sizes of the pool and of the block tables only bound
+  // what a plan holds, and the kernels check that themselves.)
+  uint64_t k = 1 << 16 | (uint64_t)(kv->num_kv_heads & 0xffff);
   k = k * 4 + (uint64_t)v.kernel;
   k = k * 2 + (v.has_owner ? 1 : 0);
   k = k * 2048 + (uint64_t)v.nwg;
   k = k * 512 + (uint64_t)v.qpg;
   k = k * 256 + (uint64_t)v.pad;
   k = k * 1024 + (uint64_t)B;
-  return k;  // 42 bits
+  return k;  // 58 bits
 }
 
 size_t aspd_plan_words(const aspd_kv* kv, const AttnVariant& v, int32_t B, int32_t NQ) {

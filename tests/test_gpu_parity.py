@@ -290,6 +290,25 @@ def test_capped_grid_and_long_segments(A):
     _compare_attention(A, gb, tt, wl, step, meta, A.aspd_attn_serial_decode, label="uncapped serial")
 
 
+@pytest.mark.parametrize("dtype,hq,hkv,tokens", [("bf16", 16, 4, 1), ("bf16", 16, 4, 20), ("f32", 4, 4, 1)])
+@pytest.mark.parametrize("other", [1, 2, 8])
+def test_a_plan_is_for_the_heads_it_was_built_for(A, dtype, hq, hkv, tokens, other):
+    """A step built with a cache of another number of KV heads at the same ratio, on the same grid: the attention call builds
+    a plan of its own (with the step's, the other heads' output would stay unwritten)."""
+    wl = W.random_small(seed=5700, dtype=dtype, num_q_heads=hq, num_kv_heads=hkv, head_dim=64, batch=2,
+                        prefix_range=(900, 1500), branches_range=(2, 4), branch_len_range=(1, 9))
+    gb, tt = _grow_both(A, wl, wl.branch_len, False)
+    new = np.full(wl.NB, tokens, dtype=np.int32)
+    meta = tt.append_parallel(new)
+    pool = torch.zeros(1, other, 16, 64, dtype=gb.kv.k.dtype, device=gb.dev).expand(wl.num_blocks, -1, -1, -1)
+    kv = A.KVCache(pool, pool, gb.kv.block_tables, hq // hkv * other)
+    step = A.aspd_build_branch_meta(kv, gb.state, A.STAGE_PARALLEL, gb._dev_i32(new), NQ=int(new.sum()),
+                                    max_new_per_seq=4 * tokens, max_workgroups=5)
+    assert step.plan_key != 0
+    call = A.aspd_attn_parallel_decode if tokens == 1 else A.aspd_attn_branch_chunk
+    _compare_attention(A, gb, tt, wl, step, meta, call, label=f"{dtype} {hkv} heads, {other} planned")
+
+
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("branches", [1, 3, 6, 11], ids=["part_of_a_tile", "one_tile", "two_tiles", "three_tiles"])
 def test_segments_of_few_pages_and_items_of_many_parts(A, hd, branches):
