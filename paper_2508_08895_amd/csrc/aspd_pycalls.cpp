@@ -216,12 +216,10 @@ bool bytes_of(PyObject* o, size_t* out) {
   return !PyErr_Occurred();
 }
 
-bool int_of(PyObject* o, int32_t* out) {  // as a ctypes int32 argument takes it
-  if (!PyLong_Check(o)) {
-    PyErr_Format(PyExc_TypeError, "an int is required, not %s", Py_TYPE(o)->tp_name);
-    return false;
-  }
-  *out = (int32_t)PyLong_AsUnsignedLongMask(o);
+bool int_of(PyObject* o, int32_t* out) {  // as a ctypes int32 argument takes it: whatever stands for a whole number
+  Ref i(PyNumber_Index(o));
+  if (!i.o) return false;
+  *out = (int32_t)PyLong_AsUnsignedLongMask(i.o);
   return !PyErr_Occurred();
 }
 

@@ -1,5 +1,6 @@
 """The compiled half of the binding hands the library what the struct() methods say, in the plain case and in every other,
 and refuses what they refuse (no GPU needed: nothing here gets as far as a launch)."""
+import numpy as np
 import pytest
 import torch
 
@@ -124,3 +125,28 @@ def test_calls_reach_the_library_and_raise_what_it_says():
         A.aspd_attn_serial_decode(kv, st, sp, q, 3, out=q, stream=_Stream)
     with pytest.raises(AttributeError):
         A.aspd_attn_serial_decode(kv, st, sp, q, ws, stream=0)
+
+
+@pytest.mark.parametrize("whole", [int, np.int64, np.int32, torch.tensor])
+def test_numbers_are_whatever_stands_for_a_whole_number(whole):
+    kv, st, sp = _objects()
+    one = torch.ones(3, dtype=torch.int32)
+    with pytest.raises(A.AspdError, match="aspd_build_branch_meta: invalid argument"):   # no such stage
+        A.aspd_build_branch_meta(kv, st, whole(9), one, step=sp, stream=_Stream)
+    st.B, st.pos_mode, sp.NQ = whole(3), whole(A.POS_SAME_MAX), whole(6)
+    with pytest.raises(A.AspdError, match="aspd_build_branch_meta: invalid argument"):
+        A.aspd_build_branch_meta(kv, st, 9, one, step=sp, stream=_Stream)
+    sp.NQ = whole(-1)
+    with pytest.raises(A.AspdError, match="aspd_build_sequence_meta: invalid argument"):
+        A.aspd_build_sequence_meta(kv, st, one, one, one, -1, step=sp, stream=_Stream)
+
+
+@pytest.mark.parametrize("number", [9.0, "9", None, np.float32(9)])
+def test_what_is_no_whole_number_is_refused(number):
+    kv, st, sp = _objects()
+    one = torch.ones(3, dtype=torch.int32)
+    with pytest.raises(TypeError):
+        A.aspd_build_branch_meta(kv, st, number, one, step=sp, plan=False, stream=_Stream)
+    st.pos_mode = number
+    with pytest.raises(TypeError):
+        A.aspd_build_branch_meta(kv, st, 9, one, step=sp, plan=False, stream=_Stream)
