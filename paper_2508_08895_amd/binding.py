@@ -122,14 +122,14 @@ _pycalls = None
 
 
 def _calls():
-    """The compiled half of the binding, loaded with the library."""
+    """The compiled half of the binding, over the library that lib() has loaded."""
     global _pycalls
     if _pycalls is None:
-        lib()
+        L = lib()
         if not os.path.exists(os.path.join(_HERE, "_pycalls.so")):
             raise FileNotFoundError(f"{_HERE}/_pycalls.so not built: run `python -m paper_2508_08895_amd.build`")
         from paper_2508_08895_amd import _pycalls as m
-        m.init(KVCache, BatchState, Step)
+        m.init(KVCache, BatchState, Step, {n: C.cast(getattr(L, n), C.c_void_p).value for n in EXPORTS})
         _pycalls = m
     return _pycalls
 

@@ -1,4 +1,4 @@
-"""Builds libaspd.so (HIP, gfx950) and the binding's _pycalls.so (host code over it) in-tree.
+"""Builds libaspd.so (HIP, gfx950; hipcc) and the binding's _pycalls.so (host code; g++, the headers of Python and torch) in-tree.
 `python -m paper_2508_08895_amd.build`."""
 from __future__ import annotations
 
@@ -29,7 +29,7 @@ def build(verbose: bool = False, extra=()) -> str:
 
 
 def build_calls(verbose: bool = False) -> str:
-    """The compiled half of the binding, against the libraries of the torch it runs beside."""
+    """The compiled half of the binding, against the libraries of the torch it runs beside (libaspd.so it is handed)."""
     import torch
     from torch.utils.cpp_extension import include_paths
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
@@ -38,8 +38,8 @@ def build_calls(verbose: bool = False) -> str:
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *[x for d in dirs for x in ("-isystem" if d != dirs[-1] else "-I", d)],
-           os.path.join(CSRC, "aspd_pycalls.cpp"), "-o", CALLS, "-L", HERE, "-l:libaspd.so", "-L", torch_lib,
-           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+           os.path.join(CSRC, "aspd_pycalls.cpp"), "-o", CALLS, "-L", torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-lc10_hip"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

@@ -26,6 +26,17 @@ namespace {
 
 PyObject *g_kv_type, *g_state_type, *g_step_type;  // the binding's classes (set once, by init)
 
+// The library's entry points, from the binding's own handle of it (set with them): this module is linked against no library,
+// so that the calls here and those by ctypes are always calls of one.
+#define ASPD_CALLS(X)                                                                                                  \
+  X(attn_parallel_decode) X(attn_branch_chunk) X(attn_serial_decode) X(attn_full_sequence)                             \
+  X(attn_parallel_decode_static) X(rope_append) X(build_branch_meta) X(sequence_plan_bytes) X(build_sequence_meta)
+#define ASPD_POINTER(name) decltype(&aspd_##name) name;
+struct {
+  ASPD_CALLS(ASPD_POINTER)
+} g_lib;
+#undef ASPD_POINTER
+
 // Names, interned at import.
 #define ASPD_NAMES(X)                                                                                                  \
   X(k) X(v) X(block_tables) X(num_q_heads) X(B) X(NB) X(stage_base) X(seq_len) X(cu_branches) X(branch_len)            \
@@ -287,11 +298,11 @@ PyObject* py_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     int rc;
     Py_BEGIN_ALLOW_THREADS;
     switch (which) {
-      case PARALLEL: rc = aspd_attn_parallel_decode(&kv, &st, &sp, q, out, (float*)lse, scale, ws, ws_bytes, stream); break;
-      case CHUNK: rc = aspd_attn_branch_chunk(&kv, &st, &sp, q, out, (float*)lse, scale, ws, ws_bytes, stream); break;
-      case SERIAL: rc = aspd_attn_serial_decode(&kv, &st, &sp, q, out, (float*)lse, scale, ws, ws_bytes, stream); break;
-      case SEQUENCE: rc = aspd_attn_full_sequence(&kv, &st, &sp, q, out, (float*)lse, scale, ws, ws_bytes, stream); break;
-      default: rc = aspd_attn_parallel_decode_static(&kv, &st, &sp, q, out, (float*)lse, scale, stream); break;
+      case PARALLEL: rc = g_lib.attn_parallel_decode(&kv, &st, &sp, q, out, (float*)lse, scale, ws, ws_bytes, stream); break;
+      case CHUNK: rc = g_lib.attn_branch_chunk(&kv, &st, &sp, q, out, (float*)lse, scale, ws, ws_bytes, stream); break;
+      case SERIAL: rc = g_lib.attn_serial_decode(&kv, &st, &sp, q, out, (float*)lse, scale, ws, ws_bytes, stream); break;
+      case SEQUENCE: rc = g_lib.attn_full_sequence(&kv, &st, &sp, q, out, (float*)lse, scale, ws, ws_bytes, stream); break;
+      default: rc = g_lib.attn_parallel_decode_static(&kv, &st, &sp, q, out, (float*)lse, scale, stream); break;
     }
     Py_END_ALLOW_THREADS;
     return PyLong_FromLong(rc);
@@ -310,7 +321,7 @@ PyObject* py_rope_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
       return nullptr;
     int rc;
     Py_BEGIN_ALLOW_THREADS;
-    rc = aspd_rope_append(&kv, &sp, q, k, v, theta, stream);
+    rc = g_lib.rope_append(&kv, &sp, q, k, v, theta, stream);
     Py_END_ALLOW_THREADS;
     return PyLong_FromLong(rc);
   });
@@ -332,7 +343,7 @@ PyObject* py_build_branch_meta(PyObject*, PyObject* const* a, Py_ssize_t n) {
       return nullptr;
     int rc;
     Py_BEGIN_ALLOW_THREADS;
-    rc = aspd_build_branch_meta(&kv, &st, stage, pos_mode, (const int32_t*)new_len, with_step ? &sp : nullptr, stream);
+    rc = g_lib.build_branch_meta(&kv, &st, stage, pos_mode, (const int32_t*)new_len, with_step ? &sp : nullptr, stream);
     Py_END_ALLOW_THREADS;
     if (rc == ASPD_OK && with_step) {
       Ref key(PyLong_FromUnsignedLongLong(sp.plan_key));
@@ -348,7 +359,7 @@ PyObject* py_sequence_plan_bytes(PyObject*, PyObject* const* a, Py_ssize_t n) {
     aspd_kv kv;
     int32_t B, NQ;
     if (!fill(a[0], &kv) || !int_of(a[1], &B) || !int_of(a[2], &NQ)) return nullptr;
-    return PyLong_FromSize_t(aspd_sequence_plan_bytes(&kv, B, NQ));
+    return PyLong_FromSize_t(g_lib.sequence_plan_bytes(&kv, B, NQ));
   });
 }
 
@@ -371,7 +382,7 @@ PyObject* py_build_sequence_meta(PyObject*, PyObject* const* a, Py_ssize_t n) {
     lay.run_len_d = (const int32_t*)run_len;
     int rc;
     Py_BEGIN_ALLOW_THREADS;
-    rc = aspd_build_sequence_meta(&kv, &st, &lay, pos_mode, &sp, stream);
+    rc = g_lib.build_sequence_meta(&kv, &st, &lay, pos_mode, &sp, stream);
     Py_END_ALLOW_THREADS;
     if (rc == ASPD_OK) {
       Ref key(PyLong_FromUnsignedLongLong(sp.plan_key));
@@ -393,9 +404,20 @@ PyObject* py_structs(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// (KVCache, BatchState, Step): the classes of the plain case
+// (KVCache, BatchState, Step, {name: address}): the classes of the plain case and the library's entry points
 PyObject* py_init(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 3, [&]() -> PyObject* {
+  return guarded(n, 4, [&]() -> PyObject* {
+    auto lib = g_lib;
+#define ASPD_LOOK_UP(name)                                                                                             \
+  {                                                                                                                    \
+    Ref address(PyMapping_GetItemString(a[3], "aspd_" #name));                                                         \
+    if (!address.o) return nullptr;                                                                                    \
+    lib.name = (decltype(lib.name))PyLong_AsVoidPtr(address.o);                                                        \
+    if (PyErr_Occurred()) return nullptr;                                                                              \
+  }
+    ASPD_CALLS(ASPD_LOOK_UP)
+#undef ASPD_LOOK_UP
+    g_lib = lib;
     PyObject** const to[3] = {&g_kv_type, &g_state_type, &g_step_type};
     for (int i = 0; i < 3; ++i) {
       Py_INCREF(a[i]);

@@ -1,5 +1,10 @@
 """The compiled half of the binding hands the library what the struct() methods say, in the plain case and in every other,
 and refuses what they refuse (no GPU needed: nothing here gets as far as a launch)."""
+import os
+import shutil
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -150,3 +155,22 @@ def test_what_is_no_whole_number_is_refused(number):
     st.pos_mode = number
     with pytest.raises(TypeError):
         A.aspd_build_branch_meta(kv, st, 9, one, step=sp, plan=False, stream=_Stream)
+
+
+def test_every_call_goes_to_the_library_that_lib_path_names(tmp_path):
+    """Another build of the library, named before the first call: the process holds that one alone."""
+    other = shutil.copy(A.LIB_PATH, tmp_path / "libaspd_other.so")
+    program = """
+import sys
+from paper_2508_08895_amd import binding as A
+A.LIB_PATH = sys.argv[1]
+import torch
+import test_binding_calls as T
+T.test_calls_reach_the_library_and_raise_what_it_says()
+loaded = {line.split()[-1] for line in open("/proc/self/maps") if "libaspd" in line}
+assert loaded == {sys.argv[1]}, loaded
+"""
+    here = os.path.dirname(os.path.abspath(__file__))
+    env = dict(os.environ, PYTHONPATH=os.pathsep.join([os.path.dirname(here), here, os.environ.get("PYTHONPATH", "")]))
+    run = subprocess.run([sys.executable, "-c", program, str(other)], env=env, capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stderr[-2000:]
