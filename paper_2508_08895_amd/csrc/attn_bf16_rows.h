@@ -654,12 +654,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
   // Of a piece: slot of its partial result (-1: the item is a whole row group), and what the merge asks for.  In LDS because
   // the loop over the pages needs the scalar registers.
   __shared__ int held[5];
-  const int n_groups = a.plan[0];
   const int Hkv = a.kv.num_kv_heads;
+  static_assert(SEQ_HDR_PIECES == 4 && SEQ_HDR_HEADS == 5 && SEQ_HDR_PLACES == 6, "in one load with the row groups");
+  const i32x8 hdr = load_words8(a.plan);
+  const int n_groups = hdr[0];
   // (places of partial results and arrivals were given away for so many heads: with others, or with fewer places, two row
   // groups would count on one word)
-  const bool listed = PIECES && a.plan[SEQ_HDR_HEADS] == Hkv && a.plan[SEQ_HDR_PLACES] <= a.parts;
-  const int n_pieces = listed ? min(a.plan[SEQ_HDR_PIECES], SEQ_ENTRIES) : 0;
+  const bool listed = (int)(hdr[SEQ_HDR_HEADS] == Hkv) & (int)(hdr[SEQ_HDR_PLACES] <= a.parts);
+  const int n_pieces = PIECES && listed ? min(hdr[SEQ_HDR_PIECES], SEQ_ENTRIES) : 0;
   const int32_t* items = a.plan + SEQ_PLAN_HDR + ((a.NQ + 3) & ~3);
   const long total = (long)(n_pieces > 0 ? n_pieces : n_groups) * Hkv;
   int* const take_from = a.counters + QUEUE_NEXT;
