@@ -96,6 +96,52 @@ def test_plan_of_large_batches_covers_every_page(B, blocks, new):
     assert set(read) == {(s, h, q) for s in range(B) for h in range(2) for q in range(first[s], first[s + 1], qpg)}
 
 
+@pytest.mark.parametrize("hkv,held,new,cap,queue", [
+    (8, [8000] * 33, 64, 0, False),    # 264 like items on 256 workgroups: two rounds, the second nearly empty
+    (8, [8000] * 64, 64, 0, True),     # two full rounds
+    (8, [8000] * 65, 64, 0, False),    # and eight items more
+    (8, [8000] * 48, 64, 0, False),
+    (8, [4000] * 33 + [8000] * 33, 64, 0, False),    # like items of two kinds
+    (8, [3900 + 9 * i for i in range(128)], 64, 0, True),
+    (8, [1000] * 36, 64, 0, False),
+    (8, [1000] * 48, 64, 0, True),     # short items: what a cut costs is more than the round that is half empty
+    (8, [0] * 33, 64, 0, True),
+    (8, [4000] * 33, 27, 0, False),
+    (2, [2000] * 3, 60, 5, False),     # six items, five workgroups
+    (2, [2000] * 5, 60, 5, True),
+    (1, [2000] * 500, 60, 1, True),    # (one workgroup takes them all, whole or not)
+    (8, [6000] + [100] * 300, 64, 0, False),         # one item long against a share
+])
+def test_whole_items_where_their_rounds_fill_the_workgroups(hkv, held, new, cap, queue):
+    """Chunks of like lengths, the number of items just above the workgroups and at whole rounds of them: whole items from a
+    queue (plan word 10) only where the last round costs no more than cutting does.  Either way every page of every item is
+    read once."""
+    B, have = len(held), np.asarray(held, dtype=np.int32)
+    blocks = (int(have.max()) + new + 15) // 16
+    pool = torch.zeros(1, hkv, 16, 64, dtype=torch.bfloat16, device="cuda")
+    kv = A.KVCache(pool, pool, torch.zeros(B, blocks, dtype=torch.int32, device="cuda"), 4 * hkv)
+    st = A.BatchState(B, blocks * 16, "cuda")
+    st.stage_base.copy_(torch.from_numpy(have))
+    st.seq_len.copy_(torch.from_numpy(have))
+    step = A.aspd_build_branch_meta(kv, st, A.STAGE_SERIAL, torch.full((B,), new, dtype=torch.int32, device="cuda"), NQ=B * new,
+                                    max_new_per_seq=new, max_workgroups=cap)
+    assert int(st.fault[0]) == 0
+    plan, nwg = step.plan.cpu().numpy().view(np.int32), step.plan_key >> 27 & 2047
+    assert nwg == (cap or 256) and B * hkv > nwg and (plan[10] > 0) == queue
+    read = {}
+    for w in range(nwg):
+        n, at = plan[32 * w + 8], plan[32 * w + 9]
+        segs = [plan[32 * w:32 * w + 8]] if n > 0 else []
+        segs += [plan[32 * nwg + 8 * (at + i):32 * nwg + 8 * (at + i + 1)] for i in range(n - 1)]
+        for d in segs:
+            s, h = int(d[0]) & 0xffff, int(d[0]) >> 16
+            assert d[1] == s * new and d[2] == new and d[5] == (have[s] + new + 15) // 16
+            assert 0 <= d[3] < d[4] <= d[5] and (not queue or (d[3] == 0 and d[4] == d[5]))
+            read.setdefault((s, h), np.zeros(d[5], dtype=int))[d[3]:d[4]] += 1
+    assert all((p == 1).all() for p in read.values())
+    assert set(read) == {(s, h) for s in range(B) for h in range(hkv)}
+
+
 @pytest.mark.parametrize("lengths", [[9001], [1, 513, 0, 2300], [300] * 70, [40, 0, 7] * 60])
 def test_metadata_of_whole_sequences_that_workgroups_share(lengths):
     """One to sixteen workgroups per sequence, sequences in one to three waves of the row groups' list."""
