@@ -460,7 +460,7 @@ __device__ __forceinline__ Shares build_schedule(const PlanArgs& a, const Sched&
   int* best = scratch + 7 * NWV;  // [2]: per round, the first candidate that fits
   if (tid < 2) best[tid] = 0x7fffffff;
   const int least = MIN_PAGES_PER_WG * page_cost(a, 1);
-  const int step = max(longest - least, 0) / (CANDIDATES * CANDIDATES) + 1;
+  const int step = max((longest - least + CANDIDATES * CANDIDATES - 2) / (CANDIDATES * CANDIDATES - 1), 1);  // (the last reaches longest)
   auto candidate = [&](int t) -> int { return min(max(longest, 1), least + t * step); };
   __syncthreads();
   if (items > 0 && items <= a.nwg) {

@@ -142,6 +142,25 @@ def test_whole_items_where_their_rounds_fill_the_workgroups(hkv, held, new, cap,
     assert set(read) == {(s, h) for s in range(B) for h in range(hkv)}
 
 
+@pytest.mark.parametrize("pages,new", [(433, 64), (432, 64), (2063, 1), (2062, 1), (40, 64)])
+def test_as_many_items_as_workgroups_stay_whole(pages, new):
+    """256 items of two nearly like lengths on 256 workgroups, an item each, also where only the last of the candidates for the
+    even pieces' cost reaches that of the longest (433 and 2063 pages)."""
+    B, hkv = 32, 8
+    have = 16 * (pages - 10 * (np.arange(B) >= 16)) - new
+    pool = torch.zeros(1, hkv, 16, 64, dtype=torch.bfloat16, device="cuda")
+    kv = A.KVCache(pool, pool, torch.zeros(B, pages, dtype=torch.int32, device="cuda"), 4 * hkv)
+    st = A.BatchState(B, pages * 16, "cuda")
+    st.stage_base.copy_(torch.from_numpy(have))
+    st.seq_len.copy_(torch.from_numpy(have))
+    step = A.aspd_build_branch_meta(kv, st, A.STAGE_SERIAL, torch.full((B,), new, dtype=torch.int32, device="cuda"), NQ=B * new,
+                                    max_new_per_seq=new, max_workgroups=256)
+    plan, nwg = step.plan.cpu().numpy().view(np.int32), step.plan_key >> 27 & 2047
+    hdr = plan[:32 * nwg].reshape(nwg, 32)
+    assert int(st.fault[0]) == 0 and nwg == B * hkv and (hdr[:, 8] == 1).all()
+    assert (hdr[:, 3] == 0).all() and np.array_equal(hdr[:, 4], ((have + new) // 16)[hdr[:, 0] & 0xffff])
+
+
 @pytest.mark.parametrize("lengths", [[9001], [1, 513, 0, 2300], [300] * 70, [40, 0, 7] * 60])
 def test_metadata_of_whole_sequences_that_workgroups_share(lengths):
     """One to sixteen workgroups per sequence, sequences in one to three waves of the row groups' list."""
