@@ -19,9 +19,10 @@
 // an unnormalised partial (running max, sum, accumulator); the workgroup that delivers the last partial
 // of an item combines them, in the same launch.
 //
-// One translation unit: attn_common.h (arguments, plan readers, partial slots), attn_bf16_math.h (one pair
-// of pages against a wave's rows), attn_bf16_stream.h (the streaming kernel), attn_bf16_rows.h (the
-// row-splitting kernels for chunks and whole sequences), attn_f32.h, attn_merge.h, and the host side below.
+// One translation unit: attn_common.h (arguments, plan readers, partial slots), attn_bf16_math.h (what the bf16
+// kernels share: how pages come into LDS and lie there, pieces of the running softmax), attn_bf16_stream.h (the streaming
+// kernel), attn_bf16_rows.h (the row-splitting kernels for chunks and whole sequences), attn_f32.h, attn_merge.h, and the
+// host side below.
 #include <algorithm>
 #include <cmath>
 #include <mutex>

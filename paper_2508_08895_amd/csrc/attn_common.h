@@ -21,7 +21,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;  // 16 bytes in registers (a native
                                                                   // vector, so arrays of it stay in VGPRs)
 
@@ -76,15 +75,11 @@ struct Seg {
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ i32x16 load_words16(const int32_t* p /* 64-byte aligned, uniform */) {
   return *(const __attribute__((address_space(4))) i32x16*)(uintptr_t)p;
 }
 __device__ __forceinline__ i32x8 load_words8(const int32_t* p /* 32-byte aligned, uniform */) {
   return *(const __attribute__((address_space(4))) i32x8*)(uintptr_t)p;
-}
-__device__ __forceinline__ i32x2 load_words2(const int32_t* p /* 8-byte aligned, uniform */) {
-  return *(const __attribute__((address_space(4))) i32x2*)(uintptr_t)p;
 }
 template <typename V>
 __device__ __forceinline__ Seg seg_of(const V& w) {
@@ -133,13 +128,10 @@ __device__ __forceinline__ float* partial_stat(const AttnArgs& a, float* slot, i
 __device__ __forceinline__ float exp2_safe_ref(float m) { return (m == -INFINITY) ? 0.f : m; }
 
 // Partials travel between workgroups that may sit on different XCDs, whose L2 caches are not kept
-// coherent for ordinary accesses.  Device-scope relaxed atomic stores write through and device-scope
-// atomic loads read past the local L2, so no cache write-back or invalidate is needed on this path.
+// coherent for ordinary accesses.  Device-scope relaxed atomic stores write through, so no cache write-back is needed on
+// this path; the workgroup that merges drops its own stale copies first (announce_partial).
 __device__ __forceinline__ void store_device_scope(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float load_device_scope(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // The same write-through store, 16 bytes wide (narrow write-through stores cost a partial-line
 // write each).  Callers order it like the 4-byte form: a later s_waitcnt vmcnt(0) covers it.
@@ -154,19 +146,10 @@ __device__ __forceinline__ void store_device_scope_x4(float* p, f32x4 v) {
 
 
 // What every kernel does first: its workgroup's header of the plan.  Returns the number of segments
-// (0: nothing to do, also for a header that fails seg_ok).  `ids`: the block ids of the pages
-// first_id, first_id + 1 of the first segment (first_id even, below PLAN_IDS).  Two loads, no branch
-// between them and their uses: scalar loads return in any order, so a wait between them would make each
-// a memory round trip of its own.
-__device__ __forceinline__ int plan_begin(const AttnArgs& a, Seg* first, int* next, int first_id = 0,
-                                          i32x2* ids = nullptr) {
+// (0: nothing to do, also for a header that fails seg_ok).
+__device__ __forceinline__ int plan_begin(const AttnArgs& a, Seg* first, int* next) {
   static_assert(PLAN_HDR_NSEG == 8 && PLAN_HDR_NEXT == 9, "segment and counts in one 64-byte load");
-  const int32_t* hdr = a.plan + (long)PLAN_HDR * blockIdx.x;
-  const i32x16 w = load_words16(hdr);
-  const i32x2 b = load_words2(hdr + PLAN_HDR_IDS + first_id);
-  // (both are needed here, so neither load is moved further down, behind other waits)
-  asm volatile("" ::"s"(w[0]), "s"(b[0]), "s"(b[1]));
-  if (ids) *ids = b;
+  const i32x16 w = load_words16(a.plan + (long)PLAN_HDR * blockIdx.x);
   *first = seg_of(w);
   *next = w[PLAN_HDR_NEXT];
   return ((int)(w[PLAN_HDR_NSEG] > 0) & (int)seg_ok(a, *first)) ? w[PLAN_HDR_NSEG] : 0;
