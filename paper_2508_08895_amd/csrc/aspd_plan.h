@@ -48,9 +48,11 @@ constexpr int PAD_STREAM = 32;       // fixed cost of a segment in pages, bandwi
 constexpr int PAD_COMPUTE = 8;       // the same for the fp32 kernel
 constexpr int PAD_ROWS = 32;         // and for the row-splitting kernel: a segment there costs about 17 us (Q operands
                                      // of 256 rows into registers, 64-128 KB of output or partial, its share of a
-                                     // merge), 25-40 pages' worth; steps with 16 / 32 / 48, us: 64-sequence chunk
-                                     // 1830 / 1750 / 1690, eight prompts 437 / 435 / 442, stage opening over 12
-                                     // sequences 317 each time
+                                     // merge), 25-40 pages' worth.  It decides where items are cut evenly and prices
+                                     // ragged shares.  One layer with 16 / 32 / 48, us: branch prefixes of 5 to 21 tokens
+                                     // behind 500 to 3 000 (20 sequences) 92 / 74 / 74, behind 200 to 9 000 (40) 257 /
+                                     // 240 / 248, behind 100 to 16 000 (40) 419 / 378 / 376, one prompt of 2 100 98 / 91 /
+                                     // 92, four of 600 73 / 74 / 80; the mean over 71 such steps 1.020 / 1 / 1.003
 
 constexpr int ROWS_PAGE_COST = 4;    // row-splitting kernel: a page takes 0.14 us + 0.038 us per wave that has rows
 static_assert(MAX_WG <= QUEUE_NEXT, "queue words");

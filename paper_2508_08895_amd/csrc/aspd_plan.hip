@@ -298,8 +298,8 @@ __device__ __forceinline__ int sum_before(const int* per_wave) {
 
 // QUEUE: sorts the row groups by cost (`bins`: the first place of each class) and returns the cost of the longest workgroup.
 // Its estimate: the item at rank k nwg, the first of a round, starts when the first of the workgroups gets free, which has
-// taken the last of every round before; what comes after it is shorter and starts on others.  Exact for two rounds and
-// for equal items.
+// taken the last of every round before; what comes after it is shorter and starts on others.  Exact for equal items, a little
+// low for others.
 __device__ __forceinline__ float queue_end(const PlanArgs& a, const Sched& sc, const Shares& sh, int* bins,
                                            int* scratch /* 3 * PLAN_THREADS / 64 */) {
   constexpr int NWV = PLAN_THREADS / 64;

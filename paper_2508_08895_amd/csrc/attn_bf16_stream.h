@@ -17,7 +17,7 @@ namespace {
 // 256 registers for everything else; and no cross-lane step, division or barrier that can be had otherwise.  Attention
 // alone in graph replay, four waves with pairs in registers -> this, us: one sequence of 2 300 tokens 14.8 -> 9.5; 27
 // mixed sequences of up to 3 000, head size 64 16.1 -> 11.7; 16 sequences of 512 to 4 096 45.2 -> 41.7; four of 16 k,
-// six branches 52.2 -> 49.6, after the merge 50.7 -> 45.2; 64 sequences of up to 8 192 231 -> 219 (6.2 TB/s).
+// six branches 52.2 -> 49.6, after the merge 50.7 -> 45.2; 64 sequences of up to 8 192 231 -> 219 (6.4 TB/s).
 //
 // S^T[key][row] = K * Q^T on 16x16x32 MFMA: lane (c, g) = (lane % 16, lane / 16) holds, of row c, the keys 4 g .. 4 g + 3
 // of the page, which is the B-operand layout of O^T[d][row] = V^T * P^T on 16x16x16 MFMA, whose A operand (V^T) comes
