@@ -1,0 +1,38 @@
+"""Rows of a wave that is not full, as the row-splitting kernels write them: 16-byte pieces that lanes exchange, sixteen rows
+at once.  Whole sequences whose last wave has 1, 15, 16, 17, 31 or 32 rows, every row against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import aspd_workloads as W
+from oracle import attend
+from oracle.sequence_layout import replay_layout
+
+pytestmark = pytest.mark.gpu
+
+TOL, LSE_TOL = 2e-2, 2e-3    # bf16 weights and results, 2^-9 each
+
+
+@pytest.mark.parametrize("heads", [(8, 8, 128), (4, 4, 64), (6, 2, 128)])
+@pytest.mark.parametrize("tokens", [1, 15, 16, 17, 31, 32, 33, 79, 271])
+def test_last_wave_of_a_row_group(heads, tokens):
+    from gpu_drive import GpuBatch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2508_08895_amd import binding as A
+    layouts = [[(0, tokens)], [(0, tokens // 2 + 1)]]
+    wl = W.random_small(seed=5900 + tokens, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2], batch=2,
+                        prefix_range=(tokens, tokens), branches_range=(1, 1), branch_len_range=(1, 1))
+    tt, meta = replay_layout(wl.block_tables, wl.block_size, layouts)
+    gb = GpuBatch(wl)
+    step = A.aspd_build_sequence_meta(gb.kv, gb.state, gb._dev_i32([0, 1, 2]), gb._dev_i32([0, 0]),
+                                      gb._dev_i32([r[0][1] for r in layouts]), NQ=meta.NQ)
+    q = wl.draw_q(meta.NQ)
+    # a row more than there are, which nothing may write
+    out = torch.full((meta.NQ + 1, *q.shape[1:]), float("nan"), dtype=q.dtype, device=gb.dev)
+    lse = torch.full((meta.NQ + 1, heads[0]), float("nan"), dtype=torch.float32, device=gb.dev)
+    A.aspd_attn_full_sequence(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace, out=out, lse=lse)
+    assert torch.isnan(out[meta.NQ]).all() and torch.isnan(lse[meta.NQ]).all()
+    ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache)
+    assert np.abs(out[:meta.NQ].float().cpu().numpy() - ref).max() <= TOL
+    assert np.abs(lse[:meta.NQ].cpu().numpy() - ref_lse).max() <= LSE_TOL
