@@ -179,30 +179,6 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
   }
   auto page_of_pair = [&](int p) -> int { return page0 + 2 * (p < hole_at ? p : p + hole); };
 
-  // ---- the loads of the start: this wave's row descriptors and Q operands, which go straight to registers, then its pages
-  // of the first two groups.  They return in that order, and a wait for a descriptor, which the compiler counts without
-  // the pages it does not know of, ends when the Q operands are there at the latest: what the rows have in common is
-  // worked out while the pages are on their way (first scores 7.1 -> 5.3 us after the launch's start; launches, us: stage
-  // opening over 12 sequences 59.6 -> 58.9, eight prompts 138.3 -> 137.3, three whole sequences 45.5 -> 45.1).
-  __syncthreads();  // LDS of the previous segment is free
-  bf16x8 qr[C::KSTEPS];
-  int slot, branch = 0, base = it.L, lo = 0;
-  {
-    const int rr = min(wave * 32 + c, R - 1);  // padding rows (and idle waves) repeat the last row
-    const int qi = div_by_g(a, rr), q = it.q0 + qi;
-    const int head = it.h * a.G + rr - qi * a.G;
-    slot = a.logical_slot[q];
-    if (SEQ) {
-      // (no owner tags: the shared mask, every row is treated like a main-branch row)
-      base = a.slot_owner ? a.row_base[q] : -1;
-      lo = a.slot_owner ? a.row_lo[q] : -1;
-    } else {
-      branch = a.q_branch[q];
-    }
-    const u32x4* qsrc = (const u32x4*)a.q + ((long)q * a.kv.num_q_heads + head) * C::CH + h;
-#pragma unroll
-    for (int t = 0; t < C::KSTEPS; ++t) qr[t] = __builtin_bit_cast(bf16x8, qsrc[2 * t]);
-  }
   // ---- staging.  Group i holds the K pages of pairs 2 i + 1 and 2 i + 2 and the V pages of pairs 2 i - 1 and
   // 2 i (what the two steps of the group multiply); wave w fetches one page of it.  Pages outside the segment
   // are fetched as the nearest one inside.  Their scores are not used; V pages that a step multiplies all the same, with
@@ -227,26 +203,59 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
 
   auto buffer_of = [&](int i) -> int { return i & (ROWS_BUFS - 1); };
   const int i_last = npairs >> 1;
-  int block = 0;  // block id of the group that is sent for next
-  auto send = [&](int i) {
+  // Block ids of the wave's pages of groups ids_from .. ids_from + 63, one per lane.  (A scalar load per group was waited for
+  // with the first operands of the next: LDS reads and scalar loads are counted together.  64-sequence chunk 1 449 -> 1 438
+  // us, 64 whole sequences 24.0 -> 23.9 ms.)
+  int ids_from = -1;
+  int ids = bt[page_of_group(ids_from + lane)];
+
+  // ---- the loads of the start: this wave's row descriptors and Q operands, which go straight to registers, then its pages
+  // of the first two groups.  They return in that order, and a wait for a descriptor, which the compiler counts without
+  // the pages it does not know of, ends when the Q operands are there at the latest: what the rows have in common is
+  // worked out while the pages are on their way (first scores 7.1 -> 5.3 us after the launch's start; launches, us: stage
+  // opening over 12 sequences 59.6 -> 58.9, eight prompts 138.3 -> 137.3, three whole sequences 45.5 -> 45.1).
+  __syncthreads();  // LDS of the previous segment is free
+  bf16x8 qr[C::KSTEPS];
+  int slot, branch = 0, base = it.L, lo = 0;
+  {
+    const int rr = min(wave * 32 + c, R - 1);  // padding rows (and idle waves) repeat the last row
+    const int qi = div_by_g(a, rr), q = it.q0 + qi;
+    const int head = it.h * a.G + rr - qi * a.G;
+    slot = a.logical_slot[q];
+    if (SEQ) {
+      // (no owner tags: the shared mask, every row is treated like a main-branch row)
+      base = a.slot_owner ? a.row_base[q] : -1;
+      lo = a.slot_owner ? a.row_lo[q] : -1;
+    } else {
+      branch = a.q_branch[q];
+    }
+    const u32x4* qsrc = (const u32x4*)a.q + ((long)q * a.kv.num_q_heads + head) * C::CH + h;
+#pragma unroll
+    for (int t = 0; t < C::KSTEPS; ++t) qr[t] = __builtin_bit_cast(bf16x8, qsrc[2 * t]);
+  }
+  auto send = [&](int i) {  // one group after the other
     if (i > i_last) return;
+    if (i - ids_from == 64) {
+      ids_from = i;
+      ids = bt[page_of_group(i + lane)];
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), here: where the register is read it would be waited for in every group
+      asm volatile("" : "+v"(ids));
+    }
+    const int block = __builtin_amdgcn_readlane(ids, i - ids_from);
     const char* src = pool + (long)min(max(block, 0), a.kv.num_blocks - 1) * a.kv.num_kv_heads * C::PAGE_B;
 #pragma unroll
     for (int k = 0; k < LPT; ++k) load_to_lds(src + k * 1024, goff ^ (k * goff_flip), l_at + buffer_of(i) * C::STAGE_B + k * 1024);
-    block = bt[page_of_group(i + 1)];
   };
   auto clear_v = [&](int i, int k) {
     *(__attribute__((address_space(3))) u32x4*)(uintptr_t)(l_at + buffer_of(i) * C::STAGE_B + k * 1024 + lane * 16) =
         u32x4{0u, 0u, 0u, 0u};
   };
   const int first_branch = !SEQ && a.cu_branches ? load_word_uniform(a.cu_branches + it.s) : 0;
-  block = bt[page_of_group(-1)];
   send(-1);
   if (!l_is_k && l_pair == 0) {  // V of pair -1, which the first full step multiplies with weights zero
 #pragma unroll
     for (int k = 0; k < LPT; ++k) clear_v(0, k);
     // (no load in flight for group 0 here: this wave's wait for group -1, whose V pages nobody reads, may come up early)
-    block = bt[page_of_group(1)];
   } else {
     send(0);
   }
@@ -391,21 +400,33 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
 #pragma unroll
     for (int t = 0; t < RV; ++t) vf[t] = v_operand(u, t);
   };
-  // `ahead`: the operands are there, and the first ones of slot 1 are fetched on the way
+  // `ahead`: the operands are there, and the first ones of slot 1 are fetched on the way.  The exponents are formed a slot
+  // before their weights, so that nothing in a slot waits for anything in it, and the additions are held where they stand
+  // (left to itself the compiler puts all sixteen, one waiting for the other, behind the last product).  Three whole
+  // sequences 129.8 -> 126.7 us, 64-sequence chunk 1 438 -> 1 426, eight prompts 375.6 -> 371.7, 64 whole sequences 23.9 ->
+  // 23.7 ms.
   auto step_full = [&](int u, bool ahead, const f32x16& s_cur, f32x16& s_next, const bf16x8 (&p_prev)[2], bf16x8 (&p_cur)[2]) {
     constexpr int PER = 16 / (2 * NP);  // weights per slot
-    float sum = 0.f;
+    float sum[2] = {0.f, 0.f}, x[PER], w_last = 0.f;
+    auto exponent = [&](int i) { return fmaf(s_cur[i], a.scale_log2, rs.neg_ref); };
     auto weights = [&](int slot_index) {
 #pragma unroll
       for (int e = 0; e < PER; ++e) {
         const int i = slot_index * PER + e;
-        const float w = __builtin_amdgcn_exp2f(fmaf(s_cur[i], a.scale_log2, rs.neg_ref));
-        sum += w;
+        const float w = __builtin_amdgcn_exp2f(x[e]);
+        if (i + PER < 16) x[e] = exponent(i + PER);
         p_cur[i >> 3][i & 7] = (__bf16)w;
+        if (i > 0) {
+          sum[i & 1] += w_last;
+          asm volatile("" : "+v"(sum[i & 1]));
+        }
+        w_last = w;
         // (converted here and not after the test of the sum, where sixteen registers would hold them until then)
         if ((i & 7) == 7) asm volatile("" : "+v"(p_cur[i >> 3]));
       }
     };
+#pragma unroll
+    for (int e = 0; e < PER; ++e) x[e] = exponent(e);
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
       s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j % RK], qr[j], j == 0 ? z : s_next, 0, 0, 0);
@@ -419,7 +440,7 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
       weights(2 * j + 1);
       __builtin_amdgcn_sched_barrier(0);
     }
-    return sum;
+    return sum[0] + sum[1] + w_last;
   };
   // The same for pairs that need a mask or are not seen at all, one part after the other.
   auto step = [&](int p, int u, const u32x4 (&tn)[2], f32x16& s_cur, f32x16& s_next, const bf16x8 (&p_prev)[2],

@@ -1,5 +1,5 @@
-"""Rows of a wave that is not full, as the row-splitting kernels write them: 16-byte pieces that lanes exchange, sixteen rows
-at once.  Whole sequences whose last wave has 1, 15, 16, 17, 31 or 32 rows, every row against the oracle."""
+"""Edges of the row-splitting kernels: rows of a wave that is not full (16-byte pieces that lanes exchange, sixteen rows at
+once), block ids of segments longer than the kernel holds at once, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -36,3 +36,25 @@ def test_last_wave_of_a_row_group(heads, tokens):
     ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache)
     assert np.abs(out[:meta.NQ].float().cpu().numpy() - ref).max() <= TOL
     assert np.abs(lse[:meta.NQ].cpu().numpy() - ref_lse).max() <= LSE_TOL
+
+
+@pytest.mark.parametrize("heads", [(2, 2, 128), (2, 1, 64)])
+@pytest.mark.parametrize("tokens", [4031, 4064, 4097, 4129, 8225])
+def test_block_ids_of_long_segments(heads, tokens):
+    """The kernel holds the block ids of 64 groups of four pages, the first of group -1, and reads them again from then on:
+    key ranges that end before, at and behind those lines, one workgroup each; rows in front of and behind the line."""
+    from gpu_drive import GpuBatch
+    from paper_2508_08895_amd import binding as A
+    wl = W.random_small(seed=6100 + tokens, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2], batch=1,
+                        prefix_range=(tokens, tokens), branches_range=(1, 1), branch_len_range=(1, 1))
+    tt, meta = replay_layout(wl.block_tables, wl.block_size, [[(0, tokens)]])
+    gb = GpuBatch(wl)
+    step = A.aspd_build_sequence_meta(gb.kv, gb.state, gb._dev_i32([0, 1]), gb._dev_i32([0]), gb._dev_i32([tokens]),
+                                      NQ=meta.NQ, max_workgroups=2)
+    q = wl.draw_q(meta.NQ)
+    out = A.aspd_attn_full_sequence(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace)
+    rows = sorted({0, 31, 4000, *range(4020, min(tokens, 4100), 7), *range(tokens - 40, tokens)})
+    ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache, rows=rows)
+    got = out.float().cpu().numpy()
+    assert np.isfinite(got).all()
+    assert np.abs(got[rows] - ref[rows]).max() <= TOL
