@@ -37,6 +37,16 @@ constexpr int PLAN_IDS = 16;
 
 // Words of the arrival counters that the queue uses (the row-splitting kernel, whose grid is smaller, has the others).
 constexpr int QUEUE_NEXT = 1022, QUEUE_DONE = 1023;
+// A whole-sequence launch has a queue per XCD from SEQ_QUEUE_ITEMS items a workgroup on.  What that gains is reads past the L2
+// and past the memory-side cache; what it costs is a search for work at the end, about 4 us a launch, and where row groups are
+// short the order by length.  One queue -> one per XCD, two layers, us: 64 sequences of 1 100 to 9 400 (one layer) 23 900 ->
+// 20 290; 9 of 2 150 to 6 900 (20 items) 1 880 -> 1 830; 13 of 1 200 to 3 200 (13) 1 359 -> 1 337; 24 of 500 to 2 000
+// 1 081 -> 1 073.  Below the line: 6 of 4 000 to 6 600 (8) 522 | 524, 40 of 400 (9) 526 | 539, 33 of 190 to 370 (5) 297 | 322,
+// 15 of 110 to 300 (2) 64 | 71.
+constexpr int SEQ_QUEUES_LOG2 = 3, SEQ_QUEUES = 1 << SEQ_QUEUES_LOG2;
+constexpr int SEQ_QUEUE_ITEMS = 12;
+constexpr int XCD_L2_BYTES = 4 << 20;
+constexpr int QUEUE_XCD = QUEUE_NEXT - SEQ_QUEUES;
 
 constexpr int MAX_WG = 512;          // upper bound of any attention grid
 constexpr int NT_MAX = 3;            // 16-row MFMA tiles per row group of the streaming bf16 kernel
@@ -55,7 +65,7 @@ constexpr int PAD_ROWS = 32;         // and for the row-splitting kernel: a segm
                                      // 92, four of 600 73 / 74 / 80; the mean over 71 such steps 1.020 / 1 / 1.003
 
 constexpr int ROWS_PAGE_COST = 4;    // row-splitting kernel: a page takes 0.14 us + 0.038 us per wave that has rows
-static_assert(MAX_WG <= QUEUE_NEXT, "queue words");
+static_assert(MAX_WG <= QUEUE_XCD, "queue words");
 
 enum AttnKernel { KERNEL_F32 = 0, KERNEL_BF16_STREAM = 1, KERNEL_BF16_ROWS = 2 };
 

@@ -169,13 +169,15 @@ __global__ __launch_bounds__(SEQ_META_THREADS) void meta_sequence_kernel(KvView 
 
 // The row groups of the attention launch: `qpg` consecutive tokens of one sequence each.  A group's key
 // range ends at its last token's slot, so groups late in a sequence cost more than early ones; workgroups
-// take groups from the list as they become free, and the list starts with the longest ranges so that
-// the launch does not end on a long one: round t lists, for every sequence that has that many, its
-// t-th group from the end.
+// take groups from the list as they become free.  Where the launch has a queue per XCD and one KV head's tokens of all
+// sequences are more than an L2 holds, the groups of a sequence follow each other, so that the workgroups of an XCD stream the
+// same pages, longest sequence and in it longest ranges first.  Otherwise the list starts with the longest ranges of all, so
+// that the launch does not end on a long one: round t lists, for every sequence that has that many, its t-th group from the
+// end.
 constexpr int WORKLIST_THREADS = 1024;
 __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(const int32_t* __restrict__ cu_seq_new,
                                                                  const int32_t* __restrict__ seq_len, int B, int NQ,
-                                                                 int qpg, int max_items, int num_kv_heads, int nwg,
+                                                                 int qpg, int max_items, int l2_items, int num_kv_heads, int nwg,
                                                                  int parts, int pieces_at, int32_t* __restrict__ plan) {
   __shared__ int ngr[ASPD_MAX_BATCH];
   __shared__ int first_item[ASPD_MAX_BATCH + 1];
@@ -218,7 +220,9 @@ __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(con
   const int n_items = first_item[B];
   int32_t* items = plan + SEQ_PLAN_HDR + ((NQ + 3) & ~3);
   // item (s, t): group ngr[s] - 1 - t of sequence s.  Its place in the list: the items of earlier rounds
-  // (min(ngr, t) of every sequence) and, in its own round, the sequences before s that still have a group.
+  // (min(ngr, t) of every sequence) and, in its own round, the sequences before s that still have a group; or, sequence by
+  // sequence, those of the longer sequences and its own t.
+  const bool in_rounds = n_items <= l2_items || n_items * num_kv_heads < SEQ_QUEUE_ITEMS * nwg;
   int group_place = 0, group_pages = 0;  // of this thread's row group (the first one, see below)
   for (int e = tid; e < n_items; e += blockDim.x) {
     int lo = 0, hi = B - 1;  // sequence of the e-th group in sequence-major order
@@ -230,7 +234,12 @@ __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(con
     const int gidx = e - first_item[s];     // group index within the sequence, 0 = first tokens
     const int t = ngr[s] - 1 - gidx;
     int place = 0;
-    for (int k = 0; k < B; ++k) place += min(ngr[k], t) + ((k < s && ngr[k] > t) ? 1 : 0);
+    if (in_rounds) {
+      for (int k = 0; k < B; ++k) place += min(ngr[k], t) + ((k < s && ngr[k] > t) ? 1 : 0);
+    } else {
+      for (int k = 0; k < B; ++k) place += ngr[k] > ngr[s] || (ngr[k] == ngr[s] && k < s) ? ngr[k] : 0;
+      place += t;
+    }
     const int T = seq_len[s];
     const int tok0 = gidx * qpg;
     const int nq = min(qpg, T - tok0);
@@ -373,7 +382,7 @@ extern "C" int aspd_build_sequence_meta(const aspd_kv* kv, aspd_state* state, co
   ASPD_HIP_CHECK(hipGetLastError());
   const int max_items = state->B + out->NQ / qpg;
   hipLaunchKernelGGL(sequence_worklist_kernel, dim3(1), dim3(WORKLIST_THREADS), 0, hs, out->cu_seq_new_d, state->seq_len_d, state->B,
-                     out->NQ, qpg, max_items, kv->num_kv_heads,
+                     out->NQ, qpg, max_items, XCD_L2_BYTES / (2 * 2 * kv->head_dim) / qpg, kv->num_kv_heads,
                      out->max_workgroups > 0 ? std::min(out->max_workgroups, aspd_device_cu_count()) : aspd_device_cu_count(),
                      aspd_sequence_may_cut(kv, state->B, out->NQ, qpg, aspd_device_cu_count())
                          ? aspd_sequence_parts(kv, state->B, out->NQ) : 0,

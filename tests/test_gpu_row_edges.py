@@ -58,3 +58,35 @@ def test_block_ids_of_long_segments(heads, tokens):
     got = out.float().cpu().numpy()
     assert np.isfinite(got).all()
     assert np.abs(got[rows] - ref[rows]).max() <= TOL
+
+
+@pytest.mark.parametrize("heads", [(1, 1, 64), (4, 2, 128), (3, 3, 64), (8, 4, 64), (12, 6, 64), (8, 8, 128), (32, 16, 64)])
+@pytest.mark.parametrize("cap", [1, 3, 9])
+def test_row_groups_from_a_queue_per_xcd(heads, cap):
+    """Every row group of every head is computed, whatever the heads' number has in common with the queues', with fewer
+    workgroups than queues and with more; the counters are left at zero (the second call finds the same)."""
+    from gpu_drive import GpuBatch
+    from paper_2508_08895_amd import binding as A
+    qpg = 256 // (heads[0] // heads[1])
+    need = 12 * cap * qpg // heads[1] + 1          # tokens from which on there is a queue per XCD
+    lengths = [need // 2, 0, need // 8 + 1, need // 2 + 37, 5]
+    wl = W.random_small(seed=6300 + cap, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2], batch=len(lengths),
+                        prefix_range=(max(lengths), max(lengths)), branches_range=(1, 1), branch_len_range=(1, 1))
+    layouts = [[(0, n)] for n in lengths]
+    tt, meta = replay_layout(wl.block_tables, wl.block_size, layouts)
+    gb = GpuBatch(wl)
+    step = A.aspd_build_sequence_meta(gb.kv, gb.state, gb._dev_i32(range(len(lengths) + 1)), gb._dev_i32([0] * len(lengths)),
+                                      gb._dev_i32(lengths), NQ=meta.NQ, max_workgroups=cap)
+    groups = sum(-(-n // qpg) for n in lengths)
+    assert groups * heads[1] >= 12 * cap
+    q = wl.draw_q(meta.NQ)
+    outs = []
+    for _ in range(2):
+        out = torch.full(q.shape, float("nan"), dtype=q.dtype, device=gb.dev)
+        A.aspd_attn_full_sequence(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace, out=out)
+        assert int(gb.workspace[:4096].view(torch.int32).abs().sum().item()) == 0
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1]) and torch.isfinite(outs[0]).all()
+    rows = list(range(0, meta.NQ, 1 if meta.NQ < 600 else 17))
+    ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache, rows=rows)
+    assert np.abs(outs[0].float().cpu().numpy()[rows] - ref[rows]).max() <= TOL
