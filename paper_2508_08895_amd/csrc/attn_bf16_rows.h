@@ -316,6 +316,11 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
     for (int mt = 0; mt < C::MT; ++mt)
       va[mt] = first + PPS * C::PAIR_B + key * (D * 2) +
                (((4 * mt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ C::vswz(key)) << 4) + 8 * (lane & 1);
+    // (one set of them, that moves: the compiler would keep those of the first stage beside these)
+#pragma unroll
+    for (int t = 0; t < C::KSTEPS; ++t) asm volatile("" : "+v"(ka[t]));
+#pragma unroll
+    for (int mt = 0; mt < C::MT; ++mt) asm volatile("" : "+v"(va[mt]));
   }
   auto next_group = [&](int i) {  // from group i's stage to the next
     const int d = buffer_of(i) == ROWS_BUFS - 1 ? -(ROWS_BUFS - 1) * C::STAGE_B : C::STAGE_B;
