@@ -64,7 +64,12 @@ constexpr int PAD_ROWS = 32;         // and for the row-splitting kernel: a segm
                                      // 240 / 248, behind 100 to 16 000 (40) 419 / 378 / 376, one prompt of 2 100 98 / 91 /
                                      // 92, four of 600 73 / 74 / 80; the mean over 71 such steps 1.020 / 1 / 1.003
 
-constexpr int ROWS_PAGE_COST = 4;    // row-splitting kernel: a page takes 0.14 us + 0.038 us per wave that has rows
+// Row-splitting kernel, cost of a page: ROWS_PAGE_COST and 1 per wave that has rows up to four, ROWS_FULL_COST more from five on
+// (measured in a stage opening over 12 sequences, us a page without a segment's start: 0.26 with four waves, 0.42 with five,
+// 0.43 with eight).  With 1 per wave up to eight -> this, us: that step 269.3 -> 260.1, 6 sequences of 1 000 to 6 000 with
+// chunks of 2 to 12 in 3 to 9 branches 123.0 -> 119.9, 30 of 1 000 to 8 000 368 -> 362; 13 other chunks between 0.989 and
+// 1.009 times as long.
+constexpr int ROWS_PAGE_COST = 4, ROWS_FULL_COST = 9;
 static_assert(MAX_WG <= QUEUE_XCD, "queue words");
 
 enum AttnKernel { KERNEL_F32 = 0, KERNEL_BF16_STREAM = 1, KERNEL_BF16_ROWS = 2 };

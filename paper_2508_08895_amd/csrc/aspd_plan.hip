@@ -107,9 +107,10 @@ __device__ __forceinline__ Groups groups_at(const PlanArgs& a, int T, int rows, 
   return g;
 }
 
-// Cost of a page of a row group of nq queries.
+// Cost of a page of a row group of nq queries.  From the fifth wave on a SIMD has two, and the others wait for it.
 __device__ __forceinline__ int page_cost(const PlanArgs& a, int nq) {
-  return a.w_page + a.w_wave * ((nq * a.rows_per_query + 31) / 32);
+  const int waves = (nq * a.rows_per_query + 31) / 32;
+  return a.w_page + a.w_wave * (waves > 4 ? ROWS_FULL_COST : waves);
 }
 // Queries of the last of a sequence's row groups.
 __device__ __forceinline__ int last_group(const PlanArgs& a, int rows, int n) { return rows - (n - 1) * a.qpg; }
