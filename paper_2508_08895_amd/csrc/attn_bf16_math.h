@@ -108,17 +108,22 @@ __device__ __forceinline__ float max8(const float (&x)[8]) {
   return m;
 }
 
+// A lane's value combined with that of the lane 32 further (both get the result), without LDS.
+template <typename F>
+__device__ __forceinline__ float over_halves(float v, F combine) {
+  const unsigned b = __builtin_bit_cast(unsigned, v);
+  const auto x = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  const unsigned x0 = x[0], x1 = x[1];  // (the compiler takes element 0 for a bit cast of x[1] itself)
+  return combine(__builtin_bit_cast(float, x0), __builtin_bit_cast(float, x1));
+}
+
 // A lane's value combined with that of the lanes 16 / 32 further (every lane gets the result), without LDS.
 template <typename F>
 __device__ __forceinline__ float over_quarters(float v, F combine) {
   const unsigned b = __builtin_bit_cast(unsigned, v);
   const auto x = __builtin_amdgcn_permlane16_swap(b, b, false, false);
   const unsigned x0 = x[0], x1 = x[1];  // (the compiler takes element 0 for a bit cast of x[1] itself)
-  const float h = combine(__builtin_bit_cast(float, x0), __builtin_bit_cast(float, x1));
-  const unsigned hb = __builtin_bit_cast(unsigned, h);
-  const auto y = __builtin_amdgcn_permlane32_swap(hb, hb, false, false);
-  const unsigned y0 = y[0], y1 = y[1];
-  return combine(__builtin_bit_cast(float, y0), __builtin_bit_cast(float, y1));
+  return over_halves(combine(__builtin_bit_cast(float, x0), __builtin_bit_cast(float, x1)), combine);
 }
 
 }  // namespace

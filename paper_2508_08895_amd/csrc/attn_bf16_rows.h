@@ -110,7 +110,7 @@ __device__ __forceinline__ float rows_raise(const f32x16& s, Rows32<D>& rs, bf16
     hi[i] = s[8 + i];
   }
   float mx = fmaxf(max8(lo), max8(hi));
-  mx = fmaxf(mx, __shfl_xor(mx, 32)) * scale_log2;  // scale > 0: the maximum commutes with it
+  mx = over_halves(mx, [](float x, float y) { return fmaxf(x, y); }) * scale_log2;  // scale > 0: the maximum commutes with it
   const float m_new = fmaxf(rs.m_run, mx);
   const float ref = exp2_safe_ref(m_new);
   const float alpha = __builtin_amdgcn_exp2f(rs.m_run - ref);
@@ -555,7 +555,7 @@ __device__ __forceinline__ int segment_rows(const AttnArgs& a, char* smem, const
   int taken = 0;
   if (take_from && tid == 0) taken = atomicAdd(take_from, 1);
   if (!wave_active) return taken;
-  rs.l_run += __shfl_xor(rs.l_run, 32);
+  rs.l_run = over_halves(rs.l_run, [](float x, float y) { return x + y; });
   const int r = wave * 32 + c;  // row inside the row group
   const Result to = result();
   if (to.complete) {
