@@ -67,6 +67,19 @@ size_t scratch_need(int head_dim, size_t plan_words, long nwg, int rows_cap) {
   return COUNTER_BYTES + plan_area_bytes(plan_words) + (size_t)2 * nwg * rows_cap * (head_dim + 4) * sizeof(float);
 }
 
+// Whether the partial results of a row-splitting launch are merged by a launch of their own, behind it.  The workgroup that
+// brings an item's last part merges by itself while the others have nothing to do, which is long where an item has many
+// parts and rows; the launch costs about 2 us, empty or not.  The line: four workgroups an item, as far as the host can count
+// items (a sequence has one per KV head at least, and so does every full row group).  Steps, merged in the launch -> behind
+// it, us: one sequence of 10 900, 204 rows (32 parts) 359 -> 161; one of 2 700, 140 rows 136 -> 93; two of up to 1 400, 230
+// rows 151 -> 129; six of 1 000 to 6 000 118 -> 105.  Below the line (three parts): stage opening over 12 sequences 260 | 272,
+// 9 of 1 600 to 9 800 273 | 303, 20 of 500 to 3 000 176 | 185.
+constexpr int MERGE_APART_PARTS = 4;
+bool merge_apart(const aspd_kv* kv, int B, int NQ, const AttnVariant& v) {
+  const long items = (long)std::max(B, (NQ + v.qpg - 1) / v.qpg) * kv->num_kv_heads;
+  return v.kernel == KERNEL_BF16_ROWS && MERGE_APART_PARTS * items <= v.nwg;
+}
+
 enum Mode { MODE_PARALLEL, MODE_CHUNK, MODE_SERIAL };
 
 int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const aspd_step* step, const void* q_d,
@@ -125,6 +138,7 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
   a.row_lo = nullptr;
   a.pieces = nullptr;
   a.parts = 0;
+  a.merge_apart = 0;
   a.NQ = step->NQ;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)kv->head_dim) : sm_scale) * LOG2E;
   a.B = state->B;
@@ -143,6 +157,7 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
     hipLaunchKernelGGL(KERNEL, dim3(a.nwg), dim3(NTHREADS), SMEM, hs, a);            \
     ASPD_HIP_CHECK(hipGetLastError());                                               \
   } while (0)
+  a.merge_apart = merge_apart(kv, state->B, step->NQ, v);
   if (v.kernel == KERNEL_BF16_ROWS) {
     if (D == 128)
       ASPD_LAUNCH((attn_bf16_rows_kernel<128, ROWS_NW>), ROWS_NW * 64,
@@ -150,6 +165,11 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
     else
       ASPD_LAUNCH((attn_bf16_rows_kernel<64, ROWS_NW>), ROWS_NW * 64,
                   (rows_smem_bytes<64>()));
+    if (a.merge_apart) {
+      if (D == 128) hipLaunchKernelGGL(merge_kernel<128>, dim3(a.nwg), dim3(MERGE_THREADS), 0, hs, a);
+      else hipLaunchKernelGGL(merge_kernel<64>, dim3(a.nwg), dim3(MERGE_THREADS), 0, hs, a);
+      ASPD_HIP_CHECK(hipGetLastError());
+    }
   } else if (v.kernel == KERNEL_BF16_STREAM) {
     // pages that no second row group reads are fetched with non-temporal loads
 #define ASPD_BF16_CASE(DD, NN)                                                                            \
@@ -315,6 +335,7 @@ extern "C" int aspd_attn_full_sequence(const aspd_kv* kv, const aspd_state* stat
   a.q = q_d;
   a.out = out_d;
   a.lse = lse_d;
+  a.merge_apart = 0;
   a.counters = (int*)workspace_d;
   // room for the partial results of the longest row groups' pieces, as a workspace of the size this library asks for has
   a.parts = aspd_sequence_parts(kv, state->B, step->NQ);

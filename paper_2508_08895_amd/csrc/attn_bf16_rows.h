@@ -657,7 +657,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
     const int taken = segment_rows<D, NW, false>(a, smem, seg, [=]() -> Result { return {complete, pslot}; },
                                                   queue > 0 ? a.counters + QUEUE_NEXT : nullptr);
-    if (!complete) announce_partial<D, true, THREADS, D / 16, 4>(a, seg, &merge_flag);
+    if (!complete && !a.merge_apart) announce_partial<D, true, THREADS, D / 16, 4>(a, seg, &merge_flag);
     int at;
     if (queue == 0) {
       if (i >= nseg) break;

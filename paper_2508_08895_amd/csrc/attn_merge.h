@@ -17,7 +17,7 @@ namespace {
 // are worked out once for all chunks of a thread (chunks of different rows before: 10 parts of 16 rows took 4.7 us of a
 // launch of 14.8; stage openings over 12 sequences, three parts of 180 rows 63.1 -> 59.9 us a layer).
 template <int D, bool BF16, int THREADS, int ELEMS, int BATCH>
-__device__ __forceinline__ void merge_parts(const AttnArgs& a, const Seg& it, int owner, int w_last) {
+__device__ __forceinline__ void merge_parts(const AttnArgs& a, const Seg& it, int owner, int w_last, int first_row, int R) {
   constexpr int LPR = D / 4 / ELEMS;     // threads per row
   constexpr int ROWS = THREADS / LPR;    // rows of a round
   // (defined here, so that nothing that is worked out from it lives in registers across the main loop)
@@ -26,9 +26,8 @@ __device__ __forceinline__ void merge_parts(const AttnArgs& a, const Seg& it, in
   const int c0 = tid % LPR;              // the thread's chunks: c0, c0 + LPR ..
   const long stride = (long)a.rows_cap * (D + 4) * sizeof(float);
   const int nparts = w_last - owner + 1;
-  const int R = it.nq * a.G;
   const char* const first = (const char*)(a.partial) + 2 * owner * stride;
-  for (int r0 = 0; r0 < R; r0 += ROWS) {
+  for (int r0 = first_row; r0 < R; r0 += ROWS) {
     const int r = r0 + tid / LPR;
     const uint32_t row_at = (uint32_t)min(r, R - 1);  // (rows past the last are the last again and not stored)
     const uint32_t at = row_at * (D * 4) + c0 * 16;
@@ -99,14 +98,14 @@ __device__ __forceinline__ void merge_parts(const AttnArgs& a, const Seg& it, in
 // costs its loads and its arithmetic whether a part stands behind it or not.
 template <int D, bool BF16, int THREADS, int ELEMS, int BATCH>
 __device__ __forceinline__ void merge_item(const AttnArgs& a, const Seg& it, int owner, int w_last) {
-  const int nparts = w_last - owner + 1;
-  if (nparts <= 2) merge_parts<D, BF16, THREADS, ELEMS, 2>(a, it, owner, w_last);
-  else if (BATCH > 3 && nparts <= 3) merge_parts<D, BF16, THREADS, ELEMS, 3>(a, it, owner, w_last);
-  else if (BATCH > 4 && nparts <= 4) merge_parts<D, BF16, THREADS, ELEMS, 4>(a, it, owner, w_last);
-  else if (BATCH > 6 && nparts <= 6) merge_parts<D, BF16, THREADS, ELEMS, 6>(a, it, owner, w_last);
-  else if (BATCH > 8 && nparts <= 8) merge_parts<D, BF16, THREADS, ELEMS, 8>(a, it, owner, w_last);
-  else if (BATCH > 12 && nparts <= 12) merge_parts<D, BF16, THREADS, ELEMS, 12>(a, it, owner, w_last);
-  else merge_parts<D, BF16, THREADS, ELEMS, BATCH>(a, it, owner, w_last);
+  const int nparts = w_last - owner + 1, R = it.nq * a.G;
+  if (nparts <= 2) merge_parts<D, BF16, THREADS, ELEMS, 2>(a, it, owner, w_last, 0, R);
+  else if (BATCH > 3 && nparts <= 3) merge_parts<D, BF16, THREADS, ELEMS, 3>(a, it, owner, w_last, 0, R);
+  else if (BATCH > 4 && nparts <= 4) merge_parts<D, BF16, THREADS, ELEMS, 4>(a, it, owner, w_last, 0, R);
+  else if (BATCH > 6 && nparts <= 6) merge_parts<D, BF16, THREADS, ELEMS, 6>(a, it, owner, w_last, 0, R);
+  else if (BATCH > 8 && nparts <= 8) merge_parts<D, BF16, THREADS, ELEMS, 8>(a, it, owner, w_last, 0, R);
+  else if (BATCH > 12 && nparts <= 12) merge_parts<D, BF16, THREADS, ELEMS, 12>(a, it, owner, w_last, 0, R);
+  else merge_parts<D, BF16, THREADS, ELEMS, BATCH>(a, it, owner, w_last, 0, R);
 }
 
 template <int D, bool BF16, int THREADS, int ELEMS, int BATCH>
@@ -131,6 +130,32 @@ __device__ __forceinline__ void announce_partial(const AttnArgs& a, const Seg& i
   if (threadIdx.x < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   __syncthreads();
   merge_item<D, BF16, THREADS, ELEMS, BATCH>(a, it, owner, w_last);
+}
+
+// The merge as a launch of its own, behind one of the row-splitting kernel that has left its partial results where they are:
+// every workgroup that holds a part of an item combines its share of the item's rows.  Bound by the round trips of a
+// workgroup, so a share is one round of rows: up to four parts 64 rows and four chunks a thread, more parts (and so fewer
+// rows) 16 rows and sixteen parts at once.
+constexpr int MERGE_THREADS = 512;
+template <int D>
+__global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(AttnArgs a) {
+  Seg seg;
+  int next;
+  const int queue = load_word_uniform(a.plan + (long)PLAN_HDR * blockIdx.x + PLAN_HDR_QUEUE);
+  const int nseg = plan_begin(a, &seg, &next);
+  if (queue > 0) return;  // whole items
+  // only the first and the last segment of a workgroup can be a part of an item
+  for (int i = 0; i < min(nseg, 2); ++i) {
+    if (i > 0) {
+      seg = plan_segment(a, next + nseg - 2);
+      if (!seg_ok(a, seg)) return;
+    }
+    if (seg_complete(seg)) continue;
+    const int n = seg.w_last - seg.owner + 1, p = (int)blockIdx.x - seg.owner, R = seg.nq * a.G;
+    const int lo = R * p / n, hi = R * (p + 1) / n;
+    if (n <= 4) merge_parts<D, true, MERGE_THREADS, 4, 4>(a, seg, seg.owner, seg.w_last, lo, hi);
+    else merge_parts<D, true, MERGE_THREADS, 1, 16>(a, seg, seg.owner, seg.w_last, lo, hi);
+  }
 }
 
 }  // namespace

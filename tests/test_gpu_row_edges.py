@@ -90,3 +90,37 @@ def test_row_groups_from_a_queue_per_xcd(heads, cap):
     rows = list(range(0, meta.NQ, 1 if meta.NQ < 600 else 17))
     ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache, rows=rows)
     assert np.abs(outs[0].float().cpu().numpy()[rows] - ref[rows]).max() <= TOL
+
+
+@pytest.mark.parametrize("heads", [(32, 8, 128), (8, 2, 64), (4, 4, 128)])
+@pytest.mark.parametrize("batch,prefix,branches,chunk", [(1, 900, 3, 11), (1, 1300, 2, 8), (2, 700, 4, 16), (1, 4200, 5, 17),
+                                                        (1, 8300, 2, 30), (3, 300, 9, 3)])
+@pytest.mark.parametrize("cap", [0, 40])
+def test_partial_results_merged_behind_the_launch(heads, batch, prefix, branches, chunk, cap):
+    """Chunks of few sequences, whose items have from two parts to 64: merged by a launch of its own where there are four
+    workgroups an item, with a share of the rows from none to a whole round (grids capped too); every row, and the bits of a
+    second call."""
+    from gpu_drive import GpuBatch
+    from oracle_drive import table_at
+    from paper_2508_08895_amd import binding as A
+    wl = W.random_small(seed=6500 + prefix, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2], batch=batch,
+                        prefix_range=(prefix, prefix + 90), branches_range=(branches, branches), branch_len_range=(1, 9),
+                        extra_tokens_per_branch=chunk + 1)
+    gb = GpuBatch(wl)
+    gb.grow_to(wl.branch_len)
+    tt = table_at(wl, wl.branch_len)
+    new = np.full(wl.NB, chunk, dtype=np.int32)
+    meta = tt.append_parallel(new)
+    step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_PARALLEL, gb._dev_i32(new), NQ=meta.NQ,
+                                    max_new_per_seq=branches * chunk, max_workgroups=cap)
+    q = wl.draw_q(meta.NQ)
+    out = torch.full((meta.NQ + 1, *q.shape[1:]), float("nan"), dtype=q.dtype, device=gb.dev)
+    lse = torch.full((meta.NQ + 1, heads[0]), float("nan"), dtype=torch.float32, device=gb.dev)
+    A.aspd_attn_branch_chunk(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace, out=out, lse=lse)
+    first = out.clone()
+    A.aspd_attn_branch_chunk(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace, out=out, lse=lse)
+    assert torch.equal(out[:meta.NQ], first[:meta.NQ])
+    assert torch.isnan(out[meta.NQ]).all() and torch.isnan(lse[meta.NQ]).all()
+    ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache)
+    assert np.abs(out[:meta.NQ].float().cpu().numpy() - ref).max() <= TOL
+    assert np.abs(lse[:meta.NQ].cpu().numpy() - ref_lse).max() <= LSE_TOL
