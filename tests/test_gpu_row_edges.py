@@ -124,3 +124,30 @@ def test_partial_results_merged_behind_the_launch(heads, batch, prefix, branches
     ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache)
     assert np.abs(out[:meta.NQ].float().cpu().numpy() - ref).max() <= TOL
     assert np.abs(lse[:meta.NQ].cpu().numpy() - ref_lse).max() <= LSE_TOL
+
+
+@pytest.mark.parametrize("heads,prefix,branches", [((32, 8, 128), 4300, 9), ((32, 8, 128), 4100, 12), ((24, 4, 128), 9000, 7),
+                                                   ((16, 4, 64), 9100, 10), ((16, 4, 64), 6000, 10), ((32, 8, 128), 2000, 12)])
+def test_decode_with_three_tiles_merged_behind_the_launch(heads, prefix, branches):
+    """One token of 33 to 48 rows a KV head behind many parts, on either side of the line from which a launch of its own
+    merges them."""
+    from gpu_drive import GpuBatch
+    from oracle_drive import table_at
+    from paper_2508_08895_amd import binding as A
+    wl = W.random_small(seed=6700 + prefix + branches, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2], batch=1,
+                        prefix_range=(prefix, prefix), branches_range=(branches, branches), branch_len_range=(1, 9))
+    gb = GpuBatch(wl)
+    gb.grow_to(wl.branch_len)
+    tt = table_at(wl, wl.branch_len)
+    for _ in range(2):
+        new = np.ones(wl.NB, dtype=np.int32)
+        meta = tt.append_parallel(new)
+        step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_PARALLEL, gb._dev_i32(new), NQ=meta.NQ, max_new_per_seq=branches)
+        q = wl.draw_q(meta.NQ)
+        out = torch.full((meta.NQ + 1, *q.shape[1:]), float("nan"), dtype=q.dtype, device=gb.dev)
+        lse = torch.full((meta.NQ + 1, heads[0]), float("nan"), dtype=torch.float32, device=gb.dev)
+        A.aspd_attn_parallel_decode(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace, out=out, lse=lse)
+        assert torch.isnan(out[meta.NQ]).all() and torch.isnan(lse[meta.NQ]).all()
+        ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache)
+        assert np.abs(out[:meta.NQ].float().cpu().numpy() - ref).max() <= TOL
+        assert np.abs(lse[:meta.NQ].cpu().numpy() - ref_lse).max() <= LSE_TOL
