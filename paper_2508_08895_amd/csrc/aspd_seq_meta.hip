@@ -223,6 +223,13 @@ __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(con
   // (min(ngr, t) of every sequence) and, in its own round, the sequences before s that still have a group; or, sequence by
   // sequence, those of the longer sequences and its own t.
   const bool in_rounds = n_items <= l2_items || n_items * num_kv_heads < SEQ_QUEUE_ITEMS * nwg;
+  __shared__ int longer[ASPD_MAX_BATCH];  // items of the sequences listed before (a loop over them for every item took 20 us)
+  if (!in_rounds && tid < B) {
+    int before = 0;
+    for (int k = 0; k < B; ++k) before += ngr[k] > mine || (ngr[k] == mine && k < tid) ? ngr[k] : 0;
+    longer[tid] = before;
+  }
+  __syncthreads();
   int group_place = 0, group_pages = 0;  // of this thread's row group (the first one, see below)
   for (int e = tid; e < n_items; e += blockDim.x) {
     int lo = 0, hi = B - 1;  // sequence of the e-th group in sequence-major order
@@ -237,8 +244,7 @@ __global__ __launch_bounds__(WORKLIST_THREADS) void sequence_worklist_kernel(con
     if (in_rounds) {
       for (int k = 0; k < B; ++k) place += min(ngr[k], t) + ((k < s && ngr[k] > t) ? 1 : 0);
     } else {
-      for (int k = 0; k < B; ++k) place += ngr[k] > ngr[s] || (ngr[k] == ngr[s] && k < s) ? ngr[k] : 0;
-      place += t;
+      place = longer[s] + t;
     }
     const int T = seq_len[s];
     const int tok0 = gidx * qpg;
