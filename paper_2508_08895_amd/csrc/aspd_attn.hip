@@ -17,7 +17,7 @@
 // processed against a KV page while it is in the workgroup's LDS, so the shared prefix is fetched once
 // for all branches.  A segment that covers its item completely writes the output; otherwise it writes
 // an unnormalised partial (running max, sum, accumulator); the workgroup that delivers the last partial
-// of an item combines them, in the same launch.
+// of an item combines them, in the same launch, or where items are few a launch behind it does (merge_apart).
 //
 // One translation unit: attn_common.h (arguments, plan readers, partial slots), attn_bf16_math.h (what the bf16
 // kernels share: how pages come into LDS and lie there, pieces of the running softmax), attn_bf16_stream.h (the streaming

@@ -10,7 +10,7 @@ namespace {
 // announces it on the item's counter (indexed by the workgroup in whose share the item starts);
 // the one that arrives last combines all partials and writes the output.  No workgroup waits for
 // another.  The partials are the "starts item" slot of the first workgroup and the "continues
-// item" slots of the following ones.
+// item" slots of the following ones.  (Where items are few, many parts each, merge_kernel below does it instead.)
 // ---------------------------------------------------------------------------------------------
 // A thread combines ELEMS 16-byte chunks of one row at a time, BATCH parts of each: all their loads and those of the row's
 // statistics are on their way at once, and nothing goes through LDS.  Bound by the instructions issued, so a row's weights
