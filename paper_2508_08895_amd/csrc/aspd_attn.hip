@@ -17,7 +17,7 @@
 // processed against a KV page while it is in the workgroup's LDS, so the shared prefix is fetched once
 // for all branches.  A segment that covers its item completely writes the output; otherwise it writes
 // an unnormalised partial (running max, sum, accumulator); the workgroup that delivers the last partial
-// of an item combines them, in the same launch, or where items are few a launch behind it does (merge_apart).
+// of an item combines them, in the same launch, or for many rows of few items a launch behind it does (merge_apart).
 //
 // One translation unit: attn_common.h (arguments, plan readers, partial slots), attn_bf16_math.h (what the bf16
 // kernels share: how pages come into LDS and lie there, pieces of the running softmax), attn_bf16_stream.h (the streaming
@@ -67,22 +67,20 @@ size_t scratch_need(int head_dim, size_t plan_words, long nwg, int rows_cap) {
   return COUNTER_BYTES + plan_area_bytes(plan_words) + (size_t)2 * nwg * rows_cap * (head_dim + 4) * sizeof(float);
 }
 
-// Whether the partial results of a launch are merged by a launch of their own, behind it.  The workgroup that brings an item's
-// last part merges by itself while the others have nothing to do, which is long where an item has many parts and rows; the
-// launch costs about 2 us, empty or not.
-// Row-splitting kernel.  The line: four workgroups an item, as far as the host can count items (a sequence has one per KV
-// head at least, and so does every full row group).  Steps, merged in the launch -> behind it, us: one sequence of 10 900, 204
-// rows (32 parts) 359 -> 161; one of 2 700, 140 rows 136 -> 93; two of up to 1 400, 230 rows 151 -> 129; six of 1 000 to
-// 6 000 118 -> 105.  Below the line (three parts): stage opening over 12 sequences 260 | 272, 9 of 1 600 to 9 800 273 | 303, 20
-// of 500 to 3 000 176 | 185.
-// Streaming kernel.  Only with three tiles of rows, and 16 parts of 128 floats a row.  Two layers, us: ten branches behind
-// 8 000 74.4 -> 63.3, behind 16 000 79.6 -> 71.3, two sequences of 3 000 61.7 -> 58.7, 4 KV heads of 64 behind 16 000 65.1 ->
-// 61.4.  Below the line: 4 heads of 64 behind 6 000 (24 parts) 48.6 | 52.4; one tile behind 16 000 57.9 | 61.0, two of
-// 16 000 with two tiles 79.2 | 83.3.
-constexpr int MERGE_APART_PARTS = 4, MERGE_APART_STREAM = 16 * 128;
+// Whether the partial results of a row-splitting launch are merged by a launch of their own, behind it.  The workgroup that
+// brings an item's last part merges by itself while the others have nothing to do, which is long where an item has many
+// parts and rows; the launch costs about 2 us, empty or not.  The line: four workgroups an item, as far as the host can count
+// items (a sequence has one per KV head at least, and so does every full row group).  Steps, merged in the launch -> behind
+// it, us: one sequence of 10 900, 204 rows (32 parts) 359 -> 161; one of 2 700, 140 rows 136 -> 93; two of up to 1 400, 230
+// rows 151 -> 129; six of 1 000 to 6 000 118 -> 105.  Below the line (three parts): stage opening over 12 sequences 260 | 272,
+// 9 of 1 600 to 9 800 273 | 303, 20 of 500 to 3 000 176 | 185.
+// (Not the streaming kernel's: its parts have few rows, and the host, which knows the width of the block table but no
+// sequence's length, cannot tell many of them from none.  Four layers behind 300 / 1 000 / 4 000 / 8 000 / 16 000 tokens in a
+// table of 2 048 blocks, in the launch | behind it, us: ten branches 74 | 81, 80 | 90, 103 | 103, 135 | 114, 149 | 130; four
+// branches in a step without a bound on its tokens 63 | 70, behind 2 000 79 | 83, behind 8 000 123 | 107.)
+constexpr int MERGE_APART_PARTS = 4;
 bool merge_apart(const aspd_kv* kv, int B, int NQ, const AttnVariant& v) {
   const long items = (long)std::max(B, (NQ + v.qpg - 1) / v.qpg) * kv->num_kv_heads;
-  if (v.kernel == KERNEL_BF16_STREAM) return v.nt == NT_MAX && MERGE_APART_STREAM * items <= (long)v.nwg * kv->head_dim;
   return v.kernel == KERNEL_BF16_ROWS && MERGE_APART_PARTS * items <= v.nwg;
 }
 
@@ -171,6 +169,11 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
     else
       ASPD_LAUNCH((attn_bf16_rows_kernel<64, ROWS_NW>), ROWS_NW * 64,
                   (rows_smem_bytes<64>()));
+    if (a.merge_apart) {
+      if (D == 128) hipLaunchKernelGGL(merge_kernel<128>, dim3(a.nwg), dim3(MERGE_THREADS), 0, hs, a);
+      else hipLaunchKernelGGL(merge_kernel<64>, dim3(a.nwg), dim3(MERGE_THREADS), 0, hs, a);
+      ASPD_HIP_CHECK(hipGetLastError());
+    }
   } else if (v.kernel == KERNEL_BF16_STREAM) {
     // pages that no second row group reads are fetched with non-temporal loads
 #define ASPD_BF16_CASE(DD, NN)                                                                            \
@@ -195,11 +198,6 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
     else ASPD_LAUNCH(attn_f32_kernel<64>, THREADS, f32_smem_bytes<64>());
   }
 #undef ASPD_LAUNCH
-    if (a.merge_apart) {
-      if (D == 128) hipLaunchKernelGGL(merge_kernel<128>, dim3(a.nwg), dim3(MERGE_THREADS), 0, hs, a);
-      else hipLaunchKernelGGL(merge_kernel<64>, dim3(a.nwg), dim3(MERGE_THREADS), 0, hs, a);
-      ASPD_HIP_CHECK(hipGetLastError());
-    }
   return ASPD_OK;
 }
 

@@ -415,8 +415,7 @@ attn_bf16_kernel(AttnArgs a) {
     const bool complete = seg_complete(seg);
     float* pslot = partial_slot(a, blockIdx.x, seg.page0 == 0 ? 1 : 0, D);
     segment_stream<D, NT, STREAM>(a, smem, seg, complete, pslot, id0, id1);
-    if (!complete && !(NT == NT_MAX && a.merge_apart))  // (with fewer tiles the test alone costs 0.1 us)
-      announce_partial<D, true, NW * 64, MERGE, (MERGE == 4 ? 6 : 16 / MERGE)>(a, seg, &merge_flag);
+    if (!complete) announce_partial<D, true, NW * 64, MERGE, (MERGE == 4 ? 6 : 16 / MERGE)>(a, seg, &merge_flag);
     if (++i >= nseg) break;
     seg = after;
     if (!seg_ok(a, seg)) break;

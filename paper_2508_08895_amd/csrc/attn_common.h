@@ -50,7 +50,7 @@ struct AttnArgs {
   const int32_t* row_lo;        // ... and the first slot of its own branch there
   const int32_t* pieces;        // ... their list of pieces, and how many pieces `partial` (null: none) has slots for
   int            parts;
-  int            merge_apart;   // partial results are left for a launch of their own
+  int            merge_apart;   // row-splitting launches: partial results are left for a launch of their own
 };
 
 // r / G for a row of a row group.  Exact: (r + 1/2) / G is at least 1 / (2 G) away from a whole number, and r < 768.

@@ -132,7 +132,7 @@ __device__ __forceinline__ void announce_partial(const AttnArgs& a, const Seg& i
   merge_item<D, BF16, THREADS, ELEMS, BATCH>(a, it, owner, w_last);
 }
 
-// The merge as a launch of its own, behind one that has left its partial results where they are:
+// The merge as a launch of its own, behind one of the row-splitting kernel that has left its partial results where they are:
 // every workgroup that holds a part of an item combines its share of the item's rows.  Bound by the round trips of a
 // workgroup, so a share is one round of rows: up to four parts 64 rows and four chunks a thread, more parts (and so fewer
 // rows) 16 rows and sixteen parts at once.

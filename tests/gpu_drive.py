@@ -1,5 +1,7 @@
 """Test helper: drive the GPU library (through the Python binding of the C ABI) along the same
 append history the oracle replays.  Only the binding and the input generators are used here."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -98,3 +100,28 @@ def assert_state_equal(gb, tt):
         assert np.array_equal(own_g[s, L[s]:T[s]], own_o[s, L[s]:T[s]]), s
     assert st.stage_open.cpu().numpy().astype(bool).tolist() == [bool(x) for x in tt.cur_parallel]
     assert gb.fault() == 0
+
+
+def kernels_of(call) -> int:
+    """Kernels that `call` launches, counted in a captured graph.  It has run once before (a kernel's first launch sets an
+    attribute) and is not run here."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip = A.lib()    # (its dependencies' symbols come with it)
+    raw, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * max(count.value, 1))()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    kernels = 0
+    for n in nodes[:count.value]:
+        kind = ctypes.c_int(-1)
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(n), ctypes.byref(kind)) == 0
+        kernels += kind.value == 0    # hipGraphNodeTypeKernel
+    return kernels
+
+
+def widen_tables(wl, blocks) -> None:
+    """Block tables of at least `blocks` columns, as a program has them that makes them for its longest context."""
+    more = max(0, blocks - wl.block_tables.shape[1])
+    wl.block_tables = np.pad(wl.block_tables, ((0, 0), (0, more)), constant_values=-1)

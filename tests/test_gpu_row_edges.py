@@ -128,9 +128,8 @@ def test_partial_results_merged_behind_the_launch(heads, batch, prefix, branches
 
 @pytest.mark.parametrize("heads,prefix,branches", [((32, 8, 128), 4300, 9), ((32, 8, 128), 4100, 12), ((24, 4, 128), 9000, 7),
                                                    ((16, 4, 64), 9100, 10), ((16, 4, 64), 6000, 10), ((32, 8, 128), 2000, 12)])
-def test_decode_with_three_tiles_merged_behind_the_launch(heads, prefix, branches):
-    """One token of 33 to 48 rows a KV head behind many parts, on either side of the line from which a launch of its own
-    merges them."""
+def test_decode_with_three_tiles_and_many_parts(heads, prefix, branches):
+    """One token of 33 to 48 rows a KV head behind key ranges of ten to 35 parts."""
     from gpu_drive import GpuBatch
     from oracle_drive import table_at
     from paper_2508_08895_amd import binding as A
@@ -151,3 +150,39 @@ def test_decode_with_three_tiles_merged_behind_the_launch(heads, prefix, branche
         ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache)
         assert np.abs(out[:meta.NQ].float().cpu().numpy() - ref).max() <= TOL
         assert np.abs(lse[:meta.NQ].cpu().numpy() - ref_lse).max() <= LSE_TOL
+
+
+@pytest.mark.parametrize("heads,prefix,branches,hint", [((32, 8, 128), 300, 12, True), ((32, 8, 128), 300, 4, False),
+                                                        ((32, 8, 128), 4100, 4, False), ((16, 4, 64), 9100, 10, True),
+                                                        ((24, 4, 128), 2000, 7, True)])
+@pytest.mark.parametrize("columns", [0, 1024])
+@pytest.mark.parametrize("static", [False, True])
+def test_decode_is_one_launch(heads, prefix, branches, hint, columns, static):
+    """Whatever the width of the block table, with the bound on a step's tokens and without: an attention call of a decoding
+    step that brings its plan launches one kernel.  (A second one for the merge, chosen by the table's width, cost steps behind
+    short contexts 2 us a layer.)"""
+    from gpu_drive import GpuBatch, kernels_of, widen_tables
+    from oracle_drive import table_at
+    from paper_2508_08895_amd import binding as A
+    wl = W.random_small(seed=6900 + prefix + branches, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2], batch=1,
+                        prefix_range=(prefix, prefix), branches_range=(branches, branches), branch_len_range=(1, 9))
+    widen_tables(wl, columns)
+    gb = GpuBatch(wl)
+    gb.grow_to(wl.branch_len)
+    tt = table_at(wl, wl.branch_len)
+    new = np.ones(wl.NB, dtype=np.int32)
+    meta = tt.append_parallel(new)
+    step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_PARALLEL, gb._dev_i32(new), NQ=meta.NQ,
+                                    max_new_per_seq=branches if hint else 0)
+    q = wl.draw_q(meta.NQ)
+    qd, out = q.to(gb.dev), torch.full((meta.NQ, heads[0], heads[2]), float("nan"), dtype=q.dtype, device=gb.dev)
+
+    def call():
+        if static:
+            A.aspd_attn_parallel_decode_static(gb.kv, gb.state, step, qd, out)
+        else:
+            A.aspd_attn_parallel_decode(gb.kv, gb.state, step, qd, gb.workspace, out=out)
+    call()
+    ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache)
+    assert np.abs(out.float().cpu().numpy() - ref).max() <= TOL
+    assert kernels_of(call) == 1
