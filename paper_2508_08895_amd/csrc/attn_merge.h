@@ -134,8 +134,12 @@ __device__ __forceinline__ void announce_partial(const AttnArgs& a, const Seg& i
 
 // The merge as a launch of its own, behind one of the row-splitting kernel that has left its partial results where they are:
 // every workgroup that holds a part of an item combines its share of the item's rows.  Bound by the round trips of a
-// workgroup, so a share is one round of rows: up to four parts 64 rows and four chunks a thread, more parts (and so fewer
-// rows) 16 rows and sixteen parts at once.
+// workgroup: one for every batch of parts, of every round of its rows.  So a class of parts takes all of them at once, and as
+// many chunks of a row a thread as the registers then hold, which makes a round (head size 128) 64 rows up to five parts, 32
+// up to twelve and 16 above: the share of a full row group is one round with 4, 5, 8 to 12 and from 16 parts on, and two with
+// the others.  (One class for all from five parts on, sixteen of them at once: four rounds with five parts, most of whose
+// loads were the last part again.  Four layers, one / three / six sequences behind 1 000 tokens 137 -> 108, 162 -> 126, 152
+// -> 122 us.)
 constexpr int MERGE_THREADS = 512;
 template <int D>
 __global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(AttnArgs a) {
@@ -153,7 +157,10 @@ __global__ __launch_bounds__(MERGE_THREADS) void merge_kernel(AttnArgs a) {
     if (seg_complete(seg)) continue;
     const int n = seg.w_last - seg.owner + 1, p = (int)blockIdx.x - seg.owner, R = seg.nq * a.G;
     const int lo = R * p / n, hi = R * (p + 1) / n;
-    if (n <= 4) merge_parts<D, true, MERGE_THREADS, 4, 4>(a, seg, seg.owner, seg.w_last, lo, hi);
+    if (n <= 3) merge_parts<D, true, MERGE_THREADS, 4, 3>(a, seg, seg.owner, seg.w_last, lo, hi);
+    else if (n <= 5) merge_parts<D, true, MERGE_THREADS, 4, 5>(a, seg, seg.owner, seg.w_last, lo, hi);
+    else if (n <= 8) merge_parts<D, true, MERGE_THREADS, 2, 8>(a, seg, seg.owner, seg.w_last, lo, hi);
+    else if (n <= 12) merge_parts<D, true, MERGE_THREADS, 2, 12>(a, seg, seg.owner, seg.w_last, lo, hi);
     else merge_parts<D, true, MERGE_THREADS, 1, 16>(a, seg, seg.owner, seg.w_last, lo, hi);
   }
 }

@@ -125,3 +125,24 @@ def widen_tables(wl, blocks) -> None:
     """Block tables of at least `blocks` columns, as a program has them that makes them for its longest context."""
     more = max(0, blocks - wl.block_tables.shape[1])
     wl.block_tables = np.pad(wl.block_tables, ((0, 0), (0, more)), constant_values=-1)
+
+
+def row_splitting_grid(wl, NQ, max_new_per_seq, cap=0) -> int:
+    """Workgroups of a launch of the row-splitting kernel on a device of at least 256 compute units."""
+    G = wl.num_q_heads // wl.num_kv_heads
+    assert max_new_per_seq * G > 48 and NQ * G > 48    # what sends a step to that kernel
+    items = (wl.B + NQ // (256 // G)) * wl.num_kv_heads
+    return min(256, max(-(-items * wl.max_blocks_per_seq // 16), items), cap or 256)
+
+
+def planned_parts(step, nwg) -> list:
+    """Parts of the items that the step's plan splits, one entry per item.  (Headers of 32 words per workgroup: of its first
+    segment, word 3 first page, 4 page behind the last, 5 pages of the item, 6 first | last << 16 workgroup that holds a part;
+    word 8 segments.  The last workgroup of a split item has it as its first segment.)"""
+    words = step.plan[:4 * 32 * nwg].view(torch.int32).view(nwg, 32).cpu().numpy()
+    parts = {}
+    for w in words[words[:, 8] > 0]:
+        if not (w[3] == 0 and w[4] == w[5]):
+            owner, last = int(w[6]) & 0xffff, int(w[6]) >> 16
+            parts[owner] = last - owner + 1
+    return sorted(parts.values())

@@ -97,9 +97,9 @@ def test_row_groups_from_a_queue_per_xcd(heads, cap):
                                                         (1, 8300, 2, 30), (3, 300, 9, 3)])
 @pytest.mark.parametrize("cap", [0, 40])
 def test_partial_results_merged_behind_the_launch(heads, batch, prefix, branches, chunk, cap):
-    """Chunks of few sequences, whose items have from two parts to 64: merged by a launch of its own where there are four
-    workgroups an item, with a share of the rows from none to a whole round (grids capped too); every row, and the bits of a
-    second call."""
+    """Chunks of few sequences, whose items have from two parts to 34 (those of up to 48 rows a KV head run the streaming
+    kernel): merged by a launch of its own where there are four workgroups an item, with a share of the rows from none to a
+    whole round (grids capped too); every row, and the bits of a second call."""
     from gpu_drive import GpuBatch
     from oracle_drive import table_at
     from paper_2508_08895_amd import binding as A
@@ -186,3 +186,47 @@ def test_decode_is_one_launch(heads, prefix, branches, hint, columns, static):
     ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache)
     assert np.abs(out.float().cpu().numpy() - ref).max() <= TOL
     assert kernels_of(call) == 1
+
+
+def _chunk_step(heads, batch, prefix, branches, chunk, columns=0, hint=True, cap=0):
+    from gpu_drive import GpuBatch, widen_tables
+    from oracle_drive import table_at
+    from paper_2508_08895_amd import binding as A
+    wl = W.random_small(seed=7100 + prefix + chunk, num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=heads[2], batch=batch,
+                        prefix_range=(prefix, prefix), branches_range=(branches, branches), branch_len_range=(1, 1),
+                        extra_tokens_per_branch=chunk, extra_tokens_per_seq=0)
+    widen_tables(wl, columns)
+    gb = GpuBatch(wl)
+    gb.grow_to(wl.branch_len)
+    tt = table_at(wl, wl.branch_len)
+    new = np.full(wl.NB, chunk, dtype=np.int32)
+    meta = tt.append_parallel(new)
+    step = A.aspd_build_branch_meta(gb.kv, gb.state, A.STAGE_PARALLEL, gb._dev_i32(new), NQ=meta.NQ,
+                                    max_new_per_seq=branches * chunk if hint else 0, max_workgroups=cap)
+    return wl, gb, tt, meta, step
+
+
+# On a grid that a table of 1 024 columns leaves whole, an item of one sequence has a part for every sixteen pages or fewer.
+@pytest.mark.parametrize("heads,branches,chunk", [((32, 8, 128), 3, 21), ((16, 4, 64), 3, 21), ((2, 2, 128), 4, 60)])
+@pytest.mark.parametrize("parts", [1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 13, 16, 17])
+def test_every_class_of_parts(heads, branches, chunk, parts):
+    """A merge behind the launch in every class of parts, at its first and its last, with as many rows as a row group has or
+    nearly: rows in one round and in two, in shares that do not come out even; and with nothing to merge."""
+    from gpu_drive import kernels_of, planned_parts, row_splitting_grid
+    from paper_2508_08895_amd import binding as A
+    wl, gb, tt, meta, step = _chunk_step(heads, 1, 256 * parts - 5 - branches * (chunk + 1), branches, chunk, columns=1024)
+    split = planned_parts(step, row_splitting_grid(wl, meta.NQ, branches * chunk))
+    assert split == ([parts] * heads[1] if parts > 1 else [])
+    q = wl.draw_q(meta.NQ)
+    qd = q.to(gb.dev)
+    out = torch.full((meta.NQ + 1, *q.shape[1:]), float("nan"), dtype=q.dtype, device=gb.dev)
+    lse = torch.full((meta.NQ + 1, heads[0]), float("nan"), dtype=torch.float32, device=gb.dev)
+
+    def call():
+        A.aspd_attn_branch_chunk(gb.kv, gb.state, step, qd, gb.workspace, out=out, lse=lse)
+    call()
+    assert kernels_of(call) == 2
+    assert torch.isnan(out[meta.NQ]).all() and torch.isnan(lse[meta.NQ]).all()
+    ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache)
+    assert np.abs(out[:meta.NQ].float().cpu().numpy() - ref).max() <= TOL
+    assert np.abs(lse[:meta.NQ].cpu().numpy() - ref_lse).max() <= LSE_TOL
