@@ -69,19 +69,26 @@ size_t scratch_need(int head_dim, size_t plan_words, long nwg, int rows_cap) {
 
 // Whether the partial results of a row-splitting launch are merged by a launch of their own, behind it.  The workgroup that
 // brings an item's last part merges by itself while the others have nothing to do, which is long where an item has many
-// parts and rows; the launch costs about 2 us, empty or not.  The line: four workgroups an item, as far as the host can count
-// items (a sequence has one per KV head at least, and so does every full row group).  Steps, merged in the launch -> behind
-// it, us: one sequence of 10 900, 204 rows (32 parts) 359 -> 161; one of 2 700, 140 rows 136 -> 93; two of up to 1 400, 230
-// rows 151 -> 129; six of 1 000 to 6 000 118 -> 105.  Below the line (three parts): stage opening over 12 sequences 260 | 272,
-// 9 of 1 600 to 9 800 273 | 303, 20 of 500 to 3 000 176 | 185.
-// (Not the streaming kernel's: its parts have few rows, and the host, which knows the width of the block table but no
-// sequence's length, cannot tell many of them from none.  Four layers behind 300 / 1 000 / 4 000 / 8 000 / 16 000 tokens in a
-// table of 2 048 blocks, in the launch | behind it, us: ten branches 74 | 81, 80 | 90, 103 | 103, 135 | 114, 149 | 130; four
-// branches in a step without a bound on its tokens 63 | 70, behind 2 000 79 | 83, behind 8 000 123 | 107.)
-constexpr int MERGE_APART_PARTS = 4;
-bool merge_apart(const aspd_kv* kv, int B, int NQ, const AttnVariant& v) {
-  const long items = (long)std::max(B, (NQ + v.qpg - 1) / v.qpg) * kv->num_kv_heads;
-  return v.kernel == KERNEL_BF16_ROWS && MERGE_APART_PARTS * items <= v.nwg;
+// parts and rows; the launch costs 2 us, empty or not.  The host knows the width of the block table but no sequence's length,
+// so what it goes by is how few the items are against the workgroups: four workgroups for each item that there is at least
+// (a sequence has one per KV head, and so does every full row group), and two and a half for each that there is at most.
+// In the launch -> behind it, four layers, 32/8 heads, a table of 2 048 blocks, us.  One sequence, 45 new tokens in three
+// branches, behind 600 tokens 131 -> 105, 1 000 133 -> 108, 2 000 159 -> 115, 4 000 218 -> 123, 10 900 341 -> 138; four
+// sequences behind 1 000 144 -> 117, 4 000 195 -> 157; six of 65 new tokens behind 1 000 (a full row group and one of a query,
+// 2.7 workgroups an item) 170 -> 142.  Behind 300 to 450 tokens as long (102 | 103, 112 | 113).  What it costs: behind 90 or
+// 200 tokens nothing is split, 77 -> 85 and 87 -> 95, a prompt of 90 tokens 69 -> 77; with a table of the sequence's own
+// width those have no launch.  On the other side of the lines: 12 sequences with three parts an item (65 us a layer) 4 %
+// longer, 9 of 1 600 to 9 800 tokens 11 %; seven of 65 new tokens (2.3 workgroups an item) behind 1 000 176 | 153, behind
+// 4 000 302 | 332.
+// (Not the streaming kernel's: its parts have few rows.  Four layers behind 300 / 1 000 / 4 000 / 8 000 / 16 000 tokens, in the
+// launch | behind it, us: ten branches 74 | 81, 80 | 90, 103 | 103, 135 | 114, 149 | 130; four branches in a step without a
+// bound on its tokens 63 | 70, behind 2 000 79 | 83, behind 8 000 123 | 107.)
+bool merge_apart(const aspd_kv* kv, int B, int NQ, int max_new_per_seq, const AttnVariant& v) {
+  if (v.kernel != KERNEL_BF16_ROWS) return false;
+  const long groups_min = std::max(B, (NQ + v.qpg - 1) / v.qpg);
+  long groups_max = (long)B + NQ / v.qpg;
+  if (max_new_per_seq > 0) groups_max = std::min(groups_max, (long)B * (((long)max_new_per_seq + v.qpg - 1) / v.qpg));
+  return 4 * groups_min * kv->num_kv_heads <= v.nwg && 5 * groups_max * kv->num_kv_heads <= 2L * v.nwg;
 }
 
 enum Mode { MODE_PARALLEL, MODE_CHUNK, MODE_SERIAL };
@@ -161,7 +168,7 @@ int attn_launch(Mode mode, const aspd_kv* kv, const aspd_state* state, const asp
     hipLaunchKernelGGL(KERNEL, dim3(a.nwg), dim3(NTHREADS), SMEM, hs, a);            \
     ASPD_HIP_CHECK(hipGetLastError());                                               \
   } while (0)
-  a.merge_apart = merge_apart(kv, state->B, step->NQ, v);
+  a.merge_apart = merge_apart(kv, state->B, step->NQ, step->max_new_per_seq, v);
   if (v.kernel == KERNEL_BF16_ROWS) {
     if (D == 128)
       ASPD_LAUNCH((attn_bf16_rows_kernel<128, ROWS_NW>), ROWS_NW * 64,

@@ -230,3 +230,32 @@ def test_every_class_of_parts(heads, branches, chunk, parts):
     ref, ref_lse = attend(tt, meta, q, wl.k_cache, wl.v_cache)
     assert np.abs(out[:meta.NQ].float().cpu().numpy() - ref).max() <= TOL
     assert np.abs(lse[:meta.NQ].cpu().numpy() - ref_lse).max() <= LSE_TOL
+
+
+@pytest.mark.parametrize("batch,prefix,branches,chunk,hint,columns,launches", [
+    (6, 300, 5, 13, True, 1024, 2),     # 65 rows, a full row group and one query each: 2.7 workgroups an item
+    (7, 300, 5, 13, True, 1024, 1),     # 2.3
+    (7, 300, 5, 13, False, 1024, 1),    # ... as far as the host can count them without the bound
+    (8, 300, 3, 15, True, 1024, 2),     # a row group each: four workgroups an item
+    (9, 300, 3, 15, True, 1024, 1),
+    (1, 300, 3, 15, False, 1024, 2),
+    (1, 300, 3, 15, True, 0, 1),        # a table of the sequence's own width: few workgroups
+    (1, 1000, 16, 1, True, 0, 2),
+])
+def test_where_the_merge_is_a_launch(batch, prefix, branches, chunk, hint, columns, launches):
+    """Either side of the lines, and the entry point without a workspace where its scratch is enough."""
+    from gpu_drive import kernels_of
+    from paper_2508_08895_amd import binding as A
+    wl, gb, tt, meta, step = _chunk_step((32, 8, 128), batch, prefix, branches, chunk, columns, hint)
+    q = wl.draw_q(meta.NQ)
+    qd = q.to(gb.dev)
+    calls = [lambda out: A.aspd_attn_branch_chunk(gb.kv, gb.state, step, qd, gb.workspace, out=out)]
+    if chunk == 1:
+        calls.append(lambda out: A.aspd_attn_parallel_decode_static(gb.kv, gb.state, step, qd, out))
+    ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache)
+    for call in calls:
+        out = torch.full_like(qd, float("nan"))
+        call(out)
+        assert np.abs(out.float().cpu().numpy() - ref).max() <= TOL
+        # (a step without the bound has its plan built for decoding: the chunk call works one out itself)
+        assert kernels_of(lambda: call(out)) == launches + (0 if hint else 1)
