@@ -1,5 +1,6 @@
 """Edges of the row-splitting kernels: rows of a wave that is not full (16-byte pieces that lanes exchange, sixteen rows at
-once), block ids of segments longer than the kernel holds at once, against the oracle."""
+once), block ids of segments longer than the kernel holds at once, the orders and queues of whole sequences' row groups, the
+merge in the launch and behind it (and decoding steps, which have none behind), against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -259,3 +260,42 @@ def test_where_the_merge_is_a_launch(batch, prefix, branches, chunk, hint, colum
         assert np.abs(out.float().cpu().numpy() - ref).max() <= TOL
         # (a step without the bound has its plan built for decoding: the chunk call works one out itself)
         assert kernels_of(lambda: call(out)) == launches + (0 if hint else 1)
+
+
+@pytest.mark.parametrize("heads,cap", [((6, 3, 128), 2), ((12, 6, 128), 5), ((16, 16, 128), 9), ((32, 8, 128), 40), ((4, 1, 64), 3)])
+def test_row_groups_sequence_by_sequence(heads, cap):
+    """More tokens than an L2 holds of one KV head: the list goes sequence by sequence, longest first and in each longest ranges
+    first, and holds every row group once; sequences of equal and of different length, with parallel stages and without, one
+    empty; odd numbers of heads, and more heads than queues."""
+    from gpu_drive import GpuBatch
+    from paper_2508_08895_amd import binding as A
+    G, D = heads[0] // heads[1], heads[2]
+    qpg, l2 = 256 // G, (4 << 20) // (4 * D)                 # tokens of a row group, and of one KV head in an L2
+    n = l2 // 4 + 57
+    layouts = [[(0, n // 3), (1, 40), (2, n // 3), (3, 7), (0, n - 2 * (n // 3) - 47)], [(0, 5)], [],
+               [(0, n)], [(0, 100), (1, n // 2), (2, n - n // 2 - 100)], [(0, n + qpg)]]
+    lengths = [sum(m for _, m in r) for r in layouts]
+    wl = W.random_small(seed=7300 + heads[0], num_q_heads=heads[0], num_kv_heads=heads[1], head_dim=D, batch=len(layouts),
+                        prefix_range=(max(lengths), max(lengths)), branches_range=(1, 1), branch_len_range=(1, 1))
+    tt, meta = replay_layout(wl.block_tables, wl.block_size, layouts)
+    gb = GpuBatch(wl)
+    step = A.aspd_build_sequence_meta(gb.kv, gb.state, gb._dev_i32(np.cumsum([0] + [len(r) for r in layouts])),
+                                      gb._dev_i32([b for r in layouts for b, _ in r]),
+                                      gb._dev_i32([m for r in layouts for _, m in r]), NQ=meta.NQ, max_workgroups=cap)
+    words = step.plan.view(torch.int32).cpu().numpy()
+    items = words[0]
+    assert items == sum(-(-m // qpg) for m in lengths) and items * qpg > l2 and items * heads[1] >= 12 * cap
+    first = np.cumsum([0] + lengths)
+    want = [(s, first[s] + t, min(qpg, lengths[s] - t), (min(t + qpg, lengths[s]) + 15) // 16)
+            for s in sorted(range(len(lengths)), key=lambda s: (-(-(-lengths[s] // qpg)), s))
+            for t in reversed(range(0, lengths[s], qpg))]
+    at = 16 + (meta.NQ + 3) // 4 * 4
+    assert words[at:at + 4 * items].reshape(items, 4).tolist() == [list(map(int, w)) for w in want]
+    q = wl.draw_q(meta.NQ)
+    out = torch.full(q.shape, float("nan"), dtype=q.dtype, device=gb.dev)
+    A.aspd_attn_full_sequence(gb.kv, gb.state, step, q.to(gb.dev), gb.workspace, out=out)
+    assert torch.isfinite(out).all()
+    assert int(gb.workspace[:4096].view(torch.int32).abs().sum().item()) == 0
+    rows = sorted({*range(0, meta.NQ, 331), *(int(x) - 1 for x in first[1:]), *(int(x) for x in first[:-1] if x < meta.NQ)})
+    ref, _ = attend(tt, meta, q, wl.k_cache, wl.v_cache, rows=rows)
+    assert np.abs(out.float().cpu().numpy()[rows] - ref[rows]).max() <= TOL
