@@ -29,7 +29,7 @@ struct PlanArgs {
   int32_t*       plan;
   int            B, nwg, qpg, pad, num_kv_heads, max_blocks_per_seq, num_blocks;
   int            has_owner;
-  int            w_page, w_wave;  // what a page costs: w_page + w_wave for every 32 rows of its row group
+  int            w_page, w_wave;  // what a page costs: w_page, and w_wave for every wave that has rows up to four (page_cost)
   int            rows_per_query;  // query heads per KV head
   int            NQ, max_items;   // rows of the step, and the items the plan has room for
 };

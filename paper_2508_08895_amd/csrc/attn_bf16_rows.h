@@ -21,7 +21,8 @@ namespace {
 // in it, beside the softmax of pair p, so that a wave by itself keeps the matrix unit and the vector unit
 // busy together.  Measured against 16x16x32 tiles without the pipeline: 64 whole sequences (18.8 TFLOP) 22.1 -> 20.8 ms,
 // where the matrix unit's share of the cycles went from 41 % to 53 % and the shader clock from 1.91 to 1.58 GHz (the
-// launch runs into the power limit); prompts of 90 to 2000 tokens 403 -> 225 us a layer.
+// launch runs into the power limit); prompts of 90 to 2000 tokens 403 -> 225 us a layer.  (Since then, with fewer reads past the
+// L2 and shorter starts: 16.7 ms, 58 % at 1.89 GHz, and 125 us.)
 //
 // 32x32x16 layout: S^T[key][row] = K * Q^T, lane (c, h) = (lane % 32, lane / 32) holds, of row c, the keys
 // 8 b + 4 h + j (b, j = 0 .. 3) of the pair, which is the B-operand layout of O^T[d][row] = V^T * P^T when the
@@ -718,7 +719,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW / 4,
   // head by head.  A workgroup whose queue is empty turns to the next.  With few items, and with pieces, whose order is that of
   // their lengths, there is one for all: who is free next matters more.  64 whole sequences of 1 100 to 9 400 tokens, one
   // queue -> one per XCD: hits in L2 4 -> 89 %, 78 -> 6.4 GB read past it, the clock at the power limit 1.56 -> 1.89 GHz, 21.3
-  // -> 16.7 ms (1 130 TFLOP/s).
+  // -> 16.7 ms (1 130 TFLOP/s).  With fewer heads than XCDs those of a class all stream their head's pages, each for its own row
+  // groups, and it gains less: 16 sequences of 4 000 to 12 000 with 2 heads 4.00 -> 3.76 ms, 12 of 8 000 to 16 000 with one
+  // 6.40 -> 5.98, 24 of 1 500 to 4 000 with 4 heads 3.80 -> 3.46, 12 of 2 000 to 8 000 with 6 heads 3.91 -> 3.70.
   const bool by_xcd = n_pieces == 0 && (long)n_groups * Hkv >= (long)SEQ_QUEUE_ITEMS * a.nwg;
   const int classes_log2 = min(__builtin_ctz(Hkv), SEQ_QUEUES_LOG2), every_log2 = SEQ_QUEUES_LOG2 - classes_log2;
   auto groups_of = [&](int x) -> int { return (n_groups - (x >> classes_log2) + (1 << every_log2) - 1) >> every_log2; };

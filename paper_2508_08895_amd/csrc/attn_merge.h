@@ -8,9 +8,10 @@ namespace {
 // ---------------------------------------------------------------------------------------------
 // Items split over several workgroups: every workgroup that has written a partial for the item
 // announces it on the item's counter (indexed by the workgroup in whose share the item starts);
-// the one that arrives last combines all partials and writes the output.  No workgroup waits for
-// another.  The partials are the "starts item" slot of the first workgroup and the "continues
-// item" slots of the following ones.  (Where items are few, many parts each, merge_kernel below does it instead.)
+// the one that arrives last combines all partials and writes the output.  For chunks of few
+// sequences a launch behind the row-splitting kernel's combines them instead (merge_kernel), and
+// nothing is announced.  No workgroup waits for another.  The partials are the "starts item" slot
+// of the first workgroup and the "continues item" slots of the following ones.
 // ---------------------------------------------------------------------------------------------
 // A thread combines ELEMS 16-byte chunks of one row at a time, BATCH parts of each: all their loads and those of the row's
 // statistics are on their way at once, and nothing goes through LDS.  Bound by the instructions issued, so a row's weights
